@@ -354,6 +354,8 @@ enum {
                             its own output tile's part, and count the tile up; the step that sums the
                             arrivals waits per tile (bounded spin: commfuse_device_status reports a
                             time-out).  Same sums, bit for bit.  Without a workspace the flag changes nothing.
+                            Where a rank step has few rows in all (decoded tokens; the kernel that packs the rows
+                            of every step into one launch) every kind's deliveries are carried, whatever k.
                             Not with CF_DEVICE_WAIT.                                                  */
     CF_DEVICE_WAIT = 64u /* bf16 RS / AG only, needs a registered workspace: the compute
                             stream does not wait for the copy stream between steps;

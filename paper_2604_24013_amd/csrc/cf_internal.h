@@ -20,6 +20,7 @@ struct GemmParams {
     static constexpr int MAX_RECV_MORE = 15;
     const float *recv_more[MAX_RECV_MORE] = {};
     int n_recv_more = 0;
+    float *land_more[MAX_RECV_MORE] = {};   // few-rows kernel only: where recv_more[i] is stored on to (nullable)
     int pf_lead = 16;    // B_in prefetch: k-tiles before the end of the k loop at which it is issued (0 = off)
     bool stream_recv = true;   // 256x256 tile: B_in lands in LDS under the main loop and is added in mid-sum (set by the launcher)
     void *out = nullptr;
@@ -122,6 +123,8 @@ struct Tuning {
     int carry = -1;                 // COMMFUSE_CARRY = 0: the one-launch reduce-scatter never carries its deliveries
                                     // under CF_FUSED_COPY (-1 = unset, 1: wherever the launch streams B_in)
     int tile_f32_bm = 0;            // COMMFUSE_TILE_F32 = "128x128" | "64x64"             (0 = unset)
+    int rows = -1;                  // COMMFUSE_ROWS = 0: never the few-rows kernel            (-1 = unset)
+    int rows_mf = 0, rows_nc = 0, rows_ks = 0;   // COMMFUSE_ROWS = "MFxNCxKS": that shape of it (0 = unset)
     unsigned spin_limit = 0;        // COMMFUSE_SPIN_LIMIT                                 (0 = unset)
     int attn_qt = -1;               // COMMFUSE_ATTN_QT = 0 | 1 | 2                        (-1 = unset)
     int attn_waves = 0;             // COMMFUSE_ATTN_WAVES = 4 | 8                         (0 = unset)
@@ -162,6 +165,12 @@ bool gemm_bf16_dl_supported(const GemmParams &p, bool w_kn);
 hipError_t launch_gemm_bf16_dl(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t);
 bool gemm_bf16_dl_streams_recv(const GemmParams &p, bool w_kn, bool out_bf16, TileChoice t);
 bool gemm_bf16_dl_carries_operand(const GemmParams &p);
+// The kernel for few rows (gemm_rows.hip; bf16 and fp32 operands): does it run this launch -- one chunk GEMM, or with
+// n_steps > 0 all steps of a rank step, whose deliveries it then carries where land_step / land_more are set?
+bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu);
+// What the tile kernels take for this launch, roughly, in microseconds (for the rule between them and the one above).
+double gemm_bf16_tile_us(const GemmParams &p, int num_cu);
+hipError_t launch_gemm_rows(const GemmParams &p, bool bf16, bool w_kn, bool out_bf16, hipStream_t s, int num_cu);
 hipError_t launch_gemm_f32(const GemmParams &p, bool w_kn, hipStream_t s, int num_cu);
 
 bool attn_slice_supported(const AttnParams &p);

@@ -887,7 +887,18 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // buffer by one of the workgroups that load it (k a multiple of the k-tile).  Otherwise the deliveries are
     // enqueued in front as without the flag.
     bool carried = false;
-    if ((flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr && do_copy && do_compute &&
+    // few rows in all: the kernel that packs the rows of every step into one launch, and carries every delivery
+    bool few_rows = false;
+    if (do_copy && do_compute && !is_dp_kind(kind) && !is_wgrad_kind(kind) && slot_bytes > 0) {
+        cf::GemmParams probe;
+        probe.W = b->W;
+        fill_shape(probe, r);
+        probe.n_steps = S;
+        few_rows = cf::gemm_rows_takes(probe, r.bf16_in, r.w_kn, num_cu_of_current_device());
+    }
+    if (few_rows && (flags & CF_FUSED_COPY))
+        carried = true;
+    if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr && do_copy && do_compute &&
         slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0) {
         cf::GemmParams probe;
         probe.W = b->W;
@@ -899,7 +910,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // layer) carries its deliveries the other way: the epilogue reads B_in from the neighbour's buffer, and the same
     // work item copies its tile's part of it to the landing buffer beside its GEMM (no counter: nobody waits for it).
     bool carried_beside = false;
-    if ((flags & CF_FUSED_COPY) && kind == CF_KIND_RS && !carried && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
+    if (!few_rows && (flags & CF_FUSED_COPY) && kind == CF_KIND_RS && !carried && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
         r.n > 0 && r.k > 0 && r.ldo == r.n) {
         cf::GemmParams probe;
         probe.W = b->W;
@@ -918,7 +929,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // before it sums the arrivals.  Needs the registered workspace (a counter per output tile, the status word).
     unsigned *pair_ready = nullptr, *pair_status = nullptr;
     int pair_tiles = 0;
-    if ((flags & CF_FUSED_COPY) && kind == CF_KIND_RS_PAIR && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
+    if (!few_rows && (flags & CF_FUSED_COPY) && kind == CF_KIND_RS_PAIR && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
         r.n > 0 && r.k > 0) {
         cf::GemmParams probe;
         probe.W = b->W;
@@ -940,7 +951,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // stream never waits for a kernel.
     int group = S;
     const bool grouped = !(flags & CF_SERIAL) && xs != cs && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr &&
-                         !carried && !carried_beside && p > 1 && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0;
+                         !carried && !carried_beside && !few_rows && p > 1 && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0;
     if (grouped) {
         cf::GemmParams probe;
         probe.W = b->W;
@@ -1068,6 +1079,15 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         gp.W = b->W;
         fill_shape(gp, r);
         gp.n_steps = g1 - g0;
+        {
+            const Workspace ws = workspace_for(cs);
+            if (ws.ptr != nullptr && ws.bytes > WS_COUNTER_BYTES) {
+                gp.counters = static_cast<unsigned *>(ws.ptr);
+                gp.ws = reinterpret_cast<float *>(static_cast<char *>(ws.ptr) + WS_COUNTER_BYTES);
+                gp.ws_bytes = ws.bytes - WS_COUNTER_BYTES;
+                gp.max_tiles = (int)(WS_TILE_COUNTER_BYTES / sizeof(unsigned));
+            }
+        }
         gp.num_cu = num_cu_of_current_device();
         for (int jj = g0; jj < g1; ++jj) {
             const int j = jj - g0;                       // the step's place in this launch
@@ -1083,11 +1103,19 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                 if (last)
                     for (int t = 1; t < p - 1; ++t)
                         gp.recv_more[gp.n_recv_more++] = static_cast<const float *>(b->recv_each[t]);
-                if (carried && !last) {              // this step's work items land the arrival of round j + 1
+                if (carried && few_rows && last && p > 1) {   // the arrivals are read from the partners' buffers and landed
+                    gp.recv_step[j] = static_cast<const float *>(b->peer_stage[0]);
+                    gp.land_step[j] = b->recv_each[0];
+                    for (int t = 1; t < p - 1; ++t) {
+                        gp.recv_more[t - 1] = static_cast<const float *>(b->peer_stage[t]);
+                        gp.land_more[t - 1] = static_cast<float *>(b->recv_each[t]);
+                    }
+                }
+                if (carried && !few_rows && !last) { // this step's work items land the arrival of round j + 1
                     gp.tail_src[j] = static_cast<const float *>(b->peer_stage[j]);
                     gp.tail_dst[j] = static_cast<float *>(b->recv_each[j]);
                 }
-                if (carried && last) {
+                if (carried && !few_rows && last) {
                     gp.tile_ready = pair_ready;
                     gp.ready_count = p - 1;
                     gp.max_tiles = (int)(WS_TILE_COUNTER_BYTES / sizeof(unsigned));
@@ -1424,7 +1452,7 @@ static Tuning read_tuning_from_environment()
 {
     Tuning t;
     memset(&t, 0, sizeof(t));                      // (padding too: the struct is hashed byte-wise into graph keys)
-    t.deep = t.prefetch = t.xcd_steps = t.k_rotate = t.stream_recv = t.attn_qt = t.carry = t.mfma16 = -1;
+    t.deep = t.prefetch = t.xcd_steps = t.k_rotate = t.stream_recv = t.attn_qt = t.carry = t.mfma16 = t.rows = -1;
     int bm = 0, bn = 0;
     if (const char *e = getenv("COMMFUSE_TILE"))
         if (sscanf(e, "%dx%d", &bm, &bn) == 2) {
@@ -1461,6 +1489,15 @@ static Tuning read_tuning_from_environment()
     if (const char *e = getenv("COMMFUSE_TILE_F32"))
         if (sscanf(e, "%dx%d", &bm, &bn) == 2)
             t.tile_f32_bm = bm;
+    if (const char *e = getenv("COMMFUSE_ROWS")) {
+        int mf = 0, nc = 0, ks = 0;
+        t.rows = atoi(e) != 0;
+        if (sscanf(e, "%dx%dx%d", &mf, &nc, &ks) == 3 && mf > 0) {
+            t.rows_mf = mf;
+            t.rows_nc = nc;
+            t.rows_ks = ks;
+        }
+    }
     if (const char *e = getenv("COMMFUSE_SPIN_LIMIT")) {
         const long v = atol(e);
         if (v > 0)

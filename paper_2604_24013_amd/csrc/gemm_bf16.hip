@@ -350,6 +350,18 @@ static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
     return t;
 }
 
+double gemm_bf16_tile_us(const GemmParams &p, int num_cu)
+{
+    // Fitted to single steps with a B_in (128x128: 256 x 4096 x 1376 19.9 us, 256 x 8192 x 3584 38.8 us; 256x128: 1024 x 8192
+    // x 1024 29.3 us, x 3584 68 us) and, for 256x256, to one round of a rank step.
+    const TileChoice t = tile_of_launch(p, num_cu);
+    const int64_t items = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * (p.n_steps > 0 ? p.n_steps : 1);
+    const int64_t wgs = (int64_t)num_cu * (t.bm == 128 && !t.deep ? 2 : 1);
+    const double kt = (p.K + 63) / 64;
+    const double round = t.bm == 128 ? 8 + 0.55 * kt : t.bn == 128 ? 14 + 0.97 * kt : 14 + 1.5 * kt;
+    return (double)((items + wgs - 1) / wgs) * round;
+}
+
 int gemm_bf16_tiles_landing_arrivals(const GemmParams &p, bool w_kn, int num_cu)
 {
     const Tuning tn = tuning();                      // COMMFUSE_CARRY=0 keeps the copies in front
@@ -411,6 +423,8 @@ hipError_t launch_gemm_bf16(const GemmParams &p, bool w_kn, bool out_bf16, hipSt
 {
     if (p.M <= 0 || p.N <= 0)
         return hipSuccess;
+    if (gemm_rows_takes(p, true, w_kn, num_cu))
+        return launch_gemm_rows(p, true, w_kn, out_bf16, s, num_cu);
     const TileChoice t = tile_of_launch(p, num_cu);
     const bool staged = staged_kernel_forced();
     if (!staged && gemm_bf16_dl_supported(p, w_kn))

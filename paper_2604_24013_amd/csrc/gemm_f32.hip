@@ -183,6 +183,8 @@ hipError_t launch_gemm_f32(const GemmParams &p, bool w_kn, hipStream_t s, int nu
 {
     if (p.M <= 0 || p.N <= 0)
         return hipSuccess;
+    if (gemm_rows_takes(p, false, w_kn, num_cu))
+        return launch_gemm_rows(p, false, w_kn, false, s, num_cu);
     const int big = ((p.M + 127) / 128) * ((p.N + 127) / 128);
     bool use_big = big >= num_cu;
     if (const int bm = tuning().tile_f32_bm)             // override: "128x128" or "64x64"

@@ -1,0 +1,105 @@
+"""The kernel for few rows (waves that split the k range, every step's rows packed into one launch) against the oracle:
+each of its tile shapes at the edges of its row tiles, column tiles and k slices, single steps and whole rank steps.
+
+Bounds: fp32 sums of K <= 8192 exact products, about sqrt(K) 2^-24 of the largest partial sum: 1e-5 for fp32 operands
+(the benchmark's bound), 1e-5 for bf16 operands too (K <= 4096 here); a bf16 output adds 2^-9 of the element."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2604_24013_amd import binding as cf
+from paper_2604_24013_amd import inputs
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = ["1x1x1", "1x2x1", "1x4x1", "2x1x1", "2x2x1", "2x4x1", "4x2x1", "4x4x1", "1x2x3", "4x4x2"]   # last: k split over workgroups
+ONE_LAUNCH = cf.CF_PERSISTENT | cf.CF_SERIAL
+
+
+@pytest.fixture
+def rows(request):
+    """Forces one shape of the kernel (None: its own rule) and registers a workspace for the k split."""
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device=H.DEV)
+    cf.set_workspace(ws)
+    torch.cuda.synchronize()
+
+    def force(shape):
+        os.environ.pop("COMMFUSE_ROWS", None)
+        if shape is not None:
+            os.environ["COMMFUSE_ROWS"] = shape
+    yield force
+    os.environ.pop("COMMFUSE_ROWS", None)
+    torch.cuda.synchronize()
+    cf.set_workspace(None)
+
+
+def _rs(p, mc, n, k, dtype, salt):
+    w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=p, m_chunk=mc, n=n, k=k, dtype=dtype)
+    data = inputs.make_rs(w, salt=salt)
+    ref = oracle.rs_rank_steps(inputs.as_f64(data["A"], dtype), inputs.as_f64(data["W"], dtype),
+                               [None] + [r.astype(np.float64) for r in data["R"][1:]], p, p - 1)
+    return w, data, ref
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("layout", [cf.CF_W_KN, cf.CF_W_NK])
+@pytest.mark.parametrize("dims", [(2, 1, 8, 8), (2, 15, 72, 56), (3, 17, 264, 64), (2, 65, 136, 1096), (2, 33, 520, 4096)])
+def test_single_steps(dims, layout, dtype, rows):
+    """m_chunk around the row tiles (1, 15, 17, 33, 65), n around the column tiles, k below / at / beyond a slice, and an
+    input of small integers bit for bit."""
+    p, mc, n, k = dims
+    w, data, ref = _rs(p, mc, n, k, dtype, 3)
+    wi, di = w, inputs.make_rs(w, salt=4)
+    rng = np.random.default_rng(5)
+    for name in ("A", "W"):
+        v = inputs.small_int_like(di[name].shape, rng)
+        di[name] = inputs.f32_to_bf16_bits(v) if dtype == "bf16" else v
+    di["R"] = [None] + [inputs.small_int_like(r.shape, rng) for r in di["R"][1:]]
+    refi = oracle.rs_rank_steps(inputs.as_f64(di["A"], dtype), inputs.as_f64(di["W"], dtype),
+                                [None] + [r.astype(np.float64) for r in di["R"][1:]], p, p - 1)
+    for shape in SHAPES + [None]:
+        rows(shape)
+        outs = H.RsRun(w, data, p - 1, layout).run_steps()
+        for i in range(p):
+            assert not np.isnan(outs[i]).any()
+            assert H.rel_err(outs[i], ref[i]) <= 1e-5, f"{shape} step {i}"
+        for got, want in zip(H.RsRun(wi, di, p - 1, layout).run_steps(), refi):
+            assert np.array_equal(got, want), shape
+
+
+@pytest.mark.parametrize("carry", [0, cf.CF_FUSED_COPY])
+@pytest.mark.parametrize("layout", [cf.CF_W_KN, cf.CF_W_NK])
+@pytest.mark.parametrize("dims", [(8, 1, 40, 72), (4, 9, 264, 520), (6, 22, 136, 200), (2, 64, 200, 8)])
+def test_packed_rank_steps(dims, layout, carry, rows):
+    """All steps of a rank step in one launch: tiles that hold rows of several steps, the deliveries copied in front or
+    landed by the launch, reduce-scatter on the ring and pairwise, all-gather with both output types."""
+    p, mc, n, k = dims
+    w, data, ref = _rs(p, mc, n, k, "bf16", 6)
+    refp = oracle.rs_pair_rank_steps(inputs.as_f64(data["A"], "bf16"), inputs.as_f64(data["W"], "bf16"),
+                                     [None] + [r.astype(np.float64) for r in data["R"][1:]], p, p - 1)
+    for shape in ("1x2x1", "2x2x1", "4x4x1", "1x4x2", None):
+        rows(shape)
+        for Run, kw, want in ((H.RsRun, dict(each=True), ref), (H.RsPairRun, dict(keep_all=True), refp)):
+            run = Run(w, data, p - 1, layout, **kw)
+            for t in run.each + run.send_each + [run.O]:
+                t.fill_(float("nan"))
+            run.run_schedule(ONE_LAUNCH | carry)
+            for i in range(p):
+                got = H.to_host_f64(run.send_each[i] if i < p - 1 else run.O)
+                assert H.rel_err(got, want[i]) <= 1e-5, f"{Run.__name__} {shape} step {i}"
+            assert all(torch.equal(a, b) for a, b in zip(run.each, run.stage)), f"{Run.__name__} {shape}"
+        for out_dtype in ("f32", "bf16"):
+            wa = inputs.scaled(inputs.CONFIGS["c3_ag_7b"], p=p, m_chunk=mc, n=n, k=k, out_dtype=out_dtype)
+            da = inputs.make_ag(wa, salt=7)
+            refa = oracle.ag_rank(inputs.as_f64(da["X"], "bf16"), [None] + [inputs.as_f64(s, "bf16") for s in da["S"][1:]],
+                                  inputs.as_f64(da["W"], "bf16"), p, p - 1)
+            run = H.AgRun(wa, da, p - 1, layout, each=True)
+            for t in run.each:
+                t.fill_(float("nan"))
+            run.run_schedule(ONE_LAUNCH | carry)
+            assert H.rel_err(H.to_host_f64(run.O), refa) <= (2.0 ** -8 if out_dtype == "bf16" else 1e-5), shape
+            assert all(torch.equal(a, b) for a, b in zip(run.each, run.stage)), shape
