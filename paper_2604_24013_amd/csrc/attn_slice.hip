@@ -424,18 +424,25 @@ __global__ __launch_bounds__(64 * NW) void attn_slice_kernel(AttnParams P)
     }
 }
 
-// Variant for slices with few queries (the per-step grids of Alg. 4 are small: seq/p queries per head): one
-// workgroup = 32 queries of one (batch element, head); its four waves split the KEYS -- wave w takes the
-// 32-key tiles w, w+4, w+8, ... -- each with its own double-buffered K/V landing zone in LDS (no barrier in
-// the walk), and the four partial results (m, l, unnormalised O) are merged through LDS at the end.
-__global__ __launch_bounds__(256) void attn_slice_ksplit_kernel(AttnParams P)
+// Keys over waves: one workgroup = 32 queries of one (batch element, head); its eight waves split the KEYS -- wave w takes
+// the 32-key tiles w, w + 8, ... -- each with K and V landing zones of its own in LDS, so that there is no barrier in the
+// walk and the waves of a SIMD drift apart (one multiplies while the other exponentiates).  The zones are single: the next
+// K tile is requested as soon as the scores have taken its predecessor out of LDS (it travels under the softmax and the
+// product with V), the next V tile after that product.  The eight partial results (m, l, unnormalised O) are merged in
+// LDS by all threads.  For slices with few queries; with a workspace the keys of a query block can be split over
+// `ksplit` workgroups on top, which park their merged partials (16.5 KiB each).
+constexpr int KW_WAVES = 8;
+constexpr int KW_PART = 64 * 64 + 2 * 64;    // floats of a workgroup's parked partial: O [8 groups][64 lanes][8], m, l [64 lanes]
+__global__ __launch_bounds__(64 * KW_WAVES) void attn_keys_over_waves_kernel(AttnParams P)
 {
+    constexpr int NW = KW_WAVES;
     constexpr int BK = 32;                   // keys per tile
     constexpr int TB = BK * ROWB;            // 8 KiB: one K (or V) tile
     constexpr int DS = DH / 16, DT = DH / 32;
-    constexpr int WAVE_LDS = 4 * TB;         // [buffer][K | V]
+    constexpr int WAVE_LDS = 2 * TB;         // [K | V]; afterwards the wave's O: 64 registers x 64 lanes
 
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * WAVE_LDS];
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * WAVE_LDS];
+    __shared__ float stat[NW][2][64];        // m, l per wave and lane
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -443,36 +450,28 @@ __global__ __launch_bounds__(256) void attn_slice_ksplit_kernel(AttnParams P)
     const int lq = lane & 31, lh = lane >> 5;
 
     const int qtiles = (P.c + 31) / 32;
-    const int head = blockIdx.x % P.heads;   // neighbouring workgroups (one per XCD in turn) take different heads:
-    const int qt = (blockIdx.x / P.heads) % qtiles;   // with 8 heads, each XCD's L2 serves one head's K and V
-    const int b = blockIdx.x / (P.heads * qtiles);
+    const int KSP = P.ksplit;
+    // neighbouring workgroups (one per XCD in turn) take different heads: with 8 heads, each XCD's L2 serves one head's K, V
+    const int head = blockIdx.x % P.heads;
+    int rest = blockIdx.x / P.heads;
+    const int split = rest % KSP;
+    rest /= KSP;
+    const int qt = rest % qtiles;
+    rest /= qtiles;
+    const int b = rest % P.batch, slice = P.l + rest / P.batch;
+    const int group = (rest * qtiles + qt) * P.heads + head;
     const int S = P.S;
 
     const size_t mat = (size_t)S * DH;
     const __bf16 *Qm = static_cast<const __bf16 *>(P.Q) + ((size_t)b * P.heads + head) * mat;
-    const __bf16 *Km = static_cast<const __bf16 *>(P.K) + ((size_t)b * P.heads + head) * mat;
-    const __bf16 *Vm = static_cast<const __bf16 *>(P.V) + ((size_t)b * P.heads + head) * mat;
-    const i32x4_t k_rsrc = make_rsrc(Km, (unsigned)(mat * 2));
-    const i32x4_t v_rsrc = make_rsrc(Vm, (unsigned)(mat * 2));
+    const i32x4_t k_rsrc = make_rsrc(static_cast<const __bf16 *>(P.K) + ((size_t)b * P.heads + head) * mat, (unsigned)(mat * 2));
+    const i32x4_t v_rsrc = make_rsrc(static_cast<const __bf16 *>(P.V) + ((size_t)b * P.heads + head) * mat, (unsigned)(mat * 2));
     const unsigned lds_base = __builtin_amdgcn_readfirstlane(
         (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem) + wave * WAVE_LDS;
     unsigned char *my = smem + wave * WAVE_LDS;
 
-    const int qi = qt * 32 + lq;
-    const bool q_ok = qi < P.c;
-    bf16x8_t qf[DS];
-    {
-        const __bf16 *qrow = Qm + (size_t)(P.l * P.c + (q_ok ? qi : 0)) * DH;
-#pragma unroll
-        for (int ks = 0; ks < DS; ++ks) {
-            bf16x8_t v = *reinterpret_cast<const bf16x8_t *>(qrow + ks * 16 + lh * 8);
-            if (!q_ok)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    v[e] = (__bf16)0.0f;
-            qf[ks] = v;
-        }
-    }
+    const int nkt = (S + BK - 1) / BK;
+    const int t0 = (int)(((long long)nkt * split) / KSP), t1 = (int)(((long long)nkt * (split + 1)) / KSP);
 
     // wave-load j (1 KiB) covers rows 4j .. 4j+3 of the tile; layouts as in the kernel above
     unsigned k_off[8], v_off[8];
@@ -484,16 +483,26 @@ __global__ __launch_bounds__(256) void attn_slice_ksplit_kernel(AttnParams P)
         const int inrow = cp << 4;
         v_off[j] = (unsigned)(row * ROWB + (((inrow >> 6) ^ (row & 3)) << 6) + (inrow & 63));
     }
-    auto issue_tile = [&](int kt, int buf) {
-        const int key0 = kt * BK;
-        const unsigned sa = lds_base + buf * 2 * TB;
+    auto issue = [&](int kt, const i32x4_t &rs, const unsigned (&off)[8], unsigned lds) __attribute__((always_inline)) {
+        const int key0 = kt * BK, soff = __builtin_amdgcn_readfirstlane(key0 * ROWB);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const bool in = key0 + j * 4 + (lane >> 4) < S;
-            direct_load_16(k_rsrc, in ? k_off[j] : OOB, key0 * ROWB, sa + j * 1024);
-            direct_load_16(v_rsrc, in ? v_off[j] : OOB, key0 * ROWB, sa + TB + j * 1024);
-        }
+        for (int j = 0; j < 8; ++j)          // keys beyond the sequence read as zero
+            direct_load_16(rs, key0 + j * 4 + (lane >> 4) < S ? off[j] : OOB, soff, lds + j * 1024);
     };
+    if (t0 + wave < t1) {
+        issue(t0 + wave, k_rsrc, k_off, lds_base);
+        issue(t0 + wave, v_rsrc, v_off, lds_base + TB);
+    }
+
+    const int qi = qt * 32 + lq;
+    const bool q_ok = qi < P.c;
+    bf16x8_t qf[DS];
+    {
+        const __bf16 *qrow = Qm + (size_t)(slice * P.c + (q_ok ? qi : 0)) * DH;
+#pragma unroll
+        for (int ks = 0; ks < DS; ++ks)
+            qf[ks] = *reinterpret_cast<const bf16x8_t *>(qrow + ks * 16 + lh * 8);   // (a query beyond the slice is not stored)
+    }
 
     const int blk = lane >> 4, i16 = lane & 15;
     const int v_kl = 4 * (blk >> 1) + (i16 >> 2);
@@ -503,69 +512,89 @@ __global__ __launch_bounds__(256) void attn_slice_ksplit_kernel(AttnParams P)
     for (int t = 0; t < DT; ++t)
         v_addr[t] = TB + v_kl * ROWB + ((t ^ (v_kl & 3)) << 6) + v_nl * 2;
 
-    f32x16_t oacc[DT];
+    f32x16_t oacc[DT], lacc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        lacc[e] = 0.0f;
 #pragma unroll
     for (int d = 0; d < DT; ++d)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
             oacc[d][e] = 0.0f;
-    float m_run = -INFINITY, l_run = 0.0f;
+    bf16x8_t ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        ones[e] = (__bf16)1.0f;
+    float m_run = -INFINITY;
     const float sl2 = P.scale * 1.4426950408889634f;
+    asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]), "+v"(qf[6]), "+v"(qf[7]));
+    // (the queries are in registers from here on: what the waits below count are the tiles' loads alone)
 
-    const int nkt = (S + BK - 1) / BK;
-    int buf = 0;
-    if (wave < nkt)
-        issue_tile(wave, 0);
-    for (int kt = wave; kt < nkt; kt += 4) {
-        wait_vmcnt<0>();                                             // tile kt has landed (this wave's own loads)
-        if (kt + 4 < nkt)
-            issue_tile(kt + 4, buf ^ 1);                             // its last readers' MFMAs were issued long ago
-        const unsigned char *st = my + buf * 2 * TB;
-
+    for (int kt = t0 + wave; kt < t1; kt += NW) {
+        const bool more = kt + NW < t1;
+        wait_vmcnt<8>();                                             // K of tile kt has landed (its V may be in flight)
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8_t kf[DS];
+#pragma unroll
+        for (int ks = 0; ks < DS; ++ks)
+            kf[ks] = *reinterpret_cast<const bf16x8_t *>(my + lq * ROWB + (((2 * ks + lh) ^ (lq & 15)) << 4));
         f32x16_t sacc;
 #pragma unroll
         for (int e = 0; e < 16; ++e)
             sacc[e] = 0.0f;
 #pragma unroll
-        for (int ks = 0; ks < DS; ++ks) {
-            const bf16x8_t kf = *reinterpret_cast<const bf16x8_t *>(st + lq * ROWB + (((2 * ks + lh) ^ (lq & 15)) << 4));
-            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], sacc, 0, 0, 0);
-        }
-        float mx = -INFINITY;
+        for (int ks = 0; ks < DS; ++ks)
+            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sacc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more)                                                    // (the last product has read its fragment: K is out of LDS)
+            issue(kt + NW, k_rsrc, k_off, lds_base);
+
+        // online softmax, as in the kernel above
+        constexpr float RAISE = 8.0f;
+        if ((kt + 1) * BK > S) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = kt * BK + 8 * (r >> 2) + 4 * lh + (r & 3);
-            const float sv = key < S ? sacc[r] * sl2 : -INFINITY;
-            sacc[r] = sv;
-            mx = fmaxf(mx, sv);
+            for (int r = 0; r < 16; ++r)
+                if (kt * BK + 8 * (r >> 2) + 4 * lh + (r & 3) >= S)
+                    sacc[r] = -INFINITY;
         }
+        float mx = sacc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r)
+            mx = fmaxf(mx, sacc[r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx);
-        const float alpha = exp2f(m_run - m_new);
-        float sum = 0.0f;
-        bf16x8_t pf[2];
+        const float mxs = mx * sl2;
+        if (__builtin_amdgcn_ballot_w64(mxs > m_run + RAISE) != 0) {
+            const float m_new = fmaxf(m_run, mxs);
+            float alpha = exp2f(m_run - m_new);
+            asm volatile("" : "+v"(alpha));
+            m_run = m_new;
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const __bf16 pb = (__bf16)exp2f(sacc[8 * s2 + e] - m_new);
-                pf[s2][e] = pb;
-                sum += (float)pb;
-            }
-        l_run = l_run * alpha + sum;
-        m_run = m_new;
-        if (__any(alpha != 1.0f)) {                                  // the running maximum settles after a few tiles
+            for (int e = 0; e < 16; ++e)
+                lacc[e] *= alpha;
 #pragma unroll
             for (int d = 0; d < DT; ++d)
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     oacc[d][e] *= alpha;
         }
+        const float nm = -m_run;
+        bf16x8_t pf[2];
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
+            for (int e = 0; e < 8; ++e)
+                pf[s2][e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sacc[8 * s2 + e], sl2, nm));
+
+        if (more)                                                    // V of tile kt has landed (K of the next may be in flight)
+            wait_vmcnt<8>();
+        else
+            wait_vmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+#pragma unroll
             for (int d = 0; d < DT; ++d) {
-                const unsigned char *pv = st + v_addr[d] + s2 * 16 * ROWB;
+                const unsigned char *pv = my + v_addr[d] + s2 * 16 * ROWB;
                 const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                     (__attribute__((address_space(3))) s16x4_t *)(pv));
                 const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -573,60 +602,103 @@ __global__ __launch_bounds__(256) void attn_slice_ksplit_kernel(AttnParams P)
                 const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
                 oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[s2], oacc[d], 0, 0, 0);
             }
-        buf ^= 1;
+            lacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf[s2], lacc, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (more)
+            issue(kt + NW, v_rsrc, v_off, lds_base + TB);
     }
-    wait_vmcnt<0>();
-    __syncthreads();                                                 // every wave is done with its tiles
 
-    // Merge the four partial results: lane L of every wave owns the same (query, d) positions.
-    float *mo = reinterpret_cast<float *>(smem);                     // [wave][lane][64] unnormalised O
-    float *ms = reinterpret_cast<float *>(smem + 4 * 64 * 64 * 4);   // [wave][lane][2]   m, l (both half-lanes summed)
-    const float l_pair = l_run + __shfl_xor(l_run, 32);
-    if (wave > 0) {
+    // Merge: register r of lane L of every wave is the same (query, d) position.
+    {
+        float *mo = reinterpret_cast<float *>(my);
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                mo[(wave * 64 + lane) * 64 + d * 16 + e] = oacc[d][e];
-        ms[(wave * 64 + lane) * 2 + 0] = m_run;
-        ms[(wave * 64 + lane) * 2 + 1] = l_pair;
+            for (int e = 0; e < 16; ++e) {
+                float v = oacc[d][e];
+                asm volatile("" : "+v"(v));
+                mo[(d * 16 + e) * 64 + lane] = v;
+            }
+        stat[wave][0][lane] = m_run;
+        stat[wave][1][lane] = lacc[0];                               // the whole row sum, in both lanes of the query
     }
     __syncthreads();
-    if (wave == 0) {
-        float m_all = m_run;
+    float m_all = -INFINITY, l_all = 0.0f, o[8];
 #pragma unroll
-        for (int w = 1; w < 4; ++w)
-            m_all = fmaxf(m_all, ms[(w * 64 + lane) * 2 + 0]);
-        const float f0 = exp2f(m_run - m_all);                       // wave 0 always has a tile: m_all is finite
-        float l_all = l_pair * f0;
+    for (int w = 0; w < NW; ++w)
+        m_all = fmaxf(m_all, stat[w][0][lane]);                      // finite: every workgroup has a tile
 #pragma unroll
-        for (int d = 0; d < DT; ++d)
+    for (int e = 0; e < 8; ++e)
+        o[e] = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                oacc[d][e] *= f0;
+    for (int w = 0; w < NW; ++w) {
+        const float f = exp2f(stat[w][0][lane] - m_all);             // 0 for a wave that saw no key
+        l_all += stat[w][1][lane] * f;
+        const float *mo = reinterpret_cast<const float *>(smem + w * WAVE_LDS);
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const float fw = exp2f(ms[(w * 64 + lane) * 2 + 0] - m_all);   // 0 for a wave that saw no key
-            l_all += ms[(w * 64 + lane) * 2 + 1] * fw;
-#pragma unroll
-            for (int d = 0; d < DT; ++d)
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    oacc[d][e] += mo[(w * 64 + lane) * 64 + d * 16 + e] * fw;
+        for (int e = 0; e < 8; ++e)                                  // this thread: registers 8 wave .. + 7 of lane
+            o[e] += mo[(wave * 8 + e) * 64 + lane] * f;
+    }
+    if (KSP > 1) {                                                   // hand-over between workgroups, as in the kernel above
+        constexpr int COHERENT = 1 | 16;
+        auto part_rsrc = [&](int sp) {
+            return __builtin_amdgcn_make_buffer_rsrc(P.ws + ((size_t)group * KSP + sp) * KW_PART, 0, KW_PART * 4, 0x00020000);
+        };
+        __amdgpu_buffer_rsrc_t rs = part_rsrc(split);
+        typedef float f32x4_t __attribute__((ext_vector_type(4)));
+        const f32x4_t o0 = {o[0], o[1], o[2], o[3]}, o1 = {o[4], o[5], o[6], o[7]};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o0), rs, tid * 32, 0, COHERENT);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o1), rs, tid * 32 + 16, 0, COHERENT);
+        if (wave == 0) {
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, m_all), rs, (4096 + lane) * 4, 0, COHERENT);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, l_all), rs, (4096 + 64 + lane) * 4, 0, COHERENT);
         }
-        if (q_ok) {
-            const float inv = 1.0f / l_all;
-            __bf16 *orow = static_cast<__bf16 *>(P.out) + ((size_t)b * P.c + qi) * P.ldo + (size_t)head * DH;
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        unsigned *arrived = reinterpret_cast<unsigned *>(smem);
+        if (tid == 0)
+            *arrived = __hip_atomic_fetch_add(&P.counters[group], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (*arrived != (unsigned)(KSP - 1))
+            return;
+        if (tid == 0)
+            __hip_atomic_store(&P.counters[group], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        m_all = -INFINITY;
+        for (int sp = 0; sp < KSP; ++sp)
+            m_all = fmaxf(m_all, __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(part_rsrc(sp), (4096 + lane) * 4, 0, COHERENT)));
+        l_all = 0.0f;
 #pragma unroll
-            for (int d = 0; d < DT; ++d)
+        for (int e = 0; e < 8; ++e)
+            o[e] = 0.0f;
+#pragma unroll 4
+        for (int sp = 0; sp < KSP; ++sp) {
+            __amdgpu_buffer_rsrc_t rp = part_rsrc(sp);
+            const float m = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rp, (4096 + lane) * 4, 0, COHERENT));
+            const float l = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rp, (4096 + 64 + lane) * 4, 0, COHERENT));
+            const f32x4_t a = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rp, tid * 32, 0, COHERENT));
+            const f32x4_t c = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rp, tid * 32 + 16, 0, COHERENT));
+            const float f = exp2f(m - m_all);
+            l_all += l * f;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    bf16x4_t h;
+            for (int e = 0; e < 4; ++e) {
+                o[e] += a[e] * f;
+                o[4 + e] += c[e] * f;
+            }
+        }
+    }
+    if (q_ok) {
+        const float inv = 1.0f / l_all;
+        // registers 8 wave .. + 7: d tile wave / 2, registers 8 (wave & 1) .. + 7 of it
+        __bf16 *orow = static_cast<__bf16 *>(P.out) + (size_t)(slice - P.l) * P.out_slice_stride + ((size_t)b * P.c + qi) * P.ldo +
+                       (size_t)head * DH + (wave >> 1) * 32 + (wave & 1) * 16 + 4 * lh;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        h[e] = (__bf16)(oacc[d][4 * g + e] * inv);
-                    *reinterpret_cast<u32x2_t *>(orow + d * 32 + 8 * g + 4 * lh) = __builtin_bit_cast(u32x2_t, h);
-                }
+        for (int g = 0; g < 2; ++g) {
+            bf16x4_t h;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                h[e] = (__bf16)(o[4 * g + e] * inv);
+            *reinterpret_cast<u32x2_t *>(orow + 8 * g) = __builtin_bit_cast(u32x2_t, h);
         }
     }
 }
@@ -639,52 +711,90 @@ bool attn_slice_supported(const AttnParams &p)
            (int64_t)p.S * DH * 2 < ((int64_t)1 << 31);
 }
 
+namespace {
+
+// Which kernel, and over how many workgroups the keys of a query block are split.  The costs (us) are fitted to
+// measurements over batch x heads x queries of the slice x keys:
+//   * keys over waves (32 queries): 6.5 + 1.6 per eight 32-key tiles and round -- each workgroup reads all its keys
+//     itself, 128 KiB per step of its eight waves, 0.9 us at the L1's rate.  2x3x280x1120: 13.5 (query blocks: 20.5 at best,
+//     40 with one workgroup per compute unit, whose sixteen partials per block took most of it), 1x1x1024x8192: 21.5 with
+//     six splits (37.6), 1x8x1024x8192: 60.1 (57.9);
+//   * query blocks, eight waves (256 queries): 7 + 2.05 per 64-key tile and round, 1.65 while a third of the chip idles.
+//     4x8x4096x8192: 523, 2x8x2319x4638: 124 (keys over waves: 167);
+//   * query blocks, four waves (128 queries): 7 + 1.38 per tile, 2.1 with two workgroups per compute unit.
+//     4x2x1181x2362: 34.4 with three splits (keys over waves: 41).
+// A split costs its hand-over: 1.5 + 0.7 per workgroup of 16.5 KiB partials, 5 + 1.5 for the query blocks' 66 / 132 KiB.
+struct AttnChoice {
+    int waves = 8;               // 0: keys over waves
+    int ksplit = 1;
+};
+
+AttnChoice choose_attn(const AttnParams &p, int num_cu)
+{
+    const int64_t heads = (int64_t)p.heads * p.batch * p.n_slices;
+    const int tiles32 = (p.S + 31) / 32, tiles64 = (p.S + 63) / 64;
+    const bool can_split = p.ws != nullptr && p.counters != nullptr;
+    AttnChoice best;
+    double best_us = 0.0;
+    for (int kind = 0; kind < 3; ++kind) {                   // keys over waves, eight waves, four waves
+        const int waves = kind == 0 ? 0 : kind == 1 ? 8 : 4;
+        const int bq = kind == 0 ? 32 : 32 * waves;
+        const int64_t groups = (p.c + bq - 1) / bq * heads;
+        for (const int k : {1, 2, 3, 4, 6, 8, 12}) {
+            const size_t part = kind == 0 ? (size_t)KW_PART : (size_t)(64 + 2) * (64 * waves);
+            if (k > 1 && (!can_split || groups > p.max_groups || groups * k > num_cu || k > (kind == 0 ? tiles32 : tiles64) ||
+                          (size_t)groups * k * part * sizeof(float) > p.ws_bytes))
+                continue;
+            const int64_t wgs = groups * k;
+            double us;
+            if (kind == 0) {
+                us = 6.5 + (double)((wgs + num_cu - 1) / num_cu) * (((tiles32 + k - 1) / k + 7) / 8) * 1.6 + (k > 1 ? 1.5 + 0.7 * k : 0.0);
+            } else {
+                const int per_cu = kind == 1 || wgs <= num_cu ? 1 : 2;
+                const double tile = kind == 1 ? (wgs * 3 <= num_cu * 2 ? 1.65 : 2.05) : (per_cu == 1 ? 1.38 : 2.1);
+                us = 7.0 + (double)((wgs + num_cu * per_cu - 1) / (num_cu * per_cu)) * ((tiles64 + k - 1) / k) * tile + (k > 1 ? 5.0 + 1.5 * k : 0.0);
+            }
+            if (best_us == 0.0 || us < best_us) {
+                best_us = us;
+                best.waves = waves;
+                best.ksplit = k;
+            }
+        }
+    }
+    return best;
+}
+
+}  // namespace
+
 hipError_t launch_attn_slice(const AttnParams &p_in, hipStream_t s, int num_cu)
 {
-    // One workgroup = NW waves of 32 queries sharing the key tiles.  Slices with few queries (the per-step grids
-    // of Alg. 4 are small) leave most of the chip idle that way: then the keys are split as well -- over
-    // several workgroups per query block if a workspace is registered, else over the waves of 32-query
-    // workgroups.
     AttnParams p = p_in;
-    int qt = 1, nw = 8, ksp = 0;
-    bool wave_split = false;
-    const Tuning tn = tuning();                          // overrides
-    if (tn.attn_waves)                                   // waves per workgroup, 4 or 8
-        nw = tn.attn_waves;
-    if (tn.attn_ksplit)                                  // workgroups per query block
-        ksp = tn.attn_ksplit;
-    if (tn.attn_qt >= 0) {                               // 32-query tiles per wave; 0 = keys over waves
-        wave_split = tn.attn_qt == 0;
-        qt = tn.attn_qt == 2 ? 2 : 1;
-        if (qt == 2)
-            nw = 4;
-    }
     if (p.n_slices < 1)
         p.n_slices = 1;
-    if (p.n_slices > 1)
-        wave_split = false;                            // several slices per launch: the query-block kernel only
-    const int bq = nw * 32 * qt;
+    AttnChoice t = choose_attn(p, num_cu);
+    int qt = 1;
+    const Tuning tn = tuning();                          // overrides
+    if (tn.attn_qt >= 0 || tn.attn_waves || tn.attn_ksplit) {
+        t.waves = tn.attn_qt == 0 ? 0 : tn.attn_qt == 2 ? 4 : tn.attn_waves ? tn.attn_waves : 8;   // 32-query tiles per wave; 0 = keys over waves
+        qt = tn.attn_qt == 2 ? 2 : 1;
+        t.ksplit = tn.attn_ksplit ? tn.attn_ksplit : 1;      // workgroups per query block
+    }
+    const bool keys_over_waves = t.waves == 0;
+    const int bq = keys_over_waves ? 32 : t.waves * 32 * qt;
     const int64_t groups = (int64_t)((p.c + bq - 1) / bq) * p.heads * p.batch * p.n_slices;
-    const bool small_grid = groups * 4 < (int64_t)num_cu * 3;
-    p.ksplit = 1;
-    if (!wave_split && qt == 1 && (small_grid || ksp > 1) && p.ws != nullptr && p.counters != nullptr) {
-        const int nkt = (p.S + BKV - 1) / BKV;
-        int k = ksp > 0 ? ksp : (int)((num_cu + groups - 1) / groups);   // one workgroup per compute unit
-        k = k > 16 ? 16 : k;
-        k = k > nkt ? nkt : k;
-        const size_t need = (size_t)groups * k * (64 + 2) * (64 * nw) * sizeof(float);
-        if (k > 1 && need <= p.ws_bytes && groups <= p.max_groups)
-            p.ksplit = k;
-    }
-    if (wave_split || (small_grid && p.ksplit == 1 && qt == 1 && p.n_slices == 1 && tn.attn_qt < 0)) {
-        const dim3 grid(((p.c + 31) / 32) * p.heads * p.batch), block(256);
-        hipLaunchKernelGGL(attn_slice_ksplit_kernel, grid, block, 0, s, p);
-        return hipGetLastError();
-    }
-    const dim3 grid((unsigned)(groups * p.ksplit)), block(64 * nw);
-    if (qt == 2)
+    const int tiles = keys_over_waves ? (p.S + 31) / 32 : (p.S + BKV - 1) / BKV;
+    p.ksplit = t.ksplit < tiles ? t.ksplit : tiles;
+    const size_t need = (size_t)groups * p.ksplit * (keys_over_waves ? (size_t)KW_PART : (size_t)(64 + 2) * (64 * t.waves)) * sizeof(float);
+    if (p.ksplit > 1 && (qt == 2 || p.ws == nullptr || p.counters == nullptr || need > p.ws_bytes || groups > p.max_groups))
+        p.ksplit = 1;
+    if (groups * p.ksplit >= ((int64_t)1 << 31))
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(groups * p.ksplit)), block(64 * (keys_over_waves ? KW_WAVES : t.waves));
+    if (keys_over_waves)
+        hipLaunchKernelGGL(attn_keys_over_waves_kernel, grid, block, 0, s, p);
+    else if (qt == 2)
         hipLaunchKernelGGL((attn_slice_kernel<2, 4>), grid, block, 0, s, p);
-    else if (nw == 8)
+    else if (t.waves == 8)
         hipLaunchKernelGGL((attn_slice_kernel<1, 8>), grid, block, 0, s, p);
     else
         hipLaunchKernelGGL((attn_slice_kernel<1, 4>), grid, block, 0, s, p);

@@ -292,3 +292,51 @@ def test_attention_bad_arguments():
     with pytest.raises(cf.CommFuseError) as ei:
         cf.attn_slice(cf.attn_desc(2, 0, 1, 1, 128, 128, 64, 0.0), 0, t, t, t, t, None)      # scale must be positive
     assert ei.value.status == cf.CF_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("ksplit", ["1", "2", "5", "16"])
+@pytest.mark.parametrize("shape", ATTN_SHAPES + [(1, 1, 1, 31), (2, 1, 1, 66), (2, 2, 1, 578)])
+def test_attention_keys_over_waves(shape, ksplit):
+    """The kernel whose eight waves split the keys, its keys split over workgroups on top (workspace registered): fewer
+    key tiles than waves, one key more than a round of the waves' tiles, more splits than tiles; one slice per launch, and
+    all slices in one launch through the schedule."""
+    p, B, h, S = shape
+    n = 64
+    dev, host, _ = _problem(730 + S, p, B, h, S, n)
+    scale = 1.0 / np.sqrt(128.0)
+    Qd, Kd, Vd = (H.to_dev(x, "bf16") for x in dev[:3])
+    desc = cf.attn_desc(p, 0, B, h, S, 128, n, scale)
+    c = S // p
+    mc = B * c
+    ref = [oracle.attention_slice(host[0], host[1], host[2], l, p, scale) for l in range(p)]
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device=H.DEV)
+    cf.set_workspace(ws)
+    torch.cuda.synchronize()
+    os.environ["COMMFUSE_ATTN_QT"] = "0"
+    os.environ["COMMFUSE_ATTN_KSPLIT"] = ksplit
+    try:
+        for l in sorted({0, p - 1}):
+            out = torch.full((mc, h * 128), float("nan"), dtype=torch.bfloat16, device=H.DEV)
+            for _ in range(2):                                    # twice: the arrival counters are left at zero
+                cf.attn_slice(desc, l, Qd, Kd, Vd, out, None)
+            torch.cuda.synchronize()
+            got = H.to_host_f64(out)
+            assert not np.isnan(got).any()
+            assert H.rel_err(got, ref[l]) <= TOL_ATTN, f"slice {l}"
+        mk = lambda: torch.zeros((mc, n), dtype=torch.float32, device=H.DEV)
+        Wd = torch.zeros((h * 128, n), dtype=torch.bfloat16, device=H.DEV)
+        attn_all = torch.full((p * mc, h * 128), float("nan"), dtype=torch.bfloat16, device=H.DEV)
+        each, sends, stage = ([mk() for _ in range(p - 1)] for _ in range(3))
+        bufs = cf.make_attn_buffers(Qd, Kd, Vd, Wd, attn_all, mk(), stage, (None, None), (None, None), None, each, sends)
+        st = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        cf.run_attn_schedule(desc, bufs, st, st, cf.CF_PERSISTENT | cf.CF_SERIAL)
+        st.synchronize()
+        got = H.to_host_f64(attn_all)
+        for l in range(p):
+            assert H.rel_err(got[l * mc:(l + 1) * mc], ref[l]) <= TOL_ATTN, f"all slices in one launch, slice {l}"
+    finally:
+        os.environ.pop("COMMFUSE_ATTN_QT", None)
+        os.environ.pop("COMMFUSE_ATTN_KSPLIT", None)
+        torch.cuda.synchronize()
+        cf.set_workspace(None)
