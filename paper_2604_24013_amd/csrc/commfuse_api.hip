@@ -333,7 +333,7 @@ cf_status ag_step_impl(const Resolved &r, int step, const void *shard, const voi
 
 // chunk_elems: elements per (sub-)step; m: sub-steps per hop
 cf_status dp_step_impl(int p, int rank, int step, float *bucket, int64_t chunk_elems, const float *recv,
-                       hipStream_t s, int m = 1, float *land = nullptr)
+                       hipStream_t s, int m = 1)
 {
     if (p < 1)
         return fail(CF_ERR_INVALID_ARG, "p = %d must be >= 1", p);
@@ -350,8 +350,8 @@ cf_status dp_step_impl(int p, int rank, int step, float *bucket, int64_t chunk_e
     if ((reinterpret_cast<uintptr_t>(bucket) | reinterpret_cast<uintptr_t>(recv)) & 3u)
         return fail(CF_ERR_MISALIGNED, "fp32 pointers must be 4-byte aligned");
     const int l = subslice_index(CF_KIND_DP, p, m, rank, step);
-    hipError_t e = cf::launch_dp_reduce(bucket + (int64_t)l * chunk_elems, recv, chunk_elems, s,
-                                        num_cu_of_current_device(), land);
+    float *const dst = bucket + (int64_t)l * chunk_elems;
+    hipError_t e = cf::launch_dp_reduce_segments(&dst, &recv, nullptr, 1, chunk_elems, s);
     if (e != hipSuccess)
         return fail_hip(e, "gradient reduce launch");
     return CF_OK;
@@ -424,7 +424,7 @@ cf_status wgrad_step_impl(const Resolved &r, int step, const void *left, const v
 
 cf_status accumulate(float *dst, const float *src, int64_t elems, hipStream_t s)
 {
-    hipError_t e = cf::launch_dp_reduce(dst, src, elems, s, num_cu_of_current_device());
+    hipError_t e = cf::launch_dp_reduce_segments(&dst, &src, nullptr, 1, elems, s);
     if (e != hipSuccess)
         return fail_hip(e, "accumulate launch");
     return CF_OK;
@@ -1036,21 +1036,26 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         if (cf_status st = check_pair_p(p))
             return st;
         hipError_t e = cf::launch_dp_reduce_multi(static_cast<float *>(b->O) + (int64_t)r.rank * r.mc, srcs, p - 1, r.mc, cs,
-                                                  num_cu_of_current_device(), carried ? lands : nullptr);
+                                                  carried ? lands : nullptr);
         if (e != hipSuccess)
             return fail_hip(e, "gradient reduce launch");
         return CF_OK;
     }
-    if (do_compute && is_dp_kind(kind)) {
-        float *bucket = static_cast<float *>(b->O);
+    if (do_compute && kind == CF_KIND_DP && p > 1 && r.mc > 0) {
+        // ring: every hop adds into a slice of its own, so the adds of the whole rank step are one launch
+        float *dsts[cf::GemmParams::MAX_STEPS], *lands[cf::GemmParams::MAX_STEPS];
+        const float *srcs[cf::GemmParams::MAX_STEPS];
         for (int j = m; j < S; ++j) {
-            const float *recv = carried ? reinterpret_cast<const float *>(stage_of(j)) : static_cast<const float *>(landing(j));
-            cf_status st = kind == CF_KIND_DP_PAIR ? dp_pair_step_impl(p, r.rank, j, bucket, r.mc, recv, cs)
-                                                   : dp_step_impl(p, r.rank, j, bucket, r.mc, recv, cs, m,
-                                                                  carried ? static_cast<float *>(landing(j)) : nullptr);
-            if (st != CF_OK)
-                return st;
+            dsts[j - m] = static_cast<float *>(b->O) + (int64_t)subslice_index(CF_KIND_DP, p, m, r.rank, j) * r.mc;
+            srcs[j - m] = carried ? reinterpret_cast<const float *>(stage_of(j)) : static_cast<const float *>(landing(j));
+            lands[j - m] = static_cast<float *>(landing(j));
+            if ((reinterpret_cast<uintptr_t>(dsts[j - m]) | reinterpret_cast<uintptr_t>(srcs[j - m]) |
+                 reinterpret_cast<uintptr_t>(lands[j - m])) & 3u)
+                return fail(CF_ERR_MISALIGNED, "fp32 pointers must be 4-byte aligned");
         }
+        hipError_t e = cf::launch_dp_reduce_segments(dsts, srcs, carried ? lands : nullptr, S - m, r.mc, cs);
+        if (e != hipSuccess)
+            return fail_hip(e, "gradient reduce launch");
         return CF_OK;
     }
     if (is_dp_kind(kind))

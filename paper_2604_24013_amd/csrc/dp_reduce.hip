@@ -15,49 +15,66 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int DP_THREADS = 256;
 constexpr int DP_UNROLL = 4;
 
+// The slices start wherever a multiple of the slice length falls, so three streams out of four may be 4-byte aligned only.
+// The 16-byte accesses of this architecture need no more than that: a wave then touches one line more per access.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+// All adds of a rank step in ONE launch: segment s adds src[s] into dst[s], `n` elements each; workgroup b works on chunk
+// b % per_seg of segment b / per_seg, U independent vectors per lane and stream in flight.
 // LAND: the delivery carried by the consumer -- src is the neighbour's buffer, and what is read from it is also stored
 // to `land`, this rank's landing buffer: 16 bytes per element (two reads, two writes) where a copy followed by the add
 // moves 20.
-template <bool LAND>
-__global__ __launch_bounds__(DP_THREADS) void dp_reduce_vec_kernel(f32x4_t *__restrict__ dst,
-                                                                  const f32x4_t *__restrict__ src, int64_t n4,
-                                                                  f32x4_t *__restrict__ land)
+struct AddSegments {
+    static constexpr int MAX = 16;
+    float *dst[MAX];
+    const float *src[MAX];
+    float *land[MAX];
+};
+
+template <bool LAND, int T, int U>
+__global__ __launch_bounds__(T) void dp_reduce_kernel(AddSegments a, int64_t n, int per_seg)
 {
     // Every element is touched exactly once: all streams bypass the caches' retention
     // (non-temporal), which measured ~25% faster than cached accesses on MI355X.
-    const int64_t stride = (int64_t)gridDim.x * DP_THREADS;
-    int64_t i = (int64_t)blockIdx.x * DP_THREADS + threadIdx.x;
-    for (; i + (DP_UNROLL - 1) * stride < n4; i += DP_UNROLL * stride) {
-        f32x4_t a[DP_UNROLL], b[DP_UNROLL];
+    const int seg = blockIdx.x / per_seg, chunk = blockIdx.x % per_seg;
+    float *const dst = a.dst[seg];
+    const float *const src = a.src[seg];
+    float *const land = a.land[seg];
+    const int64_t n4 = n / 4;
+    const int64_t base = (int64_t)chunk * T * U + threadIdx.x;
+    f32x4_u *const dst4 = reinterpret_cast<f32x4_u *>(dst);
+    const f32x4_u *const src4 = reinterpret_cast<const f32x4_u *>(src);
+    f32x4_u *const land4 = reinterpret_cast<f32x4_u *>(land);
+    f32x4_u x[U], y[U];
+    if (chunk < per_seg - 1) {                       // (every chunk but the last is whole)
 #pragma unroll
-        for (int u = 0; u < DP_UNROLL; ++u) {
-            a[u] = __builtin_nontemporal_load(&dst[i + u * stride]);
-            b[u] = __builtin_nontemporal_load(&src[i + u * stride]);
+        for (int u = 0; u < U; ++u) {
+            x[u] = __builtin_nontemporal_load(&dst4[base + u * T]);
+            y[u] = __builtin_nontemporal_load(&src4[base + u * T]);
         }
 #pragma unroll
-        for (int u = 0; u < DP_UNROLL; ++u) {
-            __builtin_nontemporal_store(b[u] + a[u], &dst[i + u * stride]);   // "O <- B_in + O"
+        for (int u = 0; u < U; ++u) {
+            __builtin_nontemporal_store(y[u] + x[u], &dst4[base + u * T]);   // "O <- B_in + O"
             if constexpr (LAND)
-                __builtin_nontemporal_store(b[u], &land[i + u * stride]);
+                __builtin_nontemporal_store(y[u], &land4[base + u * T]);
+        }
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t i = base + u * T;
+        if (i < n4) {
+            y[u] = __builtin_nontemporal_load(&src4[i]);
+            __builtin_nontemporal_store(y[u] + __builtin_nontemporal_load(&dst4[i]), &dst4[i]);
+            if constexpr (LAND)
+                __builtin_nontemporal_store(y[u], &land4[i]);
         }
     }
-    for (; i < n4; i += stride) {
-        const f32x4_t b = __builtin_nontemporal_load(&src[i]);
-        __builtin_nontemporal_store(b + __builtin_nontemporal_load(&dst[i]), &dst[i]);
-        if constexpr (LAND)
-            __builtin_nontemporal_store(b, &land[i]);
-    }
-}
-
-__global__ __launch_bounds__(DP_THREADS) void dp_reduce_scalar_kernel(float *__restrict__ dst,
-                                                                     const float *__restrict__ src, int64_t n,
-                                                                     float *__restrict__ land)
-{
-    const int64_t stride = (int64_t)gridDim.x * DP_THREADS;
-    for (int64_t i = (int64_t)blockIdx.x * DP_THREADS + threadIdx.x; i < n; i += stride) {
+    if (chunk == per_seg - 1 && (int)threadIdx.x < (int)(n - n4 * 4)) {          // the last elements of the segment
+        const int64_t i = n4 * 4 + threadIdx.x;
         const float b = src[i];
         dst[i] = b + dst[i];
-        if (land != nullptr)
+        if constexpr (LAND)
             land[i] = b;
     }
 }
@@ -72,23 +89,25 @@ struct AddBatch {
 
 // LAND: as above -- source s is also stored to land[s].
 template <bool LAND>
-__global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_kernel(f32x4_t *__restrict__ dst, AddBatch ab, int n_src,
-                                                                    int64_t n4, AddBatch lb)
+__global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_kernel(float *__restrict__ dst, AddBatch ab, int n_src,
+                                                                    int64_t n, AddBatch lb)
 {
     constexpr int U = 2;                             // vectors per lane: (n_src + 1) * U loads in flight
+    const int64_t n4 = n / 4;
     const int64_t base = (int64_t)blockIdx.x * DP_THREADS * U + threadIdx.x;
-    f32x4_t a[U];
+    f32x4_u *const dst4 = reinterpret_cast<f32x4_u *>(dst);
+    f32x4_u a[U];
 #pragma unroll
     for (int u = 0; u < U; ++u)
         if (base + u * DP_THREADS < n4)
-            a[u] = __builtin_nontemporal_load(&dst[base + u * DP_THREADS]);
+            a[u] = __builtin_nontemporal_load(&dst4[base + u * DP_THREADS]);
     for (int s = 0; s < n_src; ++s) {
-        const f32x4_t *__restrict__ src = reinterpret_cast<const f32x4_t *>(ab.src[s]);
-        f32x4_t *__restrict__ land = reinterpret_cast<f32x4_t *>(const_cast<float *>(lb.src[s]));
+        const f32x4_u *__restrict__ src = reinterpret_cast<const f32x4_u *>(ab.src[s]);
+        f32x4_u *__restrict__ land = reinterpret_cast<f32x4_u *>(const_cast<float *>(lb.src[s]));
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (base + u * DP_THREADS < n4) {
-                const f32x4_t b = __builtin_nontemporal_load(&src[base + u * DP_THREADS]);
+                const f32x4_u b = __builtin_nontemporal_load(&src[base + u * DP_THREADS]);
                 a[u] = b + a[u];
                 if constexpr (LAND)
                     __builtin_nontemporal_store(b, &land[base + u * DP_THREADS]);
@@ -97,22 +116,17 @@ __global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_kernel(f32x4_t *__
 #pragma unroll
     for (int u = 0; u < U; ++u)
         if (base + u * DP_THREADS < n4)
-            __builtin_nontemporal_store(a[u], &dst[base + u * DP_THREADS]);
-}
-
-__global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_scalar_kernel(float *__restrict__ dst, AddBatch ab, int n_src,
-                                                                           int64_t first, int64_t n, AddBatch lb, bool land)
-{
-    const int64_t stride = (int64_t)gridDim.x * DP_THREADS;
-    for (int64_t i = first + (int64_t)blockIdx.x * DP_THREADS + threadIdx.x; i < n; i += stride) {
-        float a = dst[i];
+            __builtin_nontemporal_store(a[u], &dst4[base + u * DP_THREADS]);
+    if (blockIdx.x == gridDim.x - 1 && (int)threadIdx.x < (int)(n - n4 * 4)) {
+        const int64_t i = n4 * 4 + threadIdx.x;
+        float x = dst[i];
         for (int s = 0; s < n_src; ++s) {
             const float b = ab.src[s][i];
-            a = b + a;
-            if (land)
+            x = b + x;
+            if constexpr (LAND)
                 const_cast<float *>(lb.src[s])[i] = b;
         }
-        dst[i] = a;
+        dst[i] = x;
     }
 }
 
@@ -157,54 +171,66 @@ __global__ __launch_bounds__(256) void fill_ff_kernel(unsigned *dst, size_t nwor
 
 }  // namespace
 
-hipError_t launch_dp_reduce(float *dst, const float *src, int64_t n, hipStream_t s, int num_cu, float *land)
+hipError_t launch_dp_reduce_segments(float *const *dst, const float *const *src, float *const *land, int n_seg, int64_t n,
+                                     hipStream_t s)
 {
-    if (n <= 0)
+    if (n <= 0 || n_seg <= 0)
         return hipSuccess;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src) |
-                           reinterpret_cast<uintptr_t>(land)) & 15u) == 0;
-    const int64_t n4 = aligned ? n / 4 : 0;
-    if (n4 > 0) {
-        // one workgroup per DP_THREADS * DP_UNROLL vectors: a grid that covers the slice once measured
-        // faster than a grid-stride loop over a chip-sized grid (5.9 vs 4.4 TB/s at 125M elements)
-        int64_t want = (n4 + (int64_t)DP_THREADS * DP_UNROLL - 1) / ((int64_t)DP_THREADS * DP_UNROLL);
-        const int64_t cap = (int64_t)1 << 30;
-        (void)num_cu;
-        const int blocks = (int)(want < cap ? want : cap);
-        if (land != nullptr)
-            hipLaunchKernelGGL(dp_reduce_vec_kernel<true>, dim3(blocks), dim3(DP_THREADS), 0, s, reinterpret_cast<f32x4_t *>(dst),
-                               reinterpret_cast<const f32x4_t *>(src), n4, reinterpret_cast<f32x4_t *>(land));
+    // A grid that covers the slices once measured faster than a grid-stride loop over a chip-sized grid (5.9 vs 4.4 TB/s at
+    // 125M elements).  Seven segments landing their arrivals, buffers in turn, TB/s for (threads, vectors per lane):
+    //   125M elements: (64, 1) 6.1, (256, 1) 5.9, (256, 4) 5.4, (64, 2) 5.2;   10M: 6.25, 6.1, 6.2, 5.7;
+    //   3M: 5.5, 5.8, 5.9, 6.2;   20M, segments off the 16-byte grid: 5.5, 5.7, 5.6, 5.1.
+    uintptr_t bits = 0;
+    for (int i = 0; i < n_seg; ++i)
+        bits |= reinterpret_cast<uintptr_t>(dst[i]) | reinterpret_cast<uintptr_t>(src[i]) |
+                (land != nullptr ? reinterpret_cast<uintptr_t>(land[i]) : 0);
+    const bool long_segments = n >= (int64_t)8 << 20, aligned = (bits & 15u) == 0;
+    const int threads = long_segments && aligned ? 64 : 256;
+    const int per_wg = threads * (long_segments ? 1 : 4);
+    const int64_t per_seg = (n / 4 + per_wg) / per_wg;
+    int at = 0;
+    while (at < n_seg) {                             // (as many segments per launch as its arguments and its grid take)
+        int take = n_seg - at < AddSegments::MAX ? n_seg - at : AddSegments::MAX;
+        while (take > 1 && per_seg * take >= ((int64_t)1 << 31))
+            --take;
+        if (per_seg * take >= ((int64_t)1 << 31))
+            return hipErrorInvalidValue;
+        AddSegments a = {};
+        for (int i = 0; i < take; ++i) {
+            a.dst[i] = dst[at + i];
+            a.src[i] = src[at + i];
+            a.land[i] = land != nullptr ? land[at + i] : nullptr;
+        }
+        const dim3 grid((unsigned)(per_seg * take)), block(threads);
+#define CF_ADD(T, U)                                                                                          \
+    do {                                                                                                      \
+        if (land != nullptr)                                                                                  \
+            hipLaunchKernelGGL((dp_reduce_kernel<true, T, U>), grid, block, 0, s, a, n, (int)per_seg);        \
+        else                                                                                                  \
+            hipLaunchKernelGGL((dp_reduce_kernel<false, T, U>), grid, block, 0, s, a, n, (int)per_seg);       \
+    } while (0)
+        if (threads == 64)
+            CF_ADD(64, 1);
+        else if (long_segments)
+            CF_ADD(256, 1);
         else
-            hipLaunchKernelGGL(dp_reduce_vec_kernel<false>, dim3(blocks), dim3(DP_THREADS), 0, s, reinterpret_cast<f32x4_t *>(dst),
-                               reinterpret_cast<const f32x4_t *>(src), n4, static_cast<f32x4_t *>(nullptr));
+            CF_ADD(256, 4);
+#undef CF_ADD
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
-    }
-    const int64_t done = n4 * 4;
-    if (done < n) {
-        const int64_t rest = n - done;
-        int64_t want = (rest + DP_THREADS - 1) / DP_THREADS;
-        const int64_t cap = (int64_t)num_cu * 8;
-        const int blocks = (int)(want < cap ? want : cap);
-        hipLaunchKernelGGL(dp_reduce_scalar_kernel, dim3(blocks), dim3(DP_THREADS), 0, s, dst + done, src + done, rest,
-                           land != nullptr ? land + done : nullptr);
-        return hipGetLastError();
+        at += take;
     }
     return hipSuccess;
 }
 
-hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src, int64_t n, hipStream_t s, int num_cu,
-                                  float *const *land)
+hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src, int64_t n, hipStream_t s, float *const *land)
 {
     if (n <= 0 || n_src <= 0)
         return hipSuccess;
-    uintptr_t bits = reinterpret_cast<uintptr_t>(dst);
-    for (int i = 0; i < n_src; ++i)
-        bits |= reinterpret_cast<uintptr_t>(src[i]) | (land != nullptr ? reinterpret_cast<uintptr_t>(land[i]) : 0);
-    if (n_src > AddBatch::MAX || (bits & 15u) != 0) {        // one pass per source: the same additions in the same order
+    if (n_src > AddBatch::MAX) {                     // one pass per source: the same additions in the same order
         for (int i = 0; i < n_src; ++i) {
-            hipError_t e = launch_dp_reduce(dst, src[i], n, s, num_cu, land != nullptr ? land[i] : nullptr);
+            hipError_t e = launch_dp_reduce_segments(&dst, &src[i], land != nullptr ? &land[i] : nullptr, 1, n, s);
             if (e != hipSuccess)
                 return e;
         }
@@ -215,28 +241,15 @@ hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src
         ab.src[i] = src[i];
         lb.src[i] = land != nullptr ? land[i] : nullptr;
     }
-    const int64_t n4 = n / 4;
-    if (n4 > 0) {
-        const int64_t per_wg = (int64_t)DP_THREADS * 2;
-        const int64_t want = (n4 + per_wg - 1) / per_wg;
-        if (want >= ((int64_t)1 << 31))
-            return hipErrorInvalidValue;
-        if (land != nullptr)
-            hipLaunchKernelGGL(dp_reduce_multi_kernel<true>, dim3((unsigned)want), dim3(DP_THREADS), 0, s,
-                               reinterpret_cast<f32x4_t *>(dst), ab, n_src, n4, lb);
-        else
-            hipLaunchKernelGGL(dp_reduce_multi_kernel<false>, dim3((unsigned)want), dim3(DP_THREADS), 0, s,
-                               reinterpret_cast<f32x4_t *>(dst), ab, n_src, n4, lb);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-    }
-    if (n4 * 4 < n) {
-        hipLaunchKernelGGL(dp_reduce_multi_scalar_kernel, dim3(1), dim3(DP_THREADS), 0, s, dst, ab, n_src, n4 * 4, n, lb,
-                           land != nullptr);
-        return hipGetLastError();
-    }
-    return hipSuccess;
+    const int64_t per_wg = (int64_t)DP_THREADS * 2;
+    const int64_t want = (n / 4 + per_wg) / per_wg;
+    if (want >= ((int64_t)1 << 31))
+        return hipErrorInvalidValue;
+    if (land != nullptr)
+        hipLaunchKernelGGL(dp_reduce_multi_kernel<true>, dim3((unsigned)want), dim3(DP_THREADS), 0, s, dst, ab, n_src, n, lb);
+    else
+        hipLaunchKernelGGL(dp_reduce_multi_kernel<false>, dim3((unsigned)want), dim3(DP_THREADS), 0, s, dst, ab, n_src, n, lb);
+    return hipGetLastError();
 }
 
 bool copy_batch_takes(const void *const *src, void *const *dst, int n, size_t bytes)
