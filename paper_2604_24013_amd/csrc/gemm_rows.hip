@@ -18,9 +18,8 @@
 //    stored on by the threads that read it (reduce-scatter) or by extra workgroups (all-gather: the slices);
 //  * where even that leaves compute units idle and a workspace is there, KSPLIT workgroups share a tile: partial tiles and
 //    an arrival counter with the device-coherent cache policy, summed in split order by the last to arrive.
-// Measured (one step, B_in added; us, before = 128 x 128 tiles): 8 x 4096 x 1376 bf16 18.1 -> 4.8 (2.4 TB/s of W, of which
-// 2.5 us are the launch itself), 8 x 8192 x 3584 24.7 -> 13.4 (4.4 TB/s), 128 x 8192 x 3584 34 -> 18.7, 128 x 256 x 512 fp32
-// 16.2 -> 4.3; eight steps of 8 x 1536 x 4096 packed into one launch 42.5 -> 8.6.
+// Measured (one step, B_in added; us, before = 128 x 128 tiles): 8 x 4096 x 1376 bf16 18.1 -> 4.4 (an empty kernel: 2.25),
+// 8 x 8192 x 3584 24.7 -> 13.4 (4.4 TB/s of W), 128 x 8192 x 3584 34 -> 18.7, 128 x 256 x 512 fp32 16.2 -> 3.9; eight steps of 8 x 1536 x 4096 packed into one launch 42.5 -> 8.6.
 #include "cf_internal.h"
 
 namespace cf {
@@ -36,22 +35,38 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 constexpr unsigned OOB = 0x80000000u;                // byte offset beyond any buffer this kernel accepts
 constexpr int COHERENT = 1 | 16;                     // buffer cache-policy bits sc0 | sc1
 
+// Two sizes of the kernel argument: one segment (a single step: every pointer is a scalar, and a short argument is
+// cheaper to enqueue), or the steps of a rank step.
+template <int SEG>
 struct RowsParams {
-    static constexpr int MAX_SEG = GemmParams::MAX_STEPS;
+    static constexpr int MORE = SEG == 1 ? 1 : GemmParams::MAX_RECV_MORE;
     const void *W;
     int64_t lda, ldw, ldo;
     int seg_rows, n_seg, N, K;                       // rows per segment (step), segments
     int tiles_n, tiles_r, ksplit, copy_wgs;
     float *ws;
     unsigned *counters;
-    const void *A[MAX_SEG];
-    const float *recv[MAX_SEG];                      // B_in of the segment (nullable), added to the product
-    float *land[MAX_SEG];                            // nullable: where B_in (copy_wgs == 0) or the slice A lands
-    void *out[MAX_SEG];
+    const void *A[SEG];
+    const float *recv[SEG];                          // B_in of the segment (nullable), added to the product
+    float *land[SEG];                                // nullable: where B_in (copy_wgs == 0) or the slice A lands
+    void *out[SEG];
     int n_more;                                      // further partials of the LAST segment, added after its recv
-    const float *more[GemmParams::MAX_RECV_MORE];
-    float *more_land[GemmParams::MAX_RECV_MORE];
+    const float *more[MORE];
+    float *more_land[MORE];
 };
+
+// Entry `s` (different from lane to lane) of a pointer table in the kernel argument: the whole table comes in through the
+// scalar cache and the lane picks its entry.  Indexed directly it would be a vector load from the argument's memory, one
+// trip more in front of the first operand load.
+template <int SEG, typename T>
+__device__ __forceinline__ T pick(T const (&table)[SEG], int s)
+{
+    T v = table[0];
+#pragma unroll
+    for (int i = 1; i < SEG; ++i)
+        v = s == i ? table[i] : v;
+    return v;
+}
 
 // Wave-wide 16-byte-per-lane loads straight into LDS (lane L lands at lds_addr + 16 L), awaited by the caller (vmcnt).
 __device__ __forceinline__ void direct_load_16(i32x4_t rsrc, unsigned voffset, int soffset, unsigned lds_addr)
@@ -93,8 +108,8 @@ __device__ __forceinline__ void wait_vmcnt()
 template <int MF, int NC, int NW>
 constexpr int D_ = 160 / (NW * 2 * (MF + NC)) < 4 ? 160 / (NW * 2 * (MF + NC)) : 4;
 
-template <bool BF16, bool KN, int MF, int NC, bool OUT_BF16, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams P)
+template <bool BF16, bool KN, int MF, int NC, bool OUT_BF16, int NW, int SEG>
+__global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams<SEG> P)
 {
     constexpr int ES = BF16 ? 2 : 4;
     constexpr int KSL = 128 / ES;                                    // k values of a slice
@@ -114,7 +129,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams P)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int R = P.seg_rows * P.n_seg;
+    const int R = P.seg_rows * (SEG == 1 ? 1 : P.n_seg);
+    auto seg_of = [&](int r) { return SEG == 1 ? 0 : r / P.seg_rows; };
     const int tiles = P.tiles_n * P.tiles_r;
 
     // extra workgroups: the slices of an all-gather on their way to the landing buffers
@@ -122,7 +138,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams P)
         const int row16 = P.K * ES / 16;                             // 16-byte chunks per row
         const int64_t per_seg = (int64_t)P.seg_rows * row16;
         for (int64_t i = (int64_t)c0 * (64 * NW) + tid; i < per_seg * P.n_seg; i += (int64_t)P.copy_wgs * (64 * NW)) {
-            const int s = (int)(i / per_seg);
+            const int s = SEG == 1 ? 0 : (int)(i / per_seg);
             const int64_t in = i - s * per_seg;
             const int64_t row = in / row16, off = row * P.lda * ES + (in - row * row16) * 16;
             if (P.land[s] != nullptr)
@@ -141,20 +157,24 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams P)
 
     // (segment, row) of the output pieces this thread finishes, and their B_in, requested before anything else
     int64_t ooff[QT];
-    int oseg[QT];
+    int oseg[QT];                                                    // -1: nothing to finish
+    const float *orecv[QT];
     f32x4_t rv[QT];
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
         const int q = tid + u * 64 * NW;
         const int r = r0 + q / (TN / 4), n = n0 + (q % (TN / 4)) * 4;
         oseg[u] = -1;
+        ooff[u] = 0;
+        orecv[u] = nullptr;
         rv[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         if (q < Q && r < R && n < P.N) {
-            const int s = r / P.seg_rows;
+            const int s = seg_of(r);
             oseg[u] = s;
             ooff[u] = (int64_t)(r - s * P.seg_rows) * P.ldo + n;
-            if (P.recv[s] != nullptr)
-                rv[u] = *reinterpret_cast<const f32x4_t *>(P.recv[s] + ooff[u]);
+            orecv[u] = pick(P.recv, s);
+            if (orecv[u] != nullptr)
+                rv[u] = *reinterpret_cast<const f32x4_t *>(orecv[u] + ooff[u]);
         }
     }
 
@@ -172,8 +192,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams P)
         for (int f = 0; f < MF; ++f) {
             int r = r0 + f * 16 + row;
             r = r < R ? r : R - 1;                                   // (a row beyond the last only feeds sums nobody stores)
-            const int s = r / P.seg_rows;
-            arow[f][i] = static_cast<const char *>(P.A[s]) + (int64_t)(r - s * P.seg_rows) * P.lda * ES;
+            const int s = seg_of(r);
+            arow[f][i] = static_cast<const char *>(pick(P.A, s)) + (int64_t)(r - s * P.seg_rows) * P.lda * ES;
         }
     }
     const unsigned w_bytes = (unsigned)((KN ? (int64_t)(P.K - 1) * P.ldw + P.N : (int64_t)(P.N - 1) * P.ldw + P.K) * ES);
@@ -396,9 +416,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams P)
         const int s = oseg[u];
         if (s < 0)
             continue;
-        if (P.recv[s] != nullptr) {
-            if (P.copy_wgs == 0 && P.land[s] != nullptr)
-                *reinterpret_cast<f32x4_t *>(P.land[s] + ooff[u]) = rv[u];
+        if (orecv[u] != nullptr) {
+            if (P.copy_wgs == 0)
+                if (float *const land = pick(P.land, s))
+                    *reinterpret_cast<f32x4_t *>(land + ooff[u]) = rv[u];
             if (P.n_more > 0 && s == P.n_seg - 1)                    // the pairwise schedule's arrivals, in round order
                 for (int i = 0; i < P.n_more; ++i) {
                     const f32x4_t t = *reinterpret_cast<const f32x4_t *>(P.more[i] + ooff[u]);
@@ -413,18 +434,18 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams P)
 #pragma unroll
             for (int x = 0; x < 4; ++x)
                 h[x] = static_cast<__bf16>(sum[u][x]);
-            *reinterpret_cast<bf16x4_t *>(static_cast<__bf16 *>(P.out[s]) + ooff[u]) = h;
+            *reinterpret_cast<bf16x4_t *>(static_cast<__bf16 *>(pick(P.out, s)) + ooff[u]) = h;
         } else {
-            *reinterpret_cast<f32x4_t *>(static_cast<float *>(P.out[s]) + ooff[u]) = sum[u];
+            *reinterpret_cast<f32x4_t *>(static_cast<float *>(pick(P.out, s)) + ooff[u]) = sum[u];
         }
     }
 }
 
-template <bool BF16, bool KN, int MF, int NC, bool OUT_BF16, int NW>
-hipError_t launch_shape(const RowsParams &p, hipStream_t s)
+template <bool BF16, bool KN, int MF, int NC, bool OUT_BF16, int NW, int SEG>
+hipError_t launch_shape(const RowsParams<SEG> &p, hipStream_t s)
 {
     const dim3 grid((unsigned)(p.tiles_n * p.tiles_r * p.ksplit + p.copy_wgs)), block(64 * NW);
-    hipLaunchKernelGGL((gemm_rows_kernel<BF16, KN, MF, NC, OUT_BF16, NW>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((gemm_rows_kernel<BF16, KN, MF, NC, OUT_BF16, NW, SEG>), grid, block, 0, s, p);
     return hipGetLastError();
 }
 
@@ -432,8 +453,8 @@ struct RowsShape {
     int mf = 0, nc = 0, ks = 1;                      // mf == 0: not for this kernel
 };
 
-template <bool BF16, bool OUT_BF16>
-hipError_t launch_any(const RowsParams &p, bool w_kn, RowsShape t, hipStream_t s)
+template <bool BF16, bool OUT_BF16, int SEG>
+hipError_t launch_any(const RowsParams<SEG> &p, bool w_kn, RowsShape t, hipStream_t s)
 {
 #define CF_ROWS(MF_, NC_, NW_)                                                                                      \
     if (t.mf == MF_ && t.nc == NC_) {                                                                               \
@@ -505,9 +526,10 @@ bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
     return 1.5 + rounds * (3.6 + 0.27 * ((p.K + 63) / 64)) < gemm_bf16_tile_us(p, num_cu);
 }
 
-hipError_t launch_gemm_rows(const GemmParams &g, bool bf16, bool w_kn, bool out_bf16, hipStream_t s, int num_cu)
+template <int SEG>
+static hipError_t launch_segments(const GemmParams &g, bool bf16, bool w_kn, bool out_bf16, hipStream_t s, int num_cu)
 {
-    RowsParams p = {};
+    RowsParams<SEG> p;
     p.W = g.W;
     p.lda = g.lda;
     p.ldw = g.ldw;
@@ -517,17 +539,18 @@ hipError_t launch_gemm_rows(const GemmParams &g, bool bf16, bool w_kn, bool out_
     p.N = g.N;
     p.K = g.K;
     bool lands_slice = false;
-    for (int j = 0; j < p.n_seg; ++j) {
-        p.A[j] = g.n_steps > 0 ? g.A_step[j] : g.A;
-        p.recv[j] = g.n_steps > 0 ? g.recv_step[j] : g.recv;
-        p.out[j] = g.n_steps > 0 ? g.out_step[j] : g.out;
-        p.land[j] = g.n_steps > 0 ? static_cast<float *>(g.land_step[j]) : nullptr;
+    for (int j = 0; j < SEG; ++j) {
+        const bool in = j < p.n_seg;
+        p.A[j] = !in ? nullptr : g.n_steps > 0 ? g.A_step[j] : g.A;
+        p.recv[j] = !in ? nullptr : g.n_steps > 0 ? g.recv_step[j] : g.recv;
+        p.out[j] = !in ? nullptr : g.n_steps > 0 ? g.out_step[j] : g.out;
+        p.land[j] = in && g.n_steps > 0 ? static_cast<float *>(g.land_step[j]) : nullptr;
         lands_slice = lands_slice || (p.land[j] != nullptr && p.recv[j] == nullptr);
     }
     p.n_more = g.n_recv_more;
-    for (int i = 0; i < p.n_more; ++i) {
-        p.more[i] = g.recv_more[i];
-        p.more_land[i] = g.land_more[i];
+    for (int i = 0; i < RowsParams<SEG>::MORE; ++i) {
+        p.more[i] = i < p.n_more ? g.recv_more[i] : nullptr;
+        p.more_land[i] = i < p.n_more ? g.land_more[i] : nullptr;
     }
     const int64_t rows = (int64_t)p.seg_rows * p.n_seg;
     const RowsShape t = choose_shape(rows, p.N, p.K, bf16, w_kn, num_cu);
@@ -540,6 +563,7 @@ hipError_t launch_gemm_rows(const GemmParams &g, bool bf16, bool w_kn, bool out_
         p.ksplit = 1;
     p.ws = g.ws;
     p.counters = g.counters;
+    p.copy_wgs = 0;
     if (lands_slice) {
         const int64_t chunks = rows * p.K * (bf16 ? 2 : 4) / 16;
         const int64_t want = (chunks + 2047) / 2048;
@@ -548,6 +572,13 @@ hipError_t launch_gemm_rows(const GemmParams &g, bool bf16, bool w_kn, bool out_
     if (!bf16)
         return launch_any<false, false>(p, w_kn, t, s);
     return out_bf16 ? launch_any<true, true>(p, w_kn, t, s) : launch_any<true, false>(p, w_kn, t, s);
+}
+
+hipError_t launch_gemm_rows(const GemmParams &g, bool bf16, bool w_kn, bool out_bf16, hipStream_t s, int num_cu)
+{
+    if (g.n_steps == 0 && g.n_recv_more <= RowsParams<1>::MORE)
+        return launch_segments<1>(g, bf16, w_kn, out_bf16, s, num_cu);
+    return launch_segments<GemmParams::MAX_STEPS>(g, bf16, w_kn, out_bf16, s, num_cu);
 }
 
 }  // namespace cf
