@@ -349,11 +349,9 @@ enum {
                             tile's part of it to the landing buffer beside its GEMM (packed partial sums,
                             ldo == n).  Otherwise (all-gather: k not a multiple of 64; the other kinds) the
                             flag changes nothing: the deliveries are enqueued in front.
-                            With CF_FUSED_COPY (CF_KIND_RS_PAIR) and a registered workspace: the work items
-                            of step t-1 land the arrival of round t (peer_stage[t-1] -> recv_each[t-1]), each
-                            its own output tile's part, and count the tile up; the step that sums the
-                            arrivals waits per tile (bounded spin: commfuse_device_status reports a
-                            time-out).  Same sums, bit for bit.  Without a workspace the flag changes nothing.
+                            With CF_FUSED_COPY (CF_KIND_RS_PAIR): one pass in front of the launch reads all arrivals
+                            from the partners' buffers (peer_stage), lands them (recv_each) and leaves their sum in
+                            O, which the last step adds to its product.  Same sums, bit for bit.
                             Where a rank step has few rows in all (decoded tokens; the kernel that packs the rows
                             of every step into one launch) every kind's deliveries are carried, whatever k.
                             Not with CF_DEVICE_WAIT.                                                  */
@@ -450,8 +448,7 @@ cf_status commfuse_run_attn_schedule(const cf_attn_desc *desc, const cf_attn_buf
                                      void *copy_stream, uint32_t flags);
 
 /* Synchronises `hip_stream` and reports whether any step kernel since the last call gave up a
- * bounded device-side wait -- CF_DEVICE_WAIT, or CF_KIND_RS_PAIR with CF_PERSISTENT | CF_FUSED_COPY -- (CF_ERR_HIP;
- * the status word in the workspace is cleared).  CF_OK if none did
+ * bounded device-side wait (CF_DEVICE_WAIT; CF_ERR_HIP, the status word in the workspace is cleared).  CF_OK if none did
  * or no workspace is registered.  This is the one entry point that synchronises. */
 cf_status commfuse_device_status(void *hip_stream);
 

@@ -22,6 +22,7 @@ struct GemmParams {
     int n_recv_more = 0;
     float *land_more[MAX_RECV_MORE] = {};   // few-rows kernel only: where recv_more[i] is stored on to (nullable)
     int pf_lead = 16;    // B_in prefetch: k-tiles before the end of the k loop at which it is issued (0 = off)
+    bool recv_in_epilogue = false;   // persistent mode: B_in is never streamed through LDS (few steps of the launch have one)
     bool stream_recv = true;   // 256x256 tile: B_in lands in LDS under the main loop and is added in mid-sum (set by the launcher)
     void *out = nullptr;
     int64_t lda = 0, ldw = 0, ldo = 0;
@@ -62,18 +63,11 @@ struct GemmParams {
     // (same layout as A_step[s]) by one of the workgroups that load it.  Either way the emulated transfer happens
     // inside the kernel, under its main loop.  Null = the operand is already where recv_step[s] / A_step[s] points.
     void *land_step[MAX_STEPS] = {};
-    // Pairwise schedule, the deliveries carried by the launch: every work item of step s, once its own output tile is
-    // stored, copies that tile's part of tail_src[s] (the arrival that travels while step s computes, in the sender's
-    // buffer) to tail_dst[s] (its landing buffer; both laid out like the output), written through to memory, and then
-    // counts tile_ready[tile] up.  The last step's work item waits (bounded by spin_limit; a time-out sets bit 0 of
-    // *status) until its tile's count reaches ready_count, then reads recv_step / recv_more -- the landing buffers --
-    // past the caches.  tile_ready holds max_tiles words, all zero at launch.  With tile_ready == nullptr nothing is
-    // counted and nobody waits: a reduce-scatter step whose B_in is loaded in its epilogue (recv_step[s] = the sender's
-    // buffer) lands that same B_in beside its GEMM this way (tail_src[s] = recv_step[s]).
+    // A reduce-scatter step whose B_in is loaded in its epilogue (recv_step[s] = the sender's buffer) lands that same B_in
+    // beside its GEMM: every work item of step s copies its output tile's part of tail_src[s] (= recv_step[s]) to
+    // tail_dst[s], the landing buffer (both laid out like the output), written through to memory.  Nobody waits for it.
     const float *tail_src[MAX_STEPS] = {};
     float *tail_dst[MAX_STEPS] = {};
-    unsigned *tile_ready = nullptr;
-    int ready_count = 0;
     const void *cp_src = nullptr;
     void *cp_dst = nullptr;
     size_t cp_bytes = 0;
@@ -145,13 +139,9 @@ TileChoice choose_tile_bf16(int M, int N, int K, int num_cu);
 hipError_t launch_gemm_bf16(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, int num_cu);
 // True if launch_gemm_bf16 would run the kernel that honours GemmParams::recv_more for these operands.
 bool gemm_bf16_takes_recv_list(const GemmParams &p, bool w_kn);
-// Output tiles per step if launch_gemm_bf16 can run this persistent launch with GemmParams::tail_src / tile_ready (the
-// arrivals of the pairwise schedule landed by the work items of the steps before the one that sums them), else 0.
-// The caller provides that many zeroed counters.
-int gemm_bf16_tiles_landing_arrivals(const GemmParams &p, bool w_kn, int num_cu);
 // True if a persistent reduce-scatter launch that does NOT stream B_in (gemm_bf16_carries_delivery says no) can still
 // carry its deliveries: B_in read from the sender's buffer in the epilogue and landed by the same work item beside
-// its GEMM (GemmParams::tail_src without counters).  fp32 partial sums, direct-to-LDS kernel.
+// its GEMM (GemmParams::tail_src).  fp32 partial sums, direct-to-LDS kernel.
 bool gemm_bf16_lands_beside(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu);
 // True if launch_gemm_bf16 would run this persistent launch (reduce_scatter: its steps add a received partial;
 // else an all-gather's) on a kernel that honours GemmParams::land_step (the delivery carried by the consumer)
@@ -183,7 +173,7 @@ hipError_t launch_dp_reduce_segments(float *const *dst, const float *const *src,
 // dst <- (((dst + src[0]) + src[1]) + ...) over n elements, one pass when n_src <= 15 (else one pass per source: same
 // additions, same order, same bits)
 hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src, int64_t n, hipStream_t s,
-                                  float *const *land = nullptr);
+                                  float *const *land = nullptr, bool init = false);   // init: dst <- (src[0] + src[1]) + ...
 // n (<= 16) copies of `bytes` bytes each in one launch; copy_batch_takes says whether the arguments qualify
 // (16-byte aligned pointers, bytes a multiple of 16), else the caller copies one by one
 bool copy_batch_takes(const void *const *src, void *const *dst, int n, size_t bytes);

@@ -923,26 +923,17 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // the add's 12; pairwise, p - 1 arrivals in one pass: 8 p instead of 12 p - 4).
     if ((flags & CF_FUSED_COPY) && is_dp_kind(kind) && do_copy && do_compute && slot_bytes > 0)
         carried = true;
-    // The pairwise reduce-scatter with CF_FUSED_COPY: the arrival of round t travels while step t - 1 computes, so the
-    // work items of step t - 1 land it -- each its own output tile's part, from the partner's buffer to the landing
-    // buffer, after its own stores -- and count the tile up; the last step's work item waits for its tile's count
-    // before it sums the arrivals.  Needs the registered workspace (a counter per output tile, the status word).
-    unsigned *pair_ready = nullptr, *pair_status = nullptr;
-    int pair_tiles = 0;
+    // The pairwise reduce-scatter with CF_FUSED_COPY: in one pass in front of the launch all arrivals are read from the
+    // partners' buffers, landed and summed into O, and the last step adds that one sum to its product: ((r_1 + r_2) + ...) +
+    // product, the same order of additions as the incremental form.  All compute units share that sum, where the
+    // epilogues of the last step's few tiles would take it alone, at the end (landing the arrivals tile by tile under the
+    // earlier steps and summing them there measured, us, against this: 6 ranks 390 x 2088 x 1096 54 -> 42, 8 ranks 512 x 4096 x
+    // 1376 118 -> 82, 1024 x 8192 x 3584 481 -> 467).
+    bool pair_front = false;
     if (!few_rows && (flags & CF_FUSED_COPY) && kind == CF_KIND_RS_PAIR && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
-        r.n > 0 && r.k > 0) {
-        cf::GemmParams probe;
-        probe.W = b->W;
-        fill_shape(probe, r);
-        probe.n_steps = S;
-        pair_tiles = cf::gemm_bf16_tiles_landing_arrivals(probe, r.w_kn, num_cu_of_current_device());
-        const Workspace ws = workspace_for(cs);
-        if (pair_tiles > 0 && ws.ptr != nullptr && ws.bytes >= WS_COUNTER_BYTES &&
-            (size_t)pair_tiles <= WS_TILE_COUNTER_BYTES / sizeof(unsigned)) {
-            pair_ready = static_cast<unsigned *>(ws.ptr);
-            pair_status = reinterpret_cast<unsigned *>(static_cast<char *>(ws.ptr) + WS_STATUS_OFFSET);
-            carried = true;
-        }
+        r.n > 0 && r.k > 0 && cf::tuning().carry != 0) {
+        pair_front = true;
+        carried = true;
     }
     // Without CF_SERIAL (reduce-scatter and all-gather on two streams): the rank step as a few launches, each a group
     // of consecutive (sub-)steps that fills the chip about once, and the deliveries of a group copied on the copy
@@ -1069,6 +1060,17 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                                                    : wgrad_step_impl(all, 0, b->W, moving, static_cast<float *>(b->O), cs))
             return st;
     }
+    if (pair_front) {
+        const float *srcs[cf::GemmParams::MAX_STEPS];
+        float *lands[cf::GemmParams::MAX_STEPS];
+        for (int t = 0; t < p - 1; ++t) {
+            srcs[t] = static_cast<const float *>(b->peer_stage[t]);
+            lands[t] = static_cast<float *>(b->recv_each[t]);
+        }
+        hipError_t e = cf::launch_dp_reduce_multi(static_cast<float *>(b->O), srcs, p - 1, r.mc * r.n, cs, lands, true);
+        if (e != hipSuccess)
+            return fail_hip(e, "arrival sum launch");
+    }
     // Alg. 4: the attention of a slice depends on nothing that travels, so the attention of ALL p query slices
     // is one launch with a chip-filling grid (no key split, no merge); its output [p slices x B*S/p x heads*D_h]
     // is then the left operand of the persistent projection + reduce-scatter kernel, slice by slice.
@@ -1105,7 +1107,10 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                 gp.recv_step[j] = last && p > 1 ? static_cast<const float *>(b->recv_each[0]) : nullptr;
                 gp.out_step[j] = last ? b->O : static_cast<void *>(b->send_each[j]);
                 gp.flag_step[j] = nullptr;
-                if (last)
+                if (last && pair_front)
+                    gp.recv_step[j] = static_cast<const float *>(b->O);
+                gp.recv_in_epilogue = pair_front;
+                if (last && !pair_front)
                     for (int t = 1; t < p - 1; ++t)
                         gp.recv_more[gp.n_recv_more++] = static_cast<const float *>(b->recv_each[t]);
                 if (carried && few_rows && last && p > 1) {   // the arrivals are read from the partners' buffers and landed
@@ -1115,17 +1120,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                         gp.recv_more[t - 1] = static_cast<const float *>(b->peer_stage[t]);
                         gp.land_more[t - 1] = static_cast<float *>(b->recv_each[t]);
                     }
-                }
-                if (carried && !few_rows && !last) { // this step's work items land the arrival of round j + 1
-                    gp.tail_src[j] = static_cast<const float *>(b->peer_stage[j]);
-                    gp.tail_dst[j] = static_cast<float *>(b->recv_each[j]);
-                }
-                if (carried && !few_rows && last) {
-                    gp.tile_ready = pair_ready;
-                    gp.ready_count = p - 1;
-                    gp.max_tiles = (int)(WS_TILE_COUNTER_BYTES / sizeof(unsigned));
-                    gp.status = pair_status;
-                    gp.spin_limit = spin_limit();
                 }
                 continue;
             }
@@ -1158,11 +1152,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         }
         if (grouped && do_copy)                          // this group's deliveries have landed
             CF_HIP(hipStreamWaitEvent(cs, ev[1 + g0 / group], 0));
-        if (gp.tile_ready != nullptr) {                  // the tiles' counters start at zero (a fill kernel: capturable)
-            hipError_t e0 = cf::launch_set_words(gp.tile_ready, pair_tiles, 0u, cs);
-            if (e0 != hipSuccess)
-                return fail_hip(e0, "counter fill");
-        }
         hipError_t e = cf::launch_gemm_bf16(gp, r.w_kn, r.bf16_out, cs, gp.num_cu);
         if (e != hipSuccess)
             return fail_hip(e, "persistent rank-step launch");

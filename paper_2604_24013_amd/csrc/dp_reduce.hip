@@ -87,8 +87,8 @@ struct AddBatch {
     const float *src[MAX];
 };
 
-// LAND: as above -- source s is also stored to land[s].
-template <bool LAND>
+// LAND: as above -- source s is also stored to land[s].  INIT: dst <- ((src[0] + src[1]) + ...), what it held is not read.
+template <bool LAND, bool INIT>
 __global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_kernel(float *__restrict__ dst, AddBatch ab, int n_src,
                                                                     int64_t n, AddBatch lb)
 {
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_kernel(float *__re
     f32x4_u a[U];
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (base + u * DP_THREADS < n4)
+        if (!INIT && base + u * DP_THREADS < n4)
             a[u] = __builtin_nontemporal_load(&dst4[base + u * DP_THREADS]);
     for (int s = 0; s < n_src; ++s) {
         const f32x4_u *__restrict__ src = reinterpret_cast<const f32x4_u *>(ab.src[s]);
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_kernel(float *__re
         for (int u = 0; u < U; ++u)
             if (base + u * DP_THREADS < n4) {
                 const f32x4_u b = __builtin_nontemporal_load(&src[base + u * DP_THREADS]);
-                a[u] = b + a[u];
+                a[u] = INIT && s == 0 ? b : a[u] + b;
                 if constexpr (LAND)
                     __builtin_nontemporal_store(b, &land[base + u * DP_THREADS]);
             }
@@ -119,10 +119,10 @@ __global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_kernel(float *__re
             __builtin_nontemporal_store(a[u], &dst4[base + u * DP_THREADS]);
     if (blockIdx.x == gridDim.x - 1 && (int)threadIdx.x < (int)(n - n4 * 4)) {
         const int64_t i = n4 * 4 + threadIdx.x;
-        float x = dst[i];
+        float x = INIT ? 0.0f : dst[i];
         for (int s = 0; s < n_src; ++s) {
             const float b = ab.src[s][i];
-            x = b + x;
+            x = INIT && s == 0 ? b : x + b;
             if constexpr (LAND)
                 const_cast<float *>(lb.src[s])[i] = b;
         }
@@ -224,10 +224,13 @@ hipError_t launch_dp_reduce_segments(float *const *dst, const float *const *src,
     return hipSuccess;
 }
 
-hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src, int64_t n, hipStream_t s, float *const *land)
+hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src, int64_t n, hipStream_t s, float *const *land,
+                                  bool init)
 {
     if (n <= 0 || n_src <= 0)
         return hipSuccess;
+    if (init && n_src > AddBatch::MAX)
+        return hipErrorInvalidValue;
     if (n_src > AddBatch::MAX) {                     // one pass per source: the same additions in the same order
         for (int i = 0; i < n_src; ++i) {
             hipError_t e = launch_dp_reduce_segments(&dst, &src[i], land != nullptr ? &land[i] : nullptr, 1, n, s);
@@ -245,10 +248,19 @@ hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src
     const int64_t want = (n / 4 + per_wg) / per_wg;
     if (want >= ((int64_t)1 << 31))
         return hipErrorInvalidValue;
-    if (land != nullptr)
-        hipLaunchKernelGGL(dp_reduce_multi_kernel<true>, dim3((unsigned)want), dim3(DP_THREADS), 0, s, dst, ab, n_src, n, lb);
-    else
-        hipLaunchKernelGGL(dp_reduce_multi_kernel<false>, dim3((unsigned)want), dim3(DP_THREADS), 0, s, dst, ab, n_src, n, lb);
+#define CF_MULTI(L, I) \
+    hipLaunchKernelGGL((dp_reduce_multi_kernel<L, I>), dim3((unsigned)want), dim3(DP_THREADS), 0, s, dst, ab, n_src, n, lb)
+    if (init) {
+        if (land != nullptr)
+            CF_MULTI(true, true);
+        else
+            CF_MULTI(false, true);
+    } else if (land != nullptr) {
+        CF_MULTI(true, false);
+    } else {
+        CF_MULTI(false, false);
+    }
+#undef CF_MULTI
     return hipGetLastError();
 }
 

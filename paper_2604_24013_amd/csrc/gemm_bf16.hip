@@ -362,17 +362,6 @@ double gemm_bf16_tile_us(const GemmParams &p, int num_cu)
     return (double)((items + wgs - 1) / wgs) * round;
 }
 
-int gemm_bf16_tiles_landing_arrivals(const GemmParams &p, bool w_kn, int num_cu)
-{
-    const Tuning tn = tuning();                      // COMMFUSE_CARRY=0 keeps the copies in front
-    if (p.n_steps < 2 || !gemm_bf16_takes_recv_list(p, w_kn) || (tn.carry >= 0 && tn.carry == 0))
-        return 0;
-    const TileChoice t = tile_of_launch(p, num_cu);
-    const int64_t tiles = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
-    // every workgroup of the launch must be resident at once (a work item waits for others): one grid over the chip
-    return tiles <= 1 << 20 ? (int)tiles : 0;
-}
-
 bool gemm_bf16_lands_beside(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu)
 {
     const Tuning tn = tuning();

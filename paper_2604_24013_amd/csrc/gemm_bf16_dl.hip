@@ -675,16 +675,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     __amdgpu_buffer_rsrc_t r_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(cRecv), 0, cRecv != nullptr ? (int)r_bytes : 0, 0x00020000);
     const int pf_at = nk - 1 - P.pf_lead;             // iteration after whose tile loads the prefetch is issued
-    // Arrivals landed tile by tile by the work items of the steps before (GemmParams::tail_src): the last step's item
-    // waits for its own tile's count before it reads them, in the epilogue.
     // (fp32 partial sums only, and never in the kernel that streams B_in: the launcher does not pick it for such a launch.)
     constexpr bool TAILS = PERSIST && !RLDS && !OUT_BF16;
-    const bool wait_tiles = TAILS && P.tile_ready != nullptr && step_i == P.n_steps - 1;
-    const bool pf_on = PF && cRecv != nullptr && splits == 1 && n_more == 0 && P.pf_lead > 0 && pf_at >= 0 && !wait_tiles;
-    // The arrival that travels while this step computes (pairwise schedule: the partner's partial for the own slice):
-    // this work item lands its own output tile's part of it -- from the sender's buffer to the landing buffer, written
-    // through to memory (plain stores and a write-back of the L2 before the count take twice the whole launch's time)
-    // -- and then counts the tile up for the step that sums the arrivals.  Every other workgroup of an XCD does so in
+    const bool pf_on = PF && cRecv != nullptr && splits == 1 && n_more == 0 && P.pf_lead > 0 && pf_at >= 0;
+    // The delivery landed beside the GEMM (GemmParams::tail_src): this work item copies its own output tile's part of it
+    // from the sender's buffer to the landing buffer, written through to memory.  Every other workgroup of an XCD does so in
     // front of its main loop, the others behind their epilogue: the work items of a round run in lock step, and this
     // way one half copies while the other half multiplies instead of all 256 copying at once.
     constexpr int COHERENT_LD = 1 | 16;               // buffer cache-policy bits sc0 | sc1
@@ -740,12 +735,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
                 for (int u = 0; u < TB; ++u)
                     __builtin_amdgcn_raw_buffer_store_b128(v[u], td_rsrc, off[u], 0, COHERENT_LD);
             }
-            if (P.tile_ready != nullptr) {           // (nobody waits for a copy that only lands this step's own B_in)
-                __builtin_amdgcn_s_waitcnt(0);       // this wave's stores are acknowledged
-                __syncthreads();                     // ... and every wave's
-                if (tid == 0)
-                    __hip_atomic_fetch_add(&P.tile_ready[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
         }
     };
     if (TAILS && tail_early)
@@ -776,7 +765,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // A ragged k tail (the launcher then leaves the k order unrotated: it is the last k-tile) is requested in the
     // last two iterations before the final tile; those test their loads and come after the streamed ones.
     const int tested = (RLDS && K % BK != 0) ? (nk - 1 < 2 ? nk - 1 : 2) : 0;
-    const bool streamed = RLDS && cRecv != nullptr && cFlag == nullptr && !wait_tiles && n_more == 0 && splits == 1 &&
+    const bool streamed = RLDS && cRecv != nullptr && cFlag == nullptr && n_more == 0 && splits == 1 &&
                           P.stream_recv && nk >= 2 * RQ + 2 + tested && (tested == 0 || rot == 0);
     // the left-operand stage whose memory serves as the wave-private scratch of the epilogue's stores (and, RLDS, as
     // the landing area of B_in before)
@@ -1329,26 +1318,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     const bool has_recv = cRecv != nullptr;
     if (!P.wait_at_start && !pf_on)
         wait_delivery(false);                        // B_in has travelled under the main loop
-    if (wait_tiles) {
-        // The workgroups that landed this tile's arrivals wrote them through to memory and counted up afterwards;
-        // they hold earlier work items, so they are running or done.  One lane polls, at most spin_limit times.
-        if (tid == 0) {
-            unsigned n = 0;
-            while (__hip_atomic_load(&P.tile_ready[tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) < (unsigned)P.ready_count) {
-                if (++n >= P.spin_limit) {
-                    __hip_atomic_fetch_or(P.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(32);
-            }
-            // (this item is the tile's only reader: the counter is left ready for the next launch)
-            __hip_atomic_store(&P.tile_ready[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        // the arrivals were written through another XCD's L2: drop what this one may hold of those lines, once per
-        // workgroup, so that the epilogue's loads can go through the caches (they read a line in several pieces)
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
     const bool recv_coherent = cFlag != nullptr && !P.wait_at_start;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -1496,9 +1465,9 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
     bool any_tail = false;                           // a step lands an arrival beside its GEMM (GemmParams::tail_src)
     for (int j = 0; j < p.n_steps; ++j)
         any_tail = any_tail || p.tail_src[j] != nullptr;
-    [[maybe_unused]] const bool rlds = SPREAD && NS == 2 && any_recv && !out_bf16 && !p.a_t && p.stream_recv && !any_flag &&
+    [[maybe_unused]] const bool rlds = SPREAD && NS == 2 && any_recv && !out_bf16 && !p.a_t && p.stream_recv && !p.recv_in_epilogue && !any_flag &&
                                        p.n_recv_more == 0 && p.splits == 1 && nk_all >= 18 + (p.K % BK != 0 ? 2 : 0) &&
-                                       p.tile_ready == nullptr && !any_tail;
+                                       !any_tail;
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
     int wgs = tiles_m * tiles_n * p.splits + p.cp_wgs;
     if (p.n_steps > 0) {                             // persistent: a grid that fills the chip once
@@ -1621,8 +1590,6 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         for (int j = 0; j < p.n_steps; ++j)
             if (p.land_step[j] != nullptr && p.recv_step[j] == nullptr && !gemm_bf16_dl_carries_operand(p))
                 return hipErrorInvalidValue;          // callers ask gemm_bf16_carries_delivery first
-        if (p.tile_ready != nullptr && (out_bf16 || tiles > p.max_tiles || p.status == nullptr || p.spin_limit == 0))
-            return hipErrorInvalidValue;              // callers ask gemm_bf16_tiles_landing_arrivals first
         for (int j = 0; j < p.n_steps; ++j)
             if ((p.tail_src[j] != nullptr) != (p.tail_dst[j] != nullptr) || (p.tail_src[j] != nullptr && out_bf16))
                 return hipErrorInvalidValue;
@@ -1638,8 +1605,7 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         bool cut = false;
         for (int nb = 1; nb <= 8; nb *= 2)
             cut = cut || (tiles_n_ % nb == 0 && p.n_steps % (8 / nb) == 0);
-        // (... nor when work items hand arrivals on to the last step's: step-major order keeps the producers in front)
-        p.xcd_steps = cut && p.num_cu % 8 == 0 && p.n_recv_more == 0 && p.tile_ready == nullptr && tn.xcd_steps != 0;
+        p.xcd_steps = cut && p.num_cu % 8 == 0 && p.n_recv_more == 0 && tn.xcd_steps != 0;
         // Step groups x column bands: per k-tile the 32 (or fewer) workgroups of an XCD that run side by side fetch
         // `a` left-operand bands of bm rows and `b` weight bands of bn columns, a = (step, tile row) pairs of the XCD
         // (at most its workgroups), b = the columns they spread over; the number of bands NB that makes a bm + b bn
