@@ -896,7 +896,12 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         probe.n_steps = S;
         few_rows = cf::gemm_rows_takes(probe, r.bf16_in, r.w_kn, num_cu_of_current_device());
     }
-    if (few_rows && (flags & CF_FUSED_COPY))
+    // (its loads and stores are 16 bytes wide: peers' and landing buffers off that grid are copied in front, like any bytes)
+    bool wide = true;
+    if (do_copy && b->recv_each != nullptr)
+        for (int i = 0; i < p - 1; ++i)
+            wide = wide && aligned16(b->peer_stage[i]) && aligned16(b->recv_each[i]);
+    if (few_rows && (flags & CF_FUSED_COPY) && wide)
         carried = true;
     if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr && do_copy && do_compute &&
         slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0) {
@@ -931,7 +936,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // 1376 118 -> 82, 1024 x 8192 x 3584 481 -> 467).
     bool pair_front = false;
     if (!few_rows && (flags & CF_FUSED_COPY) && kind == CF_KIND_RS_PAIR && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
-        r.n > 0 && r.k > 0 && cf::tuning().carry != 0) {
+        r.n > 0 && r.k > 0 && wide && cf::tuning().carry != 0) {
         pair_front = true;
         carried = true;
     }

@@ -103,3 +103,34 @@ def test_packed_rank_steps(dims, layout, carry, rows):
             run.run_schedule(ONE_LAUNCH | carry)
             assert H.rel_err(H.to_host_f64(run.O), refa) <= (2.0 ** -8 if out_dtype == "bf16" else 1e-5), shape
             assert all(torch.equal(a, b) for a, b in zip(run.each, run.stage)), shape
+
+
+@pytest.mark.parametrize("dims", [(4, 9, 264, 520), (4, 272, 1032, 264)])      # all rows in one launch / the tile kernels
+def test_peers_buffers_off_the_16_byte_grid(dims, rows):
+    """CF_FUSED_COPY with peers' buffers that start 8 bytes (bf16 slices) or 4 bytes (partial sums) off the grid: the
+    deliveries land as they are and the sums are those of the copies in front."""
+    p, mc, n, k = dims
+    rows(None)
+
+    def shifted(t, elems):
+        s = torch.empty(t.numel() + 16, dtype=t.dtype, device=t.device)[elems:elems + t.numel()].view(t.shape)
+        return s.copy_(t)
+    w, data, _ = _rs(p, mc, n, k, "bf16", 8)
+    wa = inputs.scaled(inputs.CONFIGS["c3_ag_7b"], p=p, m_chunk=mc, n=n, k=k, out_dtype="f32")
+    da = inputs.make_ag(wa, salt=9)
+    pair, ag = H.RsPairRun(w, data, 1, keep_all=True), H.AgRun(wa, da, 1, each=True)
+    for run, elems, kind in ((pair, 1, cf.CF_KIND_RS_PAIR), (ag, 4, cf.CF_KIND_AG)):
+        got = []
+        for flags, off in ((0, 0), (cf.CF_FUSED_COPY, elems)):
+            stage = [shifted(t, off) for t in run.stage]
+            is_ag = run is ag
+            bufs = cf.make_buffers(run.X if is_ag else run.A, run.W, run.O, stage, (None, None), (None, None), None, run.each,
+                                   None if is_ag else run.send_each)
+            for t in run.each + [run.O]:
+                t.fill_(float("nan"))
+            torch.cuda.synchronize()
+            cf.run_schedule(run.desc, kind, bufs, run.cs, run.cs, ONE_LAUNCH | flags)
+            run.cs.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(run.each, run.stage))
+            got.append(run.O.clone())
+        assert torch.equal(got[0], got[1])
