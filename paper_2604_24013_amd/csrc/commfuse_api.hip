@@ -1091,15 +1091,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         gp.W = b->W;
         fill_shape(gp, r);
         gp.n_steps = g1 - g0;
-        {
-            const Workspace ws = workspace_for(cs);
-            if (ws.ptr != nullptr && ws.bytes > WS_COUNTER_BYTES) {
-                gp.counters = static_cast<unsigned *>(ws.ptr);
-                gp.ws = reinterpret_cast<float *>(static_cast<char *>(ws.ptr) + WS_COUNTER_BYTES);
-                gp.ws_bytes = ws.bytes - WS_COUNTER_BYTES;
-                gp.max_tiles = (int)(WS_TILE_COUNTER_BYTES / sizeof(unsigned));
-            }
-        }
         gp.num_cu = num_cu_of_current_device();
         for (int jj = g0; jj < g1; ++jj) {
             const int j = jj - g0;                       // the step's place in this launch

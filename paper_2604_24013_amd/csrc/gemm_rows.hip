@@ -16,7 +16,7 @@
 //    B_in, landing buffer and output), so that W is read once and not once per step;
 //  * the received partial is requested before the k loop and added at the end; a delivery carried by the launch is
 //    stored on by the threads that read it (reduce-scatter) or by extra workgroups (all-gather: the slices);
-//  * where even that leaves compute units idle and a workspace is there, KSPLIT workgroups share a tile: partial tiles and
+//  * where even that leaves compute units idle and a single bf16 step has a workspace, KSPLIT workgroups share a tile: partial tiles and
 //    an arrival counter with the device-coherent cache policy, summed in split order by the last to arrive.
 // Measured (one step, B_in added; us, before = 128 x 128 tiles): 8 x 4096 x 1376 bf16 18.1 -> 4.4 (an empty kernel: 2.25),
 // 8 x 8192 x 3584 24.7 -> 13.4 (4.4 TB/s of W), 128 x 8192 x 3584 34 -> 18.7, 128 x 256 x 512 fp32 16.2 -> 3.9; eight steps of 8 x 1536 x 4096 packed into one launch 42.5 -> 8.6.
@@ -474,8 +474,9 @@ hipError_t launch_any(const RowsParams<SEG> &p, bool w_kn, RowsShape t, hipStrea
 // round over the chip; 64 x 64 where none is.  bf16 [k x n] weights take at least two column groups (a 32-byte piece of
 // every k-row is a quarter of a line).  Measured, us (rows x n x k, [k x n] / [n x k] weights): 8 x 4096 x 1376 32-column tiles
 // 4.8 / 4.5, 64-column 5.6 / 5.4; 64 x 8192 x 3584 32 x 64 tiles 15.2 / 14.6, 64 x 64 18.1 / 17.5, 16 x 64 24.5 / -.
-// A k range of 16 slices per wave and more on a quarter of the chip or less is split over four workgroups (8 x 256 x 8192
-// fp32 15.2 -> 9.4 us, 8 x 520 x 8192 bf16 [k x n] 12.2 -> 9.3); bf16 [n x k] tiles stream as fast unsplit (7.2 us).
+// A k range of 16 slices per wave and more on a quarter of the chip or less is split over four workgroups (8 x 520 x 8192
+// bf16 [k x n] 12.2 -> 9.3 us); bf16 [n x k] tiles stream as fast unsplit (7.2 us).  Single bf16 steps only: fp32 steps and
+// rank steps in one launch take no workspace, so that several of them may be in flight on streams that share one.
 RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num_cu)
 {
     const Tuning tn = tuning();
@@ -494,7 +495,7 @@ RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num
             break;
     }
     const int slices = (K + (bf16 ? 63 : 31)) / (bf16 ? 64 : 32);
-    if ((w_kn || !bf16) && t.mf * t.nc <= 4 && slices >= 16 * 8 && wgs * 4 <= num_cu)
+    if (w_kn && bf16 && t.mf * t.nc <= 4 && slices >= 16 * 8 && wgs * 4 <= num_cu)
         t.ks = 4;
     return t;
 }
@@ -558,7 +559,7 @@ static hipError_t launch_segments(const GemmParams &g, bool bf16, bool w_kn, boo
     p.tiles_r = (int)((rows + 16 * t.mf - 1) / (16 * t.mf));
     const size_t tiles = (size_t)p.tiles_n * p.tiles_r;
     p.ksplit = t.ks;
-    if (p.ksplit > 1 && (g.ws == nullptr || g.counters == nullptr || tiles > (size_t)g.max_tiles ||
+    if (p.ksplit > 1 && (!bf16 || g.ws == nullptr || g.counters == nullptr || tiles > (size_t)g.max_tiles ||
                          tiles * p.ksplit * (256 * t.mf * t.nc) * sizeof(float) > g.ws_bytes))
         p.ksplit = 1;
     p.ws = g.ws;

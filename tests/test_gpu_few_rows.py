@@ -134,3 +134,21 @@ def test_peers_buffers_off_the_16_byte_grid(dims, rows):
             assert all(torch.equal(a, b) for a, b in zip(run.each, run.stage))
             got.append(run.O.clone())
         assert torch.equal(got[0], got[1])
+
+
+def test_fp32_steps_and_packed_rank_steps_leave_the_workspace_alone(rows):
+    """A long k range on few tiles: only a single bf16 step may split it through the workspace.  fp32 steps and one-launch
+    rank steps may be in flight on streams that share a process-wide workspace."""
+    ws = torch.full((32 << 20,), 0x5A, dtype=torch.uint8, device=H.DEV)
+    cf.set_workspace(ws)
+    torch.cuda.synchronize()
+    before = ws.clone()
+    w, data, ref = _rs(2, 8, 256, 8192, "f32", 10)
+    for got, want in zip(H.RsRun(w, data, 1).run_steps(), ref):
+        assert H.rel_err(got, want) <= 1e-5
+    w, data, ref = _rs(2, 8, 256, 8192, "bf16", 11)
+    run = H.RsRun(w, data, 1, each=True)
+    run.run_schedule(ONE_LAUNCH | cf.CF_FUSED_COPY)
+    assert H.rel_err(H.to_host_f64(run.O), ref[-1]) <= 2e-5       # (sqrt(2) more than at k = 4096)
+    torch.cuda.synchronize()
+    assert torch.equal(ws, before)
