@@ -224,9 +224,9 @@ __global__ __launch_bounds__(64 * NW) void attn_slice_kernel(AttnParams P)
         // half a packed conversion:
         //  * keys beyond the sequence are masked in the one tile that can hold them only;
         //  * the exponentials are taken against a running reference m that is raised only when the tile's
-        //    maximum exceeds it by more than 2^RAISE (probabilities then stay below 2^RAISE: no overflow, the
-        //    same relative precision in bf16), so the rescaling of the accumulators is rare and sits in a
-        //    wave-uniform branch;
+        //    maximum exceeds it by more than 2^RAISE (probabilities then stay below 2^RAISE: no overflow), so the
+        //    rescaling of the accumulators is rare and sits in a wave-uniform branch.  (The largest probability is
+        //    then rounded like any other; choose_attn says what that means for the choice between the kernels);
         //  * the row sums l come out of the matrix pipe: one more MFMA per 16-key slice with an all-ones "A"
         //    operand adds up exactly the rounded probabilities that multiply V (every row of its result is the
         //    sum over the slice's keys, both lanes of a query get the whole sum).
@@ -549,8 +549,9 @@ __global__ __launch_bounds__(64 * KW_WAVES) void attn_keys_over_waves_kernel(Att
         if (more)                                                    // (the last product has read its fragment: K is out of LDS)
             issue(kt + NW, k_rsrc, k_off, lds_base);
 
-        // online softmax, as in the kernel above
-        constexpr float RAISE = 8.0f;
+        // online softmax, as in the kernel above with the running maximum itself as the reference: a wave walks a few
+        // tiles only, so that there is little rescaling to save by one that lags behind, and the largest probability
+        // of a wave is not rounded
         if ((kt + 1) * BK > S) {
 #pragma unroll
             for (int r = 0; r < 16; ++r)
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(64 * KW_WAVES) void attn_keys_over_waves_kernel(Att
             mx = fmaxf(mx, sacc[r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float mxs = mx * sl2;
-        if (__builtin_amdgcn_ballot_w64(mxs > m_run + RAISE) != 0) {
+        if (__builtin_amdgcn_ballot_w64(mxs > m_run) != 0) {
             const float m_new = fmaxf(m_run, mxs);
             float alpha = exp2f(m_run - m_new);
             asm volatile("" : "+v"(alpha));
@@ -715,15 +716,23 @@ namespace {
 
 // Which kernel, and over how many workgroups the keys of a query block are split.  The costs (us) are fitted to
 // measurements over batch x heads x queries of the slice x keys:
-//   * keys over waves (32 queries): 6.5 + 1.6 per eight 32-key tiles and round -- each workgroup reads all its keys
+//   * keys over waves (32 queries): 6.5 + 1.8 per eight 32-key tiles and round -- each workgroup reads all its keys
 //     itself, 128 KiB per step of its eight waves, 0.9 us at the L1's rate.  2x3x280x1120: 13.5 (query blocks: 20.5 at best,
 //     40 with one workgroup per compute unit, whose sixteen partials per block took most of it), 1x1x1024x8192: 21.5 with
 //     six splits (37.6), 1x8x1024x8192: 60.1 (57.9);
-//   * query blocks, eight waves (256 queries): 7 + 2.05 per 64-key tile and round, 1.65 while a third of the chip idles.
+//   * query blocks, eight waves (256 queries): 7 + 2.05 per 64-key tile and round, 1.65 in a round that leaves a third of the
+//     chip idle.
 //     4x8x4096x8192: 523, 2x8x2319x4638: 124 (keys over waves: 167);
 //   * query blocks, four waves (128 queries): 7 + 1.38 per tile, 2.1 with two workgroups per compute unit.
 //     4x2x1181x2362: 34.4 with three splits (keys over waves: 41).
 // A split costs its hand-over: 1.5 + 0.7 per workgroup of 16.5 KiB partials, 5 + 1.5 for the query blocks' 66 / 132 KiB.
+// The kernels round alike but not equally well, and a choice made for its time must not cost precision.  Query blocks keep a
+// softmax reference that lags behind the maximum, so that even the largest probability of a row is rounded; every split of
+// the keys starts a reference of its own.  Keys over waves keep the maximum itself, one per wave.  Error against 64 bits
+// (2-norm, scores of sigma 4; the output's rounding alone is 1.66e-3): 2x8x2319x4638 keys over waves 1.68e-3, query blocks
+// with two splits 1.87e-3, unsplit 1.89e-3; 4x2x1181x2362: 1.68e-3, seven splits 1.79e-3, three 1.84e-3.  So where query
+// blocks of 256 leave a quarter of the chip idle, query blocks are a choice only with the keys split finely enough for a
+// workgroup per compute unit (k0 splits); where no workspace takes the partials of that, a single slice has none.
 struct AttnChoice {
     int waves = 8;               // 0: keys over waves
     int ksplit = 1;
@@ -734,25 +743,44 @@ AttnChoice choose_attn(const AttnParams &p, int num_cu)
     const int64_t heads = (int64_t)p.heads * p.batch * p.n_slices;
     const int tiles32 = (p.S + 31) / 32, tiles64 = (p.S + 63) / 64;
     const bool can_split = p.ws != nullptr && p.counters != nullptr;
+    const int64_t blocks = (p.c + 255) / 256 * heads;
+    int k0 = 1;
+    bool query_blocks = true;
+    if (blocks * 4 < (int64_t)num_cu * 3) {
+        int64_t k = (num_cu + blocks - 1) / blocks;
+        k = k > 16 ? 16 : k;
+        k = k > tiles64 ? tiles64 : k;
+        if (can_split && k > 1 && blocks <= p.max_groups &&
+            (size_t)(blocks * k) * (size_t)(64 + 2) * (64 * 8) * sizeof(float) <= p.ws_bytes)
+            k0 = (int)k;
+        else
+            query_blocks = p.n_slices > 1;
+    }
     AttnChoice best;
     double best_us = 0.0;
     for (int kind = 0; kind < 3; ++kind) {                   // keys over waves, eight waves, four waves
+        if (kind != 0 && !query_blocks)
+            break;
         const int waves = kind == 0 ? 0 : kind == 1 ? 8 : 4;
         const int bq = kind == 0 ? 32 : 32 * waves;
         const int64_t groups = (p.c + bq - 1) / bq * heads;
-        for (const int k : {1, 2, 3, 4, 6, 8, 12}) {
+        for (const int k : {1, 2, 3, 4, 6, 8, 12, k0}) {
+            if (kind != 0 && k < k0)
+                continue;
             const size_t part = kind == 0 ? (size_t)KW_PART : (size_t)(64 + 2) * (64 * waves);
-            if (k > 1 && (!can_split || groups > p.max_groups || groups * k > num_cu || k > (kind == 0 ? tiles32 : tiles64) ||
+            if (k > 1 && (!can_split || groups > p.max_groups || (groups * k > num_cu && (kind == 0 || k != k0)) || k > (kind == 0 ? tiles32 : tiles64) ||
                           (size_t)groups * k * part * sizeof(float) > p.ws_bytes))
                 continue;
             const int64_t wgs = groups * k;
             double us;
             if (kind == 0) {
-                us = 6.5 + (double)((wgs + num_cu - 1) / num_cu) * (((tiles32 + k - 1) / k + 7) / 8) * 1.6 + (k > 1 ? 1.5 + 0.7 * k : 0.0);
+                us = 6.5 + (double)((wgs + num_cu - 1) / num_cu) * (((tiles32 + k - 1) / k + 7) / 8) * 1.8 + (k > 1 ? 1.5 + 0.7 * k : 0.0);
             } else {
                 const int per_cu = kind == 1 || wgs <= num_cu ? 1 : 2;
-                const double tile = kind == 1 ? (wgs * 3 <= num_cu * 2 ? 1.65 : 2.05) : (per_cu == 1 ? 1.38 : 2.1);
-                us = 7.0 + (double)((wgs + num_cu * per_cu - 1) / (num_cu * per_cu)) * ((tiles64 + k - 1) / k) * tile + (k > 1 ? 5.0 + 1.5 * k : 0.0);
+                const int64_t last = wgs % num_cu;
+                const double tile = kind == 1 ? (wgs / num_cu) * 2.05 + (last == 0 ? 0.0 : last * 3 <= num_cu * 2 ? 1.65 : 2.05)
+                                              : (double)((wgs + num_cu * per_cu - 1) / (num_cu * per_cu)) * (per_cu == 1 ? 1.38 : 2.1);
+                us = 7.0 + ((tiles64 + k - 1) / k) * tile + (k > 1 ? 5.0 + 1.5 * k : 0.0);
             }
             if (best_us == 0.0 || us < best_us) {
                 best_us = us;
