@@ -944,11 +944,12 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // of consecutive (sub-)steps that fills the chip about once, and the deliveries of a group copied on the copy
     // stream under the launches of the groups before it -- Fig. 1's overlap with a group of steps where the paper has
     // one step.  One event per group orders the two streams; every hop has its own landing buffer, so the copy
-    // stream never waits for a kernel.
+    // stream never waits for a kernel.  With few rows in all the steps stay one launch, behind one event.
     int group = S;
-    const bool grouped = !(flags & CF_SERIAL) && xs != cs && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr &&
-                         !carried && !carried_beside && !few_rows && p > 1 && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0;
-    if (grouped) {
+    const bool two_streams = !(flags & CF_SERIAL) && xs != cs && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr &&
+                             p > 1 && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0;
+    const bool grouped = two_streams && !carried && !carried_beside;
+    if (grouped && !few_rows) {
         cf::GemmParams probe;
         probe.W = b->W;
         fill_shape(probe, r);
@@ -957,11 +958,18 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     }
     const int n_groups = (S + group - 1) / group;
     std::vector<hipEvent_t> ev;
-    if (grouped) {
+    // A few-rows launch that carries its deliveries also takes shapes that no other launch carries them for, whose copies
+    // would be on the copy stream: it starts behind what that stream holds, as they would.
+    const bool joined = two_streams && few_rows && carried;
+    if (grouped || joined) {
         if (cf_status st = get_events(1 + (size_t)n_groups, &ev))
             return st;
         CF_HIP(hipEventRecord(ev[0], cs));               // the copy stream starts behind what the compute stream holds
         CF_HIP(hipStreamWaitEvent(xs, ev[0], 0));
+    }
+    if (joined) {
+        CF_HIP(hipEventRecord(ev[1], xs));
+        CF_HIP(hipStreamWaitEvent(cs, ev[1], 0));
     }
     if (grouped && do_copy) {
         for (int g = 0; g < n_groups; ++g) {             // the deliveries of group g: one batched copy launch, then its event

@@ -152,3 +152,35 @@ def test_fp32_steps_and_packed_rank_steps_leave_the_workspace_alone(rows):
     assert H.rel_err(H.to_host_f64(run.O), ref[-1]) <= 2e-5       # (sqrt(2) more than at k = 4096)
     torch.cuda.synchronize()
     assert torch.equal(ws, before)
+
+
+@pytest.mark.parametrize("flags", [cf.CF_PERSISTENT, cf.CF_PERSISTENT | cf.CF_FUSED_COPY])
+@pytest.mark.parametrize("dims", [(4, 9, 264, 520), (8, 2, 72, 4104), (4, 272, 1032, 264)])      # few rows (k not a multiple of 64) / tiles
+def test_two_streams_deliver_behind_the_copy_streams_work(dims, flags, rows):
+    """One-launch modes on two streams: what the peers deliver is written by work enqueued on the copy stream, behind a
+    long kernel there, and the schedule is called without a synchronisation: the new data arrive."""
+    p, mc, n, k = dims
+    rows(None)
+    w, data, ref = _rs(p, mc, n, k, "bf16", 12)
+    wa = inputs.scaled(inputs.CONFIGS["c3_ag_7b"], p=p, m_chunk=mc, n=n, k=k, out_dtype="f32")
+    da = inputs.make_ag(wa, salt=13)
+    refa = oracle.ag_rank(inputs.as_f64(da["X"], "bf16"), [None] + [inputs.as_f64(s, "bf16") for s in da["S"][1:]],
+                          inputs.as_f64(da["W"], "bf16"), p, p - 1)
+    busy = torch.zeros(1 << 28, device=H.DEV)                # a pass over it takes longer than the whole rank step
+    for run, want, kind in ((H.RsRun(w, data, p - 1, each=True), ref[-1], cf.CF_KIND_RS),
+                            (H.AgRun(wa, da, p - 1, each=True), refa, cf.CF_KIND_AG)):
+        if kind == cf.CF_KIND_RS and flags & cf.CF_FUSED_COPY:
+            continue                                         # (packed partial sums are carried by every launch: the copy stream is unused)
+        fresh = [t.clone() for t in run.stage]
+        for t in run.stage + run.each + [run.O]:
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(run.xs):
+            for _ in range(8):
+                busy.add_(1.0)
+            for t, f in zip(run.stage, fresh):
+                t.copy_(f)
+        cf.run_schedule(run.desc, kind, run.bufs, run.cs, run.xs, flags)
+        run.cs.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(run.each, fresh))
+        assert H.rel_err(H.to_host_f64(run.O), want) <= 1e-5
