@@ -525,7 +525,8 @@ __global__ __launch_bounds__(64 * KW_WAVES) void attn_keys_over_waves_kernel(Att
 #pragma unroll
     for (int e = 0; e < 8; ++e)
         ones[e] = (__bf16)1.0f;
-    float m_run = -INFINITY;
+    // (finite: against -inf a tile whose scores are all -inf would give NaN, and every wave starts on a tile of its own)
+    float m_run = -3.402823466e38f;
     const float sl2 = P.scale * 1.4426950408889634f;
     asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]), "+v"(qf[6]), "+v"(qf[7]));
     // (the queries are in registers from here on: what the waits below count are the tiles' loads alone)

@@ -376,3 +376,32 @@ def test_attention_rounds_no_more_than_the_probabilities(shape, heads, workspace
         model[:, a * 128:(a + 1) * 128] = oracle.round_to_bf16(R @ host[2][0, a] / R.sum(axis=1, keepdims=True))
     err = lambda x: np.linalg.norm(x - ref) / np.linalg.norm(ref)
     assert err(got) <= err(model), f"{err(got):.4e} against {err(model):.4e}"
+
+
+@pytest.mark.parametrize("tile", [0, 4, 5, 31])
+def test_attention_keys_over_waves_with_a_tile_of_minus_infinity(tile):
+    """Thirty-two keys in a row whose scores are all -inf have no weight, also where they are the first keys a wave sees (the
+    kernel that splits the keys over eight waves gives it tiles w, w + 8, ...); the first, two in between, the last."""
+    B, h, S = 1, 2, 1024
+    dev, host, _ = _problem(77, 1, B, h, S, 64)
+    Q = np.abs(host[0])
+    K = host[1].copy()
+    K[:, :, tile * 32:(tile + 1) * 32] = -np.inf
+    scale = 1.0 / np.sqrt(128.0)
+    out = torch.full((S, h * 128), float("nan"), dtype=torch.bfloat16, device=H.DEV)
+    os.environ["COMMFUSE_ATTN_QT"] = "0"
+    try:
+        cf.attn_slice(cf.attn_desc(1, 0, B, h, S, 128, 64, scale), 0, H.to_dev(inputs.f32_to_bf16_bits(Q.astype(np.float32)), "bf16"),
+                      H.to_dev(inputs.f32_to_bf16_bits(K.astype(np.float32)), "bf16"), H.to_dev(dev[2], "bf16"), out, None)
+        torch.cuda.synchronize()
+    finally:
+        os.environ.pop("COMMFUSE_ATTN_QT", None)
+    got = H.to_host_f64(out)
+    keep = np.r_[0:tile * 32, (tile + 1) * 32:S]
+    ref = np.empty_like(got)
+    for a in range(h):
+        s = Q[0, a] @ K[0, a][keep].T * scale
+        P = np.exp(s - s.max(axis=1, keepdims=True))
+        ref[:, a * 128:(a + 1) * 128] = P @ host[2][0, a][keep] / P.sum(axis=1, keepdims=True)
+    assert not np.isnan(got).any()
+    assert H.rel_err(got, ref) <= TOL_ATTN
