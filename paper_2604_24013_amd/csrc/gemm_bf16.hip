@@ -359,7 +359,16 @@ double gemm_bf16_tile_us(const GemmParams &p, int num_cu)
     const int64_t wgs = (int64_t)num_cu * (t.bm == 128 && !t.deep ? 2 : 1);
     const double kt = (p.K + 63) / 64;
     const double round = t.bm == 128 ? 8 + 0.55 * kt : t.bn == 128 ? 14 + 0.97 * kt : 14 + 1.5 * kt;
-    return (double)((items + wgs - 1) / wgs) * round;
+    const double whole = (double)((items + wgs - 1) / wgs) * round;
+    if (t.splitk <= 1 || p.n_steps > 0 || p.ws == nullptr || p.counters == nullptr || items > p.max_tiles ||
+        (size_t)t.splitk * p.M * p.N * sizeof(float) > p.ws_bytes)
+        return whole;
+    // A step whose k range the launcher splits through the workspace (the hand-over takes 10 us and more): fitted to M x N from
+    // 64 x 520 to 1024 x 2048, splits in two and three (rms 2.4 us): 384 x 4096 x 8192 59 us (the few-rows kernel 66),
+    // 256 x 8192 x 8192 61 (77), 768 x 1536 x 8192 50 (63).  Short ranges come out longer split than whole; there the
+    // smaller figure stands for the kernel.
+    const double split = 18.5 + 5.1 * (double)(items * t.splitk) / num_cu + 0.6 * (((p.K + 63) / 64 + t.splitk - 1) / t.splitk);
+    return split < whole ? split : whole;
 }
 
 bool gemm_bf16_lands_beside(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu)

@@ -184,3 +184,46 @@ def test_two_streams_deliver_behind_the_copy_streams_work(dims, flags, rows):
         run.cs.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(run.each, fresh))
         assert H.rel_err(H.to_host_f64(run.O), want) <= 1e-5
+
+
+def _which(run):
+    """Kernel that a call takes by rule, told by the bits of its result: every kernel sums in an order of its own."""
+    out = {}
+    for name, v in (("rule", None), ("tiles", "0"), ("rows", "4x4x1")):
+        os.environ.pop("COMMFUSE_ROWS", None)
+        if v is not None:
+            os.environ["COMMFUSE_ROWS"] = v
+        try:
+            out[name] = run()
+        finally:
+            os.environ.pop("COMMFUSE_ROWS", None)
+    assert not torch.equal(out["tiles"], out["rows"])
+    assert H.rel_err(H.to_host_f64(out["tiles"]), H.to_host_f64(out["rows"])) <= 2e-5
+    return next(n for n in ("tiles", "rows") if torch.equal(out["rule"], out[n]))
+
+
+# (rows, n, k, dtype, workspace): the kernel that is the faster one
+RULE_STEPS = [
+    # a k range that the tile kernel splits through a workspace
+    ((384, 4096, 8192, "bf16", True), "tiles"), ((384, 4096, 8192, "bf16", False), "rows"), ((256, 2048, 4096, "bf16", True), "rows"),
+]
+
+
+@pytest.mark.parametrize("case,want", RULE_STEPS)
+def test_rule_for_single_steps(case, want, rows):
+    mc, n, k, dtype, workspace = case
+    if not workspace:
+        cf.set_workspace(None)
+    g = torch.Generator(device=H.DEV)
+    g.manual_seed(mc + n + k)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    A, W = (torch.empty(s, device=H.DEV).normal_(0.0, 0.5, generator=g).to(dt) for s in ((2 * mc, k), (k, n)))
+    recv = torch.empty((mc, n), device=H.DEV).normal_(generator=g)
+    desc = cf.layer_desc(2, 0, mc, n, k, dtype, "f32")
+
+    def run():
+        out = torch.full((mc, n), float("nan"), device=H.DEV)
+        cf.rs_step(desc, 1, A, W, recv, out, None)
+        torch.cuda.synchronize()
+        return out
+    assert _which(run) == want
