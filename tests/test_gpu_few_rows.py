@@ -199,7 +199,7 @@ def _which(run):
             os.environ.pop("COMMFUSE_ROWS", None)
     assert not torch.equal(out["tiles"], out["rows"])
     assert H.rel_err(H.to_host_f64(out["tiles"]), H.to_host_f64(out["rows"])) <= 2e-5
-    return next(n for n in ("tiles", "rows") if torch.equal(out["rule"], out[n]))
+    return "tiles" if torch.equal(out["rule"], out["tiles"]) else "rows"
 
 
 # (rows, n, k, dtype, workspace): the kernel that is the faster one
@@ -226,4 +226,27 @@ def test_rule_for_single_steps(case, want, rows):
         cf.rs_step(desc, 1, A, W, recv, out, None)
         torch.cuda.synchronize()
         return out
+    assert _which(run) == want
+
+
+# p, rows per step, n, k
+@pytest.mark.parametrize("dims,want", [((8, 64, 8192, 512), "tiles"), ((8, 64, 8192, 1024), "tiles"), ((4, 128, 4096, 8192), "rows"),
+                                       ((2, 96, 8192, 8192), "tiles"), ((8, 8, 1536, 4096), "rows")])
+def test_rule_for_packed_rank_steps(dims, want, rows):
+    p, mc, n, k = dims
+    g = torch.Generator(device=H.DEV)
+    g.manual_seed(mc + n + k)
+    W, own = (torch.empty(s, device=H.DEV).normal_(0.0, 0.5, generator=g).to(torch.bfloat16) for s in ((k, n), (p * mc, k)))
+    stage = [torch.empty((mc, n), device=H.DEV).normal_(generator=g) for _ in range(p - 1)]
+    desc = cf.layer_desc(p, 0, mc, n, k, "bf16", "f32")
+    st = torch.cuda.Stream()
+
+    def run():
+        O, each, sends = torch.empty((mc, n), device=H.DEV), [torch.empty_like(t) for t in stage], [torch.empty_like(t) for t in stage]
+        bufs = cf.make_buffers(own, W, O, stage, (None, None), (None, None), None, each, sends)
+        torch.cuda.synchronize()
+        cf.run_schedule(desc, cf.CF_KIND_RS, bufs, st, st, ONE_LAUNCH | cf.CF_FUSED_COPY)
+        st.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(each, stage))
+        return torch.cat(sends + [O])
     assert _which(run) == want
