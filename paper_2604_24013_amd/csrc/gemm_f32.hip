@@ -179,14 +179,33 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, hipStream_t s)
 
 }  // namespace
 
+// 64 x 64 tiles until the 128 x 128 ones fill the chip.
+static bool big_tiles(const GemmParams &p, int num_cu)
+{
+    return ((p.M + 127) / 128) * ((p.N + 127) / 128) >= num_cu;
+}
+
+double gemm_f32_tile_us(const GemmParams &p, int num_cu)
+{
+    // Fitted to 512 x 256 .. 4096 x 8192 (k 256 .. 8192; within 5 %).  64 x 64: several workgroups share a compute unit.
+    // 128 x 128: two do, and a last round of one each takes half as long.
+    const double k = p.K;
+    if (!big_tiles(p, num_cu)) {
+        const int64_t tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64), deep = (tiles + num_cu - 1) / num_cu;
+        return deep <= 1 ? 4 + 0.0365 * k : deep == 2 ? 7.6 + 0.0395 * k : deep == 3 ? 8 + 0.055 * k : 10 + 0.0735 * k;
+    }
+    const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128), full = tiles / (2 * num_cu), rest = tiles % (2 * num_cu);
+    const double last = rest == 0 ? 0.0 : rest > num_cu ? 0.13 : full > 0 ? 0.065 : 0.0737;
+    return 7 + 0.02 * tiles + k * (0.124 * full + last);
+}
+
 hipError_t launch_gemm_f32(const GemmParams &p, bool w_kn, hipStream_t s, int num_cu)
 {
     if (p.M <= 0 || p.N <= 0)
         return hipSuccess;
     if (gemm_rows_takes(p, false, w_kn, num_cu))
         return launch_gemm_rows(p, false, w_kn, false, s, num_cu);
-    const int big = ((p.M + 127) / 128) * ((p.N + 127) / 128);
-    bool use_big = big >= num_cu;
+    bool use_big = big_tiles(p, num_cu);
     if (const int bm = tuning().tile_f32_bm)             // override: "128x128" or "64x64"
         use_big = bm >= 128;
     if (use_big)

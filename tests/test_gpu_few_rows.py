@@ -206,6 +206,9 @@ def _which(run):
 RULE_STEPS = [
     # a k range that the tile kernel splits through a workspace
     ((384, 4096, 8192, "bf16", True), "tiles"), ((384, 4096, 8192, "bf16", False), "rows"), ((256, 2048, 4096, "bf16", True), "rows"),
+    # fp32: grids of one round, of several rounds over short and long k ranges, and grids that 128 x 128 tiles fill
+    ((1000, 1000, 256, "f32", False), "rows"), ((768, 4096, 256, "f32", False), "tiles"), ((512, 4096, 2048, "f32", False), "rows"),
+    ((4096, 2048, 512, "f32", False), "tiles"), ((1536, 4096, 1024, "f32", False), "rows"), ((2048, 4096, 1024, "f32", False), "tiles"),
 ]
 
 
