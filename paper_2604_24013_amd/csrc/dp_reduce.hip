@@ -23,20 +23,38 @@ typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 // b % per_seg of segment b / per_seg, U independent vectors per lane and stream in flight.
 // LAND: the delivery carried by the consumer -- src is the neighbour's buffer, and what is read from it is also stored
 // to `land`, this rank's landing buffer: 16 bytes per element (two reads, two writes) where a copy followed by the add
-// moves 20.
+// moves 20.  Two sizes of the argument: a single step's (a short one is cheaper to enqueue: 0.15 us) and a rank step's.
+template <int MAX>
 struct AddSegments {
-    static constexpr int MAX = 16;
     float *dst[MAX];
     const float *src[MAX];
     float *land[MAX];
 };
+constexpr int MAX_SEGMENTS = 16;
 
-template <bool LAND, int T, int U>
-__global__ __launch_bounds__(T) void dp_reduce_kernel(AddSegments a, int64_t n, int per_seg)
+// Every element is touched exactly once: the streams bypass the caches' retention (non-temporal), which measured ~25% faster
+// than cached accesses on MI355X -- unless all that a launch touches stays in the caches (CACHED).
+template <bool CACHED>
+__device__ __forceinline__ f32x4_u load4(const f32x4_u *p)
 {
-    // Every element is touched exactly once: all streams bypass the caches' retention
-    // (non-temporal), which measured ~25% faster than cached accesses on MI355X.
-    const int seg = blockIdx.x / per_seg, chunk = blockIdx.x % per_seg;
+    if constexpr (CACHED)
+        return *p;
+    else
+        return __builtin_nontemporal_load(p);
+}
+template <bool CACHED>
+__device__ __forceinline__ void store4(f32x4_t v, f32x4_u *p)
+{
+    if constexpr (CACHED)
+        *p = v;
+    else
+        __builtin_nontemporal_store(v, p);
+}
+
+template <bool LAND, int T, int U, bool CACHED, int SEG>
+__global__ __launch_bounds__(T) void dp_reduce_kernel(AddSegments<SEG> a, int64_t n, int per_seg)
+{
+    const int seg = SEG == 1 ? 0 : blockIdx.x / per_seg, chunk = SEG == 1 ? blockIdx.x : blockIdx.x % per_seg;
     float *const dst = a.dst[seg];
     const float *const src = a.src[seg];
     float *const land = a.land[seg];
@@ -49,14 +67,14 @@ __global__ __launch_bounds__(T) void dp_reduce_kernel(AddSegments a, int64_t n, 
     if (chunk < per_seg - 1) {                       // (every chunk but the last is whole)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            x[u] = __builtin_nontemporal_load(&dst4[base + u * T]);
-            y[u] = __builtin_nontemporal_load(&src4[base + u * T]);
+            x[u] = load4<CACHED>(&dst4[base + u * T]);
+            y[u] = load4<CACHED>(&src4[base + u * T]);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            __builtin_nontemporal_store(y[u] + x[u], &dst4[base + u * T]);   // "O <- B_in + O"
+            store4<CACHED>(y[u] + x[u], &dst4[base + u * T]);         // "O <- B_in + O"
             if constexpr (LAND)
-                __builtin_nontemporal_store(y[u], &land4[base + u * T]);
+                store4<CACHED>(y[u], &land4[base + u * T]);
         }
         return;
     }
@@ -64,10 +82,10 @@ __global__ __launch_bounds__(T) void dp_reduce_kernel(AddSegments a, int64_t n, 
     for (int u = 0; u < U; ++u) {
         const int64_t i = base + u * T;
         if (i < n4) {
-            y[u] = __builtin_nontemporal_load(&src4[i]);
-            __builtin_nontemporal_store(y[u] + __builtin_nontemporal_load(&dst4[i]), &dst4[i]);
+            y[u] = load4<CACHED>(&src4[i]);
+            store4<CACHED>(y[u] + load4<CACHED>(&dst4[i]), &dst4[i]);
             if constexpr (LAND)
-                __builtin_nontemporal_store(y[u], &land4[i]);
+                store4<CACHED>(y[u], &land4[i]);
         }
     }
     if (chunk == per_seg - 1 && (int)threadIdx.x < (int)(n - n4 * 4)) {          // the last elements of the segment
@@ -169,6 +187,36 @@ __global__ __launch_bounds__(256) void fill_ff_kernel(unsigned *dst, size_t nwor
         dst[i] = 0xFFFFFFFFu;
 }
 
+template <int SEG>
+hipError_t launch_adds(float *const *dst, const float *const *src, float *const *land, int n_seg, int64_t n, int per_seg,
+                       int threads, bool long_segments, bool cached, hipStream_t s)
+{
+    AddSegments<SEG> a = {};
+    for (int i = 0; i < n_seg; ++i) {
+        a.dst[i] = dst[i];
+        a.src[i] = src[i];
+        a.land[i] = land != nullptr ? land[i] : nullptr;
+    }
+    const dim3 grid((unsigned)((int64_t)per_seg * n_seg)), block(threads);
+#define CF_ADD(T, U, C)                                                                                       \
+    do {                                                                                                      \
+        if (land != nullptr)                                                                                  \
+            hipLaunchKernelGGL((dp_reduce_kernel<true, T, U, C, SEG>), grid, block, 0, s, a, n, per_seg);     \
+        else                                                                                                  \
+            hipLaunchKernelGGL((dp_reduce_kernel<false, T, U, C, SEG>), grid, block, 0, s, a, n, per_seg);    \
+    } while (0)
+    if (threads == 64)
+        CF_ADD(64, 1, false);
+    else if (long_segments)
+        CF_ADD(256, 1, false);
+    else if (cached)
+        CF_ADD(256, 4, true);
+    else
+        CF_ADD(256, 4, false);
+#undef CF_ADD
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_dp_reduce_segments(float *const *dst, const float *const *src, float *const *land, int n_seg, int64_t n,
@@ -180,6 +228,10 @@ hipError_t launch_dp_reduce_segments(float *const *dst, const float *const *src,
     // 125M elements).  Seven segments landing their arrivals, buffers in turn, TB/s for (threads, vectors per lane):
     //   125M elements: (64, 1) 6.1, (256, 1) 5.9, (256, 4) 5.4, (64, 2) 5.2;   10M: 6.25, 6.1, 6.2, 5.7;
     //   3M: 5.5, 5.8, 5.9, 6.2;   20M, segments off the 16-byte grid: 5.5, 5.7, 5.6, 5.1.
+    // Up to 64 MB in all the caches keep what a launch touches, and non-temporal accesses only cost (us, cached against
+    // non-temporal, slices off the 16-byte grid): one segment of 1M elements landing its arrival 4.2 / 5.1, 3M 8.3 / 10.0,
+    // 5M (80 MB) 15.7 / 15.4; one of 5M without a landing (60 MB) 10.0 / 11.8, 8M 18.4 / 17.5; three of 1M 8.4 / 10.0, five 15.6 /
+    // 15.5.
     uintptr_t bits = 0;
     for (int i = 0; i < n_seg; ++i)
         bits |= reinterpret_cast<uintptr_t>(dst[i]) | reinterpret_cast<uintptr_t>(src[i]) |
@@ -188,35 +240,17 @@ hipError_t launch_dp_reduce_segments(float *const *dst, const float *const *src,
     const int threads = long_segments && aligned ? 64 : 256;
     const int per_wg = threads * (long_segments ? 1 : 4);
     const int64_t per_seg = (n / 4 + per_wg) / per_wg;
+    const bool cached = !long_segments && (double)n * n_seg * (land != nullptr ? 16 : 12) <= 64e6;
     int at = 0;
     while (at < n_seg) {                             // (as many segments per launch as its arguments and its grid take)
-        int take = n_seg - at < AddSegments::MAX ? n_seg - at : AddSegments::MAX;
+        int take = n_seg - at < MAX_SEGMENTS ? n_seg - at : MAX_SEGMENTS;
         while (take > 1 && per_seg * take >= ((int64_t)1 << 31))
             --take;
         if (per_seg * take >= ((int64_t)1 << 31))
             return hipErrorInvalidValue;
-        AddSegments a = {};
-        for (int i = 0; i < take; ++i) {
-            a.dst[i] = dst[at + i];
-            a.src[i] = src[at + i];
-            a.land[i] = land != nullptr ? land[at + i] : nullptr;
-        }
-        const dim3 grid((unsigned)(per_seg * take)), block(threads);
-#define CF_ADD(T, U)                                                                                          \
-    do {                                                                                                      \
-        if (land != nullptr)                                                                                  \
-            hipLaunchKernelGGL((dp_reduce_kernel<true, T, U>), grid, block, 0, s, a, n, (int)per_seg);        \
-        else                                                                                                  \
-            hipLaunchKernelGGL((dp_reduce_kernel<false, T, U>), grid, block, 0, s, a, n, (int)per_seg);       \
-    } while (0)
-        if (threads == 64)
-            CF_ADD(64, 1);
-        else if (long_segments)
-            CF_ADD(256, 1);
-        else
-            CF_ADD(256, 4);
-#undef CF_ADD
-        hipError_t e = hipGetLastError();
+        float *const *l = land != nullptr ? &land[at] : nullptr;
+        hipError_t e = take == 1 ? launch_adds<1>(&dst[at], &src[at], l, 1, n, (int)per_seg, threads, long_segments, cached, s)
+                                 : launch_adds<MAX_SEGMENTS>(&dst[at], &src[at], l, take, n, (int)per_seg, threads, long_segments, cached, s);
         if (e != hipSuccess)
             return e;
         at += take;
