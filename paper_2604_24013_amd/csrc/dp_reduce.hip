@@ -106,11 +106,11 @@ struct AddBatch {
 };
 
 // LAND: as above -- source s is also stored to land[s].  INIT: dst <- ((src[0] + src[1]) + ...), what it held is not read.
-template <bool LAND, bool INIT>
+// U: vectors per lane, (n_src + 1) * U loads in flight.
+template <bool LAND, bool INIT, int U>
 __global__ __launch_bounds__(DP_THREADS) void dp_reduce_multi_kernel(float *__restrict__ dst, AddBatch ab, int n_src,
                                                                     int64_t n, AddBatch lb)
 {
-    constexpr int U = 2;                             // vectors per lane: (n_src + 1) * U loads in flight
     const int64_t n4 = n / 4;
     const int64_t base = (int64_t)blockIdx.x * DP_THREADS * U + threadIdx.x;
     f32x4_u *const dst4 = reinterpret_cast<f32x4_u *>(dst);
@@ -265,7 +265,7 @@ hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src
         return hipSuccess;
     if (init && n_src > AddBatch::MAX)
         return hipErrorInvalidValue;
-    if (n_src > AddBatch::MAX) {                     // one pass per source: the same additions in the same order
+    if (n_src > AddBatch::MAX || (n_src == 1 && !init)) {    // one pass per source: the same additions in the same order
         for (int i = 0; i < n_src; ++i) {
             hipError_t e = launch_dp_reduce_segments(&dst, &src[i], land != nullptr ? &land[i] : nullptr, 1, n, s);
             if (e != hipSuccess)
@@ -278,23 +278,32 @@ hipError_t launch_dp_reduce_multi(float *dst, const float *const *src, int n_src
         ab.src[i] = src[i];
         lb.src[i] = land != nullptr ? land[i] : nullptr;
     }
-    const int64_t per_wg = (int64_t)DP_THREADS * 2;
+    // Short slices: one vector per lane, twice the workgroups (7 sources, us for one / two vectors: 30 thousand elements 4.6 / 6.4,
+    // 1M 12.0 / 14.9, 2M 23.7 / 22.3, 3M 34.1 / 33.2, 10M 108 / 110).
+    const bool short_slice = n < 3 << 19;
+    const int64_t per_wg = (int64_t)DP_THREADS * (short_slice ? 1 : 2);
     const int64_t want = (n / 4 + per_wg) / per_wg;
     if (want >= ((int64_t)1 << 31))
         return hipErrorInvalidValue;
-#define CF_MULTI(L, I) \
-    hipLaunchKernelGGL((dp_reduce_multi_kernel<L, I>), dim3((unsigned)want), dim3(DP_THREADS), 0, s, dst, ab, n_src, n, lb)
-    if (init) {
-        if (land != nullptr)
-            CF_MULTI(true, true);
-        else
-            CF_MULTI(false, true);
-    } else if (land != nullptr) {
+#define CF_MULTI_U(L, I, U) \
+    hipLaunchKernelGGL((dp_reduce_multi_kernel<L, I, U>), dim3((unsigned)want), dim3(DP_THREADS), 0, s, dst, ab, n_src, n, lb)
+#define CF_MULTI(L, I)              \
+    do {                            \
+        if (short_slice)            \
+            CF_MULTI_U(L, I, 1);    \
+        else                        \
+            CF_MULTI_U(L, I, 2);    \
+    } while (0)
+    if (init && land != nullptr)
+        CF_MULTI(true, true);
+    else if (init)
+        CF_MULTI(false, true);
+    else if (land != nullptr)
         CF_MULTI(true, false);
-    } else {
+    else
         CF_MULTI(false, false);
-    }
 #undef CF_MULTI
+#undef CF_MULTI_U
     return hipGetLastError();
 }
 

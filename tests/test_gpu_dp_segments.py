@@ -1,5 +1,5 @@
 """All adds of a ring gradient reduce in one launch: slice lengths around the vectors, the chunks and the rules of the launch
-(8M elements: one-wave workgroups), slices off the 16-byte grid; every element bit for bit (one fp32 addition each)."""
+(8M elements: one-wave workgroups; 1.5M: two vectors per lane in the pairwise sum), slices off the 16-byte grid; every element bit for bit (one fp32 addition each)."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("carry", [0, cf.CF_FUSED_COPY])
 @pytest.mark.parametrize("p,m,c", [(2, 1, 1), (8, 1, 3), (4, 2, 8), (8, 2, 4094), (3, 1, 4095), (8, 1, 4096), (8, 1, 4097), (2, 1, 12289),
-                                   (2, 1, (8 << 20) - 1), (2, 1, 8 << 20), (3, 1, (8 << 20) + 5)])
+                                   (2, 1, (8 << 20) - 1), (2, 1, 8 << 20), (3, 1, (8 << 20) + 5), (4, 1, (3 << 19) - 1), (4, 1, 3 << 19)])
 def test_ring_and_pairwise_in_one_launch(p, m, c, carry):
     rng = np.random.default_rng(c)
     g = rng.standard_normal(p * c, dtype=np.float32)
