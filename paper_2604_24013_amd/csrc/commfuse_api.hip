@@ -934,10 +934,14 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // epilogues of the last step's few tiles would take it alone, at the end (landing the arrivals tile by tile under the
     // earlier steps and summing them there measured, us, against this: 6 ranks 390 x 2088 x 1096 54 -> 42, 8 ranks 512 x 4096 x
     // 1376 118 -> 82, 1024 x 8192 x 3584 481 -> 467).
-    bool pair_front = false;
+    // Two ranks have one arrival and nothing to sum: the last step's epilogue reads it from the partner's buffer and lands
+    // it beside its GEMM, as on the ring (through O, us: 1024 x
+    // 8192 x 3584 122.5 -> 110.9, 512 x 4096 x 1376 34.5 -> 31.9, 192 x 8192 x 512 23.7 -> 20.2).
+    bool pair_front = false, pair_beside = false;
     if (!few_rows && (flags & CF_FUSED_COPY) && kind == CF_KIND_RS_PAIR && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
         r.n > 0 && r.k > 0 && wide && cf::tuning().carry != 0) {
-        pair_front = true;
+        pair_beside = p == 2;
+        pair_front = !pair_beside;
         carried = true;
     }
     // Without CF_SERIAL (reduce-scatter and all-gather on two streams): the rank step as a few launches, each a group
@@ -1113,7 +1117,12 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                 gp.flag_step[j] = nullptr;
                 if (last && pair_front)
                     gp.recv_step[j] = static_cast<const float *>(b->O);
-                gp.recv_in_epilogue = pair_front;
+                gp.recv_in_epilogue = pair_front || pair_beside;
+                if (last && pair_beside) {
+                    gp.recv_step[j] = static_cast<const float *>(b->peer_stage[0]);
+                    gp.tail_src[j] = gp.recv_step[j];
+                    gp.tail_dst[j] = static_cast<float *>(b->recv_each[0]);
+                }
                 if (last && !pair_front)
                     for (int t = 1; t < p - 1; ++t)
                         gp.recv_more[gp.n_recv_more++] = static_cast<const float *>(b->recv_each[t]);

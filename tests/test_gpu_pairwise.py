@@ -352,3 +352,32 @@ def test_rs_pair_carried_under_the_16x16x32_main_loop(k):
                         assert torch.equal(run.each[i], run.stage[i]), f"layout {layout}: delivery of round {i + 1}"
     finally:
         os.environ.pop("COMMFUSE_TILE", None)
+
+
+@pytest.mark.parametrize("tile,k", [("128x128", 328), ("256x128", 328), ("256x256", 64), ("256x256", 192), ("256x256", 1096),
+                                    ("256x256", 2304)])
+@pytest.mark.parametrize("mc,n", [(512, 768), (520, 776)])
+def test_rs_pair_of_two_ranks_lands_beside_the_gemm(mc, n, tile, k):
+    """Two ranks: the one arrival is read from the partner's buffer in the last step's epilogue and landed by its work items.
+    On whole 256x256 tiles the landing is dealt over the k-tiles of the main loop: one k-tile (nothing dealt), three,
+    seventeen with a ragged tail, thirty-six (everything dealt); otherwise in front of the main loop or behind the epilogue.
+    The bits are those of the copies in front."""
+    w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=2, m_chunk=mc, n=n, k=k)
+    data = inputs.make_rs(w, salt=29 + k)
+    ref = _oracle_pair(w, data, 1)
+    os.environ["COMMFUSE_TILE"] = tile
+    try:
+        for layout in (cf.CF_W_KN, cf.CF_W_NK):
+            got = []
+            for flags in (0, cf.CF_FUSED_COPY):
+                run = H.RsPairRun(w, data, 1, layout, keep_all=True)
+                for t in run.send_each + run.each + [run.O]:
+                    t.fill_(float("nan"))
+                run.run_schedule(cf.CF_PERSISTENT | cf.CF_SERIAL | flags)
+                assert torch.equal(run.each[0], run.stage[0])
+                for i, o in enumerate((run.send_each[0], run.O)):
+                    assert H.rel_err(H.to_host_f64(o), ref[i]) <= TIGHT_BF16
+                got.append(torch.cat([run.send_each[0], run.O]))
+            assert torch.equal(got[0], got[1])
+    finally:
+        os.environ.pop("COMMFUSE_TILE", None)
