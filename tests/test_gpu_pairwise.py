@@ -361,11 +361,12 @@ def test_rs_pair_of_two_ranks_lands_beside_the_gemm(mc, n, tile, k):
     """Two ranks: the one arrival is read from the partner's buffer in the last step's epilogue and landed by its work items.
     On whole 256x256 tiles the landing is dealt over the k-tiles of the main loop: one k-tile (nothing dealt), three,
     seventeen with a ragged tail, thirty-six (everything dealt); otherwise in front of the main loop or behind the epilogue.
-    The bits are those of the copies in front."""
+    The bits are those of the copies in front (whose single arrival is kept out of the stream that adds it in mid-sum)."""
     w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=2, m_chunk=mc, n=n, k=k)
     data = inputs.make_rs(w, salt=29 + k)
     ref = _oracle_pair(w, data, 1)
     os.environ["COMMFUSE_TILE"] = tile
+    os.environ["COMMFUSE_STREAM_RECV"] = "0"
     try:
         for layout in (cf.CF_W_KN, cf.CF_W_NK):
             got = []
@@ -381,3 +382,4 @@ def test_rs_pair_of_two_ranks_lands_beside_the_gemm(mc, n, tile, k):
             assert torch.equal(got[0], got[1])
     finally:
         os.environ.pop("COMMFUSE_TILE", None)
+        os.environ.pop("COMMFUSE_STREAM_RECV", None)
