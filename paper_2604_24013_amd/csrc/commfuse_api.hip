@@ -1756,7 +1756,11 @@ size_t commfuse_workspace_bytes(const cf_layer_desc *desc, int kind)
         return 0;                                  // the gradient path needs none
     if (resolve(desc, kind, &r) != CF_OK || !r.bf16_in)
         return 0;
-    return WS_COUNTER_BYTES + (size_t)WS_MAX_SPLITS * (size_t)r.mc * (size_t)r.n * sizeof(float);
+    cf::GemmParams step;
+    fill_shape(step, r);
+    const size_t tiles = (size_t)WS_MAX_SPLITS * (size_t)r.mc * (size_t)r.n * sizeof(float);
+    const size_t rows = cf::gemm_rows_ws_bytes(step, r.bf16_in, r.w_kn, num_cu_of_current_device());   // (whole tiles: more than the step's elements)
+    return WS_COUNTER_BYTES + (rows > tiles ? rows : tiles);
 }
 
 cf_status commfuse_set_workspace(void *device_ptr, size_t bytes, void *hip_stream)

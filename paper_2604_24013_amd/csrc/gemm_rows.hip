@@ -538,6 +538,15 @@ bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
     return us < gemm_bf16_tile_us(p, num_cu);
 }
 
+size_t gemm_rows_ws_bytes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
+{
+    if (!bf16 || p.n_steps > 0 || !gemm_rows_takes(p, bf16, w_kn, num_cu))
+        return 0;
+    const RowsShape t = choose_shape(p.M, p.N, p.K, bf16, w_kn, num_cu);
+    const size_t tiles = (size_t)((p.N + 16 * t.nc - 1) / (16 * t.nc)) * (size_t)((p.M + 16 * t.mf - 1) / (16 * t.mf));
+    return t.ks > 1 ? tiles * t.ks * (256 * t.mf * t.nc) * sizeof(float) : 0;
+}
+
 template <int SEG>
 static hipError_t launch_segments(const GemmParams &g, bool bf16, bool w_kn, bool out_bf16, hipStream_t s, int num_cu)
 {

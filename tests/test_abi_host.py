@@ -213,6 +213,10 @@ def test_schedule_argument_checks(lib):
     assert _status(cf.run_schedule, cf.layer_desc(4, 0, 16, 0, 0), cf.CF_KIND_DP, ok, None, None, cf.CF_FUSED_COPY)[0] == cf.CF_ERR_UNSUPPORTED
     # 64 KiB of arrival counters + 8 partial tiles of m_chunk x n fp32; none for the gradient path / fp32
     assert cf.workspace_bytes(d, cf.CF_KIND_RS) == 64 * 1024 + 8 * 16 * 32 * 4
+    for mc in (1, 4, 8):                             # few rows: four splits of 17 whole tiles of 16 x 32
+        few = cf.layer_desc(4, 0, mc, 520, 8192)
+        assert cf.workspace_bytes(few, cf.CF_KIND_RS) == 64 * 1024 + 17 * 4 * 16 * 32 * 4
+    assert cf.workspace_bytes(cf.layer_desc(4, 0, 16, 520, 8192), cf.CF_KIND_RS) == 64 * 1024 + 8 * 16 * 520 * 4
     assert cf.workspace_bytes(d, cf.CF_KIND_DP) == 0
     assert cf.workspace_bytes(cf.layer_desc(4, 0, 16, 32, 64, "f32"), cf.CF_KIND_AG) == 0
     assert _status(cf.set_workspace, 0x1008, 1 << 20)[0] == cf.CF_ERR_MISALIGNED

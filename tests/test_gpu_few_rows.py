@@ -253,3 +253,15 @@ def test_rule_for_packed_rank_steps(dims, want, rows):
         assert all(torch.equal(a, b) for a, b in zip(each, stage))
         return torch.cat(sends + [O])
     assert _which(run) == want
+
+
+@pytest.mark.parametrize("mc", [1, 4, 8])
+def test_the_advertised_workspace_takes_the_k_split(mc, rows):
+    """commfuse_workspace_bytes covers the partial tiles of a few-rows step whose long k range is split."""
+    w, data, ref = _rs(2, mc, 520, 8192, "bf16", 14)
+    run = H.RsRun(w, data, 1)
+    ws = torch.full((cf.workspace_bytes(run.desc, cf.CF_KIND_RS),), 0xFF, dtype=torch.uint8, device=H.DEV)
+    cf.set_workspace(ws)
+    for got, want in zip(run.run_steps(), ref):
+        assert H.rel_err(got, want) <= 2e-5                       # (sqrt(2) more than at k = 4096)
+    assert bool((ws[64 * 1024:] != 0xFF).any())
