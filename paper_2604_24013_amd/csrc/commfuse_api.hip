@@ -901,7 +901,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     if (do_copy && b->recv_each != nullptr)
         for (int i = 0; i < p - 1; ++i)
             wide = wide && aligned16(b->peer_stage[i]) && aligned16(b->recv_each[i]);
-    if (few_rows && (flags & CF_FUSED_COPY) && wide)
+    if (few_rows && (flags & CF_FUSED_COPY) && wide && cf::tuning().carry != 0)
         carried = true;
     if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr && do_copy && do_compute &&
         slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0) {

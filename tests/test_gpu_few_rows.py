@@ -265,3 +265,53 @@ def test_the_advertised_workspace_takes_the_k_split(mc, rows):
     for got, want in zip(run.run_steps(), ref):
         assert H.rel_err(got, want) <= 2e-5                       # (sqrt(2) more than at k = 4096)
     assert bool((ws[64 * 1024:] != 0xFF).any())
+
+
+@pytest.mark.parametrize("carry", [True, False])
+def test_padded_rows_carried_and_copied(carry, rows):
+    """Row strides beyond the rows, few rows: a delivery that the launch carries lands without the padding of its rows, which
+    keeps what it held; COMMFUSE_CARRY=0 has it copied in front, padding and all, also under CF_FUSED_COPY."""
+    p, mc, n, k, ldo, lda = 4, 9, 72, 72, 88, 80
+    rows(None)
+    g = torch.Generator(device=H.DEV)
+    g.manual_seed(15)
+    rnd = lambda *shape: torch.empty(shape, device=H.DEV).normal_(generator=g)
+    nan = lambda *shape, dtype=torch.float32: torch.full(shape, float("nan"), dtype=dtype, device=H.DEV)
+    W = rnd(k, n).to(torch.bfloat16)
+    st = torch.cuda.Stream()
+    if not carry:
+        os.environ["COMMFUSE_CARRY"] = "0"
+    try:
+        A, stage, each = rnd(p * mc, lda).to(torch.bfloat16), [rnd(mc, ldo) for _ in range(p - 1)], [nan(mc, ldo) for _ in range(p - 1)]
+        O, sends = nan(mc, ldo), [nan(mc, ldo) for _ in range(p - 1)]
+        desc = cf.layer_desc(p, 1, mc, n, k, "bf16", "f32", lda=lda, ldo=ldo)
+        bufs = cf.make_buffers(A, W, O, stage, (None, None), (None, None), None, each, sends)
+        torch.cuda.synchronize()
+        cf.run_schedule(desc, cf.CF_KIND_RS, bufs, st, st, ONE_LAUNCH | cf.CF_FUSED_COPY)
+        st.synchronize()
+        for j in range(p):
+            l = cf.chunk_index(cf.CF_KIND_RS, p, 1, j)
+            want = A[l * mc:(l + 1) * mc, :k].double() @ W.double() + (stage[j - 1][:, :n].double() if j else 0.0)
+            got = sends[j] if j < p - 1 else O
+            assert H.rel_err(H.to_host_f64(got[:, :n]), H.to_host_f64(want)) <= 1e-5
+            assert bool(got[:, n:].isnan().all())
+        moved = [(each, stage, n)]
+        own, stage, each = rnd(mc, lda).to(torch.bfloat16), [rnd(mc, lda).to(torch.bfloat16) for _ in range(p - 1)], \
+            [nan(mc, lda, dtype=torch.bfloat16) for _ in range(p - 1)]
+        O = nan(p * mc, ldo)
+        bufs = cf.make_buffers(own, W, O, stage, (None, None), (None, None), None, each)
+        torch.cuda.synchronize()
+        cf.run_schedule(desc, cf.CF_KIND_AG, bufs, st, st, ONE_LAUNCH | cf.CF_FUSED_COPY)
+        st.synchronize()
+        for j in range(p):
+            l = cf.chunk_index(cf.CF_KIND_AG, p, 1, j)
+            got = O[l * mc:(l + 1) * mc]
+            want = (stage[j - 1] if j else own)[:, :k].double() @ W.double()
+            assert H.rel_err(H.to_host_f64(got[:, :n]), H.to_host_f64(want)) <= 1e-5
+            assert bool(got[:, n:].isnan().all())
+        for land, sent, width in moved + [(each, stage, k)]:
+            for a, b in zip(land, sent):
+                assert torch.equal(a[:, :width], b[:, :width])
+                assert bool(a[:, width:].isnan().all()) if carry else torch.equal(a[:, width:], b[:, width:])
+    finally:
+        os.environ.pop("COMMFUSE_CARRY", None)
