@@ -515,7 +515,8 @@ RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num
 bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
 {
     const Tuning tn = tuning();
-    if (tn.rows == 0 || tn.tile_bm > 0 || tn.tile_f32_bm > 0 || tn.splitk > 0 || tn.staged || tn.deep >= 0)
+    if (tn.rows == 0 || tn.tile_bm > 0 || tn.tile_f32_bm > 0 || tn.splitk > 0 || tn.staged || tn.deep >= 0 || tn.prefetch >= 0 ||
+        tn.xcd_steps >= 0 || tn.k_rotate >= 0 || tn.xcd_bands > 0 || tn.stream_recv >= 0 || tn.mfma16 >= 0 || tn.persist_wgs > 0)
         return false;                                // an override asks for one of the tile kernels
     if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.a_t || p.wait_flag != nullptr || p.cp_bytes != 0)
         return false;

@@ -315,3 +315,30 @@ def test_padded_rows_carried_and_copied(carry, rows):
                 assert bool(a[:, width:].isnan().all()) if carry else torch.equal(a[:, width:], b[:, width:])
     finally:
         os.environ.pop("COMMFUSE_CARRY", None)
+
+
+@pytest.mark.parametrize("override", ["K_ROTATE=0", "K_ROTATE=1", "XCD_STEPS=0", "XCD_BANDS=1", "STREAM_RECV=0", "PREFETCH=0", "PERSIST_WGS=64",
+                                      "MFMA16=0", "DEEP=0", "TILE=128x128"])
+def test_overrides_of_the_tile_kernels_keep_a_launch_on_them(override, rows):
+    """A rank step that the rule gives to the few-rows kernel, told by its bits: with an override of the tile kernels set it
+    runs there."""
+    w, data, _ = _rs(8, 9, 264, 1096, "bf16", 16)
+    run = H.RsRun(w, data, 1, each=True)
+
+    def result():
+        run.run_schedule(ONE_LAUNCH)
+        return torch.cat(run.send_each + [run.O]).clone()
+    rows(None)
+    by_rule = result()
+    rows("0")
+    tiles = result()
+    rows(None)
+    name, value = ("COMMFUSE_" + override).split("=")
+    os.environ[name] = value
+    try:
+        got = result()
+    finally:
+        os.environ.pop(name, None)
+    assert not torch.equal(by_rule, tiles)
+    assert not torch.equal(got, by_rule)
+    assert H.rel_err(H.to_host_f64(got), H.to_host_f64(tiles)) <= 1e-5
