@@ -352,8 +352,8 @@ enum {
                             With CF_FUSED_COPY (CF_KIND_RS_PAIR): one pass in front of the launch reads all arrivals
                             from the partners' buffers (peer_stage), lands them (recv_each) and leaves their sum in
                             O, which the last step adds to its product (p = 2: the one arrival is read in the last
-                            step's epilogue and landed beside its GEMM).  Same sums, bit for bit (p = 2 without the
-                            flag: one arrival is added in mid-sum where the launch streams it, see CF_KIND_RS).
+                            step's epilogue and landed beside its GEMM).  Same sums, bit for bit (but p = 2 without
+                            the flag: one arrival is added in mid-sum and the k order rotated where CF_KIND_RS would).
                             Where a rank step has few rows in all (decoded tokens; the kernel that packs the rows
                             of every step into one launch) every kind's deliveries are carried, whatever k.
                             Not with CF_DEVICE_WAIT.                                                  */

@@ -22,7 +22,8 @@ struct GemmParams {
     const float *recv_more[MAX_RECV_MORE] = {};
     int n_recv_more = 0;
     int pf_lead = 16;    // B_in prefetch: k-tiles before the end of the k loop at which it is issued (0 = off)
-    bool recv_in_epilogue = false;   // persistent mode: B_in is never streamed through LDS (few steps of the launch have one)
+    bool recv_in_epilogue = false;   // persistent mode: B_in is never streamed through LDS (few steps of the launch have one),
+                                     // and every k loop starts at 0
     bool stream_recv = true;   // 256x256 tile: B_in lands in LDS under the main loop and is added in mid-sum (set by the launcher)
     void *out = nullptr;
     int64_t lda = 0, ldw = 0, ldo = 0;

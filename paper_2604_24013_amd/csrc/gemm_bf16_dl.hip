@@ -1639,7 +1639,9 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         }
         // (measured with whole steps per XCD only; a ragged k tail stays the last k-tile of every work item,
         // which keeps all earlier iterations of the 256x256 main loop branch-free)
-        p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0;
+        // (nor where the pairwise schedule carries its deliveries: the sums are bit for bit those of its copied mode, whose last
+        // step sums several partials and so keeps the k order)
+        p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0 && !p.recv_in_epilogue;
         // the 256x256 tile's main loop on 16x16x32 MFMAs (override: COMMFUSE_MFMA16 = 0 | 1)
         p.mfma16 = t.bm == 256 && t.bn == 256 && p.M % 256 == 0 && p.N % 256 == 0 && tn.mfma16 != 0;
     }

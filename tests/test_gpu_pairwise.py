@@ -227,7 +227,7 @@ def test_full_size_rs_pair(name, flags, keep_all):
     with H.Workspace(run.desc, cf.CF_KIND_RS_PAIR):       # as the benchmark runs it
         run.run_schedule(flags)
         if flags & cf.CF_FUSED_COPY:
-            run.run_schedule(flags)                       # (the tiles' counters are ready for a second launch)
+            run.run_schedule(flags)                       # (again, on what the first launch left)
         cf.device_status()
     for i in range(w.p):
         got = H.to_host_f64(run.sink[i] if i < w.p - 1 else run.O)
@@ -256,45 +256,48 @@ def test_pair_rejects_what_it_cannot_do():
         assert ei.value.status == cf.CF_ERR_UNSUPPORTED
 
 
-def test_rs_pair_carried_wait_is_bounded_and_recovers():
-    """The last step's wait for its tile's arrivals is a bounded spin.  With a limit of one poll, forced from the host,
-    a work item may give up (then the status call says so and the result is void); every kernel exits either way, and
-    the next launch -- its counters filled with zero in front -- is correct again."""
-    p, mc, n, k = 4, 256, 256, 128                   # one output tile per step: the four work items run side by side
+@pytest.mark.parametrize("workspace", [False, True])
+@pytest.mark.parametrize("tile", ["128x128", "256x256"])
+def test_rs_pair_arrivals_pass_sums_like_the_copied_mode(tile, workspace):
+    """CF_FUSED_COPY: one pass in front of the launch lands all arrivals and leaves their sum in O.  Whatever O held before is
+    not read, a registered workspace is not touched, and every bit is that of the mode that copies in front and sums in
+    the last step's epilogue."""
+    p, mc, n, k = 4, 256, 264, 128
     w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=p, m_chunk=mc, n=n, k=k)
     data = inputs.make_rs(w, salt=17)
     ref = _oracle_pair(w, data, 1)
     run = H.RsPairRun(w, data, 1, keep_all=True)
-    FC = cf.CF_PERSISTENT | cf.CF_SERIAL | cf.CF_FUSED_COPY
-    os.environ["COMMFUSE_SPIN_LIMIT"] = "1"
+    ws = torch.full((cf.workspace_bytes(run.desc, cf.CF_KIND_RS_PAIR),), 0x5A, dtype=torch.uint8, device=H.DEV)
+    before = None
+    os.environ["COMMFUSE_TILE"] = tile
     try:
-        with H.Workspace(run.desc, cf.CF_KIND_RS_PAIR):
-            run.run_schedule(FC)
-            try:
-                cf.device_status(run.cs)
-                timed_out = False
-            except cf.CommFuseError as e:
-                assert "gave up waiting" in str(e)
-                timed_out = True
-            if not timed_out:
-                assert H.rel_err(H.to_host_f64(run.O), ref[-1]) <= TIGHT_BF16
-            os.environ.pop("COMMFUSE_SPIN_LIMIT", None)
-            run.O.fill_(float("nan"))
-            for t in run.each:
+        if workspace:
+            cf.set_workspace(ws)
+            torch.cuda.synchronize()
+            before = ws.clone()
+        got = []
+        for flags in (0, cf.CF_FUSED_COPY, cf.CF_FUSED_COPY):            # (the second pass on what the first left in O)
+            if len(got) < 2:
+                run.O.fill_(float("nan"))
+            for t in run.each + run.send_each:
                 t.fill_(float("nan"))
-            run.run_schedule(FC)
-            cf.device_status(run.cs)
+            run.run_schedule(cf.CF_PERSISTENT | cf.CF_SERIAL | flags)
             assert H.rel_err(H.to_host_f64(run.O), ref[-1]) <= TIGHT_BF16
-            for i in range(p - 1):
-                assert torch.equal(run.each[i], run.stage[i])
+            assert all(torch.equal(a, b) for a, b in zip(run.each, run.stage))
+            got.append(torch.cat(run.send_each + [run.O]))
+        assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+        if workspace:
+            assert torch.equal(ws, before)
     finally:
-        os.environ.pop("COMMFUSE_SPIN_LIMIT", None)
+        os.environ.pop("COMMFUSE_TILE", None)
+        torch.cuda.synchronize()
+        cf.set_workspace(None)
 
 
 @pytest.mark.parametrize("tile", ["128x128", "256x128", "256x256"])
 def test_rs_pair_carried_on_every_tile_shape(tile):
-    """The landing of the arrivals behind the work items and the per-tile wait, on each tile shape of the one-launch
-    kernel (the work item's part of an arrival is its own output tile), several tiles per step and ragged edges."""
+    """The arrivals' sum in O, added by the last step's epilogue on each tile shape of the one-launch kernel: several tiles
+    per step and ragged edges, both weight orders, twice on the same buffers."""
     p, mc, n, k = 8, 520, 776, 328
     w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=p, m_chunk=mc, n=n, k=k)
     data = inputs.make_rs(w, salt=19)
@@ -324,9 +327,8 @@ def test_rs_pair_carried_on_every_tile_shape(tile):
 
 @pytest.mark.parametrize("k", [64, 192, 1096, 2304])
 def test_rs_pair_carried_under_the_16x16x32_main_loop(k):
-    """Whole 256x256 tiles: the kernel deals the landing of an arrival over the k-tiles of its main loop (one
-    16-byte load and one store per lane and k-tile) and copies what the k range leaves over behind the epilogue:
-    one k-tile (nothing dealt), three, seventeen with a ragged tail, thirty-six (everything dealt)."""
+    """Whole 256x256 tiles (the main loop on 16x16x32 MFMAs, the arrivals' sum in O added in the epilogue) over k ranges of
+    one k-tile, three, seventeen with a ragged tail and thirty-six: long ones must not stream O through LDS."""
     p, mc, n = 4, 512, 768
     w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=p, m_chunk=mc, n=n, k=k)
     data = inputs.make_rs(w, salt=23 + k)
@@ -361,12 +363,13 @@ def test_rs_pair_of_two_ranks_lands_beside_the_gemm(mc, n, tile, k):
     """Two ranks: the one arrival is read from the partner's buffer in the last step's epilogue and landed by its work items.
     On whole 256x256 tiles the landing is dealt over the k-tiles of the main loop: one k-tile (nothing dealt), three,
     seventeen with a ragged tail, thirty-six (everything dealt); otherwise in front of the main loop or behind the epilogue.
-    The bits are those of the copies in front (whose single arrival is kept out of the stream that adds it in mid-sum)."""
+    The bits are those of the copies in front (whose k order is kept from rotating, and whose single arrival from the
+    stream that adds it in mid-sum)."""
     w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=2, m_chunk=mc, n=n, k=k)
     data = inputs.make_rs(w, salt=29 + k)
     ref = _oracle_pair(w, data, 1)
     os.environ["COMMFUSE_TILE"] = tile
-    os.environ["COMMFUSE_STREAM_RECV"] = "0"
+    os.environ["COMMFUSE_STREAM_RECV"] = os.environ["COMMFUSE_K_ROTATE"] = "0"
     try:
         for layout in (cf.CF_W_KN, cf.CF_W_NK):
             got = []
@@ -383,3 +386,4 @@ def test_rs_pair_of_two_ranks_lands_beside_the_gemm(mc, n, tile, k):
     finally:
         os.environ.pop("COMMFUSE_TILE", None)
         os.environ.pop("COMMFUSE_STREAM_RECV", None)
+        os.environ.pop("COMMFUSE_K_ROTATE", None)
