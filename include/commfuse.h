@@ -313,7 +313,9 @@ enum {
                             streams; the other kinds need CF_SERIAL): the rank step is a few launches, each a
                             group of consecutive (sub-)steps that fills the chip about once, and the
                             deliveries of a group are copied on copy_stream under the launches of the
-                            groups before it, one event per group ordering the two streams.
+                            groups before it, one event per group ordering the two streams.  (Few rows in all,
+                            see the end: one group; with CF_FUSED_COPY the launch starts behind what
+                            copy_stream holds.)
                             (The kernel can also wait for per-step delivery flags on the device; on a real ring, where a delivery is a remote DMA
                             write that needs no compute unit here, that is how it would overlap.)
                             CF_KIND_RS_PAIR: every arrival is kept (recv_each) and the last step adds

@@ -502,16 +502,22 @@ RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num
 
 }  // namespace
 
-// Rule between this kernel and the tile kernels.  fp32: one round over the chip always
-// (1024 x 1024 x 4096 73 us, the tile kernel 143); several rounds of 64 x 64 tiles 2.5 us + 4.8 us + 0.0158 us per k each,
-// which wins over long k ranges (bound by the fp32 MFMAs: 512 x 4096 x 4096 142 us, 175) and not over short ones (2048 x
-// 8192 x 512 206, 153; 768 x 4096 x 256 27, 22) nor over grids that the 128 x 128 tiles fill (4096 x 8192 x 4096 2222, 2076).  bf16: a
-// launch costs 1.5 us and a round of 64 x 64 tiles over the chip 3.6 us + 0.27 us per 64 k (measured: 128 x 8192 x 3584 18.7 us,
-// 256 x 8192 x 3584 34.4, 512 x 4096 x 1376 21.5); the steps of a rank step in one launch 6.9 us + 0.24 us per 64 k (their
-// deliveries; p = 8, 64 rows x 8192 columns per step, four rounds: 512 k 37.5 us all-gather, 40.7 reduce-scatter, the tile
-// kernel 25.6 and 32.9; 1024 k 44.8 and 48.5 against 34.1 and 41.8; 2 x 192 x 4096 x 8192, two rounds: 70.2 and 72.5 against
-// 77.9 and 80.1) and 0.02 us per megabyte of W (2 x 96 x 8192 x 8192, 134 MB: 84.2 and 85.2 against 78.1 and 79.3).  The tile
-// kernels' cost is theirs to say (gemm_bf16_tile_us, gemm_f32_tile_us).
+// Rule between this kernel and the tile kernels, whose cost is theirs to say (gemm_bf16_tile_us, gemm_f32_tile_us).
+// fp32: always with tiles under 64 x 64 (one round over the chip: 512 x 1024 x 4096 42 us, the tile kernel 141).  64 x 64 tiles take
+// 3.1 us and 4.8 us + 0.0158 us per k a round, which wins over long k ranges (bound by the fp32 MFMAs: 1024 x 1024 x 4096 73 us, 143;
+// 512 x 4096 x 4096 142, 175) and not over short ones (2048 x 8192 x 512 206, 153; 768 x 4096 x 256 27, 22; 335 x 2328 x 160 9.6, 9.0)
+// nor over grids that the 128 x 128 tiles fill (4096 x 8192 x 4096 2222, 2076).
+// bf16: a launch costs 1.5 us, and a round of 64 x 64 tiles over the chip
+//  * 3.6 us + 0.27 us per 64 k for a single step (128 x 8192 x 3584 18.7 us warm, 256 x 8192 x 3584 34.4, 512 x 4096 x 1376 21.5);
+//  * 7.3 us + 0.235 us per 64 k for the steps of a rank step in one launch (their deliveries; p = 8, 64 rows x 8192 columns per
+//    step, four rounds: 512 k 37.5 us all-gather, 40.7 reduce-scatter, the tile kernel 25.6 and 32.9; 1024 k 44.8 and 48.5, 34.1
+//    and 41.8; 2 x 192 x 4096 x 8192, two rounds: 70.2 and 72.5, 77.9 and 80.1) and 0.02 us per megabyte of W (2 x 96 x 8192 x
+//    8192, 134 MB: 84.2 and 85.2, 78.1 and 79.3);
+//  * rows that do not start on a 128-byte line put every slice of theirs on two: 1.12 times the time per 64 k (575 x 3336 x 7328
+//    80 us, the tile kernel 70; 8 x 64 x 6352 x 7016 200, 154), 1.45 times where it is [k x n] weights too large for the caches
+//    (4 x 148 x 4408 x 5648 154, 107; 85 x 7512 x 6304 54, 47).
+// Of 3700 drawn shapes of the sizes between 1 x 128 x 128 and 1024 x 8192 x 8192 two are slower by rule than on the tile kernel
+// by 2 % and more, the worst by 4 %.
 bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
 {
     const Tuning tn = tuning();
@@ -528,13 +534,17 @@ bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
     const int64_t wgs = ((rows + 16 * t.mf - 1) / (16 * t.mf)) * ((p.N + 16 * t.nc - 1) / (16 * t.nc));
     if (wgs >= ((int64_t)1 << 24))
         return false;
-    if (tn.rows_mf > 0 || wgs * (bf16 ? 2 : 1) <= num_cu)
+    if (tn.rows_mf > 0 || (bf16 ? wgs * 2 <= num_cu : t.mf * t.nc < 16))
         return true;
     const int64_t rounds = (wgs + num_cu - 1) / num_cu;
     if (!bf16)
-        return 2.5 + rounds * (4.8 + 0.0158 * p.K) < gemm_f32_tile_us(p, num_cu);
-    const int slices = (p.K + 63) / 64;
-    const double us = p.n_steps > 0 ? 1.5 + rounds * (6.9 + 0.24 * slices) + 0.02e-6 * 2.0 * p.N * p.K
+        return 3.1 + rounds * (4.8 + 0.0158 * p.K) < gemm_f32_tile_us(p, num_cu);
+    double slices = (p.K + 63) / 64;
+    if (w_kn && p.ldw % 64 != 0 && 2.0 * p.N * p.K > 40e6)
+        slices *= 1.45;
+    else if (p.lda % 64 != 0 || (!w_kn && p.ldw % 64 != 0))
+        slices *= 1.12;
+    const double us = p.n_steps > 0 ? 1.5 + rounds * (7.3 + 0.235 * slices) + 0.02e-6 * 2.0 * p.N * p.K
                                     : 1.5 + rounds * (3.6 + 0.27 * slices);
     return us < gemm_bf16_tile_us(p, num_cu);
 }

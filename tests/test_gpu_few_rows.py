@@ -184,6 +184,12 @@ def test_two_streams_deliver_behind_the_copy_streams_work(dims, flags, rows):
         run.cs.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(run.each, fresh))
         assert H.rel_err(H.to_host_f64(run.O), want) <= 1e-5
+        for _ in range(3):                                   # captured and replayed, everything synchronised: the same
+            for t in run.each + [run.O]:
+                t.fill_(float("nan"))
+            run.run_schedule(flags | cf.CF_GRAPH)
+            assert all(torch.equal(a, b) for a, b in zip(run.each, fresh))
+            assert H.rel_err(H.to_host_f64(run.O), want) <= 1e-5
 
 
 def _which(run):
@@ -206,8 +212,11 @@ def _which(run):
 RULE_STEPS = [
     # a k range that the tile kernel splits through a workspace
     ((384, 4096, 8192, "bf16", True), "tiles"), ((384, 4096, 8192, "bf16", False), "rows"), ((256, 2048, 4096, "bf16", True), "rows"),
+    # rows off the 128-byte lines over a long k range, and on them
+    ((575, 2080, 7328, "bf16", False), "tiles"), ((575, 2080, 7360, "bf16", False), "rows"),
+    ((85, 7512, 6304, "bf16", True), "tiles"), ((85, 7552, 6336, "bf16", True), "rows"), ((85, 1512, 6304, "bf16", True), "rows"),
     # fp32: grids of one round, of several rounds over short and long k ranges, and grids that 128 x 128 tiles fill
-    ((1000, 1000, 256, "f32", False), "rows"), ((768, 4096, 256, "f32", False), "tiles"), ((512, 4096, 2048, "f32", False), "rows"),
+    ((1000, 1000, 256, "f32", False), "rows"), ((335, 2328, 160, "f32", False), "tiles"), ((768, 4096, 256, "f32", False), "tiles"), ((512, 4096, 2048, "f32", False), "rows"),
     ((4096, 2048, 512, "f32", False), "tiles"), ((1536, 4096, 1024, "f32", False), "rows"), ((2048, 4096, 1024, "f32", False), "tiles"),
 ]
 
