@@ -203,8 +203,7 @@ cf_status commfuse_ag_step(const cf_layer_desc *desc, int step, const void *shar
  *   pieces: call with p*m "ranks' worth" of pieces through commfuse_run_schedule, which
  *   honours desc->m for this kind too.)
  *   chunk_elems may be any non-negative number and the pointers need only be
- *   4-byte aligned; the 16-byte vector kernel runs when both the slice start
- *   and recv are 16-byte aligned (a scalar kernel handles the rest).
+ *   4-byte aligned (the accesses are 16 bytes wide all the same).
  */
 cf_status commfuse_dp_reduce_step(int p, int rank, int step, float *bucket, int64_t chunk_elems,
                                   const float *recv, void *hip_stream);

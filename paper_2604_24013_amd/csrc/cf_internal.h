@@ -17,7 +17,7 @@ struct GemmParams {
     const void *W = nullptr;
     const float *recv = nullptr;   // nullable: B_in of Alg. 2
     // further received partials, added after `recv` in index order before the product is added
-    // (pairwise schedule with the aggregation deferred to the last step; direct-to-LDS bf16 kernel only)
+    // (pairwise schedule with the aggregation deferred to the last step; direct-to-LDS bf16 and few-rows kernels)
     static constexpr int MAX_RECV_MORE = 15;
     const float *recv_more[MAX_RECV_MORE] = {};
     int n_recv_more = 0;
@@ -91,11 +91,11 @@ struct AttnParams {
     int l;               // slice index: queries [l*c, (l+1)*c)
     int64_t ldo;
     float scale;
-    // several slices in one launch (the 128/256-query kernel only): slices l, l+1, ..., l+n_slices-1, the output
+    // several slices in one launch: slices l, l+1, ..., l+n_slices-1, the output
     // of slice l+i starting out_slice_stride elements after that of slice l+i-1
     int n_slices = 1;
     int64_t out_slice_stride = 0;
-    // key split across workgroups (the 128-query kernel): the key tiles are divided over `ksplit` workgroups per
+    // key split across workgroups: the key tiles are divided over `ksplit` workgroups per
     // query block, which park (m, l, unnormalised O) in the workspace; the last one to finish merges them
     int ksplit = 1;
     float *ws = nullptr;
@@ -121,8 +121,8 @@ struct Tuning {
     int stream_recv = -1;           // COMMFUSE_STREAM_RECV = 0 | 1                        (-1 = unset)
     int mfma16 = -1;                // COMMFUSE_MFMA16 = 0 | 1: 16x16x32 MFMAs in the 256x256 persistent kernel (-1 = unset)
     int persist_wgs = 0;            // COMMFUSE_PERSIST_WGS = cap on the persistent kernel's grid (0 = unset)
-    int carry = -1;                 // COMMFUSE_CARRY = 0: the one-launch reduce-scatter never carries its deliveries
-                                    // under CF_FUSED_COPY (-1 = unset, 1: wherever the launch streams B_in)
+    int carry = -1;                 // COMMFUSE_CARRY = 0: a one-launch RS / AG / pairwise RS never carries its deliveries
+                                    // under CF_FUSED_COPY (-1 = unset, 1: wherever the launch can)
     int tile_f32_bm = 0;            // COMMFUSE_TILE_F32 = "128x128" | "64x64"             (0 = unset)
     int rows = -1;                  // COMMFUSE_ROWS = 0: never the few-rows kernel            (-1 = unset)
     int rows_mf = 0, rows_nc = 0, rows_ks = 0;   // COMMFUSE_ROWS = "MFxNCxKS": that shape of it (0 = unset)

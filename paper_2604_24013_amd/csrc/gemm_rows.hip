@@ -509,10 +509,10 @@ RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num
 // nor over grids that the 128 x 128 tiles fill (4096 x 8192 x 4096 2222, 2076).
 // bf16: a launch costs 1.5 us, and a round of 64 x 64 tiles over the chip
 //  * 3.6 us + 0.27 us per 64 k for a single step (128 x 8192 x 3584 18.7 us warm, 256 x 8192 x 3584 34.4, 512 x 4096 x 1376 21.5);
-//  * 7.3 us + 0.235 us per 64 k for the steps of a rank step in one launch (their deliveries; p = 8, 64 rows x 8192 columns per
-//    step, four rounds: 512 k 37.5 us all-gather, 40.7 reduce-scatter, the tile kernel 25.6 and 32.9; 1024 k 44.8 and 48.5, 34.1
-//    and 41.8; 2 x 192 x 4096 x 8192, two rounds: 70.2 and 72.5, 77.9 and 80.1) and 0.02 us per megabyte of W (2 x 96 x 8192 x
-//    8192, 134 MB: 84.2 and 85.2, 78.1 and 79.3);
+//  * 7.3 us + 0.235 us per 64 k for the steps of a rank step in one launch (their deliveries, less of them with smaller tiles;
+//    p = 8, 64 rows x 8192 columns per step, four rounds: 512 k 37.5 us all-gather, 40.7 reduce-scatter, the tile kernel 25.6
+//    and 32.9; 1024 k 44.8 and 48.5, 34.1 and 41.8; 2 x 192 x 4096 x 8192, two rounds: 70.2 and 72.5, 77.9 and 80.1) and 0.02 us
+//    per megabyte of W (2 x 96 x 8192 x 8192, 134 MB: 84.2 and 85.2, 78.1 and 79.3);
 //  * rows that do not start on a 128-byte line put every slice of theirs on two: 1.12 times the time per 64 k (575 x 3336 x 7328
 //    80 us, the tile kernel 70; 8 x 64 x 6352 x 7016 200, 154), 1.45 times where it is [k x n] weights too large for the caches
 //    (4 x 148 x 4408 x 5648 154, 107; 85 x 7512 x 6304 54, 47).
@@ -544,7 +544,7 @@ bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
         slices *= 1.45;
     else if (p.lda % 64 != 0 || (!w_kn && p.ldw % 64 != 0))
         slices *= 1.12;
-    const double us = p.n_steps > 0 ? 1.5 + rounds * (7.3 + 0.235 * slices) + 0.02e-6 * 2.0 * p.N * p.K
+    const double us = p.n_steps > 0 ? 1.5 + rounds * (3.6 + 3.7 * t.mf * t.nc / 16 + 0.235 * slices) + 0.02e-6 * 2.0 * p.N * p.K
                                     : 1.5 + rounds * (3.6 + 0.27 * slices);
     return us < gemm_bf16_tile_us(p, num_cu);
 }

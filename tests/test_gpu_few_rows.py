@@ -243,7 +243,7 @@ def test_rule_for_single_steps(case, want, rows):
 
 # p, rows per step, n, k
 @pytest.mark.parametrize("dims,want", [((8, 64, 8192, 512), "tiles"), ((8, 64, 8192, 1024), "tiles"), ((4, 128, 4096, 8192), "rows"),
-                                       ((2, 96, 8192, 8192), "tiles"), ((8, 8, 1536, 4096), "rows")])
+                                       ((2, 96, 8192, 8192), "tiles"), ((8, 8, 1536, 4096), "rows"), ((6, 130, 72, 96), "rows")])
 def test_rule_for_packed_rank_steps(dims, want, rows):
     p, mc, n, k = dims
     g = torch.Generator(device=H.DEV)

@@ -82,9 +82,8 @@ def test_rs_pair_reduced(shape, layout, dtype):
             # all steps in one launch: the same GEMMs and the same additions in the same order
             pers = H.RsPairRun(w, data, rank, layout, keep_all=True)
             PS = cf.CF_PERSISTENT | cf.CF_SERIAL
-            # (CF_FUSED_COPY: no copy is launched; the work items of step t - 1 land the arrival of round t tile by
-            # tile, the last step's work items wait for their tile's count -- with a registered workspace; without
-            # one the copies go in front as without the flag)
+            # (CF_FUSED_COPY: no copy is launched; the arrivals are landed and summed in a pass in front, beside the GEMM
+            # with two ranks, or by the few-rows launch; a registered workspace changes nothing)
             FC = PS | cf.CF_FUSED_COPY
             for flags, with_ws in ((PS, False), (PS | cf.CF_GRAPH, False), (PS | cf.CF_POISON, False), (FC, False),
                                    (FC, True), (FC | cf.CF_GRAPH, True)):
@@ -95,7 +94,7 @@ def test_rs_pair_reduced(shape, layout, dtype):
                 with ws:
                     pers.run_schedule(flags)
                     pers.run_schedule(flags)
-                    cf.device_status()               # no wait timed out
+                    cf.device_status()
                 assert np.array_equal(H.to_host_f64(pers.O), outs[-1]), f"rank {rank} flags {flags} (persistent)"
                 for i in range(p - 1):               # the partial every step sends to its partner
                     assert np.array_equal(H.to_host_f64(pers.send_each[i]), outs[i]), \
