@@ -717,7 +717,7 @@ namespace {
 
 // Which kernel, and over how many workgroups the keys of a query block are split.  The costs (us) are fitted to
 // measurements over batch x heads x queries of the slice x keys:
-//   * keys over waves (32 queries): 6.5 + 1.8 per eight 32-key tiles and round -- each workgroup reads all its keys
+//   * keys over waves (32 queries): 6.5 + 1.7 per eight 32-key tiles and round + 5 per further full round -- each workgroup reads all its keys
 //     itself, 128 KiB per step of its eight waves, 0.9 us at the L1's rate.  2x3x280x1120: 13.5 (query blocks: 20.5 at best,
 //     40 with one workgroup per compute unit, whose sixteen partials per block took most of it), 1x1x1024x8192: 21.5 with
 //     six splits (37.6), 1x8x1024x8192: 60.1 (57.9);
@@ -775,7 +775,9 @@ AttnChoice choose_attn(const AttnParams &p, int num_cu)
             const int64_t wgs = groups * k;
             double us;
             if (kind == 0) {
-                us = 6.5 + (double)((wgs + num_cu - 1) / num_cu) * (((tiles32 + k - 1) / k + 7) / 8) * 1.8 + (k > 1 ? 1.5 + 0.7 * k : 0.0);
+                const double rounds = (double)((wgs + num_cu - 1) / num_cu);
+                us = 6.5 + rounds * (((tiles32 + k - 1) / k + 7) / 8) * 1.7 + (wgs > num_cu ? 5.0 * (wgs - num_cu) / num_cu : 0.0) +
+                     (k > 1 ? 1.5 + 0.7 * k : 0.0);
             } else {
                 const int per_cu = kind == 1 || wgs <= num_cu ? 1 : 2;
                 const int64_t last = wgs % num_cu;
