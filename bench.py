@@ -246,7 +246,7 @@ def main() -> int:
             t_carry = time_calls(lambda: cf.run_schedule(rs.desc, cf.CF_KIND_RS, rs.bufs, rs.cs, rs.xs, PC), ag.cs, max(K, 50), W) if carried_too else None
             t_carry_up = time_calls(lambda: cf.run_schedule(ag.desc, cf.CF_KIND_AG, ag.bufs, ag.cs, ag.xs, PC), ag.cs, max(K, 50), W) if carried_too else None
             roofline = {"bound": "mfma",
-                        "kernel": "gemm_bf16_dl_kernel<256,256,...,persistent,B_in through LDS> (down-projection rank step: 8 chunk GEMMs, "
+                        "kernel": "gemm_bf16_dl_kernel<256,256,...,persistent,16x16x32 MFMAs> (down-projection rank step: 8 chunk GEMMs, "
                                   "fused B_in adds, every step's B_out stored)",
                         "achieved": round(ach, 1), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                         "frac": round(ach / PEAK_BF16_TFLOPS, 4),

@@ -22,9 +22,7 @@ struct GemmParams {
     const float *recv_more[MAX_RECV_MORE] = {};
     int n_recv_more = 0;
     int pf_lead = 16;    // B_in prefetch: k-tiles before the end of the k loop at which it is issued (0 = off)
-    bool recv_in_epilogue = false;   // persistent mode: B_in is never streamed through LDS (few steps of the launch have one),
-                                     // and every k loop starts at 0
-    bool stream_recv = true;   // 256x256 tile: B_in lands in LDS under the main loop and is added in mid-sum (set by the launcher)
+    bool k_in_order = false;         // persistent mode: every k loop starts at 0
     void *out = nullptr;
     int64_t lda = 0, ldw = 0, ldo = 0;
     int M = 0, N = 0, K = 0;
@@ -52,23 +50,19 @@ struct GemmParams {
     bool k_rotate = false;   // persistent mode: XCD x starts its k loops x/8 of the way into the k range (set by the launcher)
     bool xcd_steps = false;  // persistent mode: XCD x runs steps x, x+8, ... whole (set by the launcher)
     int xcd_bands = 1;       // ... or, > 1: 8 / xcd_bands step groups x xcd_bands bands of tile columns (set by the launcher)
+    bool early_recv = true;  // persistent mode: the first of B_in is requested in front of the last k-tile (set by the launcher)
     bool mfma16 = false;     // persistent mode, 256x256 tile: main loop on v_mfma_f32_16x16x32_bf16 (set by the launcher)
     const void *A_step[MAX_STEPS] = {};
     const float *recv_step[MAX_STEPS] = {};
     void *out_step[MAX_STEPS] = {};
     const unsigned *flag_step[MAX_STEPS] = {};
-    // the delivery carried by the consumer (persistent launch).  Reduce-scatter (256x256 tile with B_in through LDS):
-    // recv_step[s] points at what the neighbour sends (its buffer, not this rank's landing buffer), and the
-    // waves that add B_in also store it to land_step[s], the landing buffer.  All-gather: A_step[s] points at the
+    // the delivery carried by the consumer (persistent launch).  Reduce-scatter: recv_step[s] points at what the
+    // neighbour sends (its buffer, not this rank's landing buffer), and the epilogue that adds B_in also stores it to
+    // land_step[s], the landing buffer.  All-gather: A_step[s] points at the
     // neighbour's buffer, and every k-tile of the slice that comes in through LDS is stored on to land_step[s]
     // (same layout as A_step[s]) by one of the workgroups that load it.  Either way the emulated transfer happens
-    // inside the kernel, under its main loop.  Null = the operand is already where recv_step[s] / A_step[s] points.
+    // inside the kernel.  Null = the operand is already where recv_step[s] / A_step[s] points.
     void *land_step[MAX_STEPS] = {};
-    // A reduce-scatter step whose B_in is loaded in its epilogue (recv_step[s] = the sender's buffer) lands that same B_in
-    // beside its GEMM: every work item of step s copies its output tile's part of tail_src[s] (= recv_step[s]) to
-    // tail_dst[s], the landing buffer (both laid out like the output), written through to memory.  Nobody waits for it.
-    const float *tail_src[MAX_STEPS] = {};
-    float *tail_dst[MAX_STEPS] = {};
     const void *cp_src = nullptr;
     void *cp_dst = nullptr;
     size_t cp_bytes = 0;
@@ -118,7 +112,7 @@ struct Tuning {
     int xcd_steps = -1;             // COMMFUSE_XCD_STEPS = 0 | 1                          (-1 = unset)
     int k_rotate = -1;              // COMMFUSE_K_ROTATE = 0 | 1                           (-1 = unset)
     int xcd_bands = 0;              // COMMFUSE_XCD_BANDS = 1 | 2 | 4: column bands per step group (0 = unset: by shape)
-    int stream_recv = -1;           // COMMFUSE_STREAM_RECV = 0 | 1                        (-1 = unset)
+    int stream_recv = -1;           // COMMFUSE_STREAM_RECV = 0 | 1: one-launch rank steps: all of B_in requested behind the main loop (-1 = unset)
     int mfma16 = -1;                // COMMFUSE_MFMA16 = 0 | 1: 16x16x32 MFMAs in the 256x256 persistent kernel (-1 = unset)
     int persist_wgs = 0;            // COMMFUSE_PERSIST_WGS = cap on the persistent kernel's grid (0 = unset)
     int carry = -1;                 // COMMFUSE_CARRY = 0: a one-launch RS / AG / pairwise RS never carries its deliveries
@@ -146,10 +140,6 @@ TileChoice choose_tile_bf16(int M, int N, int K, int num_cu);
 hipError_t launch_gemm_bf16(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, int num_cu);
 // True if launch_gemm_bf16 would run the kernel that honours GemmParams::recv_more for these operands.
 bool gemm_bf16_takes_recv_list(const GemmParams &p, bool w_kn);
-// True if a persistent reduce-scatter launch that does NOT stream B_in (gemm_bf16_carries_delivery says no) can still
-// carry its deliveries: B_in read from the sender's buffer in the epilogue and landed by the same work item beside
-// its GEMM (GemmParams::tail_src).  fp32 partial sums, direct-to-LDS kernel.
-bool gemm_bf16_lands_beside(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu);
 // True if launch_gemm_bf16 would run this persistent launch (reduce_scatter: its steps add a received partial;
 // else an all-gather's) on a kernel that honours GemmParams::land_step (the delivery carried by the consumer)
 // for every step that receives.
@@ -160,7 +150,6 @@ int gemm_bf16_steps_per_launch(const GemmParams &p, bool w_kn, int num_cu);
 // Direct-to-LDS variant of the bf16 kernel (operand extents below 2^31 bytes).
 bool gemm_bf16_dl_supported(const GemmParams &p, bool w_kn);
 hipError_t launch_gemm_bf16_dl(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t);
-bool gemm_bf16_dl_streams_recv(const GemmParams &p, bool w_kn, bool out_bf16, TileChoice t);
 bool gemm_bf16_dl_carries_operand(const GemmParams &p);
 // The kernel for few rows (gemm_rows.hip; bf16 and fp32 operands): does it run this launch -- one chunk GEMM, or with
 // n_steps > 0 all steps of a rank step, whose deliveries it then carries where land_step / land_more are set?

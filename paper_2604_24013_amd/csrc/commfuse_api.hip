@@ -880,9 +880,8 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     };
     auto stage_of = [&](int j) { return static_cast<const char *>(b->peer_stage[j / m - 1]) + (size_t)(j % m) * slot_bytes; };
     // CF_FUSED_COPY with the one-launch reduce-scatter or all-gather: the delivery is carried by the consumer, no
-    // copy is launched.  Reduce-scatter: the waves that need B_in read it from the neighbour's buffer (peer_stage)
-    // under the main loop, add it, and store it to the landing buffer; only where the launch runs the kernel that
-    // brings B_in in through LDS (256x256 tile, a k range long enough).  All-gather: the kernel takes its left
+    // copy is launched.  Reduce-scatter (the attention layer's projection too): the epilogue reads B_in from the
+    // neighbour's buffer (peer_stage), adds it, and stores it to the landing buffer.  All-gather: the kernel takes its left
     // operand from the neighbour's buffer, and each k-tile that comes in through LDS is stored on to the landing
     // buffer by one of the workgroups that load it (k a multiple of the k-tile).  Otherwise the deliveries are
     // enqueued in front as without the flag.
@@ -903,25 +902,13 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
             wide = wide && aligned16(b->peer_stage[i]) && aligned16(b->recv_each[i]);
     if (few_rows && (flags & CF_FUSED_COPY) && wide && cf::tuning().carry != 0)
         carried = true;
-    if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr && do_copy && do_compute &&
+    if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && do_copy && do_compute &&
         slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0) {
         cf::GemmParams probe;
         probe.W = b->W;
         fill_shape(probe, r);
         probe.n_steps = S;
         carried = cf::gemm_bf16_carries_delivery(probe, r.w_kn, r.bf16_out, num_cu_of_current_device(), kind == CF_KIND_RS);
-    }
-    // A reduce-scatter launch that cannot stream B_in (a short k range, another tile, the projection of the attention
-    // layer) carries its deliveries the other way: the epilogue reads B_in from the neighbour's buffer, and the same
-    // work item copies its tile's part of it to the landing buffer beside its GEMM (no counter: nobody waits for it).
-    bool carried_beside = false;
-    if (!few_rows && (flags & CF_FUSED_COPY) && kind == CF_KIND_RS && !carried && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
-        r.n > 0 && r.k > 0 && r.ldo == r.n) {
-        cf::GemmParams probe;
-        probe.W = b->W;
-        fill_shape(probe, r);
-        probe.n_steps = S;
-        carried_beside = cf::gemm_bf16_lands_beside(probe, r.w_kn, r.bf16_out, num_cu_of_current_device());
     }
     // The gradient bucket with CF_FUSED_COPY: the add kernels read the arrivals from the neighbours' buffers and
     // store them on to the landing buffers in the same pass (ring: 16 bytes per element instead of a copy's 8 plus
@@ -952,7 +939,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     int group = S;
     const bool two_streams = !(flags & CF_SERIAL) && xs != cs && (kind == CF_KIND_RS || kind == CF_KIND_AG) && attn == nullptr &&
                              p > 1 && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0;
-    const bool grouped = two_streams && !carried && !carried_beside;
+    const bool grouped = two_streams && !carried;
     if (grouped && !few_rows) {
         cf::GemmParams probe;
         probe.W = b->W;
@@ -1003,7 +990,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         if (!do_compute)                                 // copies only: the compute stream still ends behind them
             CF_HIP(hipStreamWaitEvent(cs, ev[n_groups], 0));
     }
-    if (do_copy && slot_bytes > 0 && !carried && !carried_beside && !grouped) {
+    if (do_copy && slot_bytes > 0 && !carried && !grouped) {
         // all deliveries of the rank step are due now: one batched copy launch where the buffers allow it
         // (at most 16 hops of 16-byte-aligned whole hop buffers), else one hipMemcpyAsync per (sub-)step
         const void *srcs[cf::GemmParams::MAX_STEPS];
@@ -1117,11 +1104,10 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                 gp.flag_step[j] = nullptr;
                 if (last && pair_front)
                     gp.recv_step[j] = static_cast<const float *>(b->O);
-                gp.recv_in_epilogue = pair_front || pair_beside;
+                gp.k_in_order = pair_front || pair_beside;
                 if (last && pair_beside) {
                     gp.recv_step[j] = static_cast<const float *>(b->peer_stage[0]);
-                    gp.tail_src[j] = gp.recv_step[j];
-                    gp.tail_dst[j] = static_cast<float *>(b->recv_each[0]);
+                    gp.land_step[j] = b->recv_each[0];
                 }
                 if (last && !pair_front)
                     for (int t = 1; t < p - 1; ++t)
@@ -1143,11 +1129,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                 if (carried && receives(jj)) {       // read from the neighbour's buffer, land it here
                     gp.recv_step[j] = reinterpret_cast<const float *>(stage_of(jj));
                     gp.land_step[j] = landing(jj);
-                }
-                if (carried_beside && receives(jj)) { // ... in the epilogue, and landed by a copy beside the GEMM
-                    gp.recv_step[j] = reinterpret_cast<const float *>(stage_of(jj));
-                    gp.tail_src[j] = gp.recv_step[j];
-                    gp.tail_dst[j] = static_cast<float *>(landing(jj));
                 }
                 gp.out_step[j] = sends(jj) ? static_cast<void *>(b->send_each[jj / m] + (size_t)(jj % m) * r.mc * r.ldo)
                                            : static_cast<void *>(static_cast<float *>(b->O) + (size_t)(jj % m) * r.mc * r.ldo);

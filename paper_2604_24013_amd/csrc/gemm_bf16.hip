@@ -371,33 +371,24 @@ double gemm_bf16_tile_us(const GemmParams &p, int num_cu)
     return split < whole ? split : whole;
 }
 
-bool gemm_bf16_lands_beside(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu)
-{
-    const Tuning tn = tuning();
-    if (p.n_steps <= 0 || out_bf16 || p.a_t || !gemm_bf16_takes_recv_list(p, w_kn) || (tn.carry >= 0 && tn.carry == 0))
-        return false;
-    for (int j = 0; j < p.n_steps; ++j)
-        if (p.flag_step[j] != nullptr)
-            return false;
-    return !gemm_bf16_dl_streams_recv(p, w_kn, out_bf16, tile_of_launch(p, num_cu));
-}
-
 bool gemm_bf16_carries_delivery(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu, bool reduce_scatter)
 {
     if (p.M <= 0 || p.N <= 0 || p.n_steps <= 0 || staged_kernel_forced() || !gemm_bf16_dl_supported(p, w_kn))
         return false;
     for (int j = 0; j < p.n_steps; ++j)
         if (p.flag_step[j] != nullptr)
-            return false;                            // a step that waits for a flag keeps its B_in loads in the epilogue
-    if (reduce_scatter) {
-        const TileChoice t = tile_of_launch(p, num_cu);
-        if (!gemm_bf16_dl_streams_recv(p, w_kn, out_bf16, t))
-            return false;
-    } else if (!gemm_bf16_dl_carries_operand(p)) {
+            return false;                            // a step that waits for a flag: its delivery is on its way
+    if (!reduce_scatter && !gemm_bf16_dl_carries_operand(p))
         return false;
+    // (rows with padding between them: the copies in front move the padding too, and have never been in front of launches of
+    // 256x256 tiles over long k ranges)
+    if (reduce_scatter && p.ldo != p.N) {
+        const TileChoice t = tile_of_launch(p, num_cu);
+        if (t.bm != 256 || t.bn != 256 || (p.K + 63) / 64 < 18 + (p.K % 64 != 0 ? 2 : 0))
+            return false;
     }
-    // Wherever the launch can, it does (measured, with the landed tiles stored as whole 128-byte lines: 7B
-    // down-projection rank step 76 -> 57 us, 70B 482 -> 470 us against deliveries copied in front of the launch).
+    // Wherever the launch can, it does (measured against deliveries copied in front of the launch: 7B down-projection rank
+    // step 76.6 -> 57 us on warm buffers, attention layer's rank step 520 -> 492 us).
     // COMMFUSE_CARRY=0 keeps the copies in front.
     const Tuning tn = tuning();
     return tn.carry >= 0 ? tn.carry != 0 : true;

@@ -17,9 +17,9 @@
 //    after every few MFMAs.  A burst fills the address queue of the texture unit
 //    and the wave -- which issues in order -- then cannot feed the matrix pipe
 //    until its last load has been accepted.
-//  * Same fused epilogue as the register-staged kernel: Alg. 2 "O <- B_in + O",
-//    "B_out <- O", or Alg. 1's in-place slice store -- here with bounds-checked
-//    buffer loads/stores, so all B_in loads of a row block are in flight at once.
+//  * Fused epilogue: Alg. 2 "O <- B_in + O", "B_out <- O", or Alg. 1's in-place
+//    slice store, with bounds-checked buffer loads/stores in whole 128-byte lines;
+//    B_in, read once, goes on to the landing buffer from the same registers.
 //
 // Layout in LDS (per stage):
 //   activations / [n x k] weights: 128-byte rows (64 k) of eight 16-byte chunks,
@@ -38,7 +38,6 @@
 #include <cstdio>
 #include <cstdlib>
 #include <type_traits>
-
 namespace cf {
 namespace {
 
@@ -110,16 +109,6 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
 }
 
-// One 16-byte-per-lane load from global memory into registers whose completion the CALLER awaits (vmcnt): issued
-// as inline assembly so that the compiler, which cannot count the requests between a load in one trip of a loop
-// and its use in the next, does not drain the whole request queue in front of the use.
-__device__ __forceinline__ u32x4_t load_16_unawaited(i32x4_t rsrc, unsigned voffset, int soffset)
-{
-    u32x4_t v;
-    asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(v) : "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
-    return v;
-}
-
 // Scheduling hint for one slice phase: after each MFMA up to RPM LDS reads, until REMAIN reads are placed.
 template <int REMAIN, int RPM>
 __device__ __forceinline__ void interleave_mfma_reads()
@@ -143,12 +132,6 @@ __device__ __forceinline__ int xcd_remap(int pid, int total)
 // A_T: the left operand is stored [K x M] (see GemmParams::a_t); its tile then lives in LDS like a
 // [k x n] weight tile and is read with the transposing LDS read as well.
 // PERSIST: one launch runs all steps of a rank step (GemmParams::n_steps, see the work-item loop below).
-// RLDS: reduce-scatter variant of the SPREAD tile.  The received partial B_in does not wait for the epilogue: in
-// sixteen k-tiles near the end of the k loop (the last before the final one; with a ragged K the two iterations that
-// request the ragged k-tile come in between) it is brought in, one 32x32 sub-tile of every wave at a time,
-// by direct loads into an LDS landing area (no register is held while the load is in flight) and added to the
-// accumulators in mid-loop, so that the epilogue only stores.  The landing area takes the place of the third
-// left-operand stage (see the schedule below).
 // MF16: the 256x256 tile's main loop on v_mfma_f32_16x16x32_bf16 instead of v_mfma_f32_32x32x16_bf16 -- the same
 // flops from twice as many instructions that each write a quarter of the accumulator registers, which costs the chip
 // less power per flop (measured) and, where the launch is paced by the power limit, time.  A 32x32 sub-tile of the
@@ -156,13 +139,11 @@ __device__ __forceinline__ int xcd_remap(int pid, int total)
 // 16y + 4 (lane >> 4) .. + 3.  A k-tile is two 32-wide slices, each consumed in four quarter phases (one 32-row block
 // of the wave tile per phase).
 template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD, bool W_KN, bool OUT_BF16, bool A_T = false,
-          bool PERSIST = false, bool RLDS = false, bool MF16 = false>
+          bool PERSIST = false, bool MF16 = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams P, int tiles_m, int tiles_n)
 {
-    static_assert(!MF16 || (SPREAD && !A_T && NS == 2 && !RLDS),
-                  "16x16x32 main loop: 256x256 tile, left operand stored [m x k], B_in added in the epilogue");
+    static_assert(!MF16 || (SPREAD && !A_T && NS == 2), "16x16x32 main loop: 256x256 tile, left operand stored [m x k]");
     static_assert(!A_T || (W_KN && !OUT_BF16), "the transposed left operand comes with [k x n] weights and fp32 output");
-    static_assert(!RLDS || (SPREAD && !OUT_BF16 && !A_T && NS == 2), "B_in through LDS: 256x256 tile, fp32 output");
     constexpr int NW = WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;
     constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -177,19 +158,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // steady state below), which lengthens the time every load has to arrive.
     constexpr int NSA = SPREAD ? NS + 1 : NS;
     constexpr int W_BASE = NSA * A_BYTES;
-    constexpr int R_BYTES = 0;
     // wave-private scratch of the epilogue's stores (4 KiB per wave): a left-operand stage that no load targets any
-    // more -- RLDS: the stage that served as the landing area of B_in (land_stage below); else the third stage of the
-    // 256x256 tile, else the first (after a barrier: every wave is done reading the stages)
+    // more (after a barrier: every wave is done reading the stages) -- the third stage of the 256x256 tile, else the first
     constexpr int E_SCR_BYTES = 4096;
     static_assert(NW * E_SCR_BYTES <= A_BYTES || !SPREAD, "epilogue scratch inside one left-operand stage");
     static_assert(NW * E_SCR_BYTES <= NSA * A_BYTES + NS * B_BYTES, "epilogue scratch inside the stages");
-    static_assert(NS >= 2 && NS <= 4 && NSA * A_BYTES + NS * B_BYTES + R_BYTES <= 160 * 1024, "LDS budget");
+    static_assert(NS >= 2 && NS <= 4 && NSA * A_BYTES + NS * B_BYTES <= 160 * 1024, "LDS budget");
     static_assert(KS == 4, "the slice schedule below is written for four slices per stage");
     constexpr int W_ROWB = BN * 2;                   // bytes of one k-row of a [k x n] weight tile
     constexpr int A_ROWB = BM * 2;                   // bytes of one k-row of a [k x m] left-operand tile
 
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[NSA * A_BYTES + NS * B_BYTES + R_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[NSA * A_BYTES + NS * B_BYTES];
 
     const int tid0 = threadIdx.x;
 
@@ -499,7 +478,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // items of a step and tile row walk k in the same order: the k rotation comes with whole steps per XCD.)
     // Every wave stores the 4 KiB it loaded itself -- it reads them back from the stage, whole 128-byte rows per
     // eight lanes, at the global offsets it fetched them from -- so its own vmcnt wait is all the ordering needed.
-    constexpr bool CARRY_A = PERSIST && !RLDS && !A_T;
+    constexpr bool CARRY_A = PERSIST && !A_T;
     int carry_at = (CARRY_A && cLand != nullptr && cRecv == nullptr) ? tile / tiles_m : 0x7fffffff;
     __amdgpu_buffer_rsrc_t la_rsrc =
         __builtin_amdgcn_make_buffer_rsrc(cLand, 0, (CARRY_A && cLand != nullptr) ? (int)a_bytes : 0, 0x00020000);
@@ -664,112 +643,57 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 
     bf16x8_t af0[TM], wf0[TN], af1[TM], wf1[TN];
 
-    // B_in prefetch (one workgroup per CU, fp32 output, no k-split): the epilogue's loads of the received
+    // B_in prefetch (one workgroup per CU, fp32 output, no k-split): all of the epilogue's loads of the received
     // partial are issued pf_lead k-tiles before the end of the k loop and land in registers under the remaining
     // MFMAs, so that the epilogue only adds and stores.
     constexpr bool PF = !SPREAD && NS >= 3 && !OUT_BF16;
     constexpr int PFR = TM * TN * 4;                  // 16-byte loads per lane
     static_assert(!PF || (NS - 2) * LPT + PFR < 64, "vmcnt range");
     const unsigned r_bytes = (unsigned)(((int64_t)(M - 1) * P.ldo + N) * 4);
-    const unsigned r_bytes_of_recv = r_bytes;
     __amdgpu_buffer_rsrc_t r_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(cRecv), 0, cRecv != nullptr ? (int)r_bytes : 0, 0x00020000);
     const int pf_at = nk - 1 - P.pf_lead;             // iteration after whose tile loads the prefetch is issued
-    // (fp32 partial sums only, and never in the kernel that streams B_in: the launcher does not pick it for such a launch.)
-    constexpr bool TAILS = PERSIST && !RLDS && !OUT_BF16;
     const bool pf_on = PF && cRecv != nullptr && splits == 1 && n_more == 0 && P.pf_lead > 0 && pf_at >= 0;
-    // The delivery landed beside the GEMM (GemmParams::tail_src): this work item copies its own output tile's part of it
-    // from the sender's buffer to the landing buffer, written through to memory.  Every other workgroup of an XCD does so in
-    // front of its main loop, the others behind their epilogue: the work items of a round run in lock step, and this
-    // way one half copies while the other half multiplies instead of all 256 copying at once.
     constexpr int COHERENT_LD = 1 | 16;               // buffer cache-policy bits sc0 | sc1
-    // The 16x16x32 main loop deals the copy over its k-tiles instead: one 16-byte load and the store of the one before
-    // per lane and k-tile, behind the k-tile's barrier (the wait in front of the next barrier covers them: they are
-    // older than the loads it lets pass), and what the k range leaves over is copied behind the epilogue.
-    constexpr bool TL_STREAM = TAILS && MF16;
-    constexpr int TL_CPR = WTN / 4, TL_RPI = 64 / TL_CPR, TL_N = WTM / TL_RPI;     // 16-byte chunks per row, rows and instructions per wave
-    const float *const tl_src = TAILS ? P.tail_src[step_i] : nullptr;
-    const bool tl_on = TL_STREAM && tl_src != nullptr;
-    const bool tail_early = TAILS && !tl_on && (((int)blockIdx.x >> 3) & 1) != 0;
-    const i32x4_t tl_srsrc = make_rsrc(tl_src, tl_src != nullptr ? r_bytes : 0u);
-    __amdgpu_buffer_rsrc_t tl_drsrc = __builtin_amdgcn_make_buffer_rsrc(
-        TAILS ? P.tail_dst[step_i] : nullptr, 0, tl_src != nullptr ? (int)r_bytes : 0, 0x00020000);
-    const int tl_row0 = m0 + wm * WTM + lane / TL_CPR, tl_col = n0 + wn * WTN + (lane % TL_CPR) * 4;
-    const int tl_voff = (tl_row0 < M && tl_col < N) ? (int)(((int64_t)tl_row0 * P.ldo + tl_col) * 4) : (int)OOB;
-    const int tl_stride = (int)((int64_t)TL_RPI * P.ldo * 4);                      // bytes from one instruction's rows to the next's
-    int tl_c = 0;                                    // instructions issued so far
-    u32x4_t tl_v = {0u, 0u, 0u, 0u};
-    auto tl_step = [&]() __attribute__((always_inline)) {
-        if (tl_on) {
-            if (tl_c > 0 && tl_c <= TL_N)
-                __builtin_amdgcn_raw_buffer_store_b128(tl_v, tl_drsrc, tl_voff, (tl_c - 1) * tl_stride, COHERENT_LD);
-            // (the load is awaited by the wait in front of the next k-tile's barrier: it is older than the four
-            // left-operand loads that wait lets pass)
-            if (tl_c < TL_N)
-                tl_v = load_16_unawaited(tl_srsrc, (unsigned)tl_voff, tl_c * tl_stride);
-            ++tl_c;
-        }
-    };
-    auto land_arrival = [&](int first) __attribute__((always_inline)) {
-        const float *const tsrc = tl_src;
-        if (TAILS && tsrc != nullptr) {
-            __amdgpu_buffer_rsrc_t ts_rsrc =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(tsrc), 0, (int)r_bytes, 0x00020000);
-            __amdgpu_buffer_rsrc_t td_rsrc = __builtin_amdgcn_make_buffer_rsrc(P.tail_dst[step_i], 0, (int)r_bytes, 0x00020000);
-            constexpr int CPR = WTN / 4;             // 16-byte chunks in a row of the wave's part
-            constexpr int RPI = 64 / CPR;            // rows per instruction
-            constexpr int TB = 16;                   // loads in flight per lane
-            static_assert(64 % CPR == 0 && (WTM / RPI) % TB == 0, "whole batches");
-            const int sn = n0 + wn * WTN + (lane % CPR) * 4;
-#pragma unroll 1
-            for (int b = first; b < WTM / RPI; b += TB) {
-                u32x4_t v[TB];
-                int off[TB];
+    // B_in and the fp32 output are read and written as whole 128-byte lines: eight lanes to a row of a 32-column block,
+    // eight rows per instruction, four instructions to a 32x32 sub-tile.  The offsets are taken anew from an opaque
+    // copy of the lane index where they are needed: the main loop has no registers for them.
+    const unsigned rows8 = (unsigned)P.ldo * 32u;     // bytes from one instruction's eight rows to the next's
+    auto line_offsets = [&](int i, int j, int (&off)[4]) __attribute__((always_inline)) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int r = m0 + wm * WTM + i * 32 + (ln >> 3), cl = n0 + wn * WTN + j * 32 + (ln & 7) * 4;
 #pragma unroll
-                for (int u = 0; u < TB; ++u) {
-                    const int sm = m0 + wm * WTM + (b + u) * RPI + lane / CPR;
-                    off[u] = (b + u < WTM / RPI && sm < M && sn < N) ? (int)(((int64_t)sm * P.ldo + sn) * 4) : (int)OOB;
-                    v[u] = __builtin_amdgcn_raw_buffer_load_b128(ts_rsrc, off[u], 0, 0);
-                }
-#pragma unroll
-                for (int u = 0; u < TB; ++u)
-                    __builtin_amdgcn_raw_buffer_store_b128(v[u], td_rsrc, off[u], 0, COHERENT_LD);
-            }
-        }
+        for (int s4 = 0; s4 < 4; ++s4)
+            off[s4] = (MF16 || (r + 8 * s4 < M && cl < N)) ? (int)(((unsigned)r * (unsigned)P.ldo + cl) * 4u + s4 * rows8) : (int)OOB;
     };
-    if (TAILS && tail_early)
-        land_arrival(0);
-    f32x4_t pre[PF ? TM : 1][PF ? TN : 1][4];
-    auto prefetch_recv = [&](auto aux_tag) __attribute__((always_inline)) {
+    // row blocks of B_in held in registers: all of the wave tile where it is prefetched, else the one being added and the next
+    constexpr int LV = OUT_BF16 ? 1 : PF ? TM : 2;
+    u32x4_t lv[LV][OUT_BF16 ? 1 : TN][4];
+    auto load_lines = [&](int i, auto aux_tag) __attribute__((always_inline)) {
         constexpr int AUX = decltype(aux_tag)::value;
 #pragma unroll
-        for (int i = 0; i < (PF ? TM : 0); ++i) {
-            const int m = m0 + wm * WTM + i * 32 + (lane & 31);
+        for (int j = 0; j < (OUT_BF16 ? 0 : TN); ++j) {
+            int lo[4];
+            line_offsets(i, j, lo);
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int n = n0 + wn * WTN + j * 32 + g * 8 + (lane >> 5) * 4;
-                    const unsigned e = (m < M && n < N) ? (unsigned)((int64_t)m * P.ldo + n) : OOB;
-                    pre[i][j][g] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                        r_rsrc, e == OOB ? (int)OOB : (int)(e * 4), 0, AUX));
-                }
+            for (int s4 = 0; s4 < 4; ++s4)
+                lv[i % LV][j][s4] = __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, lo[s4], 0, AUX);
         }
     };
+    // (a launch that waited for its delivery's flag reads it with the device-coherent cache policy, see wait_delivery)
+    const bool recv_coherent = cFlag != nullptr && !P.wait_at_start;
+    auto load_recv = [&](int i) __attribute__((always_inline)) {
+        if (recv_coherent)
+            load_lines(i, std::integral_constant<int, COHERENT_LD>{});
+        else
+            load_lines(i, std::integral_constant<int, 0>{});
+    };
 
-    // RLDS: is B_in streamed in under the main loop for this work item?  (Uniform.)  It needs sixteen k-tiles
-    // before the last one (and before the iterations that test their loads), and one more for the change of
-    // schedule in front of them; a step that waits for a delivery flag, sums several received partials or is a
-    // k-split keeps the loads in the epilogue.
-    constexpr int RQ = TM * TN;                       // 32x32 sub-tiles per wave, one in flight at a time
-    // A ragged k tail (the launcher then leaves the k order unrotated: it is the last k-tile) is requested in the
-    // last two iterations before the final tile; those test their loads and come after the streamed ones.
-    const int tested = (RLDS && K % BK != 0) ? (nk - 1 < 2 ? nk - 1 : 2) : 0;
-    const bool streamed = RLDS && cRecv != nullptr && cFlag == nullptr && n_more == 0 && splits == 1 &&
-                          P.stream_recv && nk >= 2 * RQ + 2 + tested && (tested == 0 || rot == 0);
-    // the left-operand stage whose memory serves as the wave-private scratch of the epilogue's stores (and, RLDS, as
-    // the landing area of B_in before)
-    int land_stage = SPREAD ? NSA - 1 : 0;
+    // The epilogue's first row block of B_in is requested in front of the last k-tile (there is no register for more).
+    const bool early = P.early_recv && PERSIST && !OUT_BF16 && !pf_on && cFlag == nullptr;
+    // the left-operand stage whose memory serves as the wave-private scratch of the epilogue's stores
+    constexpr int land_stage = SPREAD ? NSA - 1 : 0;
     if constexpr (SPREAD && MF16) {
         // The schedule of the 256x256 tile (see the variant below for its reasoning) on 16x16x32 MFMAs.  A k-tile is two
         // 32-wide slices; a slice is consumed in four quarter phases, phase p = the wave tile's 32-row block p:
@@ -909,8 +833,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
                     wait_vmcnt<(NS - 2) * LPT + A_LD>();
                 }
                 __syncthreads();
-                if constexpr (TL_STREAM)
-                    tl_step();
                 __builtin_amdgcn_sched_barrier(0);
             };
             phase16(p2_t{}, afA, wfB, afB, wfA, on_t{}, ca, 1, 3, publish, c2{}, nw_, 0, c0{}, on_t{}, na, 0, 0,
@@ -931,6 +853,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         }
         // the last tile of a work item: nothing follows it
         auto last16 = [&](int ca, int cw) __attribute__((always_inline)) {
+            if (early)
+                load_lines(0, std::integral_constant<int, 0>{});
             front16(ca, cw, nothing, nothing, nothing, nothing, plain_ph2(ca, cw));
             phase16(p2_t{}, afA, wfB, afB, wfA, on_t{}, ca, 1, 3, nothing, c0{}, 0, 0, c0{}, off_t{}, 0, 0, 0, nothing, nothing);
             if (CARRY_A && nk - 1 == carry_at)
@@ -990,12 +914,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         };
         // first iteration that tests its loads (all of them when K is a multiple of the k-tile: none does)
         const int tested_at = K % BK == 0 ? nk - 1 : ((rot == 0 && nk - 1 > NS) ? nk - 1 - NS : 0);
-        // RLDS, a work item that streams B_in: the three-stage schedule runs up to the k-tile before the sixteen
-        // streamed ones, the two-stage schedule with the landing area (below) takes over there
-        const int change_at = nk - 1 - tested - 2 * RQ - 1;
-        const int plain_end = (RLDS && streamed) ? change_at : tested_at;
         int kt = 0;
-        for (; kt < plain_end; ++kt) {
+        for (; kt < tested_at; ++kt) {
             const int nxt_a = (cur_a + 1 == NSA) ? 0 : cur_a + 1;
             const int nxt_w = (cur_w + 1 == NS) ? 0 : cur_w + 1;
             body(kt, cur_a, cur_w, prev_a, nxt_a, nxt_w, std::true_type{});
@@ -1003,178 +923,24 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             cur_a = nxt_a;
             cur_w = nxt_w;
         }
-        if (!(RLDS && streamed)) {
-            for (; kt + 1 < nk; ++kt) {
-                const int nxt_a = (cur_a + 1 == NSA) ? 0 : cur_a + 1;
-                const int nxt_w = (cur_w + 1 == NS) ? 0 : cur_w + 1;
-                body(kt, cur_a, cur_w, prev_a, nxt_a, nxt_w, std::false_type{});
-                prev_a = cur_a;
-                cur_a = nxt_a;
-                cur_w = nxt_w;
-            }
-            if (nk > 0) {                                    // last tile: nothing follows it
-                using wk = std::true_type;
-                phase(af0, wf0, true, cur_a, cur_w, 1, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
-                phase(af1, wf1, true, cur_a, cur_w, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
-                phase(af0, wf0, true, cur_a, cur_w, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
-                if (CARRY_A && nk - 1 == carry_at)
-                    carry_tile(nk - 1, cur_a);
-                phase(af1, wf1, false, 0, 0, 0, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
-            }
+        for (; kt + 1 < nk; ++kt) {
+            const int nxt_a = (cur_a + 1 == NSA) ? 0 : cur_a + 1;
+            const int nxt_w = (cur_w + 1 == NS) ? 0 : cur_w + 1;
+            body(kt, cur_a, cur_w, prev_a, nxt_a, nxt_w, std::false_type{});
+            prev_a = cur_a;
+            cur_a = nxt_a;
+            cur_w = nxt_w;
         }
-        if constexpr (RLDS) {
-          if (streamed) {
-            // The streamed part: two stages of both operands and the landing area.  On entry (kt = change_at) tile
-            // kt is complete and all of tile kt+1 is in flight; the left-operand tiles kt and kt+1 keep their
-            // stages, later ones alternate between the two, and the third stage -- tile kt-1 has been read by all
-            // -- becomes the landing area, 4 KiB per wave.  Weight tile t stays in stage t & 1.  Iteration kt:
-            //     slice 0: + the weight loads of tile kt+1 (its stage was vacated at the barrier of iteration kt-1;
-            //              not in the first iteration, where they are in flight already)
-            //     slice 1 (X iterations: + the four B_in loads of one sub-tile), slice 2
-            //     wait: tile kt+1 complete (X: the B_in loads just issued may still be in flight); barrier
-            //     (Y iterations: the sub-tile is read from the landing area and added to its accumulators)
-            //     slice 3: + the left-operand loads of tile kt+2, into the stage tile kt vacated
-            // Loads return in issue order: the B_in loads of an X iteration are behind the weight loads of tile
-            // kt+1 and ahead of everything tile kt+2 needs, so they have until the wait of the following (Y)
-            // iteration, one and a half k-tiles of MFMA time, to arrive.  Each wave reads back only what it
-            // loaded itself, so its own vmcnt wait is all the ordering the landing area needs.
-            static_assert(A_LD <= NSEG && B_LD <= NSEG && NSEG == 4 && NS == 2, "one load slot per MFMA segment");
-            const int nxt_a0 = (cur_a + 1 == NSA) ? 0 : cur_a + 1;
-            const int a_of_parity[2] = {(kt & 1) ? nxt_a0 : cur_a, (kt & 1) ? cur_a : nxt_a0};
-            land_stage = prev_a;                         // (the stage of tile kt-1; kt >= 1 here)
-            const int a_ev = a_of_parity[0], a_od = a_of_parity[1];
-            const i32x4_t rr = make_rsrc(cRecv, r_bytes_of_recv);
-            __amdgpu_buffer_rsrc_t l_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                static_cast<float *>(cLand), 0, cLand != nullptr ? (int)r_bytes_of_recv : 0, 0x00020000);
-            const int land_off = land_stage * A_BYTES + wave * 4096;
-            const unsigned r_lds = lds_base + land_off;
-            // byte offset of sub-tile q = (i, j) of this wave, row 0 / column 0 of the lane pattern
-            auto r_soff = [&](int q) __attribute__((always_inline)) {
-                const int i = q / TN, j = q % TN;
-                return (int)((((int64_t)(m0 + wm * WTM + i * 32)) * P.ldo + n0 + wn * WTN + j * 32) * 4);
-            };
-            auto phase_x = [&](const bf16x8_t (&afc)[TM], const bf16x8_t (&wfc)[TN], int sa_n, int sw_n, int ks_n,
-                               bf16x8_t (&afn)[TM], bf16x8_t (&wfn)[TN], int q) __attribute__((always_inline)) {
-                const int so = __builtin_amdgcn_readfirstlane(r_soff(q));     // (uniform; kept in a scalar register)
-                // a lane outside the matrix must not touch memory: the scalar part of the address is not covered
-                // by the buffer's range check, so such a lane is given the out-of-range offset itself
-                // (computed from an opaque copy of the lane index: otherwise the offsets of all eight sub-tiles are
-                // hoisted out of the k loop and held in registers the main loop does not have)
-                int ln = lane;
-                asm volatile("" : "+v"(ln));
-                // Plane g of the landing area (load g: columns 8g + 4 (lane >> 5) .. + 3) holds its rows permuted:
-                // the lane fetches row (lane & 31) ^ (2g + (lane >> 5)), so that the eight 16-byte chunks of a row,
-                // which lie 512 bytes apart across the planes, fall into different banks when the rows are read
-                // back eight lanes to a row.
-                const int half = ln >> 5;
-                const int rn = n0 + wn * WTN + (q % TN) * 32 + half * 4;
-                auto off_of = [&](int g) __attribute__((always_inline)) {
-                    const int r = (ln & 31) ^ (2 * g + half);
-                    const int rm = m0 + wm * WTM + (q / TN) * 32 + r;
-                    return (rm < M && rn + 8 * g < N) ? (unsigned)((((int64_t)r) * P.ldo + half * 4) * 4) : OOB;
-                };
-                const unsigned v0 = off_of(0), v1 = off_of(1), v2 = off_of(2), v3 = off_of(3);
-                read_frags(sa_n, sw_n, ks_n, afn, wfn);
-                mfma_seg(afc, wfc, std::integral_constant<int, 0>{});
-                interleave_mfma_reads<NREAD, (NREAD + MPS - 1) / MPS>();
-                __builtin_amdgcn_sched_barrier(0);
-                direct_load_16(rr, v0, so, r_lds);
-                mfma_seg(afc, wfc, std::integral_constant<int, 1>{});
-                __builtin_amdgcn_sched_barrier(0);
-                direct_load_16(rr, v1, so + 32, r_lds + 1024);
-                mfma_seg(afc, wfc, std::integral_constant<int, 2>{});
-                __builtin_amdgcn_sched_barrier(0);
-                direct_load_16(rr, v2, so + 64, r_lds + 2048);
-                mfma_seg(afc, wfc, std::integral_constant<int, 3>{});
-                __builtin_amdgcn_sched_barrier(0);
-                direct_load_16(rr, v3, so + 96, r_lds + 3072);
-            };
-            auto add_landed = [&](auto q_tag) __attribute__((always_inline)) {          // "O <- B_in + O" for sub-tile q, in mid-sum
-                constexpr int q = decltype(q_tag)::value;
-                int ln = lane;
-                asm volatile("" : "+v"(ln));
-                const unsigned char *src = smem + land_off + (ln & 32) * 16;
-                f32x4_t v[4];
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    v[g] = *reinterpret_cast<const f32x4_t *>(src + g * 1024 + (((ln & 31) ^ (2 * g + (ln >> 5))) << 4));
-                    acc[q / TN][q % TN][4 * g + 0] += v[g][0];
-                    acc[q / TN][q % TN][4 * g + 1] += v[g][1];
-                    acc[q / TN][q % TN][4 * g + 2] += v[g][2];
-                    acc[q / TN][q % TN][4 * g + 3] += v[g][3];
-                }
-                // the delivery carried by the consumer: what just arrived from the neighbour's buffer is also stored to
-                // this rank's landing buffer (a lane outside the matrix is given the out-of-range offset: store dropped)
-                if (cLand != nullptr) {
-                    // Whole 128-byte lines per store: the sub-tile is read from the landing area a second time, eight
-                    // lanes to a row (chunk c of row r lies in plane c / 2 at lane slot (r ^ c) + 32 (c & 1)), so that
-                    // one store instruction writes eight full rows instead of 32-byte pieces of thirty-two.
-                    const int c = ln & 7, r8 = ln >> 3;
-                    const unsigned char *base = smem + land_off + (c >> 1) * 1024 + (32 * (c & 1)) * 16;
-                    const int rn = n0 + wn * WTN + (q % TN) * 32 + c * 4;
-#pragma unroll
-                    for (int s4 = 0; s4 < 4; ++s4) {
-                        const int row = 8 * s4 + r8;
-                        const f32x4_t t = *reinterpret_cast<const f32x4_t *>(base + ((row ^ c) << 4));
-                        const int rm = m0 + wm * WTM + (q / TN) * 32 + row;
-                        const int boff = (rm < M && rn < N) ? (int)(((int64_t)rm * P.ldo + rn) * 4) : (int)OOB;
-                        // (plain stores: non-temporal or write-through ones measured 10 - 30 % slower here)
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, t), l_rsrc, boff, 0, 0);
-                    }
-                }
-            };
-            // mode 0: plain; mode 1 (X): issues the B_in loads of sub-tile q; mode 2 (Y): adds sub-tile Q.
-            // n_w: the number of weight loads slice 0 issues (none in the iteration that takes over)
-            auto iteration_wk = [&](int kt_, auto mode_tag, int q, auto q_tag, auto wk, auto n_w) __attribute__((always_inline)) {
-                constexpr int MODE = decltype(mode_tag)::value;
-                const int cw = kt_ & 1, nw_ = cw ^ 1;
-                const int ca = cw ? a_od : a_ev, na = cw ? a_ev : a_od;
-                phase(af0, wf0, true, ca, cw, 1, af1, wf1, kt_ + 1, 0, nw_, cALD{}, n_w, wk);
-                if constexpr (MODE == 1)
-                    phase_x(af1, wf1, ca, cw, 2, af0, wf0, q);
-                else
-                    phase(af1, wf1, true, ca, cw, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk);
-                phase(af0, wf0, true, ca, cw, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk);
-                if constexpr (MODE == 1)
-                    wait_vmcnt<4>();
-                else
-                    wait_vmcnt<0>();
-                __syncthreads();
-                if constexpr (MODE == 2)
-                    add_landed(q_tag);
-                __builtin_amdgcn_sched_barrier(0);
-                phase(af1, wf1, true, na, nw_, 0, af0, wf0, kt_ + 2, ca, 0, c0{}, cALD{}, wk);
-            };
-            using m0_t = std::integral_constant<int, 0>;
-            using m1_t = std::integral_constant<int, 1>;
-            using m2_t = std::integral_constant<int, 2>;
-            iteration_wk(kt, m0_t{}, 0, c0{}, std::true_type{}, c0{});       // the iteration that takes over
-            ++kt;
-            auto pair_of = [&](auto q_tag) __attribute__((always_inline)) {
-                iteration_wk(kt, m1_t{}, decltype(q_tag)::value, c0{}, std::true_type{}, cLR{});
-                iteration_wk(kt + 1, m2_t{}, 0, q_tag, std::true_type{}, cLR{});
-                kt += 2;
-            };
-            static_assert(RQ == 8, "eight sub-tiles per wave");
-            pair_of(std::integral_constant<int, 0>{});
-            pair_of(std::integral_constant<int, 1>{});
-            pair_of(std::integral_constant<int, 2>{});
-            pair_of(std::integral_constant<int, 3>{});
-            pair_of(std::integral_constant<int, 4>{});
-            pair_of(std::integral_constant<int, 5>{});
-            pair_of(std::integral_constant<int, 6>{});
-            pair_of(std::integral_constant<int, 7>{});
-            for (; kt + 1 < nk; ++kt)                        // the iterations that request the ragged k-tile
-                iteration_wk(kt, m0_t{}, 0, c0{}, std::false_type{}, cLR{});
-            {                                                // last tile: nothing follows it
-                using wk = std::true_type;
-                const int cw = (nk - 1) & 1, ca = cw ? a_od : a_ev;
-                phase(af0, wf0, true, ca, cw, 1, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
-                phase(af1, wf1, true, ca, cw, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
-                phase(af0, wf0, true, ca, cw, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
-                phase(af1, wf1, false, 0, 0, 0, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
-            }
-          }
+        if (nk > 0) {                                    // last tile: nothing follows it
+            using wk = std::true_type;
+            if (early)
+                load_lines(0, std::integral_constant<int, 0>{});
+            phase(af0, wf0, true, cur_a, cur_w, 1, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
+            phase(af1, wf1, true, cur_a, cur_w, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
+            phase(af0, wf0, true, cur_a, cur_w, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
+            if (CARRY_A && nk - 1 == carry_at)
+                carry_tile(nk - 1, cur_a);
+            phase(af1, wf1, false, 0, 0, 0, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
         }
     } else {
         // Variant for the small tiles (few MFMAs per slice): a tile's loads go out together right
@@ -1223,10 +989,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             if constexpr (PF) {
                 if (pf_on && kt == pf_at) {
                     wait_delivery(false);
-                    if (cFlag != nullptr)
-                        prefetch_recv(std::integral_constant<int, COHERENT_LD>{});
-                    else
-                        prefetch_recv(std::integral_constant<int, 0>{});
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        load_recv(i);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -1234,6 +999,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             cur = nxt;
         }
         if (nk > 0) {
+            if (early)
+                load_lines(0, std::integral_constant<int, 0>{});
             phase_b(af0, wf0, true, cur, 1, af1, wf1, rpm1{});
             phase_b(af1, wf1, true, cur, 2, af0, wf0, rpm1{});
             phase_b(af0, wf0, true, cur, 3, af1, wf1, rpm1{});
@@ -1242,7 +1009,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase_b(af1, wf1, false, 0, 0, af0, wf0, rpm1{});
         }
     }
-    wait_vmcnt<0>();                                 // no direct load may outlive its LDS allocation
+    // no direct load may outlive its LDS allocation (the early request of B_in is younger than all of them)
+    if (early)
+        wait_vmcnt<TN * 4>();
+    else
+        wait_vmcnt<0>();
 
     // Row and first column (of four) of accumulator registers 4g .. 4g+3 of this lane's 32x32 sub-tile (i, j).
     auto e_row = [&](int i, int g) __attribute__((always_inline)) {
@@ -1310,120 +1081,86 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // Epilogue.  Accumulator register 4g+e of lane L holds row (L & 31), column 8g + 4(L >> 5) + e
     // of its 32x32 tile.  Bounds-checked buffer accesses: a lane outside the matrix reads zero
     // and its store is dropped.
-    if (!(RLDS && streamed))
-        __syncthreads();                             // the stores' scratch lies in a stage: all waves are done with them
+    __syncthreads();                                 // the stores' scratch lies in a stage: all waves are done with them
     constexpr unsigned o_elem = OUT_BF16 ? 2 : 4;
     const unsigned o_bytes = (unsigned)(((int64_t)(M - 1) * P.ldo + N) * o_elem);
     __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc(cOut, 0, (int)o_bytes, 0x00020000);
-    const bool has_recv = cRecv != nullptr;
-    if (!P.wait_at_start && !pf_on)
-        wait_delivery(false);                        // B_in has travelled under the main loop
-    const bool recv_coherent = cFlag != nullptr && !P.wait_at_start;
+    // The stores go through a wave-private LDS scratch so that they leave as whole 128-byte lines: the
+    // accumulator layout would store 32-byte (bf16: 16-byte) pieces of thirty-two rows per instruction, which
+    // the memory system handles markedly worse (measured: 70B down-projection rank step 438 -> 418 us).
+    unsigned char *const scr = smem + land_stage * A_BYTES + wave * E_SCR_BYTES;
+    if constexpr (!OUT_BF16) {
+        // B_in comes in in the layout the tile leaves in: it is read once, stored on to the landing buffer from the
+        // registers it came in (the delivery carried by the consumer) and added where the tile is read back from the
+        // scratch.  Without a B_in, or nothing to land, the buffers' ranges are empty: loads return zero, stores are dropped.
+        // Bound by memory: a reduce-scatter work item moves 768 KiB here at the rate a copy reaches.  Bringing B_in in under the
+        // main loop instead (through LDS, 32x32x16 MFMAs) or landing it by a second read beside the GEMM measured, us per
+        // carried rank step, against this: 8 x 1024 x 8192 x 3584 474 -> 436, x 1024 242 -> 223, 8 x 512 x 4096 x 1376 72.1 -> 71.5.
+        if (!P.wait_at_start && !pf_on)
+            wait_delivery(false);                    // B_in has travelled under the main loop
+        __amdgpu_buffer_rsrc_t l_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            cLand, 0, PERSIST && cRecv != nullptr && cLand != nullptr ? (int)r_bytes : 0, 0x00020000);
+        if (!pf_on && !early)
+            load_recv(0);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        unsigned eoff[TN][4];
-        f32x4_t rv[TN][4];
+        for (int i = 0; i < TM; ++i) {
+            if (!pf_on && i + 1 < TM)
+                load_recv(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < TN; ++j) {
+                int lo[4];
+                line_offsets(i, j, lo);
+                u32x4_t (&a)[4] = lv[i % LV][j];
+                for (int b = 0; b < n_more; ++b) {   // further received partials, summed in index order
+                    __amdgpu_buffer_rsrc_t m_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                        const_cast<float *>(P.recv_more[b]), 0, (int)r_bytes, 0x00020000);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int m = e_row(i, g), n = e_col(j, g);
-                eoff[j][g] = (m < M && n < N) ? (unsigned)((int64_t)m * P.ldo + n) : OOB;
+                    for (int s4 = 0; s4 < 4; ++s4)
+                        a[s4] = __builtin_bit_cast(u32x4_t, __builtin_bit_cast(f32x4_t, a[s4]) +
+                                __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(m_rsrc, lo[s4], 0, 0)));
+                }
+                // chunk c (four columns) of row r of the sub-tile goes to plane c / 2, slot (r ^ c) + 32 (c & 1): the chunks of
+                // a row lie 512 bytes apart and would all fall into one bank otherwise
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int r = MF16 ? 16 * (g >> 1) + (lane & 15) : lane & 31;
+                    const int c = MF16 ? 4 * (g & 1) + (lane >> 4) : 2 * g + (lane >> 5);
+                    *reinterpret_cast<f32x4_t *>(scr + (c >> 1) * 1024 + ((32 * (c & 1) + (r ^ c)) << 4)) = acc_get(i, j, g);
+                }
+                const int c = lane & 7, r8 = lane >> 3;
+                const unsigned char *base = scr + (c >> 1) * 1024 + (32 * (c & 1)) * 16;
+#pragma unroll
+                for (int s4 = 0; s4 < 4; ++s4) {
+                    const f32x4_t t = *reinterpret_cast<const f32x4_t *>(base + (((8 * s4 + r8) ^ c) << 4));
+                    if constexpr (PERSIST)
+                        __builtin_amdgcn_raw_buffer_store_b128(a[s4], l_rsrc, lo[s4], 0, 0);
+                    const f32x4_t o = __builtin_bit_cast(f32x4_t, a[s4]) + t;    // "O <- B_in + O"
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), o_rsrc, lo[s4], 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-        if (PF && pf_on) {
+        }
+    } else {
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    rv[j][g] = pre[PF ? i : 0][PF ? j : 0][g];
-        } else if (has_recv && !streamed) {
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int boff = eoff[j][g] == OOB ? (int)OOB : (int)(eoff[j][g] * 4);
-                    rv[j][g] = __builtin_bit_cast(f32x4_t, recv_coherent
-                                   ? __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, boff, 0, COHERENT_LD)
-                                   : __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, boff, 0, 0));
-                    if constexpr (PERSIST && RLDS) {
-                        if (cLand != nullptr) {      // (a work item that could not stream still delivers)
-                            __amdgpu_buffer_rsrc_t le_rsrc =
-                                __builtin_amdgcn_make_buffer_rsrc(static_cast<float *>(cLand), 0, (int)r_bytes, 0x00020000);
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, rv[j][g]), le_rsrc, boff, 0, 0);
-                        }
-                    }
-                }
-            // further received partials, summed in index order: one batch of independent loads per buffer
-            for (int b = 0; b < n_more; ++b) {
-                __amdgpu_buffer_rsrc_t m_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                    const_cast<float *>(P.recv_more[b]), 0, (int)r_bytes, 0x00020000);
-                f32x4_t tv[TN][4];
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        tv[j][g] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                            m_rsrc, eoff[j][g] == OOB ? (int)OOB : (int)(eoff[j][g] * 4), 0, 0));
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        rv[j][g] = rv[j][g] + tv[j][g];
-            }
-        }
-        // The stores go through a wave-private LDS scratch so that they leave as whole 128-byte lines: the
-        // accumulator layout would store 32-byte (bf16: 16-byte) pieces of thirty-two rows per instruction, which
-        // the memory system handles markedly worse (measured: 70B down-projection rank step 438 -> 418 us).
-        unsigned char *const scr = smem + land_stage * A_BYTES + wave * E_SCR_BYTES;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                f32x4_t o = acc_get(i, j, g);
-                if (has_recv && !streamed)
-                    o = rv[j][g] + o;                                    // "O <- B_in + O"
-                if constexpr (OUT_BF16) {
-                    // row (lane & 31) of the wave tile's row block i: 64-column rows of bf16 (128 bytes), their
-                    // eight 16-byte chunks XOR-ed with the row so that the rows spread over the banks
+                    // row r of the wave tile's row block i: 64-column rows of bf16 (128 bytes), their eight 16-byte
+                    // chunks XOR-ed with the row so that the rows spread over the banks
+                    const f32x4_t o = acc_get(i, j, g);
                     bf16x4_t h;
                     h[0] = static_cast<__bf16>(o[0]);
                     h[1] = static_cast<__bf16>(o[1]);
                     h[2] = static_cast<__bf16>(o[2]);
                     h[3] = static_cast<__bf16>(o[3]);
-                    if constexpr (MF16) {
-                        // row 16 (g / 2) + (lane & 15), columns 32 j + 16 (g & 1) + 4 (lane >> 4) .. + 3 of the row block
-                        const int r = 16 * (g >> 1) + (lane & 15);
-                        const int ch = j * 4 + 2 * (g & 1) + (lane >> 5);
-                        *reinterpret_cast<bf16x4_t *>(scr + r * 128 + ((ch ^ (r & 7)) << 4) + ((lane >> 4) & 1) * 8) = h;
-                    } else
-                    *reinterpret_cast<bf16x4_t *>(scr + (lane & 31) * 128 + (((j * 4 + g) ^ (lane & 7)) << 4) + (lane >> 5) * 8) = h;
-                } else {
-                    // plane g of the 32x32 sub-tile (i, j), the rows permuted within the plane (row ^ chunk number:
-                    // the chunks of a row lie 512 bytes apart and would all fall into one bank otherwise)
-                    if constexpr (MF16) {
-                        // chunk c = 4 (g & 1) + (lane >> 4) of row r = 16 (g / 2) + (lane & 15): plane c / 2, slot (r ^ c) + 32 (c & 1)
-                        const int r = 16 * (g >> 1) + (lane & 15), c = 4 * (g & 1) + (lane >> 4);
-                        *reinterpret_cast<f32x4_t *>(scr + (c >> 1) * 1024 + ((32 * (c & 1) + (r ^ c)) << 4)) = o;
-                    } else
-                    *reinterpret_cast<f32x4_t *>(scr + g * 1024 + (((lane & 32) | ((lane & 31) ^ (2 * g + (lane >> 5)))) << 4)) = o;
+                    const int r = MF16 ? 16 * (g >> 1) + (lane & 15) : lane & 31;
+                    const int ch = j * 4 + (MF16 ? 2 * (g & 1) + (lane >> 5) : g);
+                    const int half = MF16 ? (lane >> 4) & 1 : lane >> 5;
+                    *reinterpret_cast<bf16x4_t *>(scr + r * 128 + ((ch ^ (r & 7)) << 4) + half * 8) = h;
                 }
-            }
-            if constexpr (!OUT_BF16) {
-                // read back eight lanes to a row: chunk c of row r lies in plane c / 2 at lane slot (r ^ c) + 32 (c & 1)
-                const int c = lane & 7, r8 = lane >> 3;
-                const unsigned char *base = scr + (c >> 1) * 1024 + (32 * (c & 1)) * 16;
-                const int sn = n0 + wn * WTN + j * 32 + c * 4;
-#pragma unroll
-                for (int s4 = 0; s4 < 4; ++s4) {
-                    const int row = 8 * s4 + r8;
-                    const f32x4_t t = *reinterpret_cast<const f32x4_t *>(base + ((row ^ c) << 4));
-                    const int sm = m0 + wm * WTM + i * 32 + row;
-                    const int so = (sm < M && sn < N) ? (int)(((int64_t)sm * P.ldo + sn) * 4) : (int)OOB;
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, t), o_rsrc, so, 0, 0);
-                }
-            }
-        }
-        if constexpr (OUT_BF16) {
             static_assert(!OUT_BF16 || TN == 2, "a wave tile row of 64 bf16 columns is one 128-byte line");
             const int c = lane & 7, r8 = lane >> 3;                  // eight 16-byte chunks (8 columns each) per row
             const int sn = n0 + wn * WTN + c * 8;
@@ -1437,14 +1174,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             }
         }
     }
-    if constexpr (PERSIST) {
-        if (TAILS && !tail_early) {
-            if (tl_on && tl_c > 0 && tl_c <= TL_N)   // the instruction in flight when the main loop ended
-                __builtin_amdgcn_raw_buffer_store_b128(tl_v, tl_drsrc, tl_voff, (tl_c - 1) * tl_stride, COHERENT_LD);
-            land_arrival(tl_on ? (tl_c < TL_N ? tl_c : TL_N) : 0);
-        }
+    if constexpr (PERSIST)
         __syncthreads();                             // every wave is done with the LDS stages
-    }
     item += item_stride;
     } while (PERSIST && item < n_items);             // next work item
 }
@@ -1452,22 +1183,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD>
 hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s)
 {
-    // reduce-scatter steps on the 256x256 tile: the variant that brings B_in in under the main loop
-    bool any_recv = p.n_steps == 0 && p.recv != nullptr;     // (a persistent launch ignores recv and wait_flag)
-    for (int j = 0; j < p.n_steps; ++j)
-        any_recv = any_recv || p.recv_step[j] != nullptr;
-    // (only where the kernel would stream: a long enough k range, one received partial per step, no delivery flag, no
-    // k-split -- otherwise the variant with three left-operand stages is the faster one)
-    bool any_flag = p.n_steps == 0 && p.wait_flag != nullptr;
-    for (int j = 0; j < p.n_steps; ++j)
-        any_flag = any_flag || p.flag_step[j] != nullptr;
-    const int nk_all = (p.K + BK - 1) / BK;
-    bool any_tail = false;                           // a step lands an arrival beside its GEMM (GemmParams::tail_src)
-    for (int j = 0; j < p.n_steps; ++j)
-        any_tail = any_tail || p.tail_src[j] != nullptr;
-    [[maybe_unused]] const bool rlds = SPREAD && NS == 2 && any_recv && !out_bf16 && !p.a_t && p.stream_recv && !p.recv_in_epilogue && !any_flag &&
-                                       p.n_recv_more == 0 && p.splits == 1 && nk_all >= 18 + (p.K % BK != 0 ? 2 : 0) &&
-                                       !any_tail;
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
     int wgs = tiles_m * tiles_n * p.splits + p.cp_wgs;
     if (p.n_steps > 0) {                             // persistent: a grid that fills the chip once
@@ -1485,36 +1200,20 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
         if (p.a_t)
             return hipErrorInvalidValue;
         // (256x256 tile: the main loop on 16x16x32 MFMAs where the launcher asks for it, GemmParams::mfma16)
-#define CF_LAUNCH_PERSIST(WKN, OBF, RL)                                                                                         \
-    do {                                                                                                                        \
-        if constexpr (SPREAD && NS == 2) {                                                                                      \
-            if (p.mfma16 && !(RL))                                                                                              \
-                hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, false, true, false, true>),    \
-                                   grid, block, 0, s, p, tiles_m, tiles_n);                                                     \
-            else                                                                                                                \
-                hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, false, true, RL>), grid, block, \
-                                   0, s, p, tiles_m, tiles_n);                                                                  \
-        } else {                                                                                                                \
-            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, false, true, false>), grid, block,  \
-                               0, s, p, tiles_m, tiles_n);                                                                      \
-        }                                                                                                                       \
-    } while (0)
-        if (w_kn) {
-            if (out_bf16)
-                CF_LAUNCH_PERSIST(true, true, false);
-            else if (SPREAD && NS == 2 && rlds)
-                CF_LAUNCH_PERSIST(true, false, true);
-            else
-                CF_LAUNCH_PERSIST(true, false, false);
-        } else {
-            if (out_bf16)
-                CF_LAUNCH_PERSIST(false, true, false);
-            else if (SPREAD && NS == 2 && rlds)
-                CF_LAUNCH_PERSIST(false, false, true);
-            else
-                CF_LAUNCH_PERSIST(false, false, false);
-        }
-#undef CF_LAUNCH_PERSIST
+        auto go = [&](auto wkn, auto obf) {
+            if constexpr (SPREAD && NS == 2)
+                if (p.mfma16) {
+                    hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, decltype(wkn)::value, decltype(obf)::value, false, true, true>),
+                                       grid, block, 0, s, p, tiles_m, tiles_n);
+                    return;
+                }
+            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, decltype(wkn)::value, decltype(obf)::value, false, true>),
+                               grid, block, 0, s, p, tiles_m, tiles_n);
+        };
+        if (w_kn)
+            out_bf16 ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
+        else
+            out_bf16 ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
         return hipGetLastError();
     }
     if (p.a_t) {
@@ -1524,22 +1223,12 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
     } else if (w_kn) {
         if (out_bf16)
             hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, true>), grid, block, 0, s, p, tiles_m, tiles_n);
-        else if constexpr (SPREAD && NS == 2) {
-            if (rlds)
-                hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, false, false, false, true>), grid, block, 0, s, p, tiles_m, tiles_n);
-            else
-                hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, false>), grid, block, 0, s, p, tiles_m, tiles_n);
-        } else
+        else
             hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, false>), grid, block, 0, s, p, tiles_m, tiles_n);
     } else {
         if (out_bf16)
             hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, false, true>), grid, block, 0, s, p, tiles_m, tiles_n);
-        else if constexpr (SPREAD && NS == 2) {
-            if (rlds)
-                hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, false, false, false, false, true>), grid, block, 0, s, p, tiles_m, tiles_n);
-            else
-                hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, false, false>), grid, block, 0, s, p, tiles_m, tiles_n);
-        } else
+        else
             hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, false, false>), grid, block, 0, s, p, tiles_m, tiles_n);
     }
     return hipGetLastError();
@@ -1557,16 +1246,6 @@ bool gemm_bf16_dl_supported(const GemmParams &p, bool w_kn)
     return p.M > 0 && p.N > 0 && p.K > 0 && a_bytes < lim && w_bytes < lim && o_bytes < lim;
 }
 
-// Would launch_gemm_bf16_dl take the kernel variant that streams B_in through LDS (and so can carry the delivery)
-// for this persistent launch with tile t?  Mirrors the choice in launch_cfg.
-bool gemm_bf16_dl_streams_recv(const GemmParams &p, bool w_kn, bool out_bf16, TileChoice t)
-{
-    (void)w_kn;
-    const int nk_all = (p.K + BK - 1) / BK;
-    return p.n_steps > 0 && t.bm == 256 && t.bn == 256 && !out_bf16 && !p.a_t && tuning().stream_recv != 0 &&
-           p.n_recv_more == 0 && nk_all >= 18 + (p.K % BK != 0 ? 2 : 0);
-}
-
 // Can a persistent all-gather launch carry its deliveries (GemmParams::land_step with steps that add nothing)?  Every
 // tile shape can; the k-tiles must be whole (a ragged one would be stored beyond the end of its rows).
 bool gemm_bf16_dl_carries_operand(const GemmParams &p)
@@ -1580,7 +1259,6 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
     const Tuning tn = tuning();
     if (tn.prefetch >= 0)                              // override: lead of the B_in prefetch in k-tiles, 0 = off
         p.pf_lead = tn.prefetch;
-    p.stream_recv = tn.stream_recv != 0;               // override: 0 = B_in is loaded in the epilogue (256x256 tile)
     p.splits = t.splitk < 1 ? 1 : t.splitk;
     const int nk_all = (p.K + BK - 1) / BK;
     if (p.splits > nk_all)
@@ -1590,9 +1268,6 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         for (int j = 0; j < p.n_steps; ++j)
             if (p.land_step[j] != nullptr && p.recv_step[j] == nullptr && !gemm_bf16_dl_carries_operand(p))
                 return hipErrorInvalidValue;          // callers ask gemm_bf16_carries_delivery first
-        for (int j = 0; j < p.n_steps; ++j)
-            if ((p.tail_src[j] != nullptr) != (p.tail_dst[j] != nullptr) || (p.tail_src[j] != nullptr && out_bf16))
-                return hipErrorInvalidValue;
         p.splits = 1;
         p.cp_wgs = 0;
         p.cp_bytes = 0;
@@ -1641,8 +1316,9 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // which keeps all earlier iterations of the 256x256 main loop branch-free)
         // (nor where the pairwise schedule carries its deliveries: the sums are bit for bit those of its copied mode, whose last
         // step sums several partials and so keeps the k order)
-        p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0 && !p.recv_in_epilogue;
+        p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0 && !p.k_in_order;
         // the 256x256 tile's main loop on 16x16x32 MFMAs (override: COMMFUSE_MFMA16 = 0 | 1)
+        p.early_recv = tn.stream_recv != 0;
         p.mfma16 = t.bm == 256 && t.bn == 256 && p.M % 256 == 0 && p.N % 256 == 0 && tn.mfma16 != 0;
     }
     if (p.splits > 1 && (p.ws == nullptr || p.counters == nullptr ||
