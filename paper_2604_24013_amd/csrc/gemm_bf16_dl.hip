@@ -132,6 +132,7 @@ __device__ __forceinline__ int xcd_remap(int pid, int total)
 // A_T: the left operand is stored [K x M] (see GemmParams::a_t); its tile then lives in LDS like a
 // [k x n] weight tile and is read with the transposing LDS read as well.
 // PERSIST: one launch runs all steps of a rank step (GemmParams::n_steps, see the work-item loop below).
+// NT: B_in, its landed copy and the output pass the caches by (GemmParams::non_temporal, set by the launcher).
 // MF16: the 256x256 tile's main loop on v_mfma_f32_16x16x32_bf16 instead of v_mfma_f32_32x32x16_bf16 -- the same
 // flops from twice as many instructions that each write a quarter of the accumulator registers, which costs the chip
 // less power per flop (measured) and, where the launch is paced by the power limit, time.  A 32x32 sub-tile of the
@@ -139,7 +140,7 @@ __device__ __forceinline__ int xcd_remap(int pid, int total)
 // 16y + 4 (lane >> 4) .. + 3.  A k-tile is two 32-wide slices, each consumed in four quarter phases (one 32-row block
 // of the wave tile per phase).
 template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD, bool W_KN, bool OUT_BF16, bool A_T = false,
-          bool PERSIST = false, bool MF16 = false>
+          bool PERSIST = false, bool MF16 = false, bool NT = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams P, int tiles_m, int tiles_n)
 {
     static_assert(!MF16 || (SPREAD && !A_T && NS == 2), "16x16x32 main loop: 256x256 tile, left operand stored [m x k]");
@@ -655,6 +656,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     const int pf_at = nk - 1 - P.pf_lead;             // iteration after whose tile loads the prefetch is issued
     const bool pf_on = PF && cRecv != nullptr && splits == 1 && n_more == 0 && P.pf_lead > 0 && pf_at >= 0;
     constexpr int COHERENT_LD = 1 | 16;               // buffer cache-policy bits sc0 | sc1
+    constexpr int LINE_AUX = NT ? 2 : 0;              // ... and nt
     // B_in and the fp32 output are read and written as whole 128-byte lines: eight lanes to a row of a 32-column block,
     // eight rows per instruction, four instructions to a 32x32 sub-tile.  The offsets are taken anew from an opaque
     // copy of the lane index where they are needed: the main loop has no registers for them.
@@ -687,11 +689,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         if (recv_coherent)
             load_lines(i, std::integral_constant<int, COHERENT_LD>{});
         else
-            load_lines(i, std::integral_constant<int, 0>{});
+            load_lines(i, std::integral_constant<int, LINE_AUX>{});
     };
 
     // The epilogue's first row block of B_in is requested in front of the last k-tile (there is no register for more).
-    const bool early = P.early_recv && PERSIST && !OUT_BF16 && !pf_on && cFlag == nullptr;
+    const bool early = P.early_recv && PERSIST && !OUT_BF16 && !pf_on && (SPREAD || cRecv != nullptr) && cFlag == nullptr;
     // the left-operand stage whose memory serves as the wave-private scratch of the epilogue's stores
     constexpr int land_stage = SPREAD ? NSA - 1 : 0;
     if constexpr (SPREAD && MF16) {
@@ -854,7 +856,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         // the last tile of a work item: nothing follows it
         auto last16 = [&](int ca, int cw) __attribute__((always_inline)) {
             if (early)
-                load_lines(0, std::integral_constant<int, 0>{});
+                load_lines(0, std::integral_constant<int, LINE_AUX>{});
             front16(ca, cw, nothing, nothing, nothing, nothing, plain_ph2(ca, cw));
             phase16(p2_t{}, afA, wfB, afB, wfA, on_t{}, ca, 1, 3, nothing, c0{}, 0, 0, c0{}, off_t{}, 0, 0, 0, nothing, nothing);
             if (CARRY_A && nk - 1 == carry_at)
@@ -934,7 +936,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         if (nk > 0) {                                    // last tile: nothing follows it
             using wk = std::true_type;
             if (early)
-                load_lines(0, std::integral_constant<int, 0>{});
+                load_lines(0, std::integral_constant<int, LINE_AUX>{});
             phase(af0, wf0, true, cur_a, cur_w, 1, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
             phase(af1, wf1, true, cur_a, cur_w, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
             phase(af0, wf0, true, cur_a, cur_w, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
@@ -1000,7 +1002,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         }
         if (nk > 0) {
             if (early)
-                load_lines(0, std::integral_constant<int, 0>{});
+                load_lines(0, std::integral_constant<int, LINE_AUX>{});
             phase_b(af0, wf0, true, cur, 1, af1, wf1, rpm1{});
             phase_b(af1, wf1, true, cur, 2, af0, wf0, rpm1{});
             phase_b(af0, wf0, true, cur, 3, af1, wf1, rpm1{});
@@ -1092,19 +1094,23 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     if constexpr (!OUT_BF16) {
         // B_in comes in in the layout the tile leaves in: it is read once, stored on to the landing buffer from the
         // registers it came in (the delivery carried by the consumer) and added where the tile is read back from the
-        // scratch.  Without a B_in, or nothing to land, the buffers' ranges are empty: loads return zero, stores are dropped.
+        // scratch.
         // Bound by memory: a reduce-scatter work item moves 768 KiB here at the rate a copy reaches.  Bringing B_in in under the
         // main loop instead (through LDS, 32x32x16 MFMAs) or landing it by a second read beside the GEMM measured, us per
         // carried rank step, against this: 8 x 1024 x 8192 x 3584 474 -> 436, x 1024 242 -> 223, 8 x 512 x 4096 x 1376 72.1 -> 71.5.
         if (!P.wait_at_start && !pf_on)
             wait_delivery(false);                    // B_in has travelled under the main loop
         __amdgpu_buffer_rsrc_t l_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            cLand, 0, PERSIST && cRecv != nullptr && cLand != nullptr ? (int)r_bytes : 0, 0x00020000);
-        if (!pf_on && !early)
+            PERSIST ? cLand : nullptr, 0, cRecv != nullptr && cLand != nullptr ? (int)r_bytes : 0, 0x00020000);
+        // (256x256 tile: no branch, the allocator spills for it -- without a B_in, or nothing to land, the buffers' ranges are
+        // empty: loads return zero, stores are dropped)
+        const bool has_recv = SPREAD || cRecv != nullptr;
+        const bool lands = PERSIST && (SPREAD || (cRecv != nullptr && cLand != nullptr));
+        if (has_recv && !pf_on && !early)
             load_recv(0);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            if (!pf_on && i + 1 < TM)
+            if (has_recv && !pf_on && i + 1 < TM)
                 load_recv(i + 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1112,6 +1118,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
                 int lo[4];
                 line_offsets(i, j, lo);
                 u32x4_t (&a)[4] = lv[i % LV][j];
+                const u32x4_t b_in[4] = {a[0], a[1], a[2], a[3]};
                 for (int b = 0; b < n_more; ++b) {   // further received partials, summed in index order
                     __amdgpu_buffer_rsrc_t m_rsrc = __builtin_amdgcn_make_buffer_rsrc(
                         const_cast<float *>(P.recv_more[b]), 0, (int)r_bytes, 0x00020000);
@@ -1120,6 +1127,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
                         a[s4] = __builtin_bit_cast(u32x4_t, __builtin_bit_cast(f32x4_t, a[s4]) +
                                 __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(m_rsrc, lo[s4], 0, 0)));
                 }
+                if (lands)
+#pragma unroll
+                    for (int s4 = 0; s4 < 4; ++s4)
+                        __builtin_amdgcn_raw_buffer_store_b128(b_in[s4], l_rsrc, lo[s4], 0, LINE_AUX);
                 // chunk c (four columns) of row r of the sub-tile goes to plane c / 2, slot (r ^ c) + 32 (c & 1): the chunks of
                 // a row lie 512 bytes apart and would all fall into one bank otherwise
 #pragma unroll
@@ -1133,10 +1144,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 #pragma unroll
                 for (int s4 = 0; s4 < 4; ++s4) {
                     const f32x4_t t = *reinterpret_cast<const f32x4_t *>(base + (((8 * s4 + r8) ^ c) << 4));
-                    if constexpr (PERSIST)
-                        __builtin_amdgcn_raw_buffer_store_b128(a[s4], l_rsrc, lo[s4], 0, 0);
-                    const f32x4_t o = __builtin_bit_cast(f32x4_t, a[s4]) + t;    // "O <- B_in + O"
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), o_rsrc, lo[s4], 0, 0);
+                    const f32x4_t o = has_recv ? __builtin_bit_cast(f32x4_t, a[s4]) + t : t;     // "O <- B_in + O"
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), o_rsrc, lo[s4], 0, LINE_AUX);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1200,15 +1209,22 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
         if (p.a_t)
             return hipErrorInvalidValue;
         // (256x256 tile: the main loop on 16x16x32 MFMAs where the launcher asks for it, GemmParams::mfma16)
-        auto go = [&](auto wkn, auto obf) {
+        auto go_nt = [&](auto wkn, auto obf, auto nt) {
+            constexpr bool WKN = decltype(wkn)::value, OBF = decltype(obf)::value, NTP = decltype(nt)::value;
             if constexpr (SPREAD && NS == 2)
                 if (p.mfma16) {
-                    hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, decltype(wkn)::value, decltype(obf)::value, false, true, true>),
+                    hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, false, true, true, NTP>),
                                        grid, block, 0, s, p, tiles_m, tiles_n);
                     return;
                 }
-            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, decltype(wkn)::value, decltype(obf)::value, false, true>),
+            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, false, true, false, NTP>),
                                grid, block, 0, s, p, tiles_m, tiles_n);
+        };
+        auto go = [&](auto wkn, auto obf) {
+            if constexpr (!decltype(obf)::value)
+                if (p.non_temporal)
+                    return go_nt(wkn, obf, std::true_type{});
+            go_nt(wkn, obf, std::false_type{});
         };
         if (w_kn)
             out_bf16 ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
@@ -1318,6 +1334,16 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // step sums several partials and so keeps the k order)
         p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0 && !p.k_in_order;
         // the 256x256 tile's main loop on 16x16x32 MFMAs (override: COMMFUSE_MFMA16 = 0 | 1)
+        // fp32 lines past the caches: what a launch writes it never reads again, and B_in is read once.  Only where rows begin
+        // and end on 128-byte lines -- the caches put the halves of a shared line together.  us per carried rank step,
+        // cached against not: 8 x 1024 x 8192 x 1024 232 / 216, 8 x 512 x 4096 x 1376 72.2 / 69.6, 8 x 128 x 4096 x 512 (46 MB)
+        // 19.7 / 20.3, 8 x 100 x 2048 x 2048 (18 MB) 27.3 / 26.6, all-gather 8 x 1024 x 3584 x 8192 380 / 374; rows off the
+        // lines: 2 x 1000 x 3000 x 520 25.1 / 32.3, 4 x 333 x 2088 x 1096 23.9 / 26.3.
+        uintptr_t low = (uintptr_t)(p.ldo * 4) | (uintptr_t)p.N * 4;
+        for (int j = 0; j < p.n_steps; ++j)
+            low |= reinterpret_cast<uintptr_t>(p.out_step[j]) | reinterpret_cast<uintptr_t>(p.recv_step[j]) |
+                   (p.recv_step[j] != nullptr ? reinterpret_cast<uintptr_t>(p.land_step[j]) : 0);
+        p.non_temporal = !out_bf16 && low % 128 == 0;
         p.early_recv = tn.stream_recv != 0;
         p.mfma16 = t.bm == 256 && t.bn == 256 && p.M % 256 == 0 && p.N % 256 == 0 && tn.mfma16 != 0;
     }

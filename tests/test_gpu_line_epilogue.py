@@ -41,6 +41,8 @@ def _run(p, mc, n, k, layout, ldo, flags, seed=5):
     (2, 1, 8, 8, 0),             # one row, two chunks of columns
     (2, 200, 232, 1288, 24),     # padded rows, twenty-one k-tiles: carried on 256x256 tiles, else copied with the padding
     (2, 130, 96, 200, 32),       # padded rows, few k-tiles: copied
+    (8, 1024, 2048, 328, 0),     # work items for every compute unit of any tile: half of them land in front of the main loop
+    (4, 1000, 4096, 72, 0),      # likewise, tiles partly outside the matrix
 ])
 def test_carried_sums_and_landings_are_the_copied_ones(tile, layout, p, mc, n, k, pad):
     os.environ["COMMFUSE_TILE"] = tile
