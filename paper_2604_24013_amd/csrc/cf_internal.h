@@ -52,6 +52,7 @@ struct GemmParams {
     int xcd_bands = 1;       // ... or, > 1: 8 / xcd_bands step groups x xcd_bands bands of tile columns (set by the launcher)
     bool early_recv = true;  // persistent mode: the first of B_in is requested in front of the last k-tile (set by the launcher)
     bool non_temporal = false;   // persistent mode, fp32 output: B_in, its landed copy and the output pass the caches by (set by the launcher)
+    bool land_first = false; // persistent mode: every other workgroup lands its deliveries in front of the main loop (set by the launcher)
     bool mfma16 = false;     // persistent mode, 256x256 tile: main loop on v_mfma_f32_16x16x32_bf16 (set by the launcher)
     const void *A_step[MAX_STEPS] = {};
     const float *recv_step[MAX_STEPS] = {};

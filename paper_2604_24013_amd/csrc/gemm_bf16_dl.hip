@@ -692,6 +692,43 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             load_lines(i, std::integral_constant<int, LINE_AUX>{});
     };
 
+    // The delivery landed in front of the main loop (GemmParams::land_first): every other workgroup of an XCD copies its
+    // tile's part of B_in from the sender's to the landing buffer before it multiplies (its first operand tiles arrive
+    // meanwhile), the others behind it, in the epilogue.  The work items of a round start together and are equally long:
+    // otherwise all compute units multiply while the memory idles and then all move their tiles.  B_in itself is added in
+    // the epilogue in either case: a sum that starts at B_in saves the second read of it (8 x 1024 x 8192 x 1024: 202
+    // instead of 209 us) but rounds every k step at B_in's magnitude, which doubles the error against 64 bits.
+    const bool lands_first = PERSIST && !OUT_BF16 && P.land_first && cLand != nullptr && cRecv != nullptr && (((int)blockIdx.x >> 3) & 1) != 0;
+    auto land_in_front = [&]() __attribute__((always_inline)) {
+        if constexpr (PERSIST && !OUT_BF16) {
+            if (lands_first) {
+                __amdgpu_buffer_rsrc_t l_rsrc = __builtin_amdgcn_make_buffer_rsrc(cLand, 0, (int)r_bytes, 0x00020000);
+                u32x4_t v[TM][TN][4];                // (the accumulators are not in use yet)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        int lo[4];
+                        line_offsets(i, j, lo);
+#pragma unroll
+                        for (int s4 = 0; s4 < 4; ++s4)   // (through the caches: the epilogue reads it again)
+                            v[i][j][s4] = __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, lo[s4], 0, 0);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        int lo[4];
+                        line_offsets(i, j, lo);
+#pragma unroll
+                        for (int s4 = 0; s4 < 4; ++s4)
+                            __builtin_amdgcn_raw_buffer_store_b128(v[i][j][s4], l_rsrc, lo[s4], 0, LINE_AUX);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+            }
+        }
+    };
     // The epilogue's first row block of B_in is requested in front of the last k-tile (there is no register for more).
     const bool early = P.early_recv && PERSIST && !OUT_BF16 && !pf_on && (SPREAD || cRecv != nullptr) && cFlag == nullptr;
     // the left-operand stage whose memory serves as the wave-private scratch of the epilogue's stores
@@ -805,6 +842,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     #pragma unroll
         for (int t = 0; t < NS; ++t)
             issue_range(t, t, t, c0{}, cLPT{});
+        land_in_front();
         wait_vmcnt<(NS - 1) * LPT>();
         __syncthreads();
         afA[0] = frag_a16(0, 0, 0);
@@ -890,6 +928,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     #pragma unroll
         for (int t = 0; t < NS; ++t)
             issue_range(t, t, t, c0{}, cLPT{});
+        land_in_front();
         wait_vmcnt<(NS - 1) * LPT>();
         __syncthreads();
         read_frags(0, 0, 0, af0, wf0);
@@ -966,6 +1005,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 #pragma unroll
         for (int t = 0; t < NS; ++t)
             issue_range(t, t, t, c0{}, cLPT{});
+        land_in_front();
         wait_vmcnt<(NS - 1) * LPT>();
         __syncthreads();
         read_frags(0, 0, 0, af0, wf0);
@@ -1101,11 +1141,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         if (!P.wait_at_start && !pf_on)
             wait_delivery(false);                    // B_in has travelled under the main loop
         __amdgpu_buffer_rsrc_t l_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            PERSIST ? cLand : nullptr, 0, cRecv != nullptr && cLand != nullptr ? (int)r_bytes : 0, 0x00020000);
+            PERSIST ? cLand : nullptr, 0, cRecv != nullptr && cLand != nullptr && !lands_first ? (int)r_bytes : 0, 0x00020000);
         // (256x256 tile: no branch, the allocator spills for it -- without a B_in, or nothing to land, the buffers' ranges are
         // empty: loads return zero, stores are dropped)
         const bool has_recv = SPREAD || cRecv != nullptr;
-        const bool lands = PERSIST && (SPREAD || (cRecv != nullptr && cLand != nullptr));
+        const bool lands = PERSIST && (SPREAD || (cRecv != nullptr && cLand != nullptr && !lands_first));
         if (has_recv && !pf_on && !early)
             load_recv(0);
 #pragma unroll
@@ -1344,6 +1384,15 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
             low |= reinterpret_cast<uintptr_t>(p.out_step[j]) | reinterpret_cast<uintptr_t>(p.recv_step[j]) |
                    (p.recv_step[j] != nullptr ? reinterpret_cast<uintptr_t>(p.land_step[j]) : 0);
         p.non_temporal = !out_bf16 && low % 128 == 0;
+        // Half the workgroups land their deliveries in front of the main loop where the work items fill the chip and their
+        // multiplications do not far outlast the memory's part, which scales with what of the tiles lies inside the
+        // matrix.  us per carried rank step, all in the epilogue / half in front: 8 x 1024 x 8192 at k = 512 180 / 170, 1024
+        // 218 / 209, 2560 356 / 346, 3072 403 / 387, 3584 437 / 442; 8 x 512 x 4096 at 256 43.7 / 40.2, 1376 69.6 / 64.9, 2560 91.5 /
+        // 86.9.  The smaller tiles request B_in under the main loop: 8 x 256 x 4096 x 512 27.1 / 23.0, 2 x 512 x 4096 x 1376
+        // 25.4 / 25.1, 8 x 300 x 4096 x 2048 77.7 / 79.8.  Fewer work items than compute units: 4 x 333 x 2088 x 1096 23.9 / 25.5,
+        // 8 x 100 x 2048 x 2048 26.6 / 27.4.
+        const int64_t items = tiles * p.n_steps;
+        p.land_first = items >= p.num_cu && (int64_t)nk_all * tiles * t.bm * t.bn <= (int64_t)(t.bm == 256 && t.bn == 256 ? 48 : 24) * p.M * p.N;
         p.early_recv = tn.stream_recv != 0;
         p.mfma16 = t.bm == 256 && t.bn == 256 && p.M % 256 == 0 && p.N % 256 == 0 && tn.mfma16 != 0;
     }
