@@ -132,6 +132,7 @@ __device__ __forceinline__ int xcd_remap(int pid, int total)
 // A_T: the left operand is stored [K x M] (see GemmParams::a_t); its tile then lives in LDS like a
 // [k x n] weight tile and is read with the transposing LDS read as well.
 // PERSIST: one launch runs all steps of a rank step (GemmParams::n_steps, see the work-item loop below).
+// RECV: a step of the launch adds a received partial (fp32 output only).
 // NT: B_in, its landed copy and the output pass the caches by (GemmParams::non_temporal, set by the launcher).
 // MF16: the 256x256 tile's main loop on v_mfma_f32_16x16x32_bf16 instead of v_mfma_f32_32x32x16_bf16 -- the same
 // flops from twice as many instructions that each write a quarter of the accumulator registers, which costs the chip
@@ -139,11 +140,12 @@ __device__ __forceinline__ int xcd_remap(int pid, int total)
 // accumulators is then four 16x16 tiles: registers 4g .. 4g+3 with g = 2x + y hold rows 16x + (lane & 15), columns
 // 16y + 4 (lane >> 4) .. + 3.  A k-tile is two 32-wide slices, each consumed in four quarter phases (one 32-row block
 // of the wave tile per phase).
-template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD, bool W_KN, bool OUT_BF16, bool A_T = false,
+template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD, bool W_KN, bool OUT_BF16, bool RECV, bool A_T = false,
           bool PERSIST = false, bool MF16 = false, bool NT = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams P, int tiles_m, int tiles_n)
 {
     static_assert(!MF16 || (SPREAD && !A_T && NS == 2), "16x16x32 main loop: 256x256 tile, left operand stored [m x k]");
+    static_assert(!RECV || !OUT_BF16, "received partials are fp32, and so is their sum");
     static_assert(!A_T || (W_KN && !OUT_BF16), "the transposed left operand comes with [k x n] weights and fp32 output");
     constexpr int NW = WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -647,7 +649,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // B_in prefetch (one workgroup per CU, fp32 output, no k-split): all of the epilogue's loads of the received
     // partial are issued pf_lead k-tiles before the end of the k loop and land in registers under the remaining
     // MFMAs, so that the epilogue only adds and stores.
-    constexpr bool PF = !SPREAD && NS >= 3 && !OUT_BF16;
+    constexpr bool PF = !SPREAD && NS >= 3 && RECV;
     constexpr int PFR = TM * TN * 4;                  // 16-byte loads per lane
     static_assert(!PF || (NS - 2) * LPT + PFR < 64, "vmcnt range");
     const unsigned r_bytes = (unsigned)(((int64_t)(M - 1) * P.ldo + N) * 4);
@@ -670,12 +672,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             off[s4] = (MF16 || (r + 8 * s4 < M && cl < N)) ? (int)(((unsigned)r * (unsigned)P.ldo + cl) * 4u + s4 * rows8) : (int)OOB;
     };
     // row blocks of B_in held in registers: all of the wave tile where it is prefetched, else the one being added and the next
-    constexpr int LV = OUT_BF16 ? 1 : PF ? TM : 2;
-    u32x4_t lv[LV][OUT_BF16 ? 1 : TN][4];
+    constexpr int LV = !RECV ? 1 : PF ? TM : 2;
+    u32x4_t lv[LV][RECV ? TN : 1][4];
     auto load_lines = [&](int i, auto aux_tag) __attribute__((always_inline)) {
         constexpr int AUX = decltype(aux_tag)::value;
 #pragma unroll
-        for (int j = 0; j < (OUT_BF16 ? 0 : TN); ++j) {
+        for (int j = 0; j < (RECV ? TN : 0); ++j) {
             int lo[4];
             line_offsets(i, j, lo);
 #pragma unroll
@@ -698,9 +700,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // otherwise all compute units multiply while the memory idles and then all move their tiles.  B_in itself is added in
     // the epilogue in either case: a sum that starts at B_in saves the second read of it (8 x 1024 x 8192 x 1024: 202
     // instead of 209 us) but rounds every k step at B_in's magnitude, which doubles the error against 64 bits.
-    const bool lands_first = PERSIST && !OUT_BF16 && P.land_first && cLand != nullptr && cRecv != nullptr && (((int)blockIdx.x >> 3) & 1) != 0;
+    const bool lands_first = PERSIST && RECV && P.land_first && cLand != nullptr && cRecv != nullptr && (((int)blockIdx.x >> 3) & 1) != 0;
     auto land_in_front = [&]() __attribute__((always_inline)) {
-        if constexpr (PERSIST && !OUT_BF16) {
+        if constexpr (PERSIST && RECV) {
             if (lands_first) {
                 __amdgpu_buffer_rsrc_t l_rsrc = __builtin_amdgcn_make_buffer_rsrc(cLand, 0, (int)r_bytes, 0x00020000);
                 u32x4_t v[TM][TN][4];                // (the accumulators are not in use yet)
@@ -730,7 +732,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         }
     };
     // The epilogue's first row block of B_in is requested in front of the last k-tile (there is no register for more).
-    const bool early = P.early_recv && PERSIST && !OUT_BF16 && !pf_on && (SPREAD || cRecv != nullptr) && cFlag == nullptr;
+    const bool early = P.early_recv && PERSIST && RECV && !pf_on && (SPREAD || cRecv != nullptr) && cFlag == nullptr;
     // the left-operand stage whose memory serves as the wave-private scratch of the epilogue's stores
     constexpr int land_stage = SPREAD ? NSA - 1 : 0;
     if constexpr (SPREAD && MF16) {
@@ -1138,14 +1140,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         // Bound by memory: a reduce-scatter work item moves 768 KiB here at the rate a copy reaches.  Bringing B_in in under the
         // main loop instead (through LDS, 32x32x16 MFMAs) or landing it by a second read beside the GEMM measured, us per
         // carried rank step, against this: 8 x 1024 x 8192 x 3584 474 -> 436, x 1024 242 -> 223, 8 x 512 x 4096 x 1376 72.1 -> 71.5.
-        if (!P.wait_at_start && !pf_on)
+        if (RECV && !P.wait_at_start && !pf_on)
             wait_delivery(false);                    // B_in has travelled under the main loop
         __amdgpu_buffer_rsrc_t l_rsrc = __builtin_amdgcn_make_buffer_rsrc(
             PERSIST ? cLand : nullptr, 0, cRecv != nullptr && cLand != nullptr && !lands_first ? (int)r_bytes : 0, 0x00020000);
         // (256x256 tile: no branch, the allocator spills for it -- without a B_in, or nothing to land, the buffers' ranges are
         // empty: loads return zero, stores are dropped)
-        const bool has_recv = SPREAD || cRecv != nullptr;
-        const bool lands = PERSIST && (SPREAD || (cRecv != nullptr && cLand != nullptr && !lands_first));
+        const bool has_recv = RECV && (SPREAD || cRecv != nullptr);
+        const bool lands = PERSIST && RECV && (SPREAD || (cRecv != nullptr && cLand != nullptr && !lands_first));
         if (has_recv && !pf_on && !early)
             load_recv(0);
 #pragma unroll
@@ -1157,15 +1159,19 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             for (int j = 0; j < TN; ++j) {
                 int lo[4];
                 line_offsets(i, j, lo);
-                u32x4_t (&a)[4] = lv[i % LV][j];
-                const u32x4_t b_in[4] = {a[0], a[1], a[2], a[3]};
-                for (int b = 0; b < n_more; ++b) {   // further received partials, summed in index order
-                    __amdgpu_buffer_rsrc_t m_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                        const_cast<float *>(P.recv_more[b]), 0, (int)r_bytes, 0x00020000);
+                u32x4_t b_in[4], sum[4];
+                if constexpr (RECV) {
 #pragma unroll
                     for (int s4 = 0; s4 < 4; ++s4)
-                        a[s4] = __builtin_bit_cast(u32x4_t, __builtin_bit_cast(f32x4_t, a[s4]) +
-                                __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(m_rsrc, lo[s4], 0, 0)));
+                        sum[s4] = b_in[s4] = lv[i % LV][j][s4];
+                    for (int b = 0; b < n_more; ++b) {   // further received partials, summed in index order
+                        __amdgpu_buffer_rsrc_t m_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                            const_cast<float *>(P.recv_more[b]), 0, (int)r_bytes, 0x00020000);
+#pragma unroll
+                        for (int s4 = 0; s4 < 4; ++s4)
+                            sum[s4] = __builtin_bit_cast(u32x4_t, __builtin_bit_cast(f32x4_t, sum[s4]) +
+                                      __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(m_rsrc, lo[s4], 0, 0)));
+                    }
                 }
                 if (lands)
 #pragma unroll
@@ -1184,7 +1190,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 #pragma unroll
                 for (int s4 = 0; s4 < 4; ++s4) {
                     const f32x4_t t = *reinterpret_cast<const f32x4_t *>(base + (((8 * s4 + r8) ^ c) << 4));
-                    const f32x4_t o = has_recv ? __builtin_bit_cast(f32x4_t, a[s4]) + t : t;     // "O <- B_in + O"
+                    const f32x4_t o = has_recv ? __builtin_bit_cast(f32x4_t, sum[s4]) + t : t;     // "O <- B_in + O"
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), o_rsrc, lo[s4], 0, LINE_AUX);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -1232,6 +1238,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD>
 hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s)
 {
+    bool any_recv = p.n_steps == 0 && p.recv != nullptr;     // (a persistent launch ignores recv)
+    for (int j = 0; j < p.n_steps; ++j)
+        any_recv = any_recv || p.recv_step[j] != nullptr;
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
     int wgs = tiles_m * tiles_n * p.splits + p.cp_wgs;
     if (p.n_steps > 0) {                             // persistent: a grid that fills the chip once
@@ -1249,43 +1258,38 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
         if (p.a_t)
             return hipErrorInvalidValue;
         // (256x256 tile: the main loop on 16x16x32 MFMAs where the launcher asks for it, GemmParams::mfma16)
-        auto go_nt = [&](auto wkn, auto obf, auto nt) {
-            constexpr bool WKN = decltype(wkn)::value, OBF = decltype(obf)::value, NTP = decltype(nt)::value;
+        auto go = [&](auto wkn, auto obf, auto recv, auto nt) {
+            constexpr bool WKN = decltype(wkn)::value, OBF = decltype(obf)::value, RV = decltype(recv)::value, NTP = decltype(nt)::value;
             if constexpr (SPREAD && NS == 2)
                 if (p.mfma16) {
-                    hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, false, true, true, NTP>),
+                    hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, RV, false, true, true, NTP>),
                                        grid, block, 0, s, p, tiles_m, tiles_n);
                     return;
                 }
-            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, false, true, false, NTP>),
+            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, RV, false, true, false, NTP>),
                                grid, block, 0, s, p, tiles_m, tiles_n);
         };
-        auto go = [&](auto wkn, auto obf) {
-            if constexpr (!decltype(obf)::value)
-                if (p.non_temporal)
-                    return go_nt(wkn, obf, std::true_type{});
-            go_nt(wkn, obf, std::false_type{});
-        };
-        if (w_kn)
-            out_bf16 ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
-        else
-            out_bf16 ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
+        const auto yes = std::true_type{};
+        const auto no = std::false_type{};
+        auto go_f32 = [&](auto wkn, auto recv) { p.non_temporal ? go(wkn, no, recv, yes) : go(wkn, no, recv, no); };
+        auto go_w = [&](auto wkn) { out_bf16 ? go(wkn, yes, no, no) : any_recv ? go_f32(wkn, yes) : go_f32(wkn, no); };
+        w_kn ? go_w(yes) : go_w(no);
         return hipGetLastError();
     }
+    auto go = [&](auto wkn, auto obf, auto recv, auto a_t) {
+        hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, decltype(wkn)::value, decltype(obf)::value, decltype(recv)::value,
+                                                decltype(a_t)::value>), grid, block, 0, s, p, tiles_m, tiles_n);
+    };
+    const auto yes = std::true_type{};
+    const auto no = std::false_type{};
     if (p.a_t) {
         if (!w_kn || out_bf16)
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, false, true>), grid, block, 0, s, p, tiles_m, tiles_n);
+        any_recv ? go(yes, no, yes, yes) : go(yes, no, no, yes);
     } else if (w_kn) {
-        if (out_bf16)
-            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, true>), grid, block, 0, s, p, tiles_m, tiles_n);
-        else
-            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, false>), grid, block, 0, s, p, tiles_m, tiles_n);
+        out_bf16 ? go(yes, yes, no, no) : any_recv ? go(yes, no, yes, no) : go(yes, no, no, no);
     } else {
-        if (out_bf16)
-            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, false, true>), grid, block, 0, s, p, tiles_m, tiles_n);
-        else
-            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, false, false>), grid, block, 0, s, p, tiles_m, tiles_n);
+        out_bf16 ? go(no, yes, no, no) : any_recv ? go(no, no, yes, no) : go(no, no, no, no);
     }
     return hipGetLastError();
 }
@@ -1320,6 +1324,15 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
     if (p.splits > nk_all)
         p.splits = nk_all;
     const int64_t tiles = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
+    // A single step of 256x256 tiles is a rank step of one: the 16x16x32 main loop, bands of tile columns per XCD (us per
+    // step, launched for itself / as this: [n x k] weights, 2048 x 8192 x 3584 111 / 102, 4096 x 8192 x 1376 136 / 125; all-gather
+    // 4096 x 4096 x 8192 213 / 205).
+    if (p.n_steps == 0 && t.bm == 256 && t.bn == 256 && !p.a_t && p.splits == 1 && p.wait_flag == nullptr && p.cp_wgs == 0) {
+        p.n_steps = 1;
+        p.A_step[0] = p.A;
+        p.recv_step[0] = p.recv;
+        p.out_step[0] = p.out;
+    }
     if (p.n_steps > 0) {
         for (int j = 0; j < p.n_steps; ++j)
             if (p.land_step[j] != nullptr && p.recv_step[j] == nullptr && !gemm_bf16_dl_carries_operand(p))
