@@ -21,7 +21,6 @@ struct GemmParams {
     static constexpr int MAX_RECV_MORE = 15;
     const float *recv_more[MAX_RECV_MORE] = {};
     int n_recv_more = 0;
-    int pf_lead = 16;    // B_in prefetch: k-tiles before the end of the k loop at which it is issued (0 = off)
     bool k_in_order = false;         // persistent mode: every k loop starts at 0
     void *out = nullptr;
     int64_t lda = 0, ldw = 0, ldo = 0;
@@ -50,7 +49,6 @@ struct GemmParams {
     bool k_rotate = false;   // persistent mode: XCD x starts its k loops x/8 of the way into the k range (set by the launcher)
     bool xcd_steps = false;  // persistent mode: XCD x runs steps x, x+8, ... whole (set by the launcher)
     int xcd_bands = 1;       // ... or, > 1: 8 / xcd_bands step groups x xcd_bands bands of tile columns (set by the launcher)
-    bool early_recv = true;  // persistent mode: the first of B_in is requested in front of the last k-tile (set by the launcher)
     bool non_temporal = false;   // persistent mode, fp32 output: B_in, its landed copy and the output pass the caches by (set by the launcher)
     bool land_first = false; // persistent mode: every other workgroup lands its deliveries in front of the main loop (set by the launcher)
     bool mfma16 = false;     // persistent mode, 256x256 tile: main loop on v_mfma_f32_16x16x32_bf16 (set by the launcher)
@@ -110,11 +108,11 @@ struct Tuning {
     int deep = -1;                  // COMMFUSE_DEEP = 0 | 1                               (-1 = unset)
     int splitk = 0;                 // COMMFUSE_SPLITK = 1..8                              (0 = unset)
     int staged = 0;                 // COMMFUSE_KERNEL = "staged"
-    int prefetch = -1;              // COMMFUSE_PREFETCH = lead of the B_in prefetch in k-tiles (-1 = unset)
+    int prefetch = -1;              // COMMFUSE_PREFETCH: any value keeps a launch on the tile kernels (-1 = unset)
     int xcd_steps = -1;             // COMMFUSE_XCD_STEPS = 0 | 1                          (-1 = unset)
     int k_rotate = -1;              // COMMFUSE_K_ROTATE = 0 | 1                           (-1 = unset)
     int xcd_bands = 0;              // COMMFUSE_XCD_BANDS = 1 | 2 | 4: column bands per step group (0 = unset: by shape)
-    int stream_recv = -1;           // COMMFUSE_STREAM_RECV = 0 | 1: one-launch rank steps: all of B_in requested behind the main loop (-1 = unset)
+    int stream_recv = -1;           // COMMFUSE_STREAM_RECV: any value keeps a launch on the tile kernels (-1 = unset)
     int mfma16 = -1;                // COMMFUSE_MFMA16 = 0 | 1: 16x16x32 MFMAs in the 256x256 persistent kernel (-1 = unset)
     int persist_wgs = 0;            // COMMFUSE_PERSIST_WGS = cap on the persistent kernel's grid (0 = unset)
     int carry = -1;                 // COMMFUSE_CARRY = 0: a one-launch RS / AG / pairwise RS never carries its deliveries

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     const float *const cRecv = PERSIST ? P.recv_step[step_i] : P.recv;
     void *const cLand = PERSIST ? P.land_step[step_i] : nullptr;   // where the delivery is to land, if this kernel carries it
     void *const cOut = PERSIST ? P.out_step[step_i] : P.out;
-    const unsigned *const cFlag = PERSIST ? P.flag_step[step_i] : P.wait_flag;
+    const unsigned *const cFlag = PERSIST ? nullptr : P.wait_flag;
     // further received partials (GemmParams::recv_more): in a persistent launch they belong to the last step only
     const int n_more = (!PERSIST || step_i == P.n_steps - 1) ? P.n_recv_more : 0;
 
@@ -646,17 +646,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 
     bf16x8_t af0[TM], wf0[TN], af1[TM], wf1[TN];
 
-    // B_in prefetch (one workgroup per CU, fp32 output, no k-split): all of the epilogue's loads of the received
-    // partial are issued pf_lead k-tiles before the end of the k loop and land in registers under the remaining
-    // MFMAs, so that the epilogue only adds and stores.
-    constexpr bool PF = !SPREAD && NS >= 3 && RECV;
-    constexpr int PFR = TM * TN * 4;                  // 16-byte loads per lane
-    static_assert(!PF || (NS - 2) * LPT + PFR < 64, "vmcnt range");
     const unsigned r_bytes = (unsigned)(((int64_t)(M - 1) * P.ldo + N) * 4);
     __amdgpu_buffer_rsrc_t r_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(cRecv), 0, cRecv != nullptr ? (int)r_bytes : 0, 0x00020000);
-    const int pf_at = nk - 1 - P.pf_lead;             // iteration after whose tile loads the prefetch is issued
-    const bool pf_on = PF && cRecv != nullptr && splits == 1 && n_more == 0 && P.pf_lead > 0 && pf_at >= 0;
     constexpr int COHERENT_LD = 1 | 16;               // buffer cache-policy bits sc0 | sc1
     constexpr int LINE_AUX = NT ? 2 : 0;              // ... and nt
     // B_in and the fp32 output are read and written as whole 128-byte lines: eight lanes to a row of a 32-column block,
@@ -671,8 +663,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         for (int s4 = 0; s4 < 4; ++s4)
             off[s4] = (MF16 || (r + 8 * s4 < M && cl < N)) ? (int)(((unsigned)r * (unsigned)P.ldo + cl) * 4u + s4 * rows8) : (int)OOB;
     };
-    // row blocks of B_in held in registers: all of the wave tile where it is prefetched, else the one being added and the next
-    constexpr int LV = !RECV ? 1 : PF ? TM : 2;
+    // Row blocks of B_in held in registers, the one being added and the next; of them EARLY are requested where the k loop has
+    // issued its last operand load (a launch that waits for a flag requests nothing ahead).  The 256x256 tile has
+    // registers for one only.
+    constexpr int LV = RECV ? 2 : 1;
+    constexpr int EARLY = !(PERSIST && RECV) ? 0 : (BM == 256 && BN == 256) ? 1 : 2;
+    static_assert(LV <= TM, "row blocks in flight");
+    constexpr int EARLY_LOADS = EARLY * TN * 4;
     u32x4_t lv[LV][RECV ? TN : 1][4];
     auto load_lines = [&](int i, auto aux_tag) __attribute__((always_inline)) {
         constexpr int AUX = decltype(aux_tag)::value;
@@ -731,8 +728,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             }
         }
     };
-    // The epilogue's first row block of B_in is requested in front of the last k-tile (there is no register for more).
-    const bool early = P.early_recv && PERSIST && RECV && !pf_on && (SPREAD || cRecv != nullptr) && cFlag == nullptr;
+    auto request_early = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < EARLY; ++i)
+            load_lines(i, std::integral_constant<int, LINE_AUX>{});
+    };
     // the left-operand stage whose memory serves as the wave-private scratch of the epilogue's stores
     constexpr int land_stage = SPREAD ? NSA - 1 : 0;
     if constexpr (SPREAD && MF16) {
@@ -882,8 +882,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase16(p3_t{}, afB, wfB, afA, wfA, on_t{}, na, 0, 0, nothing, c2{}, nw_, 0, c2{}, on_t{}, na, 0, 1,
                     lw(std::integral_constant<int, 6>{}), lw(std::integral_constant<int, 7>{}));
         };
-        // first iteration that tests its loads (all of them when K is a multiple of the k-tile: none does)
-        const int tested_at = K % BK == 0 ? nk - 1 : ((rot == 0 && nk - 1 > NS) ? nk - 1 - NS : 0);
+        // The iterations that request a whole k-tile do not test their loads; the others (a ragged k-tile, which is the last of
+        // the range, or one beyond it, which reads zeros and moves nothing) do.
+        const int tested_at = nk - NS - (K % BK != 0 ? 1 : 0);
         int kt = 0;
         for (; kt < tested_at; ++kt) {
             const int nxt_a = (cur_a + 1 == NSA) ? 0 : cur_a + 1;
@@ -895,14 +896,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         }
         // the last tile of a work item: nothing follows it
         auto last16 = [&](int ca, int cw) __attribute__((always_inline)) {
-            if (early)
-                load_lines(0, std::integral_constant<int, LINE_AUX>{});
+            request_early();
             front16(ca, cw, nothing, nothing, nothing, nothing, plain_ph2(ca, cw));
             phase16(p2_t{}, afA, wfB, afB, wfA, on_t{}, ca, 1, 3, nothing, c0{}, 0, 0, c0{}, off_t{}, 0, 0, 0, nothing, nothing);
             if (CARRY_A && nk - 1 == carry_at)
                 carry_tile(nk - 1, ca);
             phase16(p3_t{}, afB, wfB, afA, wfA, off_t{}, 0, 0, 0, nothing, c0{}, 0, 0, c0{}, off_t{}, 0, 0, 0, nothing, nothing);
         };
+        asm volatile("" : "+s"(kt));                     // (keeps the compiler from peeling the loop below: it spills)
         for (; kt + 1 < nk; ++kt) {
             const int nxt_a = (cur_a + 1 == NSA) ? 0 : cur_a + 1;
             const int nxt_w = (cur_w + 1 == NS) ? 0 : cur_w + 1;
@@ -936,48 +937,61 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         read_frags(0, 0, 0, af0, wf0);
         __builtin_amdgcn_sched_barrier(0);
 
-        // The steady state.  When K is a multiple of the k-tile every iteration is branch-free.  Otherwise (the
-        // launcher then leaves the k order unrotated) the ragged k-tile is the last one of the range: the
-        // iterations up to the one that requests it are branch-free too, and only the last NS ones test.
+        // The steady state is branch-free: only the iteration that requests a ragged k-tile (the last of the range: the launcher
+        // then leaves the k order unrotated) tests its loads, and the last NS iterations have none to issue.
         int cur_a = 0, cur_w = 0;                        // stages of tile kt
         int prev_a = NSA - 1;                            // left-operand stage of tile kt-1 (= of tile kt+NS)
-        auto body = [&](int kt, int ca, int cw, int pa, int na, int nw_, auto wk) __attribute__((always_inline)) {
-            phase(af0, wf0, true, ca, cw, 1, af1, wf1, kt + NS, pa, 0, c0{}, cALD{}, wk);
-            phase(af1, wf1, true, ca, cw, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk);
-            phase(af0, wf0, true, ca, cw, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk);
+        // LOADS 2: loads of tile kt+NS, known to be whole; 1: tested; 0: none, R tiles behind tile kt+1 may be in flight
+        auto body = [&](int kt, int ca, int cw, int pa, int na, int nw_, auto loads_tag, auto r_tag) __attribute__((always_inline)) {
+            constexpr int LOADS = decltype(loads_tag)::value, R = decltype(r_tag)::value;
+            using wk = std::integral_constant<bool, LOADS == 2>;
+            using nA = std::integral_constant<int, LOADS ? A_LD : 0>;
+            using nW = std::integral_constant<int, LOADS ? LPT - LH : 0>;
+            constexpr int BEHIND = LOADS ? (NS - 2) * LPT + A_LD : R * LPT + EARLY_LOADS;
+            phase(af0, wf0, true, ca, cw, 1, af1, wf1, kt + NS, pa, 0, c0{}, nA{}, wk{});
+            phase(af1, wf1, true, ca, cw, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
+            phase(af0, wf0, true, ca, cw, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
             if (CARRY_A && kt == carry_at) {         // tile kt goes on to the landing buffer: its stores are the
                 carry_tile(kt, ca);                  // youngest requests and need not be awaited here
-                wait_vmcnt<(NS - 2) * LPT + 2 * A_LD>();
+                wait_vmcnt<BEHIND + A_LD>();
             } else {
-                wait_vmcnt<(NS - 2) * LPT + A_LD>();
+                wait_vmcnt<BEHIND>();
             }
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
-            phase(af1, wf1, true, na, nw_, 0, af0, wf0, kt + NS, 0, cw, cALD{}, cLR{}, wk);
+            phase(af1, wf1, true, na, nw_, 0, af0, wf0, kt + NS, 0, cw, cALD{}, nW{}, wk{});
         };
-        // first iteration that tests its loads (all of them when K is a multiple of the k-tile: none does)
-        const int tested_at = K % BK == 0 ? nk - 1 : ((rot == 0 && nk - 1 > NS) ? nk - 1 - NS : 0);
         int kt = 0;
-        for (; kt < tested_at; ++kt) {
+        auto step = [&](auto loads_tag, auto r_tag) __attribute__((always_inline)) {
             const int nxt_a = (cur_a + 1 == NSA) ? 0 : cur_a + 1;
             const int nxt_w = (cur_w + 1 == NS) ? 0 : cur_w + 1;
-            body(kt, cur_a, cur_w, prev_a, nxt_a, nxt_w, std::true_type{});
+            body(kt, cur_a, cur_w, prev_a, nxt_a, nxt_w, loads_tag, r_tag);
             prev_a = cur_a;
             cur_a = nxt_a;
             cur_w = nxt_w;
+            ++kt;
+        };
+        using l0 = std::integral_constant<int, 0>;
+        using l1 = std::integral_constant<int, 1>;
+        using l2 = std::integral_constant<int, 2>;
+        const int whole_end = nk - NS - (K % BK != 0 ? 1 : 0);
+        while (kt < whole_end)
+            step(l2{}, l0{});
+        while (kt < nk - NS)
+            step(l1{}, l0{});
+        request_early();
+        if constexpr (NS > 3) {
+            if (nk > 3)
+                step(l0{}, l2{});
         }
-        for (; kt + 1 < nk; ++kt) {
-            const int nxt_a = (cur_a + 1 == NSA) ? 0 : cur_a + 1;
-            const int nxt_w = (cur_w + 1 == NS) ? 0 : cur_w + 1;
-            body(kt, cur_a, cur_w, prev_a, nxt_a, nxt_w, std::false_type{});
-            prev_a = cur_a;
-            cur_a = nxt_a;
-            cur_w = nxt_w;
+        if constexpr (NS > 2) {
+            if (nk > 2)
+                step(l0{}, l1{});
         }
+        if (nk > 1)
+            step(l0{}, l0{});
         if (nk > 0) {                                    // last tile: nothing follows it
             using wk = std::true_type;
-            if (early)
-                load_lines(0, std::integral_constant<int, LINE_AUX>{});
             phase(af0, wf0, true, cur_a, cur_w, 1, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
             phase(af1, wf1, true, cur_a, cur_w, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
             phase(af0, wf0, true, cur_a, cur_w, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
@@ -986,7 +1000,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase(af1, wf1, false, 0, 0, 0, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
         }
     } else {
-        // Variant for the small tiles (few MFMAs per slice): a tile's loads go out together right
+        // Variant for two workgroups per CU over long k ranges: a tile's loads go out together right
         // after the barrier that frees their stage, and the LDS reads of the next slice are
         // interleaved with all MFMAs of the current one.
         auto phase_b = [&](const bf16x8_t (&afc)[TM], const bf16x8_t (&wfc)[TN], bool do_read, int stage_n, int ks_n,
@@ -1018,11 +1032,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase_b(af0, wf0, true, cur, 1, af1, wf1, rpm1{});
             phase_b(af1, wf1, true, cur, 2, af0, wf0, rpm1{});
             phase_b(af0, wf0, true, cur, 3, af1, wf1, rpm2{});   // reads early: complete at the barrier
-            // tile kt+1 complete, NS-2 later tiles may be in flight -- and, in the NS-1 iterations after the
-            // B_in prefetch went out behind tile pf_at+NS, those loads too (loads return in issue order)
-            if (PF && pf_on && kt > pf_at && kt < pf_at + NS) {
-                wait_vmcnt<(NS - 2) * LPT + PFR>();
-            } else if (CARRY_A && kt == carry_at) {  // tile kt goes on to the landing buffer (stores not awaited here)
+            // tile kt+1 complete, NS-2 later tiles may be in flight
+            if (CARRY_A && kt == carry_at) {         // tile kt goes on to the landing buffer (stores not awaited here)
                 carry_tile(kt, cur);
                 wait_vmcnt<(NS - 2) * LPT + A_LD>();
             } else {
@@ -1030,21 +1041,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             }
             __syncthreads();                 // tile kt is read by all, tile kt+1 is published
             issue_range(kt + NS, cur, cur, c0{}, cLPT{});
-            if constexpr (PF) {
-                if (pf_on && kt == pf_at) {
-                    wait_delivery(false);
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-                        load_recv(i);
-                }
-            }
             __builtin_amdgcn_sched_barrier(0);
             phase_b(af1, wf1, true, nxt, 0, af0, wf0, rpm1{});
             cur = nxt;
         }
         if (nk > 0) {
-            if (early)
-                load_lines(0, std::integral_constant<int, LINE_AUX>{});
+            request_early();
             phase_b(af0, wf0, true, cur, 1, af1, wf1, rpm1{});
             phase_b(af1, wf1, true, cur, 2, af0, wf0, rpm1{});
             phase_b(af0, wf0, true, cur, 3, af1, wf1, rpm1{});
@@ -1053,11 +1055,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase_b(af1, wf1, false, 0, 0, af0, wf0, rpm1{});
         }
     }
-    // no direct load may outlive its LDS allocation (the early request of B_in is younger than all of them)
-    if (early)
-        wait_vmcnt<TN * 4>();
-    else
-        wait_vmcnt<0>();
+    // no direct load may outlive its LDS allocation (the early requests of B_in are younger than all of them)
+    wait_vmcnt<EARLY_LOADS>();
 
     // Row and first column (of four) of accumulator registers 4g .. 4g+3 of this lane's 32x32 sub-tile (i, j).
     auto e_row = [&](int i, int g) __attribute__((always_inline)) {
@@ -1140,7 +1139,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         // Bound by memory: a reduce-scatter work item moves 768 KiB here at the rate a copy reaches.  Bringing B_in in under the
         // main loop instead (through LDS, 32x32x16 MFMAs) or landing it by a second read beside the GEMM measured, us per
         // carried rank step, against this: 8 x 1024 x 8192 x 3584 474 -> 436, x 1024 242 -> 223, 8 x 512 x 4096 x 1376 72.1 -> 71.5.
-        if (RECV && !P.wait_at_start && !pf_on)
+        if (RECV && !P.wait_at_start)
             wait_delivery(false);                    // B_in has travelled under the main loop
         __amdgpu_buffer_rsrc_t l_rsrc = __builtin_amdgcn_make_buffer_rsrc(
             PERSIST ? cLand : nullptr, 0, cRecv != nullptr && cLand != nullptr && !lands_first ? (int)r_bytes : 0, 0x00020000);
@@ -1148,11 +1147,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         // empty: loads return zero, stores are dropped)
         const bool has_recv = RECV && (SPREAD || cRecv != nullptr);
         const bool lands = PERSIST && RECV && (SPREAD || (cRecv != nullptr && cLand != nullptr && !lands_first));
-        if (has_recv && !pf_on && !early)
+        if (has_recv && EARLY == 0)
             load_recv(0);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            if (has_recv && !pf_on && i + 1 < TM)
+            if (has_recv && i + 1 < TM && i + 1 >= EARLY)
                 load_recv(i + 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1260,7 +1259,7 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
         // (256x256 tile: the main loop on 16x16x32 MFMAs where the launcher asks for it, GemmParams::mfma16)
         auto go = [&](auto wkn, auto obf, auto recv, auto nt) {
             constexpr bool WKN = decltype(wkn)::value, OBF = decltype(obf)::value, RV = decltype(recv)::value, NTP = decltype(nt)::value;
-            if constexpr (SPREAD && NS == 2)
+            if constexpr (BM == 256 && BN == 256)
                 if (p.mfma16) {
                     hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, RV, false, true, true, NTP>),
                                        grid, block, 0, s, p, tiles_m, tiles_n);
@@ -1317,17 +1316,21 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
 {
     GemmParams p = p_in;
     const Tuning tn = tuning();
-    if (tn.prefetch >= 0)                              // override: lead of the B_in prefetch in k-tiles, 0 = off
-        p.pf_lead = tn.prefetch;
     p.splits = t.splitk < 1 ? 1 : t.splitk;
     const int nk_all = (p.K + BK - 1) / BK;
     if (p.splits > nk_all)
         p.splits = nk_all;
     const int64_t tiles = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
-    // A single step of 256x256 tiles is a rank step of one: the 16x16x32 main loop, bands of tile columns per XCD (us per
+    if (p.splits > 1 && (p.ws == nullptr || p.counters == nullptr ||
+                         (size_t)p.splits * p.M * p.N * sizeof(float) > p.ws_bytes || tiles > p.max_tiles ||
+                         (int64_t)p.M * p.N * 4 >= ((int64_t)1 << 31)))
+        p.splits = 1;                          // no (or too small a) workspace: plain kernel
+    if (p.cp_src == nullptr || p.cp_dst == nullptr || p.cp_bytes == 0)
+        p.cp_wgs = 0;
+    // A single step is a rank step of one: the 16x16x32 main loop of whole 256x256 tiles, bands of tile columns per XCD (us per
     // step, launched for itself / as this: [n x k] weights, 2048 x 8192 x 3584 111 / 102, 4096 x 8192 x 1376 136 / 125; all-gather
     // 4096 x 4096 x 8192 213 / 205).
-    if (p.n_steps == 0 && t.bm == 256 && t.bn == 256 && !p.a_t && p.splits == 1 && p.wait_flag == nullptr && p.cp_wgs == 0) {
+    if (p.n_steps == 0 && !p.a_t && p.splits == 1 && p.wait_flag == nullptr && p.cp_wgs == 0) {
         p.n_steps = 1;
         p.A_step[0] = p.A;
         p.recv_step[0] = p.recv;
@@ -1406,20 +1409,17 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // 8 x 100 x 2048 x 2048 26.6 / 27.4.
         const int64_t items = tiles * p.n_steps;
         p.land_first = items >= p.num_cu && (int64_t)nk_all * tiles * t.bm * t.bn <= (int64_t)(t.bm == 256 && t.bn == 256 ? 48 : 24) * p.M * p.N;
-        p.early_recv = tn.stream_recv != 0;
         p.mfma16 = t.bm == 256 && t.bn == 256 && p.M % 256 == 0 && p.N % 256 == 0 && tn.mfma16 != 0;
     }
-    if (p.splits > 1 && (p.ws == nullptr || p.counters == nullptr ||
-                         (size_t)p.splits * p.M * p.N * sizeof(float) > p.ws_bytes || tiles > p.max_tiles ||
-                         (int64_t)p.M * p.N * 4 >= ((int64_t)1 << 31)))
-        p.splits = 1;                          // no (or too small a) workspace: plain kernel
-    if (p.cp_src == nullptr || p.cp_dst == nullptr || p.cp_bytes == 0)
-        p.cp_wgs = 0;
-    // LDS stages: as many as fit (160 KiB per CU); the 128x128 tile comes with two stages (two
-    // workgroups share a CU) or four (one workgroup per CU, tiles requested three ahead).
+    // LDS stages: as many as fit (160 KiB per CU); the 128x128 tile comes with two (two workgroups share a CU) or four (one
+    // workgroup per CU, tiles requested three ahead).  Spreading the loads over the MFMAs beats a burst behind the barrier
+    // (all-gather 8 x 512 x 1536 x 4096 on 256x128 61 / 54 us, reduce-scatter 2 x 128 x 5120 x 5248 on 128x128 53 / 37) but for
+    // two workgroups per CU over long k ranges, which cover for each other (8 x 299 x 4808 x 4104 160 / 168, 8 x 896 x 4224 x
+    // 4480 271 / 272; 8 x 480 x 2112 x 1408 41 / 36).
     if (t.bm == 256 && t.bn == 256) return launch_cfg<256, 256, 2, 4, 2, true>(p, w_kn, out_bf16, s);
-    if (t.bm == 256 && t.bn == 128) return launch_cfg<256, 128, 4, 2, 3, false>(p, w_kn, out_bf16, s);
-    if (t.deep) return launch_cfg<128, 128, 2, 2, 4, false>(p, w_kn, out_bf16, s);
+    if (t.bm == 256 && t.bn == 128) return launch_cfg<256, 128, 4, 2, 2, true>(p, w_kn, out_bf16, s);
+    if (t.deep) return launch_cfg<128, 128, 2, 2, 4, true>(p, w_kn, out_bf16, s);
+    if (nk_all <= 48) return launch_cfg<128, 128, 2, 2, 2, true>(p, w_kn, out_bf16, s);
     return launch_cfg<128, 128, 2, 2, 2, false>(p, w_kn, out_bf16, s);
 }
 

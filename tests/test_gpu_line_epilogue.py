@@ -32,34 +32,34 @@ def _run(p, mc, n, k, layout, ldo, flags, seed=5):
     return A, W if layout == cf.CF_W_KN else W.t(), stage, each, sends + [O]
 
 
-@pytest.mark.parametrize("tile", ["256x256", "256x128", "128x128"])
+@pytest.mark.parametrize("tile,deep", [("256x256", "0"), ("256x128", "0"), ("128x128", "0"), ("128x128", "1")])
 @pytest.mark.parametrize("layout", [cf.CF_W_KN, cf.CF_W_NK])
 @pytest.mark.parametrize("p,mc,n,k,pad", [
-    (4, 256, 512, 64, 0),        # whole tiles, one k-tile: the early request of B_in is the first after the prologue
+    (4, 256, 512, 64, 0),        # whole tiles, one k-tile: the early request of B_in follows the prologue
+    (4, 256, 256, 128, 0), (3, 256, 256, 192, 0), (2, 130, 264, 256, 0), (2, 256, 128, 320, 0),   # two to five k-tiles: the iterations without loads
     (8, 512, 256, 1152, 0),      # whole tiles, eighteen k-tiles
     (3, 261, 264, 136, 0),       # a tile of five rows and of eight columns, a ragged third k-tile; rows off the 128-byte lines
+    (2, 130, 264, 3080, 0),      # forty-nine k-tiles: two 128x128 tiles per compute unit issue their loads in a burst
     (2, 1, 8, 8, 0),             # one row, two chunks of columns
     (2, 200, 232, 1288, 24),     # padded rows, twenty-one k-tiles: carried on 256x256 tiles, else copied with the padding
     (2, 130, 96, 200, 32),       # padded rows, few k-tiles: copied
     (8, 1024, 2048, 328, 0),     # work items for every compute unit of any tile: half of them land in front of the main loop
     (4, 1000, 4096, 72, 0),      # likewise, tiles partly outside the matrix
 ])
-def test_carried_sums_and_landings_are_the_copied_ones(tile, layout, p, mc, n, k, pad):
-    os.environ["COMMFUSE_TILE"] = tile
+def test_carried_sums_and_landings_are_the_copied_ones(tile, deep, layout, p, mc, n, k, pad):
+    os.environ["COMMFUSE_TILE"], os.environ["COMMFUSE_DEEP"] = tile, deep
     try:
         A, W, stage, each, outs = _run(p, mc, n, k, layout, n + pad, cf.CF_FUSED_COPY)
         _, _, _, _, copied = _run(p, mc, n, k, layout, n + pad, 0)
-        os.environ["COMMFUSE_STREAM_RECV"] = "0"
-        late = _run(p, mc, n, k, layout, n + pad, cf.CF_FUSED_COPY)[4]
     finally:
         os.environ.pop("COMMFUSE_TILE", None)
-        os.environ.pop("COMMFUSE_STREAM_RECV", None)
+        os.environ.pop("COMMFUSE_DEEP", None)
     for a, b in zip(each, stage):
         assert torch.equal(a[:, :n], b[:, :n])
         if pad and (tile != "256x256" or k < 1280):
             assert torch.equal(a, b)                 # a copy in front moves the padding too
-    for i, (got, same, third) in enumerate(zip(outs, copied, late)):
-        assert torch.equal(got[:, :n], same[:, :n]) and torch.equal(got[:, :n], third[:, :n])
+    for i, (got, same) in enumerate(zip(outs, copied)):
+        assert torch.equal(got[:, :n], same[:, :n])
         assert bool(got[:, n:].isnan().all())
         l = cf.chunk_index(cf.CF_KIND_RS, p, 1 % p, i)
         want = A[l * mc:(l + 1) * mc].double() @ W.double() + (stage[i - 1][:, :n].double() if i else 0.0)
