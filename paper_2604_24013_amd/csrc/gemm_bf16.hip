@@ -364,8 +364,7 @@ static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
 
 // Tile of a launch: the one by area, but for another whose estimate is 7 % below its own -- of 261 drawn launches that change
 // or not, the change alone gains 3.7 % on average, 13 % where it is made; without the 7 % as much, and four times as many
-// come out slower (us: all-gather 4 x 777 x 2504 x 1832 on 128x128 80, on 256x256 57; reduce-scatter 8 x 32 x 4096 x 1536 on two
-// 128x128 tiles per compute unit instead of one FIG).  Then the overrides.
+// come out slower (us: all-gather 4 x 777 x 2504 x 1832 on 128x128 80, on 256x256 57; reduce-scatter 63 and 54).  Then the overrides.
 static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
 {
     TileChoice t = tile_by_area(p, num_cu);

@@ -144,7 +144,7 @@ template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD, bool W_KN, bool
           bool PERSIST = false, bool MF16 = false, bool NT = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams P, int tiles_m, int tiles_n)
 {
-    static_assert(!MF16 || (SPREAD && !A_T && NS == 2), "16x16x32 main loop: 256x256 tile, left operand stored [m x k]");
+    static_assert(!MF16 || (SPREAD && NS == 2), "16x16x32 main loop: 256x256 tile");
     static_assert(!RECV || !OUT_BF16, "received partials are fp32, and so is their sum");
     static_assert(!A_T || (W_KN && !OUT_BF16), "the transposed left operand comes with [k x n] weights and fp32 output");
     constexpr int NW = WGM * WGN;
@@ -294,7 +294,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         if constexpr (A_T) {
             const int k = pos / A_ROWB, inrow = pos % A_ROWB;
             const int q = (inrow >> 6) ^ (k & 3);
-            const int gm = m0 + q * 32 + ((inrow >> 4) & 3) * 8;
+            const int c4 = ((inrow >> 4) & 3) ^ (MF16 ? ((k >> 4) & 1) << 1 : 0);    // (as the [k x n] weights, below)
+            const int gm = m0 + q * 32 + c4 * 8;
             a_off[j] = gm < M ? (unsigned)(((int64_t)k * P.lda + gm) * 2) : OOB;
         } else {
             int row, kc;
@@ -339,13 +340,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     const int w_kstep = W_KN ? (int)(P.ldw * 2) : 2;   // bytes per unit of k along W
     const int a_kstep = A_T ? (int)(P.lda * 2) : 2;    // ... and along the left operand
     // MF16 (whole tiles only: no lane is out of range): wave-load j of a tile fetches, lane by lane, what wave-load 0
-    // fetches 64 rows further on (a [k x n] weight tile: what wave-load j - 2 fetches 32 k-rows further on -- the
-    // 32-byte halves change places every 16 k-rows), so one per-lane offset per operand (two for [k x n] weights) is
+    // fetches 64 rows further on (a tile stored by k-rows: what wave-load j - 2 fetches 32 k-rows further on -- the
+    // 32-byte halves change places every 16 k-rows), so one per-lane offset per operand (two if stored by k-rows) is
     // kept and the distance goes into the scalar part of the address
-    constexpr int W_JP = (MF16 && W_KN) ? 2 : 1;     // wave-loads of a weight tile with an offset register of their own
-    const int a_jstep = MF16 ? (int)(64 * P.lda * 2) : 0;
+    constexpr int A_JP = (MF16 && A_T) ? 2 : 1;      // wave-loads of a left-operand tile with an offset register of their own
+    constexpr int W_JP = (MF16 && W_KN) ? 2 : 1;     // ... of a weight tile
+    const int a_jstep = MF16 ? (int)((A_T ? 16 : 64) * P.lda * 2) : 0;
     const int w_jstep = MF16 ? (int)((W_KN ? 16 : 64) * P.ldw * 2) : 0;
-    // per-lane offset register and scalar distance of weight wave-load j
+    // per-lane offset register and scalar distance of wave-load j of an operand
+    auto a_reg = [](int j) { return MF16 ? j % A_JP : j; };
+    auto a_dist = [&](int j) __attribute__((always_inline)) { return (j - j % A_JP) * a_jstep; };
     auto w_reg = [](int j) { return MF16 ? j % W_JP : j; };
     auto w_dist = [&](int j) __attribute__((always_inline)) { return (j - j % W_JP) * w_jstep; };
 
@@ -375,7 +379,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         const unsigned sw = lds_base + W_BASE + stage_w * B_BYTES + wave * 1024;
         if constexpr (WHOLE_K) {
             if constexpr (idx < A_LD)
-                direct_load_16(a_rsrc, a_off[MF16 ? 0 : idx], k0 * a_kstep + idx * a_jstep, sa + idx * NW * 1024);
+                direct_load_16(a_rsrc, a_off[a_reg(idx)], k0 * a_kstep + a_dist(idx), sa + idx * NW * 1024);
             else
                 direct_load_16(w_rsrc, b_off[w_reg(idx - A_LD)], k0 * w_kstep + w_dist(idx - A_LD), sw + (idx - A_LD) * NW * 1024);
             return;
@@ -383,7 +387,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         const bool full = kt < nk && (k0 + BK) <= K;     // uniform: the common case needs no per-lane test
         if (full) {
             if constexpr (idx < A_LD)
-                direct_load_16(a_rsrc, a_off[MF16 ? 0 : idx], k0 * a_kstep + idx * a_jstep, sa + idx * NW * 1024);
+                direct_load_16(a_rsrc, a_off[a_reg(idx)], k0 * a_kstep + a_dist(idx), sa + idx * NW * 1024);
             else
                 direct_load_16(w_rsrc, b_off[w_reg(idx - A_LD)], k0 * w_kstep + w_dist(idx - A_LD), sw + (idx - A_LD) * NW * 1024);
         } else {
@@ -391,8 +395,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             const int klim = none ? -1 : K;              // chunks at k >= klim read as zero
             const int ks0 = none ? 0 : k0;
             if constexpr (idx < A_LD) {
-                const unsigned off = (k0 + chunk_k(idx, A_T, A_ROWB)) >= klim ? OOB : a_off[MF16 ? 0 : idx];
-                direct_load_16(a_rsrc, off, ks0 * a_kstep + idx * a_jstep, sa + idx * NW * 1024);
+                const unsigned off = (k0 + chunk_k(idx, A_T, A_ROWB)) >= klim ? OOB : a_off[a_reg(idx)];
+                direct_load_16(a_rsrc, off, ks0 * a_kstep + a_dist(idx), sa + idx * NW * 1024);
             } else {
                 constexpr int j = idx - A_LD;
                 const unsigned off = (k0 + chunk_k(j, W_KN, W_ROWB)) >= klim ? OOB : b_off[w_reg(j)];
@@ -410,7 +414,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 #pragma unroll
             for (int idx = lo; idx < hi; ++idx) {
                 if (idx < A_LD)
-                    direct_load_16(a_rsrc, a_off[(!MF16 && idx < A_LD) ? idx : 0], k0 * a_kstep + idx * a_jstep, sa + idx * NW * 1024);
+                    direct_load_16(a_rsrc, a_off[idx < A_LD ? a_reg(idx) : 0], k0 * a_kstep + a_dist(idx), sa + idx * NW * 1024);
                 else
                     direct_load_16(w_rsrc, b_off[idx >= A_LD ? w_reg(idx - A_LD) : 0], k0 * w_kstep + w_dist(idx - A_LD),
                                    sw + (idx - A_LD) * NW * 1024);
@@ -540,10 +544,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     if constexpr (MF16) {
         static_assert(!MF16 || (TM == 4 && TN == 2), "quarter phases are written for the 128x64 wave tile");
         const int kch = (((lane >> 4) & 1) << 1) | (lane >> 5);          // this lane's chunk of a slice
-        a_addr16 = swz_row(wm * WTM + (lane & 15), kch);
+        const int i16 = lane & 15;
+        const int kl = kch * 8 + (i16 >> 2);                                 // k of (slice 0, first half), tiles stored by k-rows
+        if constexpr (A_T) {
+            // (16-row tile t of the wave's rows lies at this address ^ 32 t: the swizzle touches those bits alone)
+            static_assert(!A_T || WTM == 128, "four 64-byte groups to a wave's rows");
+            a_addr16 = kl * A_ROWB + (((wm * WTM) >> 5 | (kl & 3)) << 6) + (((i16 & 3) * 8) ^ (((kl >> 4) & 1) << 5));
+        } else {
+            a_addr16 = swz_row(wm * WTM + (lane & 15), kch);
+        }
         if constexpr (W_KN) {
-            const int i16 = lane & 15;
-            const int kl = kch * 8 + (i16 >> 2);                             // k of (slice 0, first half)
 #pragma unroll
             for (int t = 0; t < TN16; t += 2) {
                 const int nl = wn * WTN + t * 16 + (i16 & 3) * 4;
@@ -774,7 +784,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             }
         };
         auto frag_a16 = [&](int stage_a, int sl, int t16) __attribute__((always_inline)) {
-            return *reinterpret_cast<const bf16x8_t *>(smem + stage_a * A_BYTES + (a_addr16 ^ (sl << 6)) + t16 * 2048);
+            if constexpr (A_T) {
+                const unsigned char *pa = smem + stage_a * A_BYTES + (a_addr16 ^ (t16 << 5)) + sl * 32 * A_ROWB;
+                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)(pa));
+                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)(pa + 4 * A_ROWB));
+                const s16x8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                return __builtin_bit_cast(bf16x8_t, both);
+            } else {
+                return *reinterpret_cast<const bf16x8_t *>(smem + stage_a * A_BYTES + (a_addr16 ^ (sl << 6)) + t16 * 2048);
+            }
         };
         auto frag_w16 = [&](int stage_w, int sl, auto t_tag) __attribute__((always_inline)) {
             constexpr int t = decltype(t_tag)::value;
@@ -789,7 +807,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
                 return *reinterpret_cast<const bf16x8_t *>(stw + (w_addr16[0] ^ (sl << 6)) + t * 2048);
             }
         };
-        constexpr int NRD_WF = W_KN ? 2 : 1;                 // LDS reads of one weight fragment
+        constexpr int NRD_AF = A_T ? 2 : 1, NRD_WF = W_KN ? 2 : 1;   // LDS reads of one fragment
         auto nothing = [&]() __attribute__((always_inline)) {};
         // One quarter phase on block PB with the fragments (afc, wfc).
         //   r1: fragment x = 1 of (stage s1, slice l1, block b1) into afo[1] at segment 0;  mid(): between segments 0 and 1;
@@ -804,7 +822,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             if constexpr (R1)
                 afo[1] = frag_a16(s1, l1, 2 * b1 + 1);
             mfma16_seg(pb_tag, afc, wfc, std::integral_constant<int, 0>{});
-            interleave_mfma_reads<R1 ? 1 : 0, 1>();
+            interleave_mfma_reads<R1 ? NRD_AF : 0, 1>();
             __builtin_amdgcn_sched_barrier(0);
             mid();
             if constexpr (NWF > 0)
@@ -816,7 +834,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             if constexpr (R2)
                 afc[0] = frag_a16(s2, l2, 2 * b2);
             mfma16_seg(pb_tag, afc, wfc, std::integral_constant<int, 2>{});
-            interleave_mfma_reads<R2 ? 1 : 0, 1>();
+            interleave_mfma_reads<R2 ? NRD_AF : 0, 1>();
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (NWF > 1)
                 wfn[W0 + 1] = frag_w16(sw, lw, std::integral_constant<int, W0 + 1>{});
@@ -1254,8 +1272,6 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
     }
     const dim3 grid(wgs), block(64 * WGM * WGN);
     if (p.n_steps > 0) {                             // persistent rank step: fp32 or bf16 output, either weight order
-        if (p.a_t)
-            return hipErrorInvalidValue;
         // (256x256 tile: the main loop on 16x16x32 MFMAs where the launcher asks for it, GemmParams::mfma16)
         auto go = [&](auto wkn, auto obf, auto recv, auto nt) {
             constexpr bool WKN = decltype(wkn)::value, OBF = decltype(obf)::value, RV = decltype(recv)::value, NTP = decltype(nt)::value;
@@ -1270,6 +1286,18 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
         };
         const auto yes = std::true_type{};
         const auto no = std::false_type{};
+        if (p.a_t) {                                 // (whole 256x256 tiles: the 16x16x32 main loop, see the launcher)
+            if constexpr (BM == 256 && BN == 256)
+                if (w_kn && !out_bf16 && p.mfma16) {
+                    auto go_t = [&](auto recv, auto nt) {
+                        hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, false, decltype(recv)::value, true, true, true,
+                                                                decltype(nt)::value>), grid, block, 0, s, p, tiles_m, tiles_n);
+                    };
+                    any_recv ? go_t(yes, no) : p.non_temporal ? go_t(no, yes) : go_t(no, no);
+                    return hipGetLastError();
+                }
+            return hipErrorInvalidValue;
+        }
         auto go_f32 = [&](auto wkn, auto recv) { p.non_temporal ? go(wkn, no, recv, yes) : go(wkn, no, recv, no); };
         auto go_w = [&](auto wkn) { out_bf16 ? go(wkn, yes, no, no) : any_recv ? go_f32(wkn, yes) : go_f32(wkn, no); };
         w_kn ? go_w(yes) : go_w(no);
@@ -1330,7 +1358,11 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
     // A single step is a rank step of one: the 16x16x32 main loop of whole 256x256 tiles, bands of tile columns per XCD (us per
     // step, launched for itself / as this: [n x k] weights, 2048 x 8192 x 3584 111 / 102, 4096 x 8192 x 1376 136 / 125; all-gather
     // 4096 x 4096 x 8192 213 / 205).
-    if (p.n_steps == 0 && !p.a_t && p.splits == 1 && p.wait_flag == nullptr && p.cp_wgs == 0) {
+    // A weight gradient only where it is whole 256x256 tiles (8192 rows at once into 8192 x 3584 389 / 361, into 3584 x 8192
+    // 388 / 346, in eight steps added in place 660 / 638 and 702 / 655); on the smaller tiles it loses by it: 512 rows into
+    // 1376 x 4096 110 / 120, 300 into 4096 x 2048 141 / 144, 64 into 2048 x 2048 71 / 74.
+    const bool whole_256 = t.bm == 256 && t.bn == 256 && p.M % 256 == 0 && p.N % 256 == 0 && tn.mfma16 != 0;
+    if (p.n_steps == 0 && (!p.a_t || whole_256) && p.splits == 1 && p.wait_flag == nullptr && p.cp_wgs == 0) {
         p.n_steps = 1;
         p.A_step[0] = p.A;
         p.recv_step[0] = p.recv;
@@ -1389,7 +1421,6 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // (nor where the pairwise schedule carries its deliveries: the sums are bit for bit those of its copied mode, whose last
         // step sums several partials and so keeps the k order)
         p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0 && !p.k_in_order;
-        // the 256x256 tile's main loop on 16x16x32 MFMAs (override: COMMFUSE_MFMA16 = 0 | 1)
         // fp32 lines past the caches: what a launch writes it never reads again, and B_in is read once.  Only where rows begin
         // and end on 128-byte lines -- the caches put the halves of a shared line together.  us per carried rank step,
         // cached against not: 8 x 1024 x 8192 x 1024 232 / 216, 8 x 512 x 4096 x 1376 72.2 / 69.6, 8 x 128 x 4096 x 512 (46 MB)
@@ -1409,7 +1440,7 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // 8 x 100 x 2048 x 2048 26.6 / 27.4.
         const int64_t items = tiles * p.n_steps;
         p.land_first = items >= p.num_cu && (int64_t)nk_all * tiles * t.bm * t.bn <= (int64_t)(t.bm == 256 && t.bn == 256 ? 48 : 24) * p.M * p.N;
-        p.mfma16 = t.bm == 256 && t.bn == 256 && p.M % 256 == 0 && p.N % 256 == 0 && tn.mfma16 != 0;
+        p.mfma16 = whole_256;                        // (override: COMMFUSE_MFMA16 = 0 | 1)
     }
     // LDS stages: as many as fit (160 KiB per CU); the 128x128 tile comes with two (two workgroups share a CU) or four (one
     // workgroup per CU, tiles requested three ahead).  Spreading the loads over the MFMAs beats a burst behind the barrier
