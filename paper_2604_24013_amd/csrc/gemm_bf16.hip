@@ -345,7 +345,8 @@ static TileChoice tile_by_area(const GemmParams &p, int num_cu)
 // What a launch takes with tile t, in microseconds: per work item and k-tile, R rounds over the chip, and less where the last
 // round leaves compute units idle (the others' operands come faster), plus the megabytes of fp32 output and what goes
 // with them.  Fitted (relative error, rms 0.2) to 1300 single and rank steps of 4..1024 rows x 128..8192 x 128..8192 on
-// each tile, their buffers cold in the caches.
+// each tile, their buffers cold in the caches; for weight gradients, whose left operand is read by k-rows, to 90 of 32..8192
+// rows into 256..8192 x 256..8192 (rms 0.04 to 0.12).
 static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
 {
     const int steps = p.n_steps > 0 ? p.n_steps : 1;
@@ -353,6 +354,15 @@ static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
     const double kt = (p.K + 63) / 64, mb = (double)p.M * p.N * steps * 4e-6;
     const bool two = t.bm == 128 && !t.deep;
     const double share = items / num_cu / (two ? 2 : 1), rounds = ceil(share);
+    if (p.a_t) {
+        if (t.bm == 256 && t.bn == 256)
+            return 1.8 + rounds * (6.2 + 0.88 * kt) + 0.59 * kt * share + 0.083 * mb;
+        if (t.bm == 256)
+            return 2.5 + rounds * (3.9 + 0.46 * kt) + 0.455 * kt * share + 0.071 * mb;
+        if (two)
+            return 3.4 + rounds * (1.7 + 0.35 * kt) + 0.725 * kt * share + 0.095 * mb;
+        return 2.3 + rounds * (4.3 + 0.31 * kt) + 0.27 * kt * share;
+    }
     if (t.bm == 256 && t.bn == 256)
         return rounds * (9.5 + 0.73 * kt) + 1.07 * kt * share + 0.156 * mb;
     if (t.bm == 256)
@@ -364,12 +374,13 @@ static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
 
 // Tile of a launch: the one by area, but for another whose estimate is 7 % below its own -- of 261 drawn launches that change
 // or not, the change alone gains 3.7 % on average, 13 % where it is made; without the 7 % as much, and four times as many
-// come out slower (us: all-gather 4 x 777 x 2504 x 1832 on 128x128 80, on 256x256 57; reduce-scatter 63 and 54).  Then the overrides.
+// come out slower (us: all-gather 4 x 777 x 2504 x 1832 on 128x128 80, on 256x256 57; reduce-scatter 63 and 54; weight
+// gradient, 1928 rows into 1608 x 4712, 256x128 53.6, two 128x128 per compute unit 38.2).  Then the overrides.
 static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
 {
     TileChoice t = tile_by_area(p, num_cu);
     const Tuning tn = tuning();                      // overrides: tile shape, stages, k-splits per output tile
-    if (t.splitk == 1 && !p.a_t && tn.tile_bm == 0 && tn.deep < 0) {
+    if (t.splitk == 1 && tn.tile_bm == 0 && tn.deep < 0) {
         static const TileChoice cand[4] = {{256, 256, 1}, {256, 128, 1}, {128, 128, 1, true}, {128, 128, 1}};
         const double own = tile_estimate_us(p, t, num_cu);
         double best = 0.93 * own;
