@@ -29,8 +29,8 @@ PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 SETTLE_S = 0.06               # untimed load before every timed region (see time_calls)
 # HBM-side bytes per launch of the dominant kernel from rocprofv3 counters (FETCH_SIZE x 2.00 + WRITE_SIZE): a constant
 # taken from TRAFFIC_SOURCE, not measured in this run -- to be re-derived there whenever that kernel changes
-TRAFFIC_DOWN_RANK_STEP = 1226.4e6
-TRAFFIC_DOWN_RANK_STEP_CARRIED = 1461.4e6    # the same launch carrying its deliveries: 955.5 MB read + 505.9 MB written
+TRAFFIC_DOWN_RANK_STEP = 1209.2e6
+TRAFFIC_DOWN_RANK_STEP_CARRIED = 1444.1e6    # the same launch carrying its deliveries: 940.2 MB read + 503.9 MB written
 TRAFFIC_SOURCE = "profiles/gemm_bf16_dl_kernel_70b_pair_counters.md"
 
 
