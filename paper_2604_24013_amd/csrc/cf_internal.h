@@ -45,7 +45,6 @@ struct GemmParams {
     // above); A, recv, out and wait_flag are then ignored
     static constexpr int MAX_STEPS = 16;
     int n_steps = 0;
-    int num_cu = 256;
     bool k_rotate = false;   // persistent mode: XCD x starts its k loops x/8 of the way into the k range (set by the launcher)
     bool xcd_steps = false;  // persistent mode: XCD x runs steps x, x+8, ... whole (set by the launcher)
     int xcd_bands = 1;       // ... or, > 1: 8 / xcd_bands step groups x xcd_bands bands of tile columns (set by the launcher)
@@ -149,7 +148,7 @@ bool gemm_bf16_carries_delivery(const GemmParams &p, bool w_kn, bool out_bf16, i
 int gemm_bf16_steps_per_launch(const GemmParams &p, bool w_kn, int num_cu);
 // Direct-to-LDS variant of the bf16 kernel (operand extents below 2^31 bytes).
 bool gemm_bf16_dl_supported(const GemmParams &p, bool w_kn);
-hipError_t launch_gemm_bf16_dl(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t);
+hipError_t launch_gemm_bf16_dl(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t, int num_cu);
 bool gemm_bf16_dl_carries_operand(const GemmParams &p);
 // The kernel for few rows (gemm_rows.hip; bf16 and fp32 operands): does it run this launch -- one chunk GEMM, or with
 // n_steps > 0 all steps of a rank step, whose deliveries it then carries where land_step / land_more are set?

@@ -1090,7 +1090,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         gp.W = b->W;
         fill_shape(gp, r);
         gp.n_steps = g1 - g0;
-        gp.num_cu = num_cu_of_current_device();
         for (int jj = g0; jj < g1; ++jj) {
             const int j = jj - g0;                       // the step's place in this launch
             if (kind == CF_KIND_RS_PAIR) {
@@ -1146,7 +1145,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         }
         if (grouped && do_copy)                          // this group's deliveries have landed
             CF_HIP(hipStreamWaitEvent(cs, ev[1 + g0 / group], 0));
-        hipError_t e = cf::launch_gemm_bf16(gp, r.w_kn, r.bf16_out, cs, gp.num_cu);
+        hipError_t e = cf::launch_gemm_bf16(gp, r.w_kn, r.bf16_out, cs, num_cu_of_current_device());
         if (e != hipSuccess)
             return fail_hip(e, "persistent rank-step launch");
       }

@@ -470,7 +470,7 @@ hipError_t launch_gemm_bf16(const GemmParams &p, bool w_kn, bool out_bf16, hipSt
     const TileChoice t = tile_of_launch(p, num_cu);
     const bool staged = staged_kernel_forced();
     if (!staged && gemm_bf16_dl_supported(p, w_kn))
-        return launch_gemm_bf16_dl(p, w_kn, out_bf16, s, t);
+        return launch_gemm_bf16_dl(p, w_kn, out_bf16, s, t, num_cu);
     if (p.n_recv_more != 0 || p.a_t || p.n_steps > 0)
         return hipErrorInvalidValue;                 // callers ask gemm_bf16_takes_recv_list first
     if (t.bm == 256 && t.bn == 256) return launch_cfg<256, 256, 2, 4>(p, w_kn, out_bf16, s);

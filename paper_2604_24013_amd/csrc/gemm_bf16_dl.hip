@@ -1253,7 +1253,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD>
-hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s)
+hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, int num_cu)
 {
     bool any_recv = p.n_steps == 0 && p.recv != nullptr;     // (a persistent launch ignores recv)
     for (int j = 0; j < p.n_steps; ++j)
@@ -1263,10 +1263,10 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
     if (p.n_steps > 0) {                             // persistent: a grid that fills the chip once
         constexpr int per_cu = (NS * (BM + BN) * 64 * 2 <= 80 * 1024) ? 2 : 1;
         const int items = tiles_m * tiles_n * p.n_steps;
-        wgs = items < p.num_cu * per_cu ? items : p.num_cu * per_cu;
+        wgs = items < num_cu * per_cu ? items : num_cu * per_cu;
         if (p.xcd_steps)                             // whole octets of workgroups: the same number per XCD
-            wgs = (tiles_m * tiles_n * p.n_steps / 8 < p.num_cu * per_cu / 8 ? tiles_m * tiles_n * p.n_steps / 8
-                                                                            : p.num_cu * per_cu / 8) * 8;
+            wgs = (tiles_m * tiles_n * p.n_steps / 8 < num_cu * per_cu / 8 ? tiles_m * tiles_n * p.n_steps / 8
+                                                                            : num_cu * per_cu / 8) * 8;
         if (const int cap = tuning().persist_wgs; cap >= 8 && cap < wgs)   // override: leave compute units free
             wgs = p.xcd_steps ? cap / 8 * 8 : cap;
     }
@@ -1340,7 +1340,7 @@ bool gemm_bf16_dl_carries_operand(const GemmParams &p)
     return p.n_steps > 0 && !p.a_t && p.K % BK == 0;
 }
 
-hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t)
+hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t, int num_cu)
 {
     GemmParams p = p_in;
     const Tuning tn = tuning();
@@ -1384,7 +1384,7 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         bool cut = false;
         for (int nb = 1; nb <= 8; nb *= 2)
             cut = cut || (tiles_n_ % nb == 0 && p.n_steps % (8 / nb) == 0);
-        p.xcd_steps = cut && p.num_cu % 8 == 0 && p.n_recv_more == 0 && tn.xcd_steps != 0;
+        p.xcd_steps = cut && num_cu % 8 == 0 && p.n_recv_more == 0 && tn.xcd_steps != 0;
         // Step groups x column bands: per k-tile the 32 (or fewer) workgroups of an XCD that run side by side fetch
         // `a` left-operand bands of bm rows and `b` weight bands of bn columns, a = (step, tile row) pairs of the XCD
         // (at most its workgroups), b = the columns they spread over; the number of bands NB that makes a bm + b bn
@@ -1395,7 +1395,7 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
             const int tiles_m = (p.M + t.bm - 1) / t.bm, tiles_n = (p.N + t.bn - 1) / t.bn;
             const int per_cu = (t.bm == 128 && t.bn == 128 && !t.deep) ? 2 : 1;
             const int items_x = tiles_m * tiles_n * p.n_steps / 8;
-            const int wgs_x = items_x < p.num_cu * per_cu / 8 ? items_x : p.num_cu * per_cu / 8;
+            const int wgs_x = items_x < num_cu * per_cu / 8 ? items_x : num_cu * per_cu / 8;
             long best = -1;
             for (int nb = 1; nb <= 8; nb *= 2) {
                 if (tiles_n % nb != 0 || p.n_steps % (8 / nb) != 0)
@@ -1439,7 +1439,7 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // 25.4 / 25.1, 8 x 300 x 4096 x 2048 77.7 / 79.8.  Fewer work items than compute units: 4 x 333 x 2088 x 1096 23.9 / 25.5,
         // 8 x 100 x 2048 x 2048 26.6 / 27.4.
         const int64_t items = tiles * p.n_steps;
-        p.land_first = items >= p.num_cu && (int64_t)nk_all * tiles * t.bm * t.bn <= (int64_t)(t.bm == 256 && t.bn == 256 ? 48 : 24) * p.M * p.N;
+        p.land_first = items >= num_cu && (int64_t)nk_all * tiles * t.bm * t.bn <= (int64_t)(t.bm == 256 && t.bn == 256 ? 48 : 24) * p.M * p.N;
         p.mfma16 = whole_256;                        // (override: COMMFUSE_MFMA16 = 0 | 1)
     }
     // LDS stages: as many as fit (160 KiB per CU); the 128x128 tile comes with two (two workgroups share a CU) or four (one
@@ -1447,11 +1447,11 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
     // (all-gather 8 x 512 x 1536 x 4096 on 256x128 61 / 54 us, reduce-scatter 2 x 128 x 5120 x 5248 on 128x128 53 / 37) but for
     // two workgroups per CU over long k ranges, which cover for each other (8 x 299 x 4808 x 4104 160 / 168, 8 x 896 x 4224 x
     // 4480 271 / 272; 8 x 480 x 2112 x 1408 41 / 36).
-    if (t.bm == 256 && t.bn == 256) return launch_cfg<256, 256, 2, 4, 2, true>(p, w_kn, out_bf16, s);
-    if (t.bm == 256 && t.bn == 128) return launch_cfg<256, 128, 4, 2, 2, true>(p, w_kn, out_bf16, s);
-    if (t.deep) return launch_cfg<128, 128, 2, 2, 4, true>(p, w_kn, out_bf16, s);
-    if (nk_all <= 48) return launch_cfg<128, 128, 2, 2, 2, true>(p, w_kn, out_bf16, s);
-    return launch_cfg<128, 128, 2, 2, 2, false>(p, w_kn, out_bf16, s);
+    if (t.bm == 256 && t.bn == 256) return launch_cfg<256, 256, 2, 4, 2, true>(p, w_kn, out_bf16, s, num_cu);
+    if (t.bm == 256 && t.bn == 128) return launch_cfg<256, 128, 4, 2, 2, true>(p, w_kn, out_bf16, s, num_cu);
+    if (t.deep) return launch_cfg<128, 128, 2, 2, 4, true>(p, w_kn, out_bf16, s, num_cu);
+    if (nk_all <= 48) return launch_cfg<128, 128, 2, 2, 2, true>(p, w_kn, out_bf16, s, num_cu);
+    return launch_cfg<128, 128, 2, 2, 2, false>(p, w_kn, out_bf16, s, num_cu);
 }
 
 }  // namespace cf
