@@ -902,8 +902,10 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
             wide = wide && aligned16(b->peer_stage[i]) && aligned16(b->recv_each[i]);
     if (few_rows && (flags & CF_FUSED_COPY) && wide && cf::tuning().carry != 0)
         carried = true;
-    if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && do_copy && do_compute &&
-        slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0) {
+    // (the attention layer's partial sums with padding between their rows are copied in front, whatever the tile: their padding
+    // lands with them)
+    if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && (attn == nullptr || r.ldo == r.n) &&
+        do_copy && do_compute && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0) {
         cf::GemmParams probe;
         probe.W = b->W;
         fill_shape(probe, r);

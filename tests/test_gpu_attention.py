@@ -405,3 +405,29 @@ def test_attention_keys_over_waves_with_a_tile_of_minus_infinity(tile):
         ref[:, a * 128:(a + 1) * 128] = P @ host[2][0, a][keep] / P.sum(axis=1, keepdims=True)
     assert not np.isnan(got).any()
     assert H.rel_err(got, ref) <= TOL_ATTN
+
+
+@pytest.mark.parametrize("heads", [10, 8])
+def test_padded_partial_sums_land_with_their_padding(heads):
+    """Rows of 8192 with 64 columns of padding, 256x256 tiles, k ranges of twenty and sixteen k-tiles: what lands in recv_each is
+    what the neighbour's buffer holds, padding included, and the sums are those without CF_FUSED_COPY, bit for bit."""
+    p, S, n, ldo = 8, 2048, 8192, 8192 + 64
+    mc = S // p
+    g = torch.Generator(device=H.DEV).manual_seed(heads)
+    rnd = lambda *s: torch.empty(s, device=H.DEV).normal_(generator=g)
+    nan = lambda: torch.full((mc, ldo), float("nan"), device=H.DEV)
+    Q, K, V = (rnd(1, heads, S, 128).bfloat16() for _ in range(3))
+    W, stage = rnd(heads * 128, n).mul_(0.05).bfloat16(), [rnd(mc, ldo) for _ in range(p - 1)]
+    desc = cf.attn_desc(p, 1, 1, heads, S, 128, n, 128 ** -0.5, ldo=ldo)
+    outs = []
+    for flags in (cf.CF_FUSED_COPY, 0):
+        O, each, sends = nan(), [nan() for _ in stage], [nan() for _ in stage]
+        attn_all = torch.empty((S, heads * 128), dtype=torch.bfloat16, device=H.DEV)
+        bufs = cf.make_attn_buffers(Q, K, V, W, attn_all, O, stage, (None, None), (None, None), None, each, sends)
+        st = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        cf.run_attn_schedule(desc, bufs, st, st, cf.CF_PERSISTENT | cf.CF_SERIAL | flags)
+        st.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(each, stage))
+        outs.append([t[:, :n] for t in sends + [O]])
+    assert all(torch.equal(a, b) for a, b in zip(*outs))

@@ -30,3 +30,20 @@ def test_grids_follow_the_devices_compute_units(dry, monkeypatch, cus):
     for call in calls:
         (kernel, grid, block), = dry.calls(call)
         assert kernel.startswith("gemm_bf16_dl_kernel<256, 256,") and (grid, block) == (cus, 512)
+
+
+def _tables(p):
+    return [[P(10 * t + i) for i in range(p - 1)] for t in (1, 3, 5)]
+
+
+@pytest.mark.parametrize("seq,heads,n", [(8192, 10, 8192), (8192, 8, 8192), (512, 2, 264)])
+@pytest.mark.parametrize("pad", [0, 64])
+def test_attention_layers_padded_partial_sums_are_copied_in_front(dry, seq, heads, n, pad):
+    """A copy lands the padding between the rows of a partial sum, the projection's epilogue does not."""
+    p = 8
+    stage, each, sends = _tables(p)
+    bufs = cf.make_attn_buffers(P(0), P(1), P(2), P(3), P(4), P(5), stage, (None, None), (None, None), None, each, sends)
+    desc = cf.attn_desc(p, 1, 1, heads, seq, 128, n, 0.1, ldo=n + pad)
+    kernels = [c[0] for c in dry.calls(lambda: cf.run_attn_schedule(desc, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))]
+    few_rows = kernels[-1].startswith("gemm_rows_kernel")             # (carried without the padding)
+    assert ["copy" in k for k in kernels] == ([True, False, False] if pad and not few_rows else [False, False])
