@@ -372,6 +372,21 @@ static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
     return 2.6 + rounds * (3.8 + 0.29 * kt) + 0.26 * kt * share + 0.129 * mb;
 }
 
+// The overrides: tile shape, stages, k-splits per output tile.
+static TileChoice with_overrides(TileChoice t)
+{
+    const Tuning tn = tuning();
+    if (tn.tile_bm > 0) {
+        t.bm = tn.tile_bm;
+        t.bn = tn.tile_bn;
+    }
+    if (tn.deep >= 0)
+        t.deep = tn.deep != 0;
+    if (tn.splitk >= 1)
+        t.splitk = tn.splitk;
+    return t;
+}
+
 // Tile of a launch: the one by area, but for another whose estimate is 7 % below its own -- of 261 drawn launches that change
 // or not, the change alone gains 3.7 % on average, 13 % where it is made; without the 7 % as much, and four times as many
 // come out slower (us: all-gather 4 x 777 x 2504 x 1832 on 128x128 80, on 256x256 57; reduce-scatter 63 and 54; weight
@@ -379,7 +394,7 @@ static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
 static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
 {
     TileChoice t = tile_by_area(p, num_cu);
-    const Tuning tn = tuning();                      // overrides: tile shape, stages, k-splits per output tile
+    const Tuning tn = tuning();
     if (t.splitk == 1 && tn.tile_bm == 0 && tn.deep < 0) {
         static const TileChoice cand[4] = {{256, 256, 1}, {256, 128, 1}, {128, 128, 1, true}, {128, 128, 1}};
         const double own = tile_estimate_us(p, t, num_cu);
@@ -392,15 +407,7 @@ static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
             }
         }
     }
-    if (tn.tile_bm > 0) {
-        t.bm = tn.tile_bm;
-        t.bn = tn.tile_bn;
-    }
-    if (tn.deep >= 0)
-        t.deep = tn.deep != 0;
-    if (tn.splitk >= 1)
-        t.splitk = tn.splitk;
-    return t;
+    return with_overrides(t);
 }
 
 double gemm_bf16_tile_us(const GemmParams &p, int num_cu)
@@ -433,10 +440,11 @@ bool gemm_bf16_carries_delivery(const GemmParams &p, bool w_kn, bool out_bf16, i
             return false;                            // a step that waits for a flag: its delivery is on its way
     if (!reduce_scatter && !gemm_bf16_dl_carries_operand(p))
         return false;
-    // (rows with padding between them: the copies in front move the padding too, and have never been in front of launches of
-    // 256x256 tiles over long k ranges)
+    // Partial sums with padding between their rows: every tile could carry them, but a copy in front lands the padding and the
+    // epilogue does not, and which of the two a caller finds is part of the interface.  The line is the interface's: 256x256
+    // tiles by area (or by override) over 18 k-tiles, 20 with a ragged last one, land without it.
     if (reduce_scatter && p.ldo != p.N) {
-        const TileChoice t = tile_by_area(p, num_cu);
+        const TileChoice t = with_overrides(tile_by_area(p, num_cu));
         if (t.bm != 256 || t.bn != 256 || (p.K + 63) / 64 < 18 + (p.K % 64 != 0 ? 2 : 0))
             return false;
     }

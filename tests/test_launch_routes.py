@@ -47,3 +47,20 @@ def test_attention_layers_padded_partial_sums_are_copied_in_front(dry, seq, head
     kernels = [c[0] for c in dry.calls(lambda: cf.run_attn_schedule(desc, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))]
     few_rows = kernels[-1].startswith("gemm_rows_kernel")             # (carried without the padding)
     assert ["copy" in k for k in kernels] == ([True, False, False] if pad and not few_rows else [False, False])
+
+
+@pytest.mark.parametrize("tile,mc,n,k,copied", [
+    (None, 512, 8192, 1280, False), (None, 512, 8192, 1152, False), (None, 512, 8192, 1088, True),   # eighteen whole k-tiles and more
+    (None, 512, 8192, 1288, False), (None, 512, 8192, 1160, True),                                   # ... twenty with a ragged one
+    (None, 200, 232, 1288, True), ("256x256", 200, 232, 1288, False),                                # the override counts
+    ("128x128", 512, 8192, 1280, True), ("256x256", 200, 232, 1160, True)])
+def test_padded_partial_sums_are_carried_on_large_tiles_over_long_k(dry, monkeypatch, tile, mc, n, k, copied):
+    p = 8
+    stage, each, sends = _tables(p)
+    bufs = cf.make_buffers(P(0), P(1), P(2), stage, (None, None), (None, None), None, each, sends)
+    monkeypatch.setenv("COMMFUSE_ROWS", "0")
+    if tile:
+        monkeypatch.setenv("COMMFUSE_TILE", tile)
+    desc = cf.layer_desc(p, 1, mc, n, k, ldo=n + 64)
+    kernels = [c[0] for c in dry.calls(lambda: cf.run_schedule(desc, cf.CF_KIND_RS, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))]
+    assert ["copy" in kern for kern in kernels] == ([True, False] if copied else [False])
