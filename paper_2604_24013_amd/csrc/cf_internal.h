@@ -41,8 +41,8 @@ struct GemmParams {
     unsigned spin_limit = 0;
     bool wait_at_start = false;   // true: before the first operand load; false: before the B_in loads
     // persistent mode (direct-to-LDS bf16 kernel only): n_steps > 0 makes one launch run that many chunk GEMMs
-    // of the same shape, step s with its own left operand, B_in, output and delivery flag (each nullable as
-    // above); A, recv, out and wait_flag are then ignored
+    // of the same shape, step s with its own left operand, B_in (nullable as above) and output; A, recv and out are then
+    // ignored, and a wait_flag is refused
     static constexpr int MAX_STEPS = 16;
     int n_steps = 0;
     bool k_rotate = false;   // persistent mode: XCD x starts its k loops x/8 of the way into the k range (set by the launcher)
@@ -54,7 +54,6 @@ struct GemmParams {
     const void *A_step[MAX_STEPS] = {};
     const float *recv_step[MAX_STEPS] = {};
     void *out_step[MAX_STEPS] = {};
-    const unsigned *flag_step[MAX_STEPS] = {};
     // the delivery carried by the consumer (persistent launch).  Reduce-scatter: recv_step[s] points at what the
     // neighbour sends (its buffer, not this rank's landing buffer), and the epilogue that adds B_in also stores it to
     // land_step[s], the landing buffer.  All-gather: A_step[s] points at the

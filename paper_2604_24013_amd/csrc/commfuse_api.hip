@@ -1102,7 +1102,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                                (size_t)pair_slice(p, r.rank, j) * r.mc * r.lda * in_elem(r);
                 gp.recv_step[j] = last && p > 1 ? static_cast<const float *>(b->recv_each[0]) : nullptr;
                 gp.out_step[j] = last ? b->O : static_cast<void *>(b->send_each[j]);
-                gp.flag_step[j] = nullptr;
                 if (last && pair_front)
                     gp.recv_step[j] = static_cast<const float *>(b->O);
                 gp.k_in_order = pair_front || pair_beside;
@@ -1143,7 +1142,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                 gp.recv_step[j] = nullptr;
                 gp.out_step[j] = static_cast<char *>(b->O) + (size_t)c * r.mc * r.ldo * (r.bf16_out ? 2 : 4);
             }
-            gp.flag_step[j] = nullptr;               // everything was delivered before the launch
         }
         if (grouped && do_copy)                          // this group's deliveries have landed
             CF_HIP(hipStreamWaitEvent(cs, ev[1 + g0 / group], 0));

@@ -435,9 +435,6 @@ bool gemm_bf16_carries_delivery(const GemmParams &p, bool w_kn, bool out_bf16, i
 {
     if (p.M <= 0 || p.N <= 0 || p.n_steps <= 0 || staged_kernel_forced() || !gemm_bf16_dl_supported(p, w_kn))
         return false;
-    for (int j = 0; j < p.n_steps; ++j)
-        if (p.flag_step[j] != nullptr)
-            return false;                            // a step that waits for a flag: its delivery is on its way
     if (!reduce_scatter && !gemm_bf16_dl_carries_operand(p))
         return false;
     // Partial sums with padding between their rows: every tile could carry them, but a copy in front lands the padding and the

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // (step, output tile) are dealt out round robin, step-major, to the workgroups of a grid that fills the
     // chip once; a workgroup goes on to its next item as soon as it is done with the last one, so tiles of
     // different steps run side by side (the chunk GEMMs of Alg. 1 / Alg. 2 do not depend on each other; only
-    // the add of B_in / the arrival of the slice does, which the per-step delivery flag guards) and nothing
+    // the add of B_in / the arrival of the slice does, and both are there before the launch) and nothing
     // is launched, drained or refilled between steps.  Every workgroup's loop is finite: the kernel exits.
     const int tiles_per_step = tiles_m * tiles_n * P.splits;
     // XCD-per-step mapping (GemmParams::xcd_steps): XCD x (workgroups x, x+8, ...) runs the steps x, x+8, ...
@@ -1342,6 +1342,8 @@ bool gemm_bf16_dl_carries_operand(const GemmParams &p)
 
 hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t, int num_cu)
 {
+    if (p_in.n_steps > 0 && p_in.wait_flag != nullptr)
+        return hipErrorInvalidValue;                  // the work-item loop waits for nothing
     GemmParams p = p_in;
     const Tuning tn = tuning();
     p.splits = t.splitk < 1 ? 1 : t.splitk;

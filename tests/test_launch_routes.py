@@ -1,5 +1,6 @@
 """What a call enqueues -- which kernels, in which grid, and which copies -- read off the library's host code without a GPU."""
 import os
+import re
 
 import pytest
 
@@ -64,3 +65,14 @@ def test_padded_partial_sums_are_carried_on_large_tiles_over_long_k(dry, monkeyp
     desc = cf.layer_desc(p, 1, mc, n, k, ldo=n + 64)
     kernels = [c[0] for c in dry.calls(lambda: cf.run_schedule(desc, cf.CF_KIND_RS, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))]
     assert ["copy" in kern for kern in kernels] == ([True, False] if copied else [False])
+
+
+def test_kernels_read_every_pointer_of_the_launch_argument():
+    """A buffer or flag that a caller may set and no kernel looks at would be ignored in silence."""
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_24013_amd", "csrc")
+    read = lambda name: re.sub(r"//[^\n]*", "", open(os.path.join(csrc, name)).read())
+    struct = re.search(r"struct GemmParams \{(.*?)\n\};", read("cf_internal.h"), re.S)[1]
+    pointers = re.findall(r"\*(?:const )?(\w+)(?:\[\w+\])? = ", struct)
+    assert {"A", "W", "recv", "out", "wait_flag"} <= set(pointers)
+    kernels = read("gemm_bf16_dl.hip") + read("gemm_rows.hip") + read("gemm_f32.hip")
+    assert [p for p in pointers if not re.search(rf"\b[Pg]\.{p}\b", kernels)] == []
