@@ -206,7 +206,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // different steps run side by side (the chunk GEMMs of Alg. 1 / Alg. 2 do not depend on each other; only
     // the add of B_in / the arrival of the slice does, and both are there before the launch) and nothing
     // is launched, drained or refilled between steps.  Every workgroup's loop is finite: the kernel exits.
-    const int tiles_per_step = tiles_m * tiles_n * P.splits;
+    // (The k range of a persistent launch is never split, and the kernel has no code for it: a path on which the splits that
+    // finish first leave with requests of B_in outstanding made the compiler drain the request queue on every trip of six
+    // main loops.  us with / without that path: reduce-scatter step 1408 x 6400 x 8128 236 / 193, rank steps 8 x 700 x 8192 x
+    // 3584 307 / 295, 8 x 960 x 4096 x 2048 140 / 133.)
+    const int tiles_per_step = tiles_m * tiles_n * (PERSIST ? 1 : P.splits);
     // XCD-per-step mapping (GemmParams::xcd_steps): XCD x (workgroups x, x+8, ...) runs the steps x, x+8, ...
     // whole, so a step's own operand (A of the step) passes through one L2 only, instead of through all
     // eight when every XCD holds a band of every step's tiles.  With GemmParams::xcd_bands = NB > 1 the XCDs form
@@ -240,7 +244,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     const int n_more = (!PERSIST || step_i == P.n_steps - 1) ? P.n_recv_more : 0;
 
     // Work item = (output tile, k-split); the splits of a tile are neighbours in the remapped order.
-    const int splits = P.splits;
+    const int splits = PERSIST ? 1 : P.splits;
     const int work = by_xcd ? (xcd_band * (tiles_n / xcd_nb) + item / rows_x) * tiles_m + (item % rows_x) % tiles_m
                             : xcd_remap(PERSIST ? item % tiles_per_step : (int)blockIdx.x, tiles_per_step);
     const int tile = work / splits, split = work % splits;
