@@ -1427,16 +1427,31 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // (nor where the pairwise schedule carries its deliveries: the sums are bit for bit those of its copied mode, whose last
         // step sums several partials and so keeps the k order)
         p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0 && !p.k_in_order;
-        // fp32 lines past the caches: what a launch writes it never reads again, and B_in is read once.  Only where rows begin
+        // fp32 lines past the caches: what a launch writes it never reads again, and B_in is read once.  Where rows begin
         // and end on 128-byte lines -- the caches put the halves of a shared line together.  us per carried rank step,
         // cached against not: 8 x 1024 x 8192 x 1024 232 / 216, 8 x 512 x 4096 x 1376 72.2 / 69.6, 8 x 128 x 4096 x 512 (46 MB)
         // 19.7 / 20.3, 8 x 100 x 2048 x 2048 (18 MB) 27.3 / 26.6, all-gather 8 x 1024 x 3584 x 8192 380 / 374; rows off the
         // lines: 2 x 1000 x 3000 x 520 25.1 / 32.3, 4 x 333 x 2088 x 1096 23.9 / 26.3.
+        // Not, without a B_in, where rows lie a multiple of 16 KiB apart -- the lines of a tile then fall on few memory channels,
+        // which the caches' write-backs spread over time --, unless the L2 caches hold the output anyway (32 MiB; what is left in
+        // them is written back at the end of the launch) or the launch moves more than the last-level cache holds for
+        // whoever reads the output next (256 MiB, and an eighth).  us cached / past the caches, buffers that come round / fresh
+        // ones: all-gather steps 4096 x 8192 x 1024 71 / 88 and 76 / 89, with a reader behind 99 / 119 and 107 / 128; 2048 x 8192 x
+        // 1024 38 / 41 and 38 / 42; all-gather 8 x 512 x 8192 x 512 49 / 57 and 57 / 57; 512 rows into 4096 x 4096 25.5 / 27.7.
+        // Other rows: 4096 x 7936 x 1024 70 / 71 and 74 / 74, 4096 x 6144 x 1024 60 / 57 and 66 / 57.  1024 x 4096 x 1024 15.6 / 14.2
+        // and 17.3 / 15.2.  All-gather 8 x 1024 x 8192 x 1024 (302 MB) 138 / 139 and 145 / 142, with a reader 212 / 220; 8 x 1024 x
+        // 8192 x 3584 (386 MB) 367 / 361 and 367 / 362, with a reader 429 / 429.
+        bool any_recv = false;
         uintptr_t low = (uintptr_t)(p.ldo * 4) | (uintptr_t)p.N * 4;
-        for (int j = 0; j < p.n_steps; ++j)
+        for (int j = 0; j < p.n_steps; ++j) {
             low |= reinterpret_cast<uintptr_t>(p.out_step[j]) | reinterpret_cast<uintptr_t>(p.recv_step[j]) |
                    (p.recv_step[j] != nullptr ? reinterpret_cast<uintptr_t>(p.land_step[j]) : 0);
-        p.non_temporal = !out_bf16 && low % 128 == 0;
+            any_recv = any_recv || p.recv_step[j] != nullptr;
+        }
+        const int64_t out_bytes = (int64_t)p.M * p.N * 4 * p.n_steps;
+        const int64_t moved = out_bytes + ((int64_t)p.M * p.n_steps + p.N) * p.K * 2;
+        p.non_temporal = !out_bf16 && low % 128 == 0 &&
+                         (any_recv || p.ldo * 4 % (16 << 10) != 0 || out_bytes <= (int64_t)32 << 20 || moved > (int64_t)288 << 20);
         // Half the workgroups land their deliveries in front of the main loop where the work items fill the chip and their
         // multiplications do not far outlast the memory's part, which scales with what of the tiles lies inside the
         // matrix.  us per carried rank step, all in the epilogue / half in front: 8 x 1024 x 8192 at k = 512 180 / 170, 1024

@@ -76,3 +76,16 @@ def test_kernels_read_every_pointer_of_the_launch_argument():
     assert {"A", "W", "recv", "out", "wait_flag"} <= set(pointers)
     kernels = read("gemm_bf16_dl.hip") + read("gemm_rows.hip") + read("gemm_f32.hip")
     assert [p for p in pointers if not re.search(rf"\b[Pg]\.{p}\b", kernels)] == []
+
+
+@pytest.mark.parametrize("mc,n,k,past_the_caches", [
+    (4096, 8192, 1024, False), (4096, 8192, 3584, False), (2048, 4096, 1024, True), (2304, 4096, 1024, False),   # 32 MiB of output, and more
+    (4096, 7936, 1024, True), (4096, 6144, 1024, True), (4096, 8200, 1024, False),    # rows 31, 24 KiB apart; rows off the lines
+    (8192, 8192, 1024, False), (8192, 8192, 3584, True)])                             # 288 MiB and more moved
+def test_outputs_stay_in_the_caches_where_rows_lie_16_kib_apart(dry, mc, n, k, past_the_caches):
+    shape = lambda p: cf.layer_desc(p, 0, mc, n, k)
+    ag, = dry.calls(lambda: cf.ag_step(shape(1), 0, P(0), P(1), P(2)))
+    rs, = dry.calls(lambda: cf.rs_step(shape(2), 1, P(0), P(1), P(2), P(3)))
+    nt = lambda call: call[0].split(", ")[-1] == "true>"
+    assert nt(ag) == past_the_caches
+    assert nt(rs) == (n % 32 == 0)                    # with a B_in: wherever rows begin and end on the lines
