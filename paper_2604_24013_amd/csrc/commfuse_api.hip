@@ -886,15 +886,18 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // buffer by one of the workgroups that load it (k a multiple of the k-tile).  Otherwise the deliveries are
     // enqueued in front as without the flag.
     bool carried = false;
+    // the launch as the rules ask about it: its shape, and which steps will add a B_in
+    cf::GemmParams probe;
+    probe.W = b->W;
+    fill_shape(probe, r);
+    probe.n_steps = S;
+    for (int j = 0; j < S && j < cf::GemmParams::MAX_STEPS; ++j)
+        if (kind == CF_KIND_RS ? receives(j) : kind == CF_KIND_RS_PAIR && j == S - 1 && p > 1)
+            probe.recv_step[j] = static_cast<const float *>(b->O);
     // few rows in all: the kernel that packs the rows of every step into one launch, and carries every delivery
     bool few_rows = false;
-    if (do_copy && do_compute && !is_dp_kind(kind) && !is_wgrad_kind(kind) && slot_bytes > 0) {
-        cf::GemmParams probe;
-        probe.W = b->W;
-        fill_shape(probe, r);
-        probe.n_steps = S;
+    if (do_copy && do_compute && !is_dp_kind(kind) && !is_wgrad_kind(kind) && slot_bytes > 0)
         few_rows = cf::gemm_rows_takes(probe, r.bf16_in, r.w_kn, num_cu_of_current_device());
-    }
     // (its loads and stores are 16 bytes wide: peers' and landing buffers off that grid are copied in front, like any bytes)
     bool wide = true;
     if (do_copy && b->recv_each != nullptr)
@@ -906,10 +909,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // lands with them)
     if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && (attn == nullptr || r.ldo == r.n) &&
         do_copy && do_compute && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0) {
-        cf::GemmParams probe;
-        probe.W = b->W;
-        fill_shape(probe, r);
-        probe.n_steps = S;
         carried = cf::gemm_bf16_carries_delivery(probe, r.w_kn, r.bf16_out, num_cu_of_current_device(), kind == CF_KIND_RS);
     }
     // The gradient bucket with CF_FUSED_COPY: the add kernels read the arrivals from the neighbours' buffers and
@@ -943,10 +942,6 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                              p > 1 && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0;
     const bool grouped = two_streams && !carried;
     if (grouped && !few_rows) {
-        cf::GemmParams probe;
-        probe.W = b->W;
-        fill_shape(probe, r);
-        probe.n_steps = S;
         group = cf::gemm_bf16_steps_per_launch(probe, r.w_kn, num_cu_of_current_device());
     }
     const int n_groups = (S + group - 1) / group;

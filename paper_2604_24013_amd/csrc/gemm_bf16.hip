@@ -342,11 +342,22 @@ static TileChoice tile_by_area(const GemmParams &p, int num_cu)
     return t;
 }
 
+// Share of a launch's (sub-)steps that add a B_in.
+static double share_with_recv(const GemmParams &p)
+{
+    if (p.n_steps <= 0)
+        return p.recv != nullptr ? 1.0 : 0.0;
+    int n = 0;
+    for (int j = 0; j < p.n_steps; ++j)
+        n += p.recv_step[j] != nullptr;
+    return (double)n / p.n_steps;
+}
+
 // What a launch takes with tile t, in microseconds: per work item and k-tile, R rounds over the chip, and less where the last
-// round leaves compute units idle (the others' operands come faster), plus the megabytes of fp32 output and what goes
-// with them.  Fitted (relative error, rms 0.2) to 1300 single and rank steps of 4..1024 rows x 128..8192 x 128..8192 on
-// each tile, their buffers cold in the caches; for weight gradients, whose left operand is read by k-rows, to 90 of 32..8192
-// rows into 256..8192 x 256..8192 (rms 0.04 to 0.12).
+// round leaves compute units idle (the others' operands come faster), plus the megabytes of fp32 output, of the left operand
+// and what goes with a B_in.  Fitted (relative error, rms 0.07 to 0.13) to 3200 steps and carried rank steps of 16..8192 rows x
+// 128..8192 x 128..8192 on each tile, on buffers that come round and on ones cold in the caches; for weight gradients, whose left
+// operand is read by k-rows, to 90 of 32..8192 rows into 256..8192 x 256..8192 (rms 0.04 to 0.12).
 static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
 {
     const int steps = p.n_steps > 0 ? p.n_steps : 1;
@@ -363,13 +374,15 @@ static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
             return 3.4 + rounds * (1.7 + 0.35 * kt) + 0.725 * kt * share + 0.095 * mb;
         return 2.3 + rounds * (4.3 + 0.31 * kt) + 0.27 * kt * share;
     }
+    const double ma = (double)p.M * p.K * steps * 2e-6, r = share_with_recv(p);
     if (t.bm == 256 && t.bn == 256)
-        return rounds * (9.5 + 0.73 * kt) + 1.07 * kt * share + 0.156 * mb;
+        return 0.6 + rounds * (6.4 + 0.98 * kt + 3.8 * r) + 0.24 * kt * share + (0.11 + 0.3 * r) * mb + 0.14 * ma;
     if (t.bm == 256)
-        return 3.1 + rounds * (3.9 + 0.41 * kt) + 0.50 * kt * share + 0.159 * mb;
+        return 1.5 + rounds * (3.8 + 0.56 * kt + 1.8 * r) + 0.17 * kt * share + (0.098 + 0.17 * r) * mb + 0.22 * ma;
     if (two)
-        return 2.5 + 1.6 * ceil(items / num_cu) + rounds * (1.2 + 0.38 * kt) + 0.75 * kt * share + 0.09 * mb;
-    return 2.6 + rounds * (3.8 + 0.29 * kt) + 0.26 * kt * share + 0.129 * mb;
+        return 2.1 + ceil(items / num_cu) * (2.1 + 0.12 * kt) + rounds * (0.4 * kt + 0.87 * r) + 0.34 * kt * share +
+               (0.022 + 0.23 * r) * mb + 0.07 * ma;
+    return 2.0 + rounds * (3.6 + 0.36 * kt + 1.2 * r) + 0.14 * kt * share + (0.038 + 0.13 * r) * mb + 0.1 * ma;
 }
 
 // The overrides: tile shape, stages, k-splits per output tile.
@@ -387,18 +400,20 @@ static TileChoice with_overrides(TileChoice t)
     return t;
 }
 
-// Tile of a launch: the one by area, but for another whose estimate is 7 % below its own -- of 261 drawn launches that change
-// or not, the change alone gains 3.7 % on average, 13 % where it is made; without the 7 % as much, and four times as many
-// come out slower (us: all-gather 4 x 777 x 2504 x 1832 on 128x128 80, on 256x256 57; reduce-scatter 63 and 54; weight
-// gradient, 1928 rows into 1608 x 4712, 256x128 53.6, two 128x128 per compute unit 38.2).  Then the overrides.
-static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
+// Tile of a launch before the overrides: the one whose estimate is lowest, unless the one by area splits the k range.  256x256 by
+// area changes for an estimate 5 % lower only, for one 10 % lower where the tiles are whole (the 16x16x32 main loop): there it is
+// loosest.  us on 256x256 / 256x128, all-gather step 8192 x 3072 x 1024 59 / 75, reduce-scatter steps 2048 x 8192 x 1024 53 / 59,
+// 8192 x 8192 x 1024 234 / 273, 4096 x 6144 x 1024 83 / 73, 2560 x 8192 x 4096 197 / 178.  Of 3200 launches drawn from the sizes
+// above the tile so chosen is 0.6 % behind the fastest on average and 10 % and more behind in 20; by area alone 4.4 % and 540, by
+// an estimate that knew neither B_in nor left operand, fitted to 1024 rows at most, 1.5 % and 85.  Weight gradients change for an
+// estimate 7 % lower: 1928 rows into 1608 x 4712, 256x128 53.6, two 128x128 per compute unit 38.2.
+static TileChoice tile_by_estimate(const GemmParams &p, int num_cu)
 {
     TileChoice t = tile_by_area(p, num_cu);
-    const Tuning tn = tuning();
-    if (t.splitk == 1 && tn.tile_bm == 0 && tn.deep < 0) {
+    if (t.splitk == 1) {
         static const TileChoice cand[4] = {{256, 256, 1}, {256, 128, 1}, {128, 128, 1, true}, {128, 128, 1}};
-        const double own = tile_estimate_us(p, t, num_cu);
-        double best = 0.93 * own;
+        const bool large = t.bm == 256 && t.bn == 256, whole = p.M % 256 == 0 && p.N % 256 == 0;
+        double best = (p.a_t ? 0.93 : large ? (whole ? 0.9 : 0.95) : 1.0) * tile_estimate_us(p, t, num_cu);
         for (const TileChoice &c : cand) {
             const double us = tile_estimate_us(p, c, num_cu);
             if (us < best) {
@@ -407,7 +422,13 @@ static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
             }
         }
     }
-    return with_overrides(t);
+    return t;
+}
+
+static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
+{
+    const Tuning tn = tuning();
+    return with_overrides(tn.tile_bm == 0 && tn.deep < 0 ? tile_by_estimate(p, num_cu) : tile_by_area(p, num_cu));
 }
 
 double gemm_bf16_tile_us(const GemmParams &p, int num_cu)

@@ -89,3 +89,19 @@ def test_outputs_stay_in_the_caches_where_rows_lie_16_kib_apart(dry, mc, n, k, p
     nt = lambda call: call[0].split(", ")[-1] == "true>"
     assert nt(ag) == past_the_caches
     assert nt(rs) == (n % 32 == 0)                    # with a B_in: wherever rows begin and end on the lines
+
+
+@pytest.mark.parametrize("add,mc,n,k,tile", [
+    (False, 8192, 3072, 1024, "256, 256"),            # 59 us; on 256x128 75
+    (False, 4864, 7296, 3136, "256, 256"),            # 224; 233
+    (True, 2048, 8192, 1024, "256, 256"),             # whole rounds of whole tiles: 53; 59
+    (False, 4992, 7168, 384, "128, 128"),             # few k-tiles: 42; on 256x256 53
+    (True, 3712, 6144, 1280, "256, 128"),             # with a B_in, added behind the main loop: 78; on 256x256 90
+    (True, 3200, 4992, 8000, "256, 128"),             # 228; 325 (260 tiles of 256x256 on 256 compute units)
+])
+def test_tile_of_large_steps(dry, add, mc, n, k, tile):
+    if add:
+        calls = dry.calls(lambda: cf.rs_step(cf.layer_desc(2, 0, mc, n, k, w_layout=cf.CF_W_NK), 1, P(0), P(1), P(2), P(3)))
+    else:
+        calls = dry.calls(lambda: cf.ag_step(cf.layer_desc(1, 0, mc, n, k, w_layout=cf.CF_W_NK), 0, P(0), P(1), P(2)))
+    assert [c[0].startswith(f"gemm_bf16_dl_kernel<{tile},") for c in calls] == [True]
