@@ -152,7 +152,11 @@ bool gemm_bf16_dl_carries_operand(const GemmParams &p);
 // The kernel for few rows (gemm_rows.hip; bf16 and fp32 operands): does it run this launch -- one chunk GEMM, or with
 // n_steps > 0 all steps of a rank step, whose deliveries it then carries where land_step / land_more are set?
 bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu);
-// What the tile kernels take for this launch, roughly, in microseconds (for the rule between them and the one above).
+// Share of a launch's (sub-)steps that add a B_in: none of an all-gather's, the last of a pairwise reduce-scatter's.
+double gemm_share_with_recv(const GemmParams &p);
+// What the tile kernels take for this launch, roughly, in microseconds (for the rule between them and the one above):
+// the steps of a rank step in one launch, and single steps.
+double gemm_bf16_rank_step_us(const GemmParams &p, int num_cu);
 double gemm_bf16_tile_us(const GemmParams &p, int num_cu);
 double gemm_f32_tile_us(const GemmParams &p, int num_cu);
 // Bytes of partial tiles that kernel parks when it splits the k range of this single step (0: it does not).

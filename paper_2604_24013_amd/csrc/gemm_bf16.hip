@@ -342,8 +342,7 @@ static TileChoice tile_by_area(const GemmParams &p, int num_cu)
     return t;
 }
 
-// Share of a launch's (sub-)steps that add a B_in.
-static double share_with_recv(const GemmParams &p)
+double gemm_share_with_recv(const GemmParams &p)
 {
     if (p.n_steps <= 0)
         return p.recv != nullptr ? 1.0 : 0.0;
@@ -374,7 +373,7 @@ static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
             return 3.4 + rounds * (1.7 + 0.35 * kt) + 0.725 * kt * share + 0.095 * mb;
         return 2.3 + rounds * (4.3 + 0.31 * kt) + 0.27 * kt * share;
     }
-    const double ma = (double)p.M * p.K * steps * 2e-6, r = share_with_recv(p);
+    const double ma = (double)p.M * p.K * steps * 2e-6, r = gemm_share_with_recv(p);
     if (t.bm == 256 && t.bn == 256)
         return 0.6 + rounds * (6.4 + 0.98 * kt + 3.8 * r) + 0.24 * kt * share + (0.11 + 0.3 * r) * mb + 0.14 * ma;
     if (t.bm == 256)
@@ -429,6 +428,13 @@ static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
 {
     const Tuning tn = tuning();
     return with_overrides(tn.tile_bm == 0 && tn.deep < 0 ? tile_by_estimate(p, num_cu) : tile_by_area(p, num_cu));
+}
+
+double gemm_bf16_rank_step_us(const GemmParams &p, int num_cu)
+{
+    const double us = tile_estimate_us(p, tile_by_estimate(p, num_cu), num_cu);
+    // an all-gather of ragged k-tiles has its deliveries copied in front: 6 us, and 0.8 us per megabyte of them
+    return gemm_share_with_recv(p) == 0.0 && !gemm_bf16_dl_carries_operand(p) ? us + 6.0 : us;
 }
 
 double gemm_bf16_tile_us(const GemmParams &p, int num_cu)

@@ -507,17 +507,23 @@ RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num
 // 3.1 us and 4.8 us + 0.0158 us per k a round, which wins over long k ranges (bound by the fp32 MFMAs: 1024 x 1024 x 4096 73 us, 143;
 // 512 x 4096 x 4096 142, 175) and not over short ones (2048 x 8192 x 512 206, 153; 768 x 4096 x 256 27, 22; 335 x 2328 x 160 9.6, 9.0)
 // nor over grids that the 128 x 128 tiles fill (4096 x 8192 x 4096 2222, 2076).
-// bf16: a launch costs 1.5 us, and a round of 64 x 64 tiles over the chip
-//  * 3.6 us + 0.27 us per 64 k for a single step (128 x 8192 x 3584 18.7 us warm, 256 x 8192 x 3584 34.4, 512 x 4096 x 1376 21.5);
-//  * 7.3 us + 0.235 us per 64 k for the steps of a rank step in one launch (their deliveries, less of them with smaller tiles;
-//    p = 8, 64 rows x 8192 columns per step, four rounds: 512 k 37.5 us all-gather, 40.7 reduce-scatter, the tile kernel 25.6
-//    and 32.9; 1024 k 44.8 and 48.5, 34.1 and 41.8; 2 x 192 x 4096 x 8192, two rounds: 70.2 and 72.5, 77.9 and 80.1) and 0.02 us
-//    per megabyte of W (2 x 96 x 8192 x 8192, 134 MB: 84.2 and 85.2, 78.1 and 79.3);
-//  * rows that do not start on a 128-byte line put every slice of theirs on two: 1.12 times the time per 64 k (575 x 3336 x 7328
-//    80 us, the tile kernel 70; 8 x 64 x 6352 x 7016 200, 154), 1.45 times where it is [k x n] weights too large for the caches
-//    (4 x 148 x 4408 x 5648 154, 107; 85 x 7512 x 6304 54, 47).
-// Of 3700 drawn shapes of the sizes between 1 x 128 x 128 and 1024 x 8192 x 8192 two are slower by rule than on the tile kernel
-// by 2 % and more, the worst by 4 %.
+// bf16: half a round over the chip and less always.  Rows that do not start on a 128-byte line put every slice of theirs on two: 1.12
+// times the time per 64 k (575 x 3336 x 7328 80 us, the tile kernel 70), 1.45 times where it is [k x n] weights too large for the
+// caches (4 x 148 x 4408 x 5648 154, 107; 85 x 7512 x 6304 54, 47).
+//  * Single steps: 1.5 us, and 3.6 us + 0.27 us per 64 k a round of 64 x 64 tiles (128 x 8192 x 3584 18.7 us warm, 256 x 8192 x 3584
+//    34.4, 512 x 4096 x 1376 21.5).  Of 851 drawn steps of 16 to 1024 rows x 128..8192 x 128..8192, each timed on both kernels on
+//    buffers that come round and on cold ones, 7 are 10 % and more behind the faster kernel by this rule, 0.3 % on average.
+//  * The steps of a rank step in one launch: a constant, what a round of tiles costs (by their area, a 64 x 64 tile being 1), what
+//    64 k cost a round and the loads of the whole launch, the megabytes of W, and of fp32 output with the deliveries that go with
+//    it; taken where 0.97 of that is less than the tile kernels' figure.  Fitted (relative error, rms 0.12) to 949 carried rank
+//    steps of 2 x 16 to 8 x 384 rows x 128..8192 x 128..8000.  Of these 0 of 498 reduce-scatters and 3 of 451 all-gathers are 10 %
+//    and more behind the faster kernel (by figures of earlier tile kernels 23 and 14), of 551 drawn later 1 and 2.  us, this
+//    kernel / the tile kernel: reduce-scatter 8 x 32 x 5272 x 816 [k x n] 27 / 18, 8 x 192 x 512 x 192 [k x n] 10.3 / 7.7, 2 x 192 x
+//    2816 x 5760 [n x k] 47 / 38, 2 x 80 x 4864 x 3712 [k x n] 22 / 30, 2 x 272 x 1152 x 2368 [n x k] 16 / 20; all-gather 8 x 144 x
+//    4224 x 3328 [k x n] 111 / 62, 4 x 80 x 3200 x 512 [n x k] 13.1 / 8.4, 4 x 80 x 1408 x 640 [n x k] 7.2 / 9.0.
+//  * ... over k ranges of 8192 and more, and under the pairwise schedule of more than two ranks, which that fit has not seen: 1.5 us,
+//    7.3 us + 0.235 us per 64 k a round, and 0.02 us per megabyte of W (2 x 96 x 8192 x 8192, 134 MB: 62, the tile kernel 57;
+//    4 x 128 x 4096 x 8192 61, 57).
 bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
 {
     const Tuning tn = tuning();
@@ -544,6 +550,13 @@ bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
         slices *= 1.45;
     else if (p.lda % 64 != 0 || (!w_kn && p.ldw % 64 != 0))
         slices *= 1.12;
+    const double adds = gemm_share_with_recv(p);
+    if (p.n_steps > 0 && p.K < 8192 && (adds == 0.0 || adds >= 0.5)) {
+        const double area = t.mf * t.nc / 16.0, share = (double)wgs / num_cu, mw = 2e-6 * p.N * p.K, mo = 4e-6 * rows * p.N;
+        const double us = 3.2 + rounds * 3.7 * area + slices * (rounds * (0.067 + 0.051 * area) + 0.174 * share * area) +
+                          0.065 * mw + 0.54 * mo;
+        return 0.97 * us < gemm_bf16_rank_step_us(p, num_cu);
+    }
     const double us = p.n_steps > 0 ? 1.5 + rounds * (3.6 + 3.7 * t.mf * t.nc / 16 + 0.235 * slices) + 0.02e-6 * 2.0 * p.N * p.K
                                     : 1.5 + rounds * (3.6 + 0.27 * slices);
     return us < gemm_bf16_tile_us(p, num_cu);

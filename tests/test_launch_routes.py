@@ -105,3 +105,33 @@ def test_tile_of_large_steps(dry, add, mc, n, k, tile):
     else:
         calls = dry.calls(lambda: cf.ag_step(cf.layer_desc(1, 0, mc, n, k, w_layout=cf.CF_W_NK), 0, P(0), P(1), P(2)))
     assert [c[0].startswith(f"gemm_bf16_dl_kernel<{tile},") for c in calls] == [True]
+
+
+@pytest.mark.parametrize("kind,p,mc,n,k,layout,few_rows", [
+    # us on the few-rows kernel and on the tile kernel
+    (cf.CF_KIND_RS, 8, 32, 5272, 816, cf.CF_W_KN, False),        # 27; 18
+    (cf.CF_KIND_RS, 8, 192, 512, 192, cf.CF_W_KN, False),        # 10.3; 7.7
+    (cf.CF_KIND_RS, 2, 80, 4864, 3712, cf.CF_W_KN, True),        # 22; 30
+    (cf.CF_KIND_RS, 2, 272, 1152, 2368, cf.CF_W_NK, True),       # 16; 20
+    (cf.CF_KIND_AG, 8, 144, 4224, 3328, cf.CF_W_KN, False),      # 111; 62
+    (cf.CF_KIND_AG, 4, 80, 3200, 512, cf.CF_W_NK, False),        # 13.1; 8.4
+    (cf.CF_KIND_AG, 4, 80, 1408, 640, cf.CF_W_NK, True),         # 7.2; 9.0
+    (cf.CF_KIND_AG, 8, 34, 7040, 5096, cf.CF_W_NK, True),        # ragged k-tiles: the tile kernel's deliveries are copied in front
+])
+def test_rule_between_few_rows_and_tiles_for_rank_steps(dry, kind, p, mc, n, k, layout, few_rows):
+    stage, each, sends = _tables(p)
+    bufs = cf.make_buffers(P(0), P(1), P(2), stage, (None, None), (None, None), None, each, sends)
+    desc = cf.layer_desc(p, p - 1, mc, n, k, w_layout=layout)
+    calls = dry.calls(lambda: cf.run_schedule(desc, kind, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))
+    assert ["gemm_rows_kernel" in c[0] for c in calls] == [few_rows]
+
+
+@pytest.mark.parametrize("p,mc,n,k", [(4, 72, 136, 1376), (6, 130, 72, 96), (8, 264, 392, 200)])
+def test_pairwise_steps_and_rank_steps_take_the_same_kernel(dry, p, mc, n, k):
+    """(whose sums are then the same bits)"""
+    stage, each, sends = _tables(p)
+    bufs = cf.make_buffers(P(0), P(1), P(2), stage, (None, None), (None, None), None, each, sends)
+    desc = cf.layer_desc(p, 0, mc, n, k)
+    one, = dry.calls(lambda: cf.run_schedule(desc, cf.CF_KIND_RS_PAIR, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))
+    step, = dry.calls(lambda: cf.rs_pair_step(desc, 0, P(0), P(1), None, None, P(3)))
+    assert one[0].startswith("gemm_rows_kernel") and step[0].startswith("gemm_rows_kernel")
