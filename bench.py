@@ -627,8 +627,8 @@ def main() -> int:
                    "p": 8, "rank": 0, "mode": head_mode, "us_per_step_by_mode": pair_modes,
                    "mode_note": "persistent = every delivery enqueued in front of ONE kernel per layer (nothing is hidden: "
                                 "hidden_fraction ~ 0); persistent+carried = no copy is enqueued, that one kernel reads what the "
-                                "neighbours send from their buffers under its main loop and stores it to this rank's landing "
-                                "buffers; streams / graph / fused-copy / device-wait overlap each delivery with the step kernel "
+                                "neighbours send from their buffers (slices under its main loop, partial sums in its epilogue) and "
+                                "stores it to this rank's landing buffers; streams / graph / fused-copy / device-wait overlap each delivery with the step kernel "
                                 "before it"},
         "frac_mfma_peak": round(value / PEAK_BF16_TFLOPS, 4),
         # of the headline mode, against its own compute-only and copy-only times

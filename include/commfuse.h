@@ -315,8 +315,8 @@ enum {
                             groups before it, one event per group ordering the two streams.  (Few rows in all,
                             see the end: one group; with CF_FUSED_COPY the launch starts behind what
                             copy_stream holds.)
-                            (The kernel can also wait for per-step delivery flags on the device; on a real ring, where a delivery is a remote DMA
-                            write that needs no compute unit here, that is how it would overlap.)
+                            (The kernel waits for nothing on the device: what it reads has been delivered, or lies in the
+                            neighbours' buffers, before the launch.)
                             CF_KIND_RS_PAIR: every arrival is kept (recv_each) and the last step adds
                             them all, as commfuse_rs_pair_last_step does.
                             Weight-gradient kinds: recv_each must be in GATHERED order -- with
@@ -337,24 +337,24 @@ enum {
                             the neighbours' buffers (peer_stage) and store them on to recv_each in the
                             same pass (same sums, bit for bit).
                             With CF_FUSED_COPY (CF_KIND_RS, CF_KIND_AG): the delivery is carried by the
-                            consumer -- no copy is launched, the emulated transfer runs inside the kernel,
-                            under its main loop.  Reduce-scatter: the waves that need B_in read it from the
-                            neighbour's buffer (peer_stage), add it in mid-sum, and store it to the landing
-                            buffer (recv_each).  All-gather: the kernel takes the gathered slices from the
+                            consumer -- no copy is launched, the emulated transfer runs inside the kernel.
+                            Reduce-scatter (the projection of the attention layer too): the epilogue reads B_in from
+                            the neighbour's buffer (peer_stage), adds it to the finished product and stores it to the
+                            landing buffer (recv_each); where the work items fill the chip and are not much longer than
+                            their share of the memory traffic, half of the workgroups land theirs in front of their main
+                            loop.  All-gather: the kernel takes the gathered slices from the
                             neighbours' buffers as its left operand, and every k-tile that comes in is
-                            stored on to the landing buffer by one of the workgroups that load it.  (A row
-                            block lands without the padding of its rows.)  A reduce-scatter launch that
-                            cannot do that (a tile other than 256x256, a k range under 18 k-tiles of 64, or
-                            20 with a ragged last one; the projection of the attention layer) reads B_in
-                            from the neighbour's buffer in its epilogue, and the same work item copies its
-                            tile's part of it to the landing buffer beside its GEMM (packed partial sums,
-                            ldo == n).  Otherwise (all-gather: k not a multiple of 64; the other kinds) the
-                            flag changes nothing: the deliveries are enqueued in front.
+                            stored on to the landing buffer by one of the workgroups that load it.  A carried row
+                            block lands without the padding of its rows, one copied in front with it.  Copied in front,
+                            as without the flag, are: an all-gather whose k is not a multiple of 64; partial sums with
+                            padding between their rows (ldo != n), unless 256x256 is the tile by the step's area and k
+                            fills 18 k-tiles of 64 (20 with a ragged last one) -- the attention layer's in any case --;
+                            the other kinds.
                             With CF_FUSED_COPY (CF_KIND_RS_PAIR): one pass in front of the launch reads all arrivals
                             from the partners' buffers (peer_stage), lands them (recv_each) and leaves their sum in
-                            O, which the last step adds to its product (p = 2: the one arrival is read in the last
-                            step's epilogue and landed beside its GEMM).  Same sums, bit for bit (but p = 2 without
-                            the flag: one arrival is added in mid-sum and the k order rotated where CF_KIND_RS would).
+                            O, which the last step adds to its product (p = 2: the last step's epilogue reads the one
+                            arrival and lands it).  Same sums, bit for bit, as without the flag (but p = 2, whose k order
+                            is rotated without it where CF_KIND_RS would).
                             Where a rank step has few rows in all (decoded tokens; the kernel that packs the rows
                             of every step into one launch) every kind's deliveries are carried, whatever k.
                             Not with CF_DEVICE_WAIT.                                                  */

@@ -923,13 +923,13 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // earlier steps and summing them there measured, us, against this: 6 ranks 390 x 2088 x 1096 54 -> 42, 8 ranks 512 x 4096 x
     // 1376 118 -> 82, 1024 x 8192 x 3584 481 -> 467).
     // Two ranks have one arrival and nothing to sum: the last step's epilogue reads it from the partner's buffer and lands
-    // it beside its GEMM, as on the ring (through O, us: 1024 x
-    // 8192 x 3584 122.5 -> 110.9, 512 x 4096 x 1376 34.5 -> 31.9, 192 x 8192 x 512 23.7 -> 20.2).
-    bool pair_front = false, pair_beside = false;
+    // it, as on the ring (through O, us: 1024 x 8192 x 3584 122.5 -> 110.9, 512 x 4096 x 1376 34.5 -> 31.9, 192 x 8192 x 512 23.7 ->
+    // 20.2).
+    bool pair_front = false, pair_single = false;
     if (!few_rows && (flags & CF_FUSED_COPY) && kind == CF_KIND_RS_PAIR && do_copy && do_compute && slot_bytes > 0 && r.mc > 0 &&
         r.n > 0 && r.k > 0 && wide && cf::tuning().carry != 0) {
-        pair_beside = p == 2;
-        pair_front = !pair_beside;
+        pair_single = p == 2;
+        pair_front = !pair_single;
         carried = true;
     }
     // Without CF_SERIAL (reduce-scatter and all-gather on two streams): the rank step as a few launches, each a group
@@ -1099,8 +1099,8 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
                 gp.out_step[j] = last ? b->O : static_cast<void *>(b->send_each[j]);
                 if (last && pair_front)
                     gp.recv_step[j] = static_cast<const float *>(b->O);
-                gp.k_in_order = pair_front || pair_beside;
-                if (last && pair_beside) {
+                gp.k_in_order = pair_front || pair_single;
+                if (last && pair_single) {
                     gp.recv_step[j] = static_cast<const float *>(b->peer_stage[0]);
                     gp.land_step[j] = b->recv_each[0];
                 }

@@ -358,9 +358,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     auto w_dist = [&](int j) __attribute__((always_inline)) { return (j - j % W_JP) * w_jstep; };
 
     // Direct load number `idx` (0 .. LPT-1: the A wave-loads, then the W wave-loads) of local k-tile
-    // kt into `stage`.  A tile beyond the end of this split's k range is requested all the same, with
-    // every lane out of range (it reads zeros and moves no data), so that the number of loads per
-    // tile -- and with it every vmcnt below -- is the same in every iteration.
+    // kt into `stage`.  Where the waits count on it -- in the prologue, and in the loops that test their loads -- a tile beyond
+    // the end of this split's k range is requested all the same, with every lane out of range: it reads zeros and moves no
+    // data.
     // Persistent mode: the workgroups of step group g of G (XCD x of 8 without column bands) walk the k range
     // starting g/G of the way in and wrap around, so that the XCDs that read the same weight tiles -- and would ask
     // for the same lines at the same moment -- are spread over the k range (measured: 1 % of the pair's rank step).
@@ -371,10 +371,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         const int kk = ktb + kt + rot;
         return kk >= nk_all ? kk - nk_all : kk;
     };
-    // With WHOLE_K (a k-tile known to be whole) the load is issued without any test: a
+    // With WHOLE_K (a k-tile known to be whole, and inside the range) the load is issued without any test: a
     // branch after every MFMA segment of the main loop costs more than it looks (measured: 4 - 6 % of the launch,
-    // and a select on the offset still 1 %).  A tile beyond the end of the range is then fetched for real -- the
-    // k-tile index wraps around (ktile), so it is a tile of the matrix -- into a stage that nobody reads.
+    // and a select on the offset still 1 %).
     auto issue_load = [&](int kt, int stage_a, int stage_w, auto idx_tag, auto whole_k_tag) __attribute__((always_inline)) {
         constexpr int idx = decltype(idx_tag)::value;
         constexpr bool WHOLE_K = decltype(whole_k_tag)::value;

@@ -82,8 +82,8 @@ def test_rs_pair_reduced(shape, layout, dtype):
             # all steps in one launch: the same GEMMs and the same additions in the same order
             pers = H.RsPairRun(w, data, rank, layout, keep_all=True)
             PS = cf.CF_PERSISTENT | cf.CF_SERIAL
-            # (CF_FUSED_COPY: no copy is launched; the arrivals are landed and summed in a pass in front, beside the GEMM
-            # with two ranks, or by the few-rows launch; a registered workspace changes nothing)
+            # (CF_FUSED_COPY: no copy is launched; the arrivals are landed and summed in a pass in front, in the
+            # epilogue with two ranks, or by the few-rows launch; a registered workspace changes nothing)
             FC = PS | cf.CF_FUSED_COPY
             for flags, with_ws in ((PS, False), (PS | cf.CF_GRAPH, False), (PS | cf.CF_POISON, False), (FC, False),
                                    (FC, True), (FC | cf.CF_GRAPH, True)):
@@ -358,17 +358,14 @@ def test_rs_pair_carried_under_the_16x16x32_main_loop(k):
 @pytest.mark.parametrize("tile,k", [("128x128", 328), ("256x128", 328), ("256x256", 64), ("256x256", 192), ("256x256", 1096),
                                     ("256x256", 2304)])
 @pytest.mark.parametrize("mc,n", [(512, 768), (520, 776)])
-def test_rs_pair_of_two_ranks_lands_beside_the_gemm(mc, n, tile, k):
-    """Two ranks: the one arrival is read from the partner's buffer in the last step's epilogue and landed by its work items.
-    On whole 256x256 tiles the landing is dealt over the k-tiles of the main loop: one k-tile (nothing dealt), three,
-    seventeen with a ragged tail, thirty-six (everything dealt); otherwise in front of the main loop or behind the epilogue.
-    The bits are those of the copies in front (whose k order is kept from rotating, and whose single arrival from the
-    stream that adds it in mid-sum)."""
+def test_rs_pair_of_two_ranks_lands_in_the_epilogue(mc, n, tile, k):
+    """Two ranks: the one arrival is read from the partner's buffer in the last step's epilogue and landed from the same
+    registers, on every tile, whole and partly outside the matrix, over k ranges of one to thirty-six k-tiles.  The bits are those of the copies in front (whose k order is kept from rotating)."""
     w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=2, m_chunk=mc, n=n, k=k)
     data = inputs.make_rs(w, salt=29 + k)
     ref = _oracle_pair(w, data, 1)
     os.environ["COMMFUSE_TILE"] = tile
-    os.environ["COMMFUSE_STREAM_RECV"] = os.environ["COMMFUSE_K_ROTATE"] = "0"
+    os.environ["COMMFUSE_K_ROTATE"] = "0"
     try:
         for layout in (cf.CF_W_KN, cf.CF_W_NK):
             got = []
@@ -384,5 +381,4 @@ def test_rs_pair_of_two_ranks_lands_beside_the_gemm(mc, n, tile, k):
             assert torch.equal(got[0], got[1])
     finally:
         os.environ.pop("COMMFUSE_TILE", None)
-        os.environ.pop("COMMFUSE_STREAM_RECV", None)
         os.environ.pop("COMMFUSE_K_ROTATE", None)

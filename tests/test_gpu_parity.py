@@ -261,13 +261,13 @@ def test_integer_inputs_are_bit_exact(dtype, layout):
             assert np.array_equal(outs[i], ref[i]), f"rank {rank} step {i}"
 
 
-@pytest.mark.parametrize("stream", ["1", "0"])
+@pytest.mark.parametrize("mc,n", [(264, 520), (512, 512)])
 @pytest.mark.parametrize("layout", [cf.CF_W_KN, cf.CF_W_NK])
-def test_b_in_added_in_mid_sum_is_bit_exact_on_integers(layout, stream):
-    """256x256 tile with a long k range: the received partial lands in LDS under the main loop and is added to
-    the accumulators in mid-sum (another order of the same additions).  On small-integer data every order gives
-    the same bits, per-step launches and the one-launch rank step alike; with the path switched off too."""
-    p, mc, n, k = 4, 264, 520, 1224                     # 20 k-tiles (the last ragged), tiles ragged in M and N
+def test_b_in_on_256x256_tiles_is_bit_exact_on_integers(layout, mc, n):
+    """256x256 tile with a long k range, ragged tiles (32x32x16 main loop) and whole ones (16x16x32): the received partial is
+    added to the finished product in the epilogue.  On small-integer data every order of the additions gives the same
+    bits, per-step launches and the one-launch rank step alike, deliveries copied in front and carried."""
+    p, k = 4, 1224                                      # 20 k-tiles, the last ragged
     w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=p, m_chunk=mc, n=n, k=k)
     rng = np.random.default_rng(78)
     A = inputs.small_int_like((p * mc, k), rng, -4, 4)
@@ -275,7 +275,6 @@ def test_b_in_added_in_mid_sum_is_bit_exact_on_integers(layout, stream):
     R = [None] + [inputs.small_int_like((mc, n), rng, -50, 50) for _ in range(p - 1)]
     data = {"A": inputs._as_dtype(A, "bf16"), "W": inputs._as_dtype(W, "bf16"), "R": R}
     os.environ["COMMFUSE_TILE"] = "256x256"
-    os.environ["COMMFUSE_STREAM_RECV"] = stream
     try:
         for rank in (0, p - 1):
             ref = _oracle_rs(w, data, rank)
@@ -294,7 +293,6 @@ def test_b_in_added_in_mid_sum_is_bit_exact_on_integers(layout, stream):
                     assert torch.equal(run.each[i], run.stage[i]), f"rank {rank} hop {i + 1} (flags {fl})"
     finally:
         os.environ.pop("COMMFUSE_TILE", None)
-        os.environ.pop("COMMFUSE_STREAM_RECV", None)
 
 
 @pytest.mark.parametrize("layout", [cf.CF_W_KN, cf.CF_W_NK])
@@ -682,8 +680,7 @@ def test_persistent_mfma16_main_loop(k, mfma16):
             w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=8, m_chunk=m_chunk, n=n, k=k)
             data = inputs.make_rs(w, salt=81 + k)
             ref = _oracle_rs(w, data, rank)
-            # (CF_FUSED_COPY: these k ranges are too short for B_in to be streamed, so the epilogue reads it from the
-            # neighbour's buffer and the work item lands it by a copy beside its GEMM)
+            # (CF_FUSED_COPY: the epilogue reads B_in from the neighbour's buffer and lands it)
             for layout, flags in ((cf.CF_W_KN, PERSISTENT_SERIAL), (cf.CF_W_NK, PERSISTENT_SERIAL),
                                   (cf.CF_W_KN, PERSISTENT_SERIAL | cf.CF_FUSED_COPY), (cf.CF_W_NK, PERSISTENT_SERIAL | cf.CF_FUSED_COPY)):
                 run = H.RsRun(w, data, rank, layout, m=m, each=True)
