@@ -136,8 +136,8 @@ def main() -> int:
     # or not overlapped at all (one stream, each delivery after the kernel before it: the copies then run
     # at full speed and disturb no GEMM -- a reference point for what the overlap buys); "persistent": all
     # steps of a rank step in one kernel launch, the deliveries enqueued before it; "persistent+carried": no copy is
-    # enqueued, the kernel's own waves read B_in from the neighbour's buffer under the main loop and store it to the
-    # landing buffer; "persistent-groups": two streams again -- a few launches per layer, each a group of steps that fills
+    # enqueued, the kernel's own waves read what the neighbour sends from its buffer (slices under the main loop, B_in in
+    # the epilogue) and store it to the landing buffer; "persistent-groups": two streams again -- a few launches per layer, each a group of steps that fills
     # the chip about once, the deliveries of a group on the copy stream under the launches of the groups before it
     MODES = (("streams", 0), ("graph", cf.CF_GRAPH), ("fused-copy", cf.CF_FUSED_COPY),
              ("fused-copy+graph", cf.CF_FUSED_COPY | cf.CF_GRAPH), ("device-wait", cf.CF_DEVICE_WAIT),

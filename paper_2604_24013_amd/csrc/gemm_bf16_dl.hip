@@ -1455,7 +1455,7 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // multiplications do not far outlast the memory's part, which scales with what of the tiles lies inside the
         // matrix.  us per carried rank step, all in the epilogue / half in front: 8 x 1024 x 8192 at k = 512 180 / 170, 1024
         // 218 / 209, 2560 356 / 346, 3072 403 / 387, 3584 437 / 442; 8 x 512 x 4096 at 256 43.7 / 40.2, 1376 69.6 / 64.9, 2560 91.5 /
-        // 86.9.  The smaller tiles request B_in under the main loop: 8 x 256 x 4096 x 512 27.1 / 23.0, 2 x 512 x 4096 x 1376
+        // 86.9.  The smaller tiles, with two row blocks requested early: 8 x 256 x 4096 x 512 27.1 / 23.0, 2 x 512 x 4096 x 1376
         // 25.4 / 25.1, 8 x 300 x 4096 x 2048 77.7 / 79.8.  Fewer work items than compute units: 4 x 333 x 2088 x 1096 23.9 / 25.5,
         // 8 x 100 x 2048 x 2048 26.6 / 27.4.
         const int64_t items = tiles * p.n_steps;

@@ -95,7 +95,7 @@ RS_SHAPES = [
     (4, 72, 136, 1376),     # the 7B down-projection's K (21*64 + 32)
     (1, 40, 8, 8),          # p = 1: plain GEMM, minimum n and k
     (8, 520, 392, 200),     # several tiles in both directions plus tails
-    (3, 200, 264, 1160),    # 19 k-tiles, the last ragged: long enough for B_in to be brought in under the main loop
+    (3, 200, 264, 1160),    # 19 k-tiles, the last ragged
     (2, 256, 512, 1152),    # 18 whole k-tiles, exact tiles
 ]
 
@@ -513,7 +513,7 @@ def test_device_wait_sees_fresh_data_every_time():
 
 @pytest.mark.parametrize("tile", [None, "256x256", "256x128", "128x128"])
 @pytest.mark.parametrize("m", [1, 2])
-@pytest.mark.parametrize("k", [328, 1224, 1280])      # 6 k-tiles; 20 (ragged) and 20 whole: B_in comes in under the main loop
+@pytest.mark.parametrize("k", [328, 1224, 1280])      # 6 k-tiles; 20 (ragged) and 20 whole
 def test_persistent_rank_step(m, tile, k):
     """CF_PERSISTENT: all steps in one launch; work items (step, tile) round robin over one chip-filling grid."""
     w = inputs.scaled(inputs.CONFIGS["c2_rs_7b"], p=8, m_chunk=264, n=520, k=k)
@@ -525,9 +525,8 @@ def test_persistent_rank_step(m, tile, k):
     refa = _oracle_ag(wa, da, rank)
     _tile_env(tile)
     try:
-        # (with CF_FUSED_COPY the reduce-scatter launch carries its deliveries itself where it brings B_in in through
-        # LDS -- the 256x256 tile with the longer k ranges -- and the all-gather launch where k is whole k-tiles;
-        # they have them copied in front otherwise: same results)
+        # (with CF_FUSED_COPY the reduce-scatter launch carries its deliveries itself, and the all-gather launch where k
+        # is whole k-tiles; it has them copied in front otherwise: same results)
         # (without CF_SERIAL: groups of steps per launch, the deliveries of a group on the copy stream under the launches
         # before it)
         for flags in (cf.CF_PERSISTENT | cf.CF_SERIAL, cf.CF_PERSISTENT | cf.CF_SERIAL | cf.CF_GRAPH,
