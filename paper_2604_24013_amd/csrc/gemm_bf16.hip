@@ -354,16 +354,17 @@ double gemm_share_with_recv(const GemmParams &p)
 
 // What a launch takes with tile t, in microseconds: per work item and k-tile, R rounds over the chip, and less where the last
 // round leaves compute units idle (the others' operands come faster), plus the megabytes of fp32 output, of the left operand
-// and what goes with a B_in.  Fitted (relative error, rms 0.07 to 0.13) to 3200 steps and carried rank steps of 16..8192 rows x
+// and what goes with a B_in, which the share r of the steps has.  Fitted (relative error, rms 0.07 to 0.13) to 3200 steps and carried rank steps of 16..8192 rows x
 // 128..8192 x 128..8192 on each tile, on buffers that come round and on ones cold in the caches; for weight gradients, whose left
 // operand is read by k-rows, to 90 of 32..8192 rows into 256..8192 x 256..8192 (rms 0.04 to 0.12).
-static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
+static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu, double r)
 {
     const int steps = p.n_steps > 0 ? p.n_steps : 1;
-    const double items = (double)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * steps;
+    const int64_t items = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * steps;
     const double kt = (p.K + 63) / 64, mb = (double)p.M * p.N * steps * 4e-6;
     const bool two = t.bm == 128 && !t.deep;
-    const double share = items / num_cu / (two ? 2 : 1), rounds = ceil(share);
+    const int64_t wgs = (int64_t)num_cu * (two ? 2 : 1);
+    const double share = (double)items / wgs, rounds = (double)((items + wgs - 1) / wgs);
     if (p.a_t) {
         if (t.bm == 256 && t.bn == 256)
             return 1.8 + rounds * (6.2 + 0.88 * kt) + 0.59 * kt * share + 0.083 * mb;
@@ -373,13 +374,13 @@ static double tile_estimate_us(const GemmParams &p, TileChoice t, int num_cu)
             return 3.4 + rounds * (1.7 + 0.35 * kt) + 0.725 * kt * share + 0.095 * mb;
         return 2.3 + rounds * (4.3 + 0.31 * kt) + 0.27 * kt * share;
     }
-    const double ma = (double)p.M * p.K * steps * 2e-6, r = gemm_share_with_recv(p);
+    const double ma = (double)p.M * p.K * steps * 2e-6;
     if (t.bm == 256 && t.bn == 256)
         return 0.6 + rounds * (6.4 + 0.98 * kt + 3.8 * r) + 0.24 * kt * share + (0.11 + 0.3 * r) * mb + 0.14 * ma;
     if (t.bm == 256)
         return 1.5 + rounds * (3.8 + 0.56 * kt + 1.8 * r) + 0.17 * kt * share + (0.098 + 0.17 * r) * mb + 0.22 * ma;
     if (two)
-        return 2.1 + ceil(items / num_cu) * (2.1 + 0.12 * kt) + rounds * (0.4 * kt + 0.87 * r) + 0.34 * kt * share +
+        return 2.1 + (double)((items + num_cu - 1) / num_cu) * (2.1 + 0.12 * kt) + rounds * (0.4 * kt + 0.87 * r) + 0.34 * kt * share +
                (0.022 + 0.23 * r) * mb + 0.07 * ma;
     return 2.0 + rounds * (3.6 + 0.36 * kt + 1.2 * r) + 0.14 * kt * share + (0.038 + 0.13 * r) * mb + 0.1 * ma;
 }
@@ -406,20 +407,23 @@ static TileChoice with_overrides(TileChoice t)
 // above the tile so chosen is 0.6 % behind the fastest on average and 10 % and more behind in 20; by area alone 4.4 % and 540, by
 // an estimate that knew neither B_in nor left operand, fitted to 1024 rows at most, 1.5 % and 85.  Weight gradients change for an
 // estimate 7 % lower: 1928 rows into 1608 x 4712, 256x128 53.6, two 128x128 per compute unit 38.2.
-static TileChoice tile_by_estimate(const GemmParams &p, int num_cu)
+static TileChoice tile_by_estimate(const GemmParams &p, int num_cu, double *t_us = nullptr)
 {
     TileChoice t = tile_by_area(p, num_cu);
     if (t.splitk == 1) {
         static const TileChoice cand[4] = {{256, 256, 1}, {256, 128, 1}, {128, 128, 1, true}, {128, 128, 1}};
         const bool large = t.bm == 256 && t.bn == 256, whole = p.M % 256 == 0 && p.N % 256 == 0;
-        double best = (p.a_t ? 0.93 : large ? (whole ? 0.9 : 0.95) : 1.0) * tile_estimate_us(p, t, num_cu);
+        const double r = gemm_share_with_recv(p), area_us = tile_estimate_us(p, t, num_cu, r);
+        double best = (p.a_t ? 0.93 : large ? (whole ? 0.9 : 0.95) : 1.0) * area_us, its_us = area_us;
         for (const TileChoice &c : cand) {
-            const double us = tile_estimate_us(p, c, num_cu);
+            const double us = tile_estimate_us(p, c, num_cu, r);
             if (us < best) {
-                best = us;
+                best = its_us = us;
                 t = c;
             }
         }
+        if (t_us != nullptr)
+            *t_us = its_us;
     }
     return t;
 }
@@ -432,7 +436,8 @@ static TileChoice tile_of_launch(const GemmParams &p, int num_cu)
 
 double gemm_bf16_rank_step_us(const GemmParams &p, int num_cu)
 {
-    const double us = tile_estimate_us(p, tile_by_estimate(p, num_cu), num_cu);
+    double us = 0.0;
+    tile_by_estimate(p, num_cu, &us);                // (a rank step's k range is not split)
     // an all-gather of ragged k-tiles has its deliveries copied in front: 6 us, and 0.8 us per megabyte of them
     return gemm_share_with_recv(p) == 0.0 && !gemm_bf16_dl_carries_operand(p) ? us + 6.0 : us;
 }
