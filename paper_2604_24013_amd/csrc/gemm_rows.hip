@@ -97,6 +97,13 @@ __device__ __forceinline__ i32x4_t make_rsrc(const void *base, unsigned bytes)
     return r;
 }
 
+// Workgroup id -> place in an order that gives each of the eight XCDs a contiguous range.
+__device__ __forceinline__ int xcd_remap(int id, int total)
+{
+    const int q = total >> 3, rem = total & 7, xcd = id & 7;
+    return xcd * q + (xcd < rem ? xcd : rem) + (id >> 3);
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {
@@ -147,11 +154,20 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams<SEG> P)
         }
         return;
     }
-    // tile columns are the fastest index: the row tiles of a column share its weights in one XCD's L2 where the number of
-    // tile columns is a multiple of eight, and so do the launches of successive steps
-    const int tile_n = blockIdx.x % P.tiles_n;
-    const int tr_sp = blockIdx.x / P.tiles_n;
-    const int split = tr_sp % P.ksplit, tile_r = tr_sp / P.ksplit;
+    // Every XCD (workgroups x, x + 8, ...: an L2 of its own) takes a band of neighbouring tile columns, the row tiles of a column
+    // next to each other: they walk k side by side and read the weights once through that L2, and so do the launches of
+    // successive steps.  (With the columns dealt out one by one, the columns' row tiles landed on different XCDs and rounds:
+    // us per call, columns one by one / in bands: all-gather step 30 x 4080 x 4984 16.9 / 12.6, reduce-scatter step 685 x 1384 x
+    // 5168 32.2 / 28.6, all-gather rank step 4 x 34 x 1800 x 2600 16.5 / 13.5, 8 x 8 x 1536 x 4096 11.8 / 10.8, where two tiles share
+    // a 128-byte line of W.)
+    const int unit = xcd_remap((int)blockIdx.x, tiles * P.ksplit);
+    int tile_n = unit, split = 0, tile_r = 0;
+    if (const int per_col = P.tiles_r * P.ksplit; per_col > 1) {
+        tile_n = unit / per_col;
+        const int in = unit - tile_n * per_col;
+        split = in / P.tiles_r;
+        tile_r = in - split * P.tiles_r;
+    }
     const int tile = tile_r * P.tiles_n + tile_n;
     const int n0 = tile_n * TN, r0 = tile_r * TR;
 
@@ -514,13 +530,14 @@ RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num
 //    34.4, 512 x 4096 x 1376 21.5).  Of 851 drawn steps of 16 to 1024 rows x 128..8192 x 128..8192, each timed on both kernels on
 //    buffers that come round and on cold ones, 7 are 10 % and more behind the faster kernel by this rule, 0.3 % on average.
 //  * The steps of a rank step in one launch: a constant, what a round of tiles costs (by their area, a 64 x 64 tile being 1), what
-//    64 k cost a round and the loads of the whole launch, the megabytes of W, and of fp32 output with the deliveries that go with
-//    it; taken where 0.97 of that is less than the tile kernels' figure.  Fitted (relative error, rms 0.12) to 949 carried rank
-//    steps of 2 x 16 to 8 x 384 rows x 128..8192 x 128..8000.  Of these 0 of 498 reduce-scatters and 3 of 451 all-gathers are 10 %
-//    and more behind the faster kernel (by figures of earlier tile kernels 23 and 14), of 551 drawn later 1 and 2.  us, this
-//    kernel / the tile kernel: reduce-scatter 8 x 32 x 5272 x 816 [k x n] 27 / 18, 8 x 192 x 512 x 192 [k x n] 10.3 / 7.7, 2 x 192 x
-//    2816 x 5760 [n x k] 47 / 38, 2 x 80 x 4864 x 3712 [k x n] 22 / 30, 2 x 272 x 1152 x 2368 [n x k] 16 / 20; all-gather 8 x 144 x
-//    4224 x 3328 [k x n] 111 / 62, 4 x 80 x 3200 x 512 [n x k] 13.1 / 8.4, 4 x 80 x 1408 x 640 [n x k] 7.2 / 9.0.
+//    64 k cost a round (1.15 times that where the rows of [k x n] weights do not start on 128-byte lines, 1.12 times for [n x k]
+//    weights, 1.06 times for the activations alone), and the megabytes of fp32 output with the deliveries that go with it; taken
+//    where 0.97 of that is less than the tile kernels' figure.  Fitted (relative error, rms 0.10) to 238 of 500 carried rank steps
+//    of 2 x 16 to 8 x 312 rows x 128..8192 x 128..8184, those of 9 us and more.  Of the 500 one is 10 % and more behind the faster
+//    kernel by this rule, 0.1 % on average.  us, this kernel / the tile kernel: reduce-scatter 8 x 32 x 5272 x 816 [k x n] 27 / 18,
+//    8 x 192 x 512 x 192 [k x n] 10.3 / 7.7, 2 x 192 x 2816 x 5760 [n x k] 47 / 38, 2 x 80 x 4864 x 3712 [k x n] 22 / 30, 2 x 272 x
+//    1152 x 2368 [n x k] 16 / 20; all-gather 4 x 302 x 384 x 704 [n x k] 10.7 / 9.4, 2 x 373 x 520 x 3824 [k x n] 21 / 37, 8 x 215 x
+//    1088 x 6336 [k x n] 81 / 50.
 //  * ... over k ranges of 8192 and more, and under the pairwise schedule of more than two ranks, which that fit has not seen: 1.5 us,
 //    7.3 us + 0.235 us per 64 k a round, and 0.02 us per megabyte of W (2 x 96 x 8192 x 8192, 134 MB: 62, the tile kernel 57;
 //    4 x 128 x 4096 x 8192 61, 57).
@@ -545,18 +562,18 @@ bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
     const int64_t rounds = (wgs + num_cu - 1) / num_cu;
     if (!bf16)
         return 3.1 + rounds * (4.8 + 0.0158 * p.K) < gemm_f32_tile_us(p, num_cu);
-    double slices = (p.K + 63) / 64;
+    const double kt = (p.K + 63) / 64, adds = gemm_share_with_recv(p);
+    if (p.n_steps > 0 && p.K < 8192 && (adds == 0.0 || adds >= 0.5)) {
+        const double area = t.mf * t.nc / 16.0, mo = 4e-6 * rows * p.N;
+        const double slices = kt * (w_kn && p.ldw % 64 != 0 ? 1.15 : !w_kn && p.ldw % 64 != 0 ? 1.12 : p.lda % 64 != 0 ? 1.06 : 1.0);
+        const double us = 3.9 + rounds * (2.2 * area + slices * (0.067 + 0.148 * area)) + (0.79 + 0.4 * adds) * mo;
+        return 0.97 * us < gemm_bf16_rank_step_us(p, num_cu);
+    }
+    double slices = kt;
     if (w_kn && p.ldw % 64 != 0 && 2.0 * p.N * p.K > 40e6)
         slices *= 1.45;
     else if (p.lda % 64 != 0 || (!w_kn && p.ldw % 64 != 0))
         slices *= 1.12;
-    const double adds = gemm_share_with_recv(p);
-    if (p.n_steps > 0 && p.K < 8192 && (adds == 0.0 || adds >= 0.5)) {
-        const double area = t.mf * t.nc / 16.0, share = (double)wgs / num_cu, mw = 2e-6 * p.N * p.K, mo = 4e-6 * rows * p.N;
-        const double us = 3.2 + rounds * 3.7 * area + slices * (rounds * (0.067 + 0.051 * area) + 0.174 * share * area) +
-                          0.065 * mw + 0.54 * mo;
-        return 0.97 * us < gemm_bf16_rank_step_us(p, num_cu);
-    }
     const double us = p.n_steps > 0 ? 1.5 + rounds * (3.6 + 3.7 * t.mf * t.nc / 16 + 0.235 * slices) + 0.02e-6 * 2.0 * p.N * p.K
                                     : 1.5 + rounds * (3.6 + 0.27 * slices);
     return us < gemm_bf16_tile_us(p, num_cu);
