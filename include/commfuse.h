@@ -346,7 +346,8 @@ enum {
                             neighbours' buffers as its left operand, and every k-tile that comes in is
                             stored on to the landing buffer by one of the workgroups that load it.  A carried row
                             block lands without the padding of its rows, one copied in front with it.  Copied in front,
-                            as without the flag, are: an all-gather whose k is not a multiple of 64; partial sums with
+                            as without the flag, are: slices of an all-gather with padding between their rows (lda != k)
+                            whose k is not a multiple of 64; partial sums with
                             padding between their rows (ldo != n), unless 256x256 is the tile by the step's area and k
                             fills 18 k-tiles of 64 (20 with a ragged last one) -- the attention layer's in any case --;
                             the other kinds.

@@ -883,8 +883,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // copy is launched.  Reduce-scatter (the attention layer's projection too): the epilogue reads B_in from the
     // neighbour's buffer (peer_stage), adds it, and stores it to the landing buffer.  All-gather: the kernel takes its left
     // operand from the neighbour's buffer, and each k-tile that comes in through LDS is stored on to the landing
-    // buffer by one of the workgroups that load it (k a multiple of the k-tile).  Otherwise the deliveries are
-    // enqueued in front as without the flag.
+    // buffer by one of the workgroups that load it.  Otherwise the deliveries are enqueued in front as without the flag.
     bool carried = false;
     // the launch as the rules ask about it: its shape, and which steps will add a B_in
     cf::GemmParams probe;
@@ -909,7 +908,8 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     // lands with them)
     if (!few_rows && (flags & CF_FUSED_COPY) && (kind == CF_KIND_RS || kind == CF_KIND_AG) && (attn == nullptr || r.ldo == r.n) &&
         do_copy && do_compute && slot_bytes > 0 && r.mc > 0 && r.n > 0 && r.k > 0) {
-        carried = cf::gemm_bf16_carries_delivery(probe, r.w_kn, r.bf16_out, num_cu_of_current_device(), kind == CF_KIND_RS);
+        carried = cf::gemm_bf16_carries_delivery(probe, r.w_kn, r.bf16_out, num_cu_of_current_device(), kind == CF_KIND_RS) &&
+                  (kind == CF_KIND_RS || r.k % 64 == 0 || wide);
     }
     // The gradient bucket with CF_FUSED_COPY: the add kernels read the arrivals from the neighbours' buffers and
     // store them on to the landing buffers in the same pass (ring: 16 bytes per element instead of a copy's 8 plus
@@ -947,8 +947,9 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     const int n_groups = (S + group - 1) / group;
     std::vector<hipEvent_t> ev;
     // A few-rows launch that carries its deliveries also takes shapes that no other launch carries them for, whose copies
-    // would be on the copy stream: it starts behind what that stream holds, as they would.
-    const bool joined = two_streams && few_rows && carried;
+    // would be on the copy stream: it starts behind what that stream holds, as they would.  So does an all-gather over a ragged
+    // k range.
+    const bool joined = two_streams && carried && (few_rows || (kind == CF_KIND_AG && r.k % 64 != 0));
     if (grouped || joined) {
         if (cf_status st = get_events(1 + (size_t)n_groups, &ev))
             return st;

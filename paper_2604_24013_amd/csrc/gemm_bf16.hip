@@ -438,7 +438,7 @@ double gemm_bf16_rank_step_us(const GemmParams &p, int num_cu)
 {
     double us = 0.0;
     tile_by_estimate(p, num_cu, &us);                // (a rank step's k range is not split)
-    // an all-gather of ragged k-tiles has its deliveries copied in front: 6 us, and 0.8 us per megabyte of them
+    // an all-gather that cannot carry its deliveries has them copied in front: 6 us, and 0.8 us per megabyte of them
     return gemm_share_with_recv(p) == 0.0 && !gemm_bf16_dl_carries_operand(p) ? us + 6.0 : us;
 }
 

@@ -492,12 +492,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     int carry_at = (CARRY_A && cLand != nullptr && cRecv == nullptr) ? tile / tiles_m : 0x7fffffff;
     __amdgpu_buffer_rsrc_t la_rsrc =
         __builtin_amdgcn_make_buffer_rsrc(cLand, 0, (CARRY_A && cLand != nullptr) ? (int)a_bytes : 0, 0x00020000);
-    auto carry_tile = [&](int kt, int stage_a) __attribute__((always_inline)) {
+    // (A ragged k-tile is the last of a work item, LAST: its lanes beyond the k range store nothing.)
+    auto carry_tile = [&](int kt, int stage_a, auto last_tag) __attribute__((always_inline)) {
         const int k0 = ktile(kt) * BK;
+        const bool ragged = decltype(last_tag)::value && k0 + BK > K;
 #pragma unroll
         for (int j = 0; j < A_LD; ++j) {
             const u32x4_t t = *reinterpret_cast<const u32x4_t *>(smem + stage_a * A_BYTES + (j * NW + wave) * 1024 + lane * 16);
-            __builtin_amdgcn_raw_buffer_store_b128(t, la_rsrc, (int)a_off[MF16 ? 0 : j], k0 * 2 + j * a_jstep, 0);
+            unsigned off = a_off[MF16 ? 0 : j];
+            if (ragged)
+                off = k0 + chunk_k(j, false, 0) < K ? off : OOB;
+            __builtin_amdgcn_raw_buffer_store_b128(t, la_rsrc, (int)off, k0 * 2 + j * a_jstep, 0);
         }
         carry_at += tiles_n;
     };
@@ -890,7 +895,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
                     la(std::integral_constant<int, 2>{}), la(std::integral_constant<int, 3>{}), plain_ph2(ca, cw));
             auto publish = [&]() __attribute__((always_inline)) {
                 if (CARRY_A && kt == carry_at) {     // tile kt goes on to the landing buffer: its stores are the
-                    carry_tile(kt, ca);              // youngest requests and need not be awaited here
+                    carry_tile(kt, ca, std::false_type{});              // youngest requests and need not be awaited here
                     wait_vmcnt<(NS - 2) * LPT + 2 * A_LD>();
                 } else {
                     wait_vmcnt<(NS - 2) * LPT + A_LD>();
@@ -921,7 +926,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             front16(ca, cw, nothing, nothing, nothing, nothing, plain_ph2(ca, cw));
             phase16(p2_t{}, afA, wfB, afB, wfA, on_t{}, ca, 1, 3, nothing, c0{}, 0, 0, c0{}, off_t{}, 0, 0, 0, nothing, nothing);
             if (CARRY_A && nk - 1 == carry_at)
-                carry_tile(nk - 1, ca);
+                carry_tile(nk - 1, ca, std::true_type{});
             phase16(p3_t{}, afB, wfB, afA, wfA, off_t{}, 0, 0, 0, nothing, c0{}, 0, 0, c0{}, off_t{}, 0, 0, 0, nothing, nothing);
         };
         asm volatile("" : "+s"(kt));                     // (keeps the compiler from peeling the loop below: it spills)
@@ -973,7 +978,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase(af1, wf1, true, ca, cw, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
             phase(af0, wf0, true, ca, cw, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
             if (CARRY_A && kt == carry_at) {         // tile kt goes on to the landing buffer: its stores are the
-                carry_tile(kt, ca);                  // youngest requests and need not be awaited here
+                carry_tile(kt, ca, std::false_type{});                  // youngest requests and need not be awaited here
                 wait_vmcnt<BEHIND + A_LD>();
             } else {
                 wait_vmcnt<BEHIND>();
@@ -1017,7 +1022,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase(af1, wf1, true, cur_a, cur_w, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
             phase(af0, wf0, true, cur_a, cur_w, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
             if (CARRY_A && nk - 1 == carry_at)
-                carry_tile(nk - 1, cur_a);
+                carry_tile(nk - 1, cur_a, std::true_type{});
             phase(af1, wf1, false, 0, 0, 0, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
         }
     } else {
@@ -1055,7 +1060,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase_b(af0, wf0, true, cur, 3, af1, wf1, rpm2{});   // reads early: complete at the barrier
             // tile kt+1 complete, NS-2 later tiles may be in flight
             if (CARRY_A && kt == carry_at) {         // tile kt goes on to the landing buffer (stores not awaited here)
-                carry_tile(kt, cur);
+                carry_tile(kt, cur, std::false_type{});
                 wait_vmcnt<(NS - 2) * LPT + A_LD>();
             } else {
                 wait_vmcnt<(NS - 2) * LPT>();
@@ -1072,7 +1077,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase_b(af1, wf1, true, cur, 2, af0, wf0, rpm1{});
             phase_b(af0, wf0, true, cur, 3, af1, wf1, rpm1{});
             if (CARRY_A && nk - 1 == carry_at)
-                carry_tile(nk - 1, cur);
+                carry_tile(nk - 1, cur, std::true_type{});
             phase_b(af1, wf1, false, 0, 0, af0, wf0, rpm1{});
         }
     }
@@ -1337,10 +1342,13 @@ bool gemm_bf16_dl_supported(const GemmParams &p, bool w_kn)
 }
 
 // Can a persistent all-gather launch carry its deliveries (GemmParams::land_step with steps that add nothing)?  Every
-// tile shape can; the k-tiles must be whole (a ragged one would be stored beyond the end of its rows).
+// tile shape can.  Slices with padding between their rows only over whole k-tiles: a copy in front moves the padding and the
+// kernel does not, and which of the two a caller finds is part of the interface.  (All slices whose k is no multiple of 64
+// used to be copied in front, us per rank step copied / carried: 4 x 130 x 2280 x 1696 25.4 / 16.6, 8 x 264 x 632 x 2848 40.0 /
+// 26.4, 8 x 103 x 2176 x 816 17.9 / 12.5, 4 x 177 x 2256 x 5976 73.5 / 48.3, 8 x 705 x 4888 x 4184 246 / 242.)
 bool gemm_bf16_dl_carries_operand(const GemmParams &p)
 {
-    return p.n_steps > 0 && !p.a_t && p.K % BK == 0;
+    return p.n_steps > 0 && !p.a_t && (p.K % BK == 0 || p.lda == p.K);
 }
 
 hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t, int num_cu)

@@ -135,3 +135,15 @@ def test_pairwise_steps_and_rank_steps_take_the_same_kernel(dry, p, mc, n, k):
     one, = dry.calls(lambda: cf.run_schedule(desc, cf.CF_KIND_RS_PAIR, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))
     step, = dry.calls(lambda: cf.rs_pair_step(desc, 0, P(0), P(1), None, None, P(3)))
     assert one[0].startswith("gemm_rows_kernel") and step[0].startswith("gemm_rows_kernel")
+
+
+@pytest.mark.parametrize("k,pad,off,copied", [(1096, 0, 0, False), (1096, 8, 0, True), (1096, 0, 8, True), (1088, 64, 0, False), (1088, 0, 0, False)])
+def test_slices_over_a_ragged_k_range_are_carried(dry, monkeypatch, k, pad, off, copied):
+    """... unless a copy would move the padding between their rows, or lies off the 16-byte grid."""
+    p = 8
+    stage, each, _ = _tables(p)
+    stage[2] += off
+    bufs = cf.make_buffers(P(0), P(1), P(2), stage, (None, None), (None, None), None, each)
+    desc = cf.layer_desc(p, 1, 512, 1536, k, lda=k + pad)
+    kernels = [c[0] for c in dry.calls(lambda: cf.run_schedule(desc, cf.CF_KIND_AG, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))]
+    assert kernels[-1].startswith("gemm_bf16_dl_kernel") and (len(kernels) > 1) == copied
