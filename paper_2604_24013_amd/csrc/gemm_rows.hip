@@ -490,8 +490,10 @@ hipError_t launch_any(const RowsParams<SEG> &p, bool w_kn, RowsShape t, hipStrea
 // round over the chip; 64 x 64 where none is.  bf16 [k x n] weights take at least two column groups (a 32-byte piece of
 // every k-row is a quarter of a line).  Measured, us (rows x n x k, [k x n] / [n x k] weights): 8 x 4096 x 1376 32-column tiles
 // 4.8 / 4.5, 64-column 5.6 / 5.4; 64 x 8192 x 3584 32 x 64 tiles 15.2 / 14.6, 64 x 64 18.1 / 17.5, 16 x 64 24.5 / -.
-// A k range of 16 slices per wave and more on a quarter of the chip or less is split over four workgroups (8 x 520 x 8192
-// bf16 [k x n] 12.2 -> 9.3 us); bf16 [n x k] tiles stream as fast unsplit (7.2 us).  Single bf16 steps only: fp32 steps and
+// A k range of [k x n] weights on a small part of the chip is split: over four workgroups from 48 slices where a quarter of the
+// chip has a tile or less, over two from 64 where half has (us whole / split, bf16: 20 x 136 x 7824 17.4 / 8.5, 28 x 1008 x 7016
+// 14.2 / 9.2, 44 x 272 x 5568 11.8 / 8.0; in two 54 x 632 x 4480 10.3 / 8.7, 20 x 1176 x 7224 16.9 / 11.4; at 40 slices 57 x 400 x
+// 2512 6.7 / 6.9).  bf16 [n x k] tiles stream as fast unsplit (84 x 160 x 4096 5.9 / 6.8).  Single bf16 steps only: fp32 steps and
 // rank steps in one launch take no workspace, so that several of them may be in flight on streams that share one.
 RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num_cu)
 {
@@ -511,8 +513,8 @@ RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num
             break;
     }
     const int slices = (K + (bf16 ? 63 : 31)) / (bf16 ? 64 : 32);
-    if (w_kn && bf16 && t.mf * t.nc <= 4 && slices >= 16 * 8 && wgs * 4 <= num_cu)
-        t.ks = 4;
+    if (w_kn && bf16 && t.mf * t.nc <= 4)
+        t.ks = slices >= 48 && wgs * 4 <= num_cu ? 4 : slices >= 64 && wgs * 2 <= num_cu ? 2 : 1;
     return t;
 }
 
