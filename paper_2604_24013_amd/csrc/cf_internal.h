@@ -161,6 +161,8 @@ double gemm_bf16_tile_us(const GemmParams &p, int num_cu);
 double gemm_f32_tile_us(const GemmParams &p, int num_cu);
 // Bytes of partial tiles that kernel parks when it splits the k range of this single step (0: it does not).
 size_t gemm_rows_ws_bytes(const GemmParams &p, bool bf16, bool w_kn, int num_cu);
+// ... and the tile kernels, of this single step or weight gradient.
+size_t gemm_bf16_split_ws_bytes(const GemmParams &p, bool w_kn, int num_cu);
 hipError_t launch_gemm_rows(const GemmParams &p, bool bf16, bool w_kn, bool out_bf16, hipStream_t s, int num_cu);
 hipError_t launch_gemm_f32(const GemmParams &p, bool w_kn, hipStream_t s, int num_cu);
 

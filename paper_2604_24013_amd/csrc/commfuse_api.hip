@@ -1723,10 +1723,24 @@ cf_status commfuse_run_attn_schedule(const cf_attn_desc *desc, const cf_attn_buf
 size_t commfuse_workspace_bytes(const cf_layer_desc *desc, int kind)
 {
     Resolved r;
-    if (is_wgrad_kind(kind)) {                     // k-splits of a [k x n] gradient tile
+    const int ncu = num_cu_of_current_device();
+    if (is_wgrad_kind(kind)) {                     // k-splits of a [k x n] gradient tile, over one step's rows or all of them
         if (resolve(desc, kind, &r) != CF_OK || !r.bf16_in)
             return 0;
-        return WS_COUNTER_BYTES + (size_t)WS_MAX_SPLITS * (size_t)r.k * (size_t)r.n * sizeof(float);
+        size_t bytes = (size_t)WS_MAX_SPLITS * (size_t)r.k * (size_t)r.n * sizeof(float);
+        cf::GemmParams g;
+        g.a_t = true;
+        g.lda = r.lda;
+        g.ldw = r.ldw;
+        g.ldo = r.ldo;
+        g.M = (int)r.k;
+        g.N = (int)r.n;
+        for (const int64_t rows : {r.mc, r.mc * r.m * r.p}) {
+            g.K = (int)rows;
+            const size_t parts = cf::gemm_bf16_split_ws_bytes(g, true, ncu);
+            bytes = parts > bytes ? parts : bytes;
+        }
+        return WS_COUNTER_BYTES + bytes;
     }
     if (kind != CF_KIND_RS && kind != CF_KIND_AG && kind != CF_KIND_RS_PAIR)
         return 0;                                  // the gradient path needs none
@@ -1734,9 +1748,10 @@ size_t commfuse_workspace_bytes(const cf_layer_desc *desc, int kind)
         return 0;
     cf::GemmParams step;
     fill_shape(step, r);
-    const size_t tiles = (size_t)WS_MAX_SPLITS * (size_t)r.mc * (size_t)r.n * sizeof(float);
-    const size_t rows = cf::gemm_rows_ws_bytes(step, r.bf16_in, r.w_kn, num_cu_of_current_device());   // (whole tiles: more than the step's elements)
-    return WS_COUNTER_BYTES + (rows > tiles ? rows : tiles);
+    size_t bytes = (size_t)WS_MAX_SPLITS * (size_t)r.mc * (size_t)r.n * sizeof(float);
+    for (const size_t parts : {cf::gemm_rows_ws_bytes(step, r.bf16_in, r.w_kn, ncu), cf::gemm_bf16_split_ws_bytes(step, r.w_kn, ncu)})
+        bytes = parts > bytes ? parts : bytes;     // (whole tiles: more than the step's elements)
+    return WS_COUNTER_BYTES + bytes;
 }
 
 cf_status commfuse_set_workspace(void *device_ptr, size_t bytes, void *hip_stream)

@@ -284,6 +284,14 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
 
 }  // namespace
 
+// What the main loop and the hand-over of a k range split over ks workgroups per 128x128 tile take, in microseconds: a round,
+// the k-tiles of a split and what all of them together ask of the caches, and the partial tiles (64 KiB each) there and back.
+static double bf16_split_us(int tiles, int ktiles, int ks, int num_cu)
+{
+    const double per = (ktiles + ks - 1) / ks;
+    return 4.5 + 0.34 * per + 0.23 * per * tiles * ks / num_cu + (ks > 1 ? 1.1 + 0.55 * ks + 0.011 * tiles * ks : 0.0);
+}
+
 TileChoice choose_tile_bf16(int M, int N, int K, int num_cu)
 {
     // Measured on MI355X: the kernels are bound by the rate at which a CU can pull operand tiles
@@ -297,12 +305,19 @@ TileChoice choose_tile_bf16(int M, int N, int K, int num_cu)
     if (tiles(256, 128) >= want) return TileChoice{256, 128, 1};
     const int t128 = tiles(128, 128);
     if (t128 > num_cu) return t;                 // two workgroups per CU, two stages each
+    // A grid of one workgroup per compute unit and less: the number of splits with the lowest estimate (us of a launch, fitted to
+    // 229 weight gradients of 128..5768 rows split in 1 to 8, rms 0.06, but for a constant; steps fit it too).  us unsplit / as
+    // chosen: 552 x 536 over 5768 rows 43.7 / 19.5 (in six), 520 x 856 over 2544 in four 25 / 15.4, 776 x 1368 over 912 12.1 (unsplit; two 15).
     t.deep = true;
     const int ktiles = (K + 63) / 64;
-    if (t128 * 3 <= num_cu && ktiles / 3 >= 16)
-        t.splitk = 3;
-    else if (t128 * 2 <= num_cu && ktiles / 2 >= 16)
-        t.splitk = 2;
+    double best = 0.0;
+    for (int ks = 1; ks <= 8 && t128 * ks <= num_cu && ktiles >= 2 * ks; ++ks) {
+        const double us = bf16_split_us(t128, ktiles, ks, num_cu);
+        if (ks == 1 || us < best) {
+            best = us;
+            t.splitk = ks;
+        }
+    }
     return t;
 }
 
@@ -444,23 +459,41 @@ double gemm_bf16_rank_step_us(const GemmParams &p, int num_cu)
 
 double gemm_bf16_tile_us(const GemmParams &p, int num_cu)
 {
-    // Fitted to single steps with a B_in (128x128: 256 x 4096 x 1376 19.9 us, 256 x 8192 x 3584 38.8 us; 256x128: 1024 x 8192
-    // x 1024 29.3 us, x 3584 68 us) and, for 256x256, to one round of a rank step.
     const TileChoice t = tile_by_area(p, num_cu);
-    const int64_t items = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * (p.n_steps > 0 ? p.n_steps : 1);
-    const int64_t wgs = (int64_t)num_cu * (t.bm == 128 && !t.deep ? 2 : 1);
-    const double kt = (p.K + 63) / 64;
-    const double round = t.bm == 128 ? 8 + 0.55 * kt : t.bn == 128 ? 14 + 0.97 * kt : 14 + 1.5 * kt;
-    const double whole = (double)((items + wgs - 1) / wgs) * round;
-    if (t.splitk <= 1 || p.n_steps > 0 || p.ws == nullptr || p.counters == nullptr || items > p.max_tiles ||
-        (size_t)t.splitk * p.M * p.N * sizeof(float) > p.ws_bytes)
-        return whole;
-    // A step whose k range the launcher splits through the workspace (the hand-over takes 10 us and more): fitted to M x N from
-    // 64 x 520 to 1024 x 2048, splits in two and three (rms 2.4 us): 384 x 4096 x 8192 59 us (the few-rows kernel 66),
-    // 256 x 8192 x 8192 61 (77), 768 x 1536 x 8192 50 (63).  Short ranges come out longer split than whole; there the
-    // smaller figure stands for the kernel.
-    const double split = 18.5 + 5.1 * (double)(items * t.splitk) / num_cu + 0.6 * (((p.K + 63) / 64 + t.splitk - 1) / t.splitk);
-    return split < whole ? split : whole;
+    const int64_t tiles = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
+    if (p.n_steps > 0) {                             // rank steps over k ranges that tile_estimate_us has not seen
+        const int64_t items = tiles * p.n_steps, wgs = (int64_t)num_cu * (t.bm == 128 && !t.deep ? 2 : 1);
+        const double kt = (p.K + 63) / 64;
+        const double round = t.bm == 128 ? 8 + 0.55 * kt : t.bn == 128 ? 14 + 0.97 * kt : 14 + 1.5 * kt;
+        return (double)((items + wgs - 1) / wgs) * round;
+    }
+    double us = 0.0;
+    if (t.splitk > 1 && p.ws != nullptr && p.counters != nullptr && tiles <= p.max_tiles &&
+        (size_t)(tiles * t.splitk) * t.bm * t.bn * sizeof(float) <= p.ws_bytes) {
+        // a step whose k range the launcher splits through the workspace: fitted to 759 steps of 64..1024 x 128..8192 x 512..8192
+        // with a B_in, split in 1 to 8 (rms 0.08): 213 x 3496 x 6448 in four 28 us (the few-rows kernel 33), 372 x 4736 x 2184 in two 22
+        const double per = ((p.K + 63) / 64 + t.splitk - 1) / t.splitk, all = (double)(tiles * t.splitk);
+        us = 7.6 + 0.44 * per + 0.145 * per * all / num_cu + 0.61 * t.splitk + 0.012 * all;
+    } else {
+        tile_by_estimate(p, num_cu, &us);
+        if (us == 0.0)                               // (no workspace for the splits: 384 x 4096 x 8192 72 us, the few-rows kernel 61)
+            us = 1.05 * tile_estimate_us(p, TileChoice{128, 128, 1, true}, num_cu, gemm_share_with_recv(p));
+    }
+    return us;
+}
+
+size_t gemm_bf16_split_ws_bytes(const GemmParams &p_in, bool w_kn, int num_cu)
+{
+    GemmParams p = p_in;                             // (as it is launched with a workspace)
+    p.ws = reinterpret_cast<float *>(16);
+    p.counters = reinterpret_cast<unsigned *>(16);
+    p.ws_bytes = ~(size_t)0;
+    p.max_tiles = 1 << 30;
+    if (p.M <= 0 || p.N <= 0 || p.K <= 0 || gemm_rows_takes(p, true, w_kn, num_cu))
+        return 0;
+    const TileChoice t = tile_of_launch(p, num_cu);
+    const size_t tiles = (size_t)((p.M + t.bm - 1) / t.bm) * (size_t)((p.N + t.bn - 1) / t.bn);
+    return t.splitk > 1 ? tiles * t.splitk * t.bm * t.bn * sizeof(float) : 0;
 }
 
 bool gemm_bf16_carries_delivery(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu, bool reduce_scatter)

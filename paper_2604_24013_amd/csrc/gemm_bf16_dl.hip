@@ -1084,14 +1084,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // no direct load may outlive its LDS allocation (the early requests of B_in are younger than all of them)
     wait_vmcnt<EARLY_LOADS>();
 
-    // Row and first column (of four) of accumulator registers 4g .. 4g+3 of this lane's 32x32 sub-tile (i, j).
-    auto e_row = [&](int i, int g) __attribute__((always_inline)) {
-        return MF16 ? m0 + wm * WTM + i * 32 + 16 * (g >> 1) + (lane & 15) : m0 + wm * WTM + i * 32 + (lane & 31);
-    };
-    auto e_col = [&](int j, int g) __attribute__((always_inline)) {
-        return MF16 ? n0 + wn * WTN + j * 32 + 16 * (g & 1) + 4 * (lane >> 4) : n0 + wn * WTN + j * 32 + g * 8 + (lane >> 5) * 4;
-    };
-
     // Split-K: every split parks its fp32 partial tile in the workspace; the split that finishes
     // last sums all partials in split order (so the result does not depend on which one that is),
     // then runs the epilogue.  No split ever waits for another.
@@ -1099,23 +1091,27 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // L2s around the hand-over, the partial tiles and the arrival counter are accessed with the
     // device-coherent cache policy (sc0 sc1: stores write through to memory, loads and the atomic
     // are served there), which keeps every other line of every L2 in place.
+    // Bound by the trips to memory: so a partial is parked in the order the threads hold it, 1 KiB of whole lines per store (as
+    // a row-major plane it left in 16-byte pieces, each a write to memory of its own), and the last split has the partials of
+    // two splits in flight at once.  us, before / now: weight gradients 552 x 536 over 5768 rows
+    // in three splits 34.8 / 23.3, 1200 x 520 over 2584 24.5 / 18.3, 520 x 856 over 2544 24.8 / 17.8.
     if (splits > 1) {
         constexpr int COHERENT = 1 | 16;         // buffer cache-policy bits sc0 | sc1
-        const size_t plane = (size_t)M * N;
-        __amdgpu_buffer_rsrc_t ws_rsrc =
-            __builtin_amdgcn_make_buffer_rsrc(P.ws + (size_t)split * plane, 0, (int)(plane * 4), 0x00020000);
+        constexpr int TILE_FLOATS = BM * BN;
+        // (row blocks and splits at a time: the four-stage 128x128 tile, the one that a rule splits, has registers for all of two)
+        constexpr int IB = NS > 2 ? TM : 1, SP_AHEAD = NS > 2 ? 2 : 1;
+        auto part_rsrc = [&](int sp) __attribute__((always_inline)) {
+            return __builtin_amdgcn_make_buffer_rsrc(P.ws + ((size_t)tile * splits + sp) * TILE_FLOATS, 0, TILE_FLOATS * 4, 0x00020000);
+        };
+        auto part_offset = [&](int i, int j, int g) __attribute__((always_inline)) { return (((i * TN + j) * 4 + g) * 64 * NW + tid) * 16; };
+        __amdgpu_buffer_rsrc_t ws_rsrc = part_rsrc(split);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int m = e_row(i, g), n = e_col(j, g);
-                    const int boff = (m < M && n < N) ? (int)(((unsigned)m * (unsigned)N + n) * 4u) : (int)OOB;
-                    const f32x4_t o = acc_get(i, j, g);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), ws_rsrc, boff, 0, COHERENT);
-                }
-        }
+                for (int g = 0; g < 4; ++g)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc_get(i, j, g)), ws_rsrc, part_offset(i, j, g), 0, COHERENT);
         __builtin_amdgcn_s_waitcnt(0);           // this wave's partial stores are acknowledged
         __syncthreads();                         // ... and every wave's
         unsigned *arrived = reinterpret_cast<unsigned *>(smem);   // the stages are no longer read by anyone
@@ -1127,23 +1123,25 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
         if (tid == 0)                            // leave the counter ready for the next launch
             __hip_atomic_store(&P.counters[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
+        for (int i0 = 0; i0 < TM; i0 += IB) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int i = i0; i < i0 + IB; ++i)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int m = e_row(i, g), n = e_col(j, g);
-                    const int boff = (m < M && n < N) ? (int)(((unsigned)m * (unsigned)N + n) * 4u) : (int)OOB;
-                    f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
-                    for (int sp = 0; sp < splits; ++sp) {
-                        __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                            P.ws + (size_t)sp * plane, 0, (int)(plane * 4), 0x00020000);
-                        const f32x4_t v =
-                            __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, boff, 0, COHERENT));
-                        sum = sp == 0 ? v : sum + v;
-                    }
-                    acc_set(i, j, g, sum);
-                }
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        acc_set(i, j, g, f32x4_t{0.f, 0.f, 0.f, 0.f});
+#pragma unroll SP_AHEAD
+            for (int sp = 0; sp < splits; ++sp) {
+                __amdgpu_buffer_rsrc_t rs = part_rsrc(sp);
+#pragma unroll
+                for (int i = i0; i < i0 + IB; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g)
+                            acc_set(i, j, g, acc_get(i, j, g) + __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, part_offset(i, j, g), 0, COHERENT)));
+            }
         }
     }
 
@@ -1362,9 +1360,8 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
     if (p.splits > nk_all)
         p.splits = nk_all;
     const int64_t tiles = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
-    if (p.splits > 1 && (p.ws == nullptr || p.counters == nullptr ||
-                         (size_t)p.splits * p.M * p.N * sizeof(float) > p.ws_bytes || tiles > p.max_tiles ||
-                         (int64_t)p.M * p.N * 4 >= ((int64_t)1 << 31)))
+    if (p.splits > 1 && (p.ws == nullptr || p.counters == nullptr || tiles > p.max_tiles ||
+                         (size_t)tiles * p.splits * t.bm * t.bn * sizeof(float) > p.ws_bytes))
         p.splits = 1;                          // no (or too small a) workspace: plain kernel
     if (p.cp_src == nullptr || p.cp_dst == nullptr || p.cp_bytes == 0)
         p.cp_wgs = 0;

@@ -525,12 +525,12 @@ RowsShape choose_shape(int64_t rows, int N, int K, bool bf16, bool w_kn, int num
 // 3.1 us and 4.8 us + 0.0158 us per k a round, which wins over long k ranges (bound by the fp32 MFMAs: 1024 x 1024 x 4096 73 us, 143;
 // 512 x 4096 x 4096 142, 175) and not over short ones (2048 x 8192 x 512 206, 153; 768 x 4096 x 256 27, 22; 335 x 2328 x 160 9.6, 9.0)
 // nor over grids that the 128 x 128 tiles fill (4096 x 8192 x 4096 2222, 2076).
-// bf16: half a round over the chip and less always.  Rows that do not start on a 128-byte line put every slice of theirs on two: 1.12
-// times the time per 64 k (575 x 3336 x 7328 80 us, the tile kernel 70), 1.45 times where it is [k x n] weights too large for the
-// caches (4 x 148 x 4408 x 5648 154, 107; 85 x 7512 x 6304 54, 47).
-//  * Single steps: 1.5 us, and 3.6 us + 0.27 us per 64 k a round of 64 x 64 tiles (128 x 8192 x 3584 18.7 us warm, 256 x 8192 x 3584
-//    34.4, 512 x 4096 x 1376 21.5).  Of 851 drawn steps of 16 to 1024 rows x 128..8192 x 128..8192, each timed on both kernels on
-//    buffers that come round and on cold ones, 7 are 10 % and more behind the faster kernel by this rule, 0.3 % on average.
+// bf16: half a round over the chip and less always.  Rows that do not start on a 128-byte line put every slice of theirs on two.
+//  * Single steps: 4.6 us, what 64 k cost a round of tiles (by their area, a 64 x 64 tile being 1; 1.12 times that where
+//    k-contiguous rows do not start on 128-byte lines) and the megabytes of fp32 output (fitted to 326 steps, rms 0.12).  Of 350 drawn steps of 16 to 1024 rows x 128..8192 x
+//    128..8192, each timed on both kernels, 3 are 10 % and more behind the faster one by this rule, 0.2 % on average.  us, this
+//    kernel / the tile kernel: 319 x 1688 x 4528 [k x n] 23 / 32 (now in six splits), 213 x 3496 x 6448 33 / 28 (in four),
+//    165 x 3472 x 168 [n x k] 5.1 / 6.5, 474 x 1072 x 7768 28.7 / 25.9, 584 x 6456 x 2232 48 / 26.
 //  * The steps of a rank step in one launch: a constant, what a round of tiles costs (by their area, a 64 x 64 tile being 1), what
 //    64 k cost a round (1.15 times that where the rows of [k x n] weights do not start on 128-byte lines, 1.12 times for [n x k]
 //    weights, 1.06 times for the activations alone), and the megabytes of fp32 output with the deliveries that go with it; taken
@@ -564,20 +564,15 @@ bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu)
     const int64_t rounds = (wgs + num_cu - 1) / num_cu;
     if (!bf16)
         return 3.1 + rounds * (4.8 + 0.0158 * p.K) < gemm_f32_tile_us(p, num_cu);
-    const double kt = (p.K + 63) / 64, adds = gemm_share_with_recv(p);
+    const double kt = (p.K + 63) / 64, adds = gemm_share_with_recv(p), area = t.mf * t.nc / 16.0, mo = 4e-6 * rows * p.N;
+    const bool off_lines = p.lda % 64 != 0 || (!w_kn && p.ldw % 64 != 0);
     if (p.n_steps > 0 && p.K < 8192 && (adds == 0.0 || adds >= 0.5)) {
-        const double area = t.mf * t.nc / 16.0, mo = 4e-6 * rows * p.N;
         const double slices = kt * (w_kn && p.ldw % 64 != 0 ? 1.15 : !w_kn && p.ldw % 64 != 0 ? 1.12 : p.lda % 64 != 0 ? 1.06 : 1.0);
-        const double us = 3.9 + rounds * (2.2 * area + slices * (0.067 + 0.148 * area)) + (0.79 + 0.4 * adds) * mo;
-        return 0.97 * us < gemm_bf16_rank_step_us(p, num_cu);
+        return 0.97 * (3.9 + rounds * (2.2 * area + slices * (0.067 + 0.148 * area)) + (0.79 + 0.4 * adds) * mo) < gemm_bf16_rank_step_us(p, num_cu);
     }
-    double slices = kt;
-    if (w_kn && p.ldw % 64 != 0 && 2.0 * p.N * p.K > 40e6)
-        slices *= 1.45;
-    else if (p.lda % 64 != 0 || (!w_kn && p.ldw % 64 != 0))
-        slices *= 1.12;
-    const double us = p.n_steps > 0 ? 1.5 + rounds * (3.6 + 3.7 * t.mf * t.nc / 16 + 0.235 * slices) + 0.02e-6 * 2.0 * p.N * p.K
-                                    : 1.5 + rounds * (3.6 + 0.27 * slices);
+    const double slices = kt * (off_lines ? 1.12 : 1.0);
+    const double us = p.n_steps > 0 ? 1.5 + rounds * (3.6 + 3.7 * area + 0.235 * slices) + 0.02e-6 * 2.0 * p.N * p.K
+                                    : 4.6 + rounds * slices * (0.035 + 0.177 * area) + (0.38 + 0.2 * adds) * mo;
     return us < gemm_bf16_tile_us(p, num_cu);
 }
 

@@ -147,3 +147,39 @@ def test_slices_over_a_ragged_k_range_are_carried(dry, monkeypatch, k, pad, off,
     desc = cf.layer_desc(p, 1, 512, 1536, k, lda=k + pad)
     kernels = [c[0] for c in dry.calls(lambda: cf.run_schedule(desc, cf.CF_KIND_AG, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))]
     assert kernels[-1].startswith("gemm_bf16_dl_kernel") and (len(kernels) > 1) == copied
+
+
+@pytest.mark.parametrize("m,n,rows,tiles,splits", [(552, 536, 5768, 25, 7), (520, 856, 2544, 35, 4), (776, 1368, 912, 77, 1), (2048, 2048, 8192, 256, 1)])
+def test_splits_of_a_weight_gradient(dry, m, n, rows, tiles, splits):
+    cf_lib = dry.calls(lambda: (cf.set_workspace(P(9), 1 << 30), cf.wgrad_step(cf.layer_desc(1, 0, rows, n, m), 0, P(0), P(1), P(2)), cf.set_workspace(None)))
+    (kernel, grid, _), = [c for c in cf_lib if "gemm" in c[0]]
+    assert grid == tiles * splits or (splits == 1 and grid < tiles)
+
+
+def test_a_workspace_too_small_for_the_partial_tiles_leaves_the_k_range_whole(dry):
+    grids = []
+    for room in (0, 16):                                          # 25 tiles of 64 KiB in seven splits, to the byte and 16 bytes short
+        calls = dry.calls(lambda: (cf.set_workspace(P(9), (64 << 10) + 25 * 7 * (64 << 10) - room),
+                                   cf.wgrad_step(cf.layer_desc(1, 0, 5768, 536, 552), 0, P(0), P(1), P(2)), cf.set_workspace(None)))
+        grids += [c[1] for c in calls if "gemm" in c[0]]
+    assert grids == [175, 25]
+
+
+@pytest.mark.parametrize("kind,p,mc,n,k", [(cf.CF_KIND_WGRAD_X, 8, 721, 536, 552), (cf.CF_KIND_RS, 2, 213, 3496, 6448), (cf.CF_KIND_RS, 2, 130, 5000, 8184),
+                                           (cf.CF_KIND_AG, 2, 200, 712, 8192)])
+def test_workspace_bytes_cover_the_splits(dry, kind, p, mc, n, k):
+    """A workspace of that size lets a call split as a larger one does."""
+    desc = cf.layer_desc(p, 0, mc, n, k)
+    need = cf.workspace_bytes(desc, kind)
+    def grid(size):
+        def call():
+            cf.set_workspace(P(9), size)
+            if kind == cf.CF_KIND_WGRAD_X:
+                cf.wgrad_step(cf.layer_desc(1, 0, p * mc, n, k), 0, P(0), P(1), P(2))
+            elif kind == cf.CF_KIND_RS:
+                cf.rs_step(desc, 1, P(0), P(1), P(2), P(3))
+            else:
+                cf.ag_step(desc, 1, P(0), P(1), P(2))
+            cf.set_workspace(None)
+        return [c for c in dry.calls(call) if "gemm" in c[0]]
+    assert grid(need) == grid(1 << 32)
