@@ -336,7 +336,7 @@ enum {
                             CF_FUSED_COPY no copy is launched: the add kernels read the arrivals from
                             the neighbours' buffers (peer_stage) and store them on to recv_each in the
                             same pass (same sums, bit for bit).
-                            With CF_FUSED_COPY (CF_KIND_RS, CF_KIND_AG): the delivery is carried by the
+                            With CF_FUSED_COPY (CF_KIND_RS, CF_KIND_AG, CF_KIND_WGRAD_*): the delivery is carried by the
                             consumer -- no copy is launched, the emulated transfer runs inside the kernel.
                             Reduce-scatter (the projection of the attention layer too): the epilogue reads B_in from
                             the neighbour's buffer (peer_stage), adds it to the finished product and stores it to the
@@ -344,7 +344,10 @@ enum {
                             their share of the memory traffic, half of the workgroups land theirs in front of their main
                             loop.  All-gather: the kernel takes the gathered slices from the
                             neighbours' buffers as its left operand, and every k-tile that comes in is
-                            stored on to the landing buffer by one of the workgroups that load it.  A carried row
+                            stored on to the landing buffer by one of the workgroups that load it.  Weight gradient:
+                            likewise, whichever operand travels, where the launch runs whole 256x256 tiles of dW, the
+                            blocks of m_chunk rows are multiples of 64 from 128 on and have no padding between their
+                            rows (same sums, bit for bit; else copied in front).  A carried row
                             block lands without the padding of its rows, one copied in front with it.  Copied in front,
                             as without the flag, are: slices of an all-gather with padding between their rows (lda != k)
                             whose k is not a multiple of 64; partial sums with

@@ -65,6 +65,12 @@ struct GemmParams {
     void *cp_dst = nullptr;
     size_t cp_bytes = 0;
     int cp_wgs = 0;
+    // A weight gradient that carries its deliveries (one step, a_t, whole 256x256 tiles): the rows of one operand come in
+    // blocks of hop_tiles k-tiles, block b at A_step[1 + b] -- the address that row 0 of a gathered buffer would have --, and
+    // every k-tile but those of block hop_own is stored on to land_step[0], the gathered buffer, by one of the workgroups that
+    // load it.  hop_right: it is the right operand that travels.  A (W) points at block 0.
+    int hop_tiles = 0, hop_own = 0;
+    bool hop_right = false;
     // Few-rows kernel only: where recv_more[i] is stored on to (nullable).  Last on purpose: between recv_more and out it made
     // every single step of the tile kernels with [n x k] weights 0.65 us longer (384 x 4096 x 512: 14.2 -> 14.85 us), with code
     // that differs in nothing but register numbers and the fields' offsets in the kernel argument.
@@ -141,6 +147,8 @@ bool gemm_bf16_takes_recv_list(const GemmParams &p, bool w_kn);
 // True if launch_gemm_bf16 would run this persistent launch (reduce_scatter: its steps add a received partial;
 // else an all-gather's) on a kernel that honours GemmParams::land_step (the delivery carried by the consumer)
 // for every step that receives.
+// the same for a weight gradient (GemmParams::hop_tiles), of the shape that is launched
+bool gemm_bf16_carries_gathered(const GemmParams &p, int num_cu);
 bool gemm_bf16_carries_delivery(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu, bool reduce_scatter);
 // Steps per launch when a persistent rank step of p.n_steps steps is cut into launches that fill the chip about once
 // each (equal groups; p.n_steps when the whole rank step is one round or less).
@@ -149,6 +157,7 @@ int gemm_bf16_steps_per_launch(const GemmParams &p, bool w_kn, int num_cu);
 bool gemm_bf16_dl_supported(const GemmParams &p, bool w_kn);
 hipError_t launch_gemm_bf16_dl(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t, int num_cu);
 bool gemm_bf16_dl_carries_operand(const GemmParams &p);
+bool gemm_bf16_dl_carries_gathered(const GemmParams &p);
 // The kernel for few rows (gemm_rows.hip; bf16 and fp32 operands): does it run this launch -- one chunk GEMM, or with
 // n_steps > 0 all steps of a rank step, whose deliveries it then carries where land_step / land_more are set?
 bool gemm_rows_takes(const GemmParams &p, bool bf16, bool w_kn, int num_cu);

@@ -357,9 +357,37 @@ cf_status dp_step_impl(int p, int rank, int step, float *bucket, int64_t chunk_e
     return CF_OK;
 }
 
+// the deliveries of a weight gradient's moving operand (GemmParams::hop_tiles)
+struct HopJob {
+    const void *block[cf::GemmParams::MAX_STEPS - 1] = {};   // where row 0 of a gathered buffer would lie, per block of rows
+    void *land = nullptr;                                    // the gathered buffer; null: nothing is carried
+    int rank = 0, tiles = 0;                                 // the block that is in it already; k-tiles per block
+    bool right = false;
+    void to(cf::GemmParams *gp) const
+    {
+        gp->hop_tiles = tiles;
+        gp->hop_own = rank;
+        gp->hop_right = right;
+        gp->land_step[0] = land;
+        for (int i = 0; i < cf::GemmParams::MAX_STEPS - 1; ++i)
+            gp->A_step[1 + i] = block[i];
+    }
+};
+
 // dW (+)= left^T right: the chunk GEMM with the contraction over the m_chunk rows of both operands.
+void fill_wgrad_shape(cf::GemmParams &gp, const Resolved &r)
+{
+    gp.a_t = true;
+    gp.lda = r.lda;
+    gp.ldw = r.ldw;
+    gp.ldo = r.ldo;
+    gp.M = (int)r.k;                               // rows of dW
+    gp.N = (int)r.n;
+    gp.K = (int)r.mc;                              // contraction: the slice's rows
+}
+
 cf_status wgrad_step_impl(const Resolved &r, int step, const void *left, const void *right, float *dW, hipStream_t s,
-                          const CopyJob *job = nullptr)
+                          const CopyJob *job = nullptr, const HopJob *hops = nullptr)
 {
     if (cf_status st = check_step(r, step))
         return st;
@@ -372,17 +400,13 @@ cf_status wgrad_step_impl(const Resolved &r, int step, const void *left, const v
     if (r.k == 0 || r.n == 0)
         return CF_OK;
     cf::GemmParams gp;
-    gp.a_t = true;
+    fill_wgrad_shape(gp, r);
     gp.A = left;
     gp.W = right;
     gp.recv = step > 0 ? dW : nullptr;             // in place: every element is read, then written, by one lane
     gp.out = dW;
-    gp.lda = r.lda;
-    gp.ldw = r.ldw;
-    gp.ldo = r.ldo;
-    gp.M = (int)r.k;                               // rows of dW
-    gp.N = (int)r.n;
-    gp.K = (int)r.mc;                              // contraction: the slice's rows
+    if (hops != nullptr && hops->land != nullptr)
+        hops->to(&gp);
     if (gp.K == 0) {                               // nothing to contract: the gradient of an empty slice is zero
         if (step == 0)
             for (int64_t row = 0; row < r.k; ++row) {
@@ -911,6 +935,31 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         carried = cf::gemm_bf16_carries_delivery(probe, r.w_kn, r.bf16_out, num_cu_of_current_device(), kind == CF_KIND_RS) &&
                   (kind == CF_KIND_RS || r.k % 64 == 0 || wide);
     }
+    // The weight gradient with CF_FUSED_COPY: the kernel takes each block of rows from the neighbour's buffer and stores it on to
+    // the gathered one.
+    Resolved all = r;                                // a weight gradient's one GEMM: all rows of the gathered and the local operand
+    HopJob hops;
+    if (is_wgrad_kind(kind)) {
+        all.m = 1;
+        all.mc = r.mc * S;
+    }
+    if (is_wgrad_kind(kind) && (flags & CF_FUSED_COPY) && do_copy && do_compute && wide && slot_bytes > 0 && p < cf::GemmParams::MAX_STEPS &&
+        r.mc * m % 64 == 0 && r.bf16_in) {
+        hops.rank = r.rank;
+        hops.tiles = (int)(r.mc * m / 64);
+        hops.right = kind == CF_KIND_WGRAD_G;
+        cf::GemmParams gp;
+        fill_wgrad_shape(gp, all);
+        hops.to(&gp);
+        carried = cf::gemm_bf16_carries_gathered(gp, num_cu_of_current_device());
+        hops.block[r.rank] = reinterpret_cast<const void *>(gathered);
+        for (int i = 1; i < p; ++i) {
+            const int c = chunk_index(CF_KIND_AG, p, r.rank, i);
+            hops.block[c] = reinterpret_cast<const void *>(reinterpret_cast<uintptr_t>(b->peer_stage[i - 1]) - (uintptr_t)c * slot_bytes * m);
+        }
+        if (carried)
+            hops.land = reinterpret_cast<void *>(gathered);
+    }
     // The gradient bucket with CF_FUSED_COPY: the add kernels read the arrivals from the neighbours' buffers and
     // store them on to the landing buffers in the same pass (ring: 16 bytes per element instead of a copy's 8 plus
     // the add's 12; pairwise, p - 1 arrivals in one pass: 8 p instead of 12 p - 4).
@@ -1054,12 +1103,9 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     if (is_dp_kind(kind))
         return CF_OK;
     if (do_compute && is_wgrad_kind(kind)) {
-        Resolved all = r;
-        all.m = 1;
-        all.mc = r.mc * S;                           // all rows of the gathered and the local operand
-        const void *moving = reinterpret_cast<const void *>(gathered);
-        if (cf_status st = kind == CF_KIND_WGRAD_X ? wgrad_step_impl(all, 0, moving, b->W, static_cast<float *>(b->O), cs)
-                                                   : wgrad_step_impl(all, 0, b->W, moving, static_cast<float *>(b->O), cs))
+        const void *moving = carried ? hops.block[0] : reinterpret_cast<const void *>(gathered);
+        if (cf_status st = kind == CF_KIND_WGRAD_X ? wgrad_step_impl(all, 0, moving, b->W, static_cast<float *>(b->O), cs, nullptr, &hops)
+                                                   : wgrad_step_impl(all, 0, b->W, moving, static_cast<float *>(b->O), cs, nullptr, &hops))
             return st;
     }
     if (pair_front) {

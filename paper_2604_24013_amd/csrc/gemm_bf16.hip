@@ -517,6 +517,20 @@ bool gemm_bf16_carries_delivery(const GemmParams &p, bool w_kn, bool out_bf16, i
     return tn.carry >= 0 ? tn.carry != 0 : true;
 }
 
+// A weight gradient carries its deliveries on whole 256x256 tiles with whole k-tiles per block of rows: the loop there has the
+// registers, and a k-tile that lies in two neighbours' buffers would need two descriptors per load.  The copy in front moves the
+// operand twice and leaves the kernel to read it again; here the launch writes it once.  us of both data and both weight
+// gradients, copied / carried, results the same bits: 8 x 1024 x 8192 x 3584 1616 / 1566, 8 x 512 x 8192 x 3584 856 / 838, 8 x 128
+// x 8192 x 3584 317 / 306, 8 x 1024 x 5120 x 2560 869 / 823, 8 x 256 x 4096 x 4096 277 / 264; level at 2 x 1024 x 8192 x 3584 (465).
+bool gemm_bf16_carries_gathered(const GemmParams &p, int num_cu)
+{
+    const Tuning tn = tuning();
+    if (p.M <= 0 || p.N <= 0 || p.K <= 0 || staged_kernel_forced() || !gemm_bf16_dl_supported(p, true) || tn.carry == 0 || tn.mfma16 == 0)
+        return false;
+    const TileChoice t = tile_of_launch(p, num_cu);
+    return t.bm == 256 && t.bn == 256 && t.splitk <= 1 && gemm_bf16_dl_carries_gathered(p);
+}
+
 int gemm_bf16_steps_per_launch(const GemmParams &p, bool w_kn, int num_cu)
 {
     if (p.M <= 0 || p.N <= 0 || p.n_steps <= 1 || staged_kernel_forced() || !gemm_bf16_dl_supported(p, w_kn))

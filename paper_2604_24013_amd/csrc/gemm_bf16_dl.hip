@@ -141,7 +141,7 @@ __device__ __forceinline__ int xcd_remap(int pid, int total)
 // 16y + 4 (lane >> 4) .. + 3.  A k-tile is two 32-wide slices, each consumed in four quarter phases (one 32-row block
 // of the wave tile per phase).
 template <int BM, int BN, int WGM, int WGN, int NS, bool SPREAD, bool W_KN, bool OUT_BF16, bool RECV, bool A_T = false,
-          bool PERSIST = false, bool MF16 = false, bool NT = false>
+          bool PERSIST = false, bool MF16 = false, int HOPS = 0, bool NT = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams P, int tiles_m, int tiles_n)
 {
     static_assert(!MF16 || (SPREAD && NS == 2), "16x16x32 main loop: 256x256 tile");
@@ -285,8 +285,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // Buffer resources; all byte extents are below 2^31 (host-checked).
     const unsigned a_bytes = (unsigned)((A_T ? ((int64_t)(K - 1) * P.lda + M) : ((int64_t)(M - 1) * P.lda + K)) * 2);
     const unsigned w_bytes = (unsigned)((W_KN ? ((int64_t)(K - 1) * P.ldw + N) : ((int64_t)(N - 1) * P.ldw + K)) * 2);
-    const i32x4_t a_rsrc = make_rsrc(cA, a_bytes);
-    const i32x4_t w_rsrc = make_rsrc(P.W, w_bytes);
+    i32x4_t a_rsrc = make_rsrc(cA, a_bytes);
+    i32x4_t w_rsrc = make_rsrc(P.W, w_bytes);
     const unsigned lds_base = __builtin_amdgcn_readfirstlane(
         (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem);
 
@@ -489,12 +489,49 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
     // Every wave stores the 4 KiB it loaded itself -- it reads them back from the stage, whole 128-byte rows per
     // eight lanes, at the global offsets it fetched them from -- so its own vmcnt wait is all the ordering needed.
     constexpr bool CARRY_A = PERSIST && !A_T;
+    // Weight gradient likewise (GemmParams::hop_tiles): the operand that travels is either one, and comes in from one buffer per
+    // block of rows, to whose descriptor the loads go over with the first k-tile of the block (one test per k-tile).  An
+    // instance of its own: in the plain one the tests cost weight-gradient steps 1.5 % (8192 rows into 8192 x 3584 381 / 387 us).
+    // HOPS: 1 the left one, 2 the right one.
+    static_assert(HOPS == 0 || (PERSIST && A_T && MF16 && !RECV), "a weight gradient on whole tiles, written once");
+    constexpr bool hop_right = HOPS == 2;
     int carry_at = (CARRY_A && cLand != nullptr && cRecv == nullptr) ? tile / tiles_m : 0x7fffffff;
-    __amdgpu_buffer_rsrc_t la_rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(cLand, 0, (CARRY_A && cLand != nullptr) ? (int)a_bytes : 0, 0x00020000);
+    int hop_at = 0x7fffffff;                             // the k-tile with which the next block of rows begins
+    if (HOPS != 0) {
+        carry_at = hop_right ? tile % tiles_m : tile / tiles_m;
+        hop_at = P.hop_tiles;
+    }
+    const int carry_step = hop_right ? tiles_m : tiles_n;
+    __amdgpu_buffer_rsrc_t la_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        cLand, 0, ((CARRY_A || HOPS != 0) && cLand != nullptr) ? (int)(hop_right ? w_bytes : a_bytes) : 0, 0x00020000);
+    // k-tile kt is about to be requested: the first of a block of rows takes the loads to that block's buffer
+    auto next_hop = [&](int kt) __attribute__((always_inline)) {
+        if (HOPS != 0 && kt == hop_at && kt < nk) {
+            const i32x4_t r = make_rsrc(P.A_step[1 + kt / P.hop_tiles], hop_right ? w_bytes : a_bytes);
+            if (hop_right)
+                w_rsrc = r;
+            else
+                a_rsrc = r;
+            hop_at += P.hop_tiles;
+        }
+    };
     // (A ragged k-tile is the last of a work item, LAST: its lanes beyond the k range store nothing.)
-    auto carry_tile = [&](int kt, int stage_a, auto last_tag) __attribute__((always_inline)) {
+    auto carry_tile = [&](int kt, int stage_a, int stage_w, auto last_tag) __attribute__((always_inline)) {
         const int k0 = ktile(kt) * BK;
+        if constexpr (HOPS != 0) {
+            static_assert(HOPS == 0 || A_LD == B_LD, "the waits count the same stores for either operand");
+            const unsigned own = (unsigned)(kt - P.hop_own * P.hop_tiles) < (unsigned)P.hop_tiles ? OOB : 0;   // nothing to land
+#pragma unroll
+            for (int j = 0; j < A_LD; ++j) {
+                const int at = (hop_right ? W_BASE + stage_w * B_BYTES : stage_a * A_BYTES) + (j * NW + wave) * 1024 + lane * 16;
+                const u32x4_t t = *reinterpret_cast<const u32x4_t *>(smem + at);
+                const unsigned off = hop_right ? b_off[w_reg(j)] : a_off[a_reg(j)];
+                const int dist = hop_right ? k0 * w_kstep + w_dist(j) : k0 * a_kstep + a_dist(j);
+                __builtin_amdgcn_raw_buffer_store_b128(t, la_rsrc, (int)(off | own), dist, 0);
+            }
+            carry_at += carry_step;
+            return;
+        }
         const bool ragged = decltype(last_tag)::value && k0 + BK > K;
 #pragma unroll
         for (int j = 0; j < A_LD; ++j) {
@@ -891,11 +928,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             auto lw = [&](auto idx_tag) __attribute__((always_inline)) {       // a weight load of tile kt+NS
                 return [&, kt, cw]() __attribute__((always_inline)) { issue_load(kt + NS, 0, cw, decltype(idx_tag){}, wk); };
             };
+            next_hop(kt + NS);
             front16(ca, cw, la(std::integral_constant<int, 0>{}), la(std::integral_constant<int, 1>{}),
                     la(std::integral_constant<int, 2>{}), la(std::integral_constant<int, 3>{}), plain_ph2(ca, cw));
             auto publish = [&]() __attribute__((always_inline)) {
-                if (CARRY_A && kt == carry_at) {     // tile kt goes on to the landing buffer: its stores are the
-                    carry_tile(kt, ca, std::false_type{});              // youngest requests and need not be awaited here
+                if ((CARRY_A || HOPS != 0) && kt == carry_at) {   // tile kt goes on to the landing buffer: its stores are the
+                    carry_tile(kt, ca, cw, std::false_type{});          // youngest requests and need not be awaited here
                     wait_vmcnt<(NS - 2) * LPT + 2 * A_LD>();
                 } else {
                     wait_vmcnt<(NS - 2) * LPT + A_LD>();
@@ -925,8 +963,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             request_early();
             front16(ca, cw, nothing, nothing, nothing, nothing, plain_ph2(ca, cw));
             phase16(p2_t{}, afA, wfB, afB, wfA, on_t{}, ca, 1, 3, nothing, c0{}, 0, 0, c0{}, off_t{}, 0, 0, 0, nothing, nothing);
-            if (CARRY_A && nk - 1 == carry_at)
-                carry_tile(nk - 1, ca, std::true_type{});
+            if ((CARRY_A || HOPS != 0) && nk - 1 == carry_at)
+                carry_tile(nk - 1, ca, cw, std::true_type{});
             phase16(p3_t{}, afB, wfB, afA, wfA, off_t{}, 0, 0, 0, nothing, c0{}, 0, 0, c0{}, off_t{}, 0, 0, 0, nothing, nothing);
         };
         asm volatile("" : "+s"(kt));                     // (keeps the compiler from peeling the loop below: it spills)
@@ -978,7 +1016,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase(af1, wf1, true, ca, cw, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
             phase(af0, wf0, true, ca, cw, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
             if (CARRY_A && kt == carry_at) {         // tile kt goes on to the landing buffer: its stores are the
-                carry_tile(kt, ca, std::false_type{});                  // youngest requests and need not be awaited here
+                carry_tile(kt, ca, 0, std::false_type{});               // youngest requests and need not be awaited here
                 wait_vmcnt<BEHIND + A_LD>();
             } else {
                 wait_vmcnt<BEHIND>();
@@ -1022,7 +1060,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase(af1, wf1, true, cur_a, cur_w, 2, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
             phase(af0, wf0, true, cur_a, cur_w, 3, af1, wf1, 0, 0, 0, c0{}, c0{}, wk{});
             if (CARRY_A && nk - 1 == carry_at)
-                carry_tile(nk - 1, cur_a, std::true_type{});
+                carry_tile(nk - 1, cur_a, 0, std::true_type{});
             phase(af1, wf1, false, 0, 0, 0, af0, wf0, 0, 0, 0, c0{}, c0{}, wk{});
         }
     } else {
@@ -1060,7 +1098,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase_b(af0, wf0, true, cur, 3, af1, wf1, rpm2{});   // reads early: complete at the barrier
             // tile kt+1 complete, NS-2 later tiles may be in flight
             if (CARRY_A && kt == carry_at) {         // tile kt goes on to the landing buffer (stores not awaited here)
-                carry_tile(kt, cur, std::false_type{});
+                carry_tile(kt, cur, 0, std::false_type{});
                 wait_vmcnt<(NS - 2) * LPT + A_LD>();
             } else {
                 wait_vmcnt<(NS - 2) * LPT>();
@@ -1077,7 +1115,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(GemmParams
             phase_b(af1, wf1, true, cur, 2, af0, wf0, rpm1{});
             phase_b(af0, wf0, true, cur, 3, af1, wf1, rpm1{});
             if (CARRY_A && nk - 1 == carry_at)
-                carry_tile(nk - 1, cur, std::true_type{});
+                carry_tile(nk - 1, cur, 0, std::true_type{});
             phase_b(af1, wf1, false, 0, 0, af0, wf0, rpm1{});
         }
     }
@@ -1283,11 +1321,11 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
             constexpr bool WKN = decltype(wkn)::value, OBF = decltype(obf)::value, RV = decltype(recv)::value, NTP = decltype(nt)::value;
             if constexpr (BM == 256 && BN == 256)
                 if (p.mfma16) {
-                    hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, RV, false, true, true, NTP>),
+                    hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, RV, false, true, true, 0, NTP>),
                                        grid, block, 0, s, p, tiles_m, tiles_n);
                     return;
                 }
-            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, RV, false, true, false, NTP>),
+            hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, WKN, OBF, RV, false, true, false, 0, NTP>),
                                grid, block, 0, s, p, tiles_m, tiles_n);
         };
         const auto yes = std::true_type{};
@@ -1295,11 +1333,17 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
         if (p.a_t) {                                 // (whole 256x256 tiles: the 16x16x32 main loop, see the launcher)
             if constexpr (BM == 256 && BN == 256)
                 if (w_kn && !out_bf16 && p.mfma16) {
-                    auto go_t = [&](auto recv, auto nt) {
+                    auto go_t = [&](auto recv, auto hops, auto nt) {
                         hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, NS, SPREAD, true, false, decltype(recv)::value, true, true, true,
-                                                                decltype(nt)::value>), grid, block, 0, s, p, tiles_m, tiles_n);
+                                                                decltype(hops)::value, decltype(nt)::value>), grid, block, 0, s, p, tiles_m, tiles_n);
                     };
-                    any_recv ? go_t(yes, no) : p.non_temporal ? go_t(no, yes) : go_t(no, no);
+                    auto go_nt = [&](auto hops) { p.non_temporal ? go_t(no, hops, yes) : go_t(no, hops, no); };
+                    if (any_recv)
+                        go_t(yes, std::integral_constant<int, 0>{}, no);
+                    else if (p.hop_tiles == 0)
+                        go_nt(std::integral_constant<int, 0>{});
+                    else
+                        p.hop_right ? go_nt(std::integral_constant<int, 2>{}) : go_nt(std::integral_constant<int, 1>{});
                     return hipGetLastError();
                 }
             return hipErrorInvalidValue;
@@ -1349,6 +1393,14 @@ bool gemm_bf16_dl_carries_operand(const GemmParams &p)
     return p.n_steps > 0 && !p.a_t && (p.K % BK == 0 || p.lda == p.K);
 }
 
+// ... and a weight gradient (GemmParams::hop_tiles) on 256x256 tiles?  Whole tiles, blocks of whole k-tiles, two at the least (the
+// prologue requests two), at rows without padding between them.
+bool gemm_bf16_dl_carries_gathered(const GemmParams &p)
+{
+    return p.a_t && p.recv == nullptr && p.hop_tiles >= 2 && p.K % (p.hop_tiles * BK) == 0 && p.K / (p.hop_tiles * BK) < GemmParams::MAX_STEPS &&
+           p.M % 256 == 0 && p.N % 256 == 0 && (p.hop_right ? p.ldw == p.N : p.lda == p.M);
+}
+
 hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16, hipStream_t s, TileChoice t, int num_cu)
 {
     if (p_in.n_steps > 0 && p_in.wait_flag != nullptr)
@@ -1372,6 +1424,8 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
     // 388 / 346, in eight steps added in place 660 / 638 and 702 / 655); on the smaller tiles it loses by it: 512 rows into
     // 1376 x 4096 110 / 120, 300 into 4096 x 2048 141 / 144, 64 into 2048 x 2048 71 / 74.
     const bool whole_256 = t.bm == 256 && t.bn == 256 && p.M % 256 == 0 && p.N % 256 == 0 && tn.mfma16 != 0;
+    if (p.hop_tiles > 0 && !(p.n_steps == 0 && p.a_t && whole_256 && p.splits == 1 && p.wait_flag == nullptr && p.cp_wgs == 0))
+        return hipErrorInvalidValue;                  // callers ask gemm_bf16_carries_gathered first
     if (p.n_steps == 0 && (!p.a_t || whole_256) && p.splits == 1 && p.wait_flag == nullptr && p.cp_wgs == 0) {
         p.n_steps = 1;
         p.A_step[0] = p.A;
@@ -1380,7 +1434,8 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
     }
     if (p.n_steps > 0) {
         for (int j = 0; j < p.n_steps; ++j)
-            if (p.land_step[j] != nullptr && p.recv_step[j] == nullptr && !gemm_bf16_dl_carries_operand(p))
+            if (p.land_step[j] != nullptr && p.recv_step[j] == nullptr && !gemm_bf16_dl_carries_operand(p) &&
+                !(p.n_steps == 1 && whole_256 && gemm_bf16_dl_carries_gathered(p)))
                 return hipErrorInvalidValue;          // callers ask gemm_bf16_carries_delivery first
         p.splits = 1;
         p.cp_wgs = 0;
@@ -1430,7 +1485,7 @@ hipError_t launch_gemm_bf16_dl(const GemmParams &p_in, bool w_kn, bool out_bf16,
         // which keeps all earlier iterations of the 256x256 main loop branch-free)
         // (nor where the pairwise schedule carries its deliveries: the sums are bit for bit those of its copied mode, whose last
         // step sums several partials and so keeps the k order)
-        p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0 && !p.k_in_order;
+        p.k_rotate = p.xcd_steps && tn.k_rotate != 0 && p.K % BK == 0 && !p.k_in_order && p.hop_tiles == 0;
         // fp32 lines past the caches: what a launch writes it never reads again, and B_in is read once.  Where rows begin
         // and end on 128-byte lines -- the caches put the halves of a shared line together.  us per carried rank step,
         // cached against not: 8 x 1024 x 8192 x 1024 232 / 216, 8 x 512 x 4096 x 1376 72.2 / 69.6, 8 x 128 x 4096 x 512 (46 MB)

@@ -183,3 +183,22 @@ def test_workspace_bytes_cover_the_splits(dry, kind, p, mc, n, k):
             cf.set_workspace(None)
         return [c for c in dry.calls(call) if "gemm" in c[0]]
     assert grid(need) == grid(1 << 32)
+
+
+@pytest.mark.parametrize("kind", [cf.CF_KIND_WGRAD_X, cf.CF_KIND_WGRAD_G])
+@pytest.mark.parametrize("mc,k,n,pad,off,copied", [
+    (1024, 8192, 3584, 0, 0, False), (1024, 3584, 8192, 0, 0, False), (1000, 8192, 3584, 0, 0, True), (1024, 8192, 3592, 0, 0, True),
+    (1024, 8192, 3584, 64, 0, True), (1024, 8192, 3584, 0, 8, True), (64, 8192, 3584, 0, 0, True)])
+def test_weight_gradients_of_whole_tiles_carry_their_deliveries(dry, kind, mc, k, n, pad, off, copied):
+    """(padding between the rows that travel lands with a copy only; the kernel's loads are 16 bytes wide)"""
+    p, rank = 8, 3
+    width = k if kind == cf.CF_KIND_WGRAD_X else n
+    hop = mc * (width + pad) * 2
+    block = lambda c: P(20) + c * hop
+    stage = [P(10 + i) + off for i in range(p - 1)]
+    each = [block((rank - i) % p) for i in range(1, p)]
+    left = kind == cf.CF_KIND_WGRAD_X
+    desc = cf.layer_desc(p, rank, mc, n, k, lda=k + pad * left, ldw=n + pad * (not left))
+    bufs = cf.make_buffers(block(rank), P(1), P(2), stage, (None, None), (None, None), None, each)
+    kernels = [c[0] for c in dry.calls(lambda: cf.run_schedule(desc, kind, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))]
+    assert kernels[-1].startswith("gemm_bf16_dl_kernel") and (len(kernels) > 1) == copied
