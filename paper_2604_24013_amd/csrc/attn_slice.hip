@@ -173,7 +173,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
         v_addr[t] = V_BASE + v_kl * ROWB + (((t) ^ (v_kl & 3)) << 6) + v_nl * 2;
 
     f32x16_t oacc[DT];
-    float m_run = -INFINITY;
+    float m_run = -3.402823466e38f;      // (finite: against -inf a tile whose scores are all -inf would give NaN)
     float l_run = 0.0f;                  // of the keys this lane holds; the query's other half lives in lane ^ 32
 #pragma unroll
     for (int d = 0; d < DT; ++d)
@@ -233,9 +233,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
         const auto both = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, mx), __builtin_bit_cast(unsigned, mx), false, false);
         const unsigned half0 = both[0], half1 = both[1];
         const float mxs = fmaxf(__builtin_bit_cast(float, half0), __builtin_bit_cast(float, half1)) * sl2;   // scale > 0: the maximum of the scaled scores
-        if (__builtin_amdgcn_ballot_w64(mxs > m_run + RAISE) != 0) { // finite: every tile holds a key
+        if (__builtin_amdgcn_ballot_w64(mxs > m_run + RAISE) != 0) { // (not where all scores so far are -inf)
             const float m_new = fmaxf(m_run, mxs);
-            float alpha = exp2f(m_run - m_new);                      // 0 on the first tile (m_run = -inf)
+            float alpha = exp2f(m_run - m_new);                      // 0 on the first tile with a finite score
             asm volatile("" : "+v"(alpha));                          // (keeps this a branch, as above)
             m_run = m_new;
             l_run *= alpha;

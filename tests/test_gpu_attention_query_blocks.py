@@ -1,0 +1,69 @@
+"""Attention in query blocks of 256 and 128: tiles whose scores are all -inf.  Needs an MI355X: run with ``-m gpu``."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_24013_amd import binding as cf
+from paper_2604_24013_amd import inputs
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+TOL_ATTN = 2.0 ** -7                     # probabilities and output rounded to bf16 (2^-9 each)
+
+
+def _bf16(x):
+    bits = inputs.f32_to_bf16_bits(np.asarray(x, np.float32))
+    return H.to_dev(bits, "bf16"), inputs.bf16_bits_to_f32(bits).astype(np.float64)
+
+
+@pytest.fixture
+def variant():
+    """Forces 32 * waves queries per workgroup and a number of key splits; yields the registered workspace."""
+    ws = torch.empty(16 << 20, dtype=torch.uint8, device=H.DEV)
+    cf.set_workspace(ws)
+    torch.cuda.synchronize()
+
+    def use(waves, ksplit):
+        os.environ.update(COMMFUSE_ATTN_QT={0: "0", 8: "1", 4: "2"}[waves], COMMFUSE_ATTN_KSPLIT=str(ksplit))
+        return ws
+    yield use
+    for v in ("COMMFUSE_ATTN_QT", "COMMFUSE_ATTN_KSPLIT"):
+        os.environ.pop(v, None)
+    torch.cuda.synchronize()
+    cf.set_workspace(None)
+
+
+def _attend(Qd, Kd, Vd, scale):
+    B, h, S, _ = Qd.shape
+    out = torch.full((B * S, h * 128), float("nan"), dtype=torch.bfloat16, device=H.DEV)
+    cf.attn_slice(cf.attn_desc(1, 0, B, h, S, 128, 64, scale), 0, Qd, Kd, Vd, out, None)
+    torch.cuda.synchronize()
+    return H.to_host_f64(out)
+
+
+@pytest.mark.parametrize("waves", [8, 4, 0])
+@pytest.mark.parametrize("ksplit,first,last", [
+    (1, 0, 64), (1, 0, 512), (1, 192, 320), (1, 960, 1010),          # the first keys, tiles on both buffers, the last
+    (2, 512, 576), (3, 320, 448),                                    # the first keys of a split
+    (2, 0, 512), (3, 640, 1010)])                                    # all keys of a split
+def test_tiles_of_minus_infinity_have_no_weight(variant, waves, ksplit, first, last):
+    rng = np.random.default_rng(first + last)
+    S, h, scale = 1010, 2, 128 ** -0.5
+    variant(waves, ksplit)
+    Qd, Q = _bf16(np.abs(rng.standard_normal((1, h, S, 128))) + 0.01)
+    K = rng.standard_normal((1, h, S, 128))
+    K[:, :, first:last] = -np.inf
+    Kd, K = _bf16(K)
+    Vd, V = _bf16(rng.standard_normal((1, h, S, 128)))
+    got = _attend(Qd, Kd, Vd, scale)
+    keep = np.r_[0:first, last:S]
+    ref = np.empty_like(got)
+    for a in range(h):
+        s = Q[0, a] @ K[0, a][keep].T * scale
+        P = np.exp(s - s.max(axis=1, keepdims=True))
+        ref[:, a * 128:(a + 1) * 128] = P @ V[0, a][keep] / P.sum(axis=1, keepdims=True)
+    assert not np.isnan(got).any()
+    assert H.rel_err(got, ref) <= TOL_ATTN
