@@ -292,7 +292,7 @@ static double bf16_split_us(int tiles, int ktiles, int ks, int num_cu)
     return 4.5 + 0.34 * per + 0.23 * per * tiles * ks / num_cu + (ks > 1 ? 1.1 + 0.55 * ks + 0.011 * tiles * ks : 0.0);
 }
 
-TileChoice choose_tile_bf16(int M, int N, int K, int num_cu)
+TileChoice choose_tile_bf16(int M, int N, int K, int num_cu, int parts)
 {
     // Measured on MI355X: the kernels are bound by the rate at which a CU can pull operand tiles
     // through its L1 (64 B/clk), so the largest tile that still fills the chip wins; a grid of at
@@ -308,10 +308,12 @@ TileChoice choose_tile_bf16(int M, int N, int K, int num_cu)
     // A grid of one workgroup per compute unit and less: the number of splits with the lowest estimate (us of a launch, fitted to
     // 229 weight gradients of 128..5768 rows split in 1 to 8, rms 0.06, but for a constant; steps fit it too).  us unsplit / as
     // chosen: 552 x 536 over 5768 rows 43.7 / 19.5 (in six), 520 x 856 over 2544 in four 25 / 15.4, 776 x 1368 over 912 12.1 (unsplit; two 15).
+    // Of the splits whose partial tiles the workspace takes: with room for 8 k n floats 144 x 640 over 7000 rows runs in four (in eight
+    // with more room, 18.0 us) 20.8, 296 x 584 over 7752 in five (in seven 20.3) 21.7; left whole they take 47 and 56.
     t.deep = true;
     const int ktiles = (K + 63) / 64;
     double best = 0.0;
-    for (int ks = 1; ks <= 8 && t128 * ks <= num_cu && ktiles >= 2 * ks; ++ks) {
+    for (int ks = 1; ks <= 8 && (ks == 1 || t128 * ks <= parts) && ktiles >= 2 * ks; ++ks) {
         const double us = bf16_split_us(t128, ktiles, ks, num_cu);
         if (ks == 1 || us < best) {
             best = us;
@@ -334,7 +336,8 @@ bool gemm_bf16_takes_recv_list(const GemmParams &p, bool w_kn)
 // Tile of a launch by area: the per-step choice, or the persistent rank step's cost model.
 static TileChoice tile_by_area(const GemmParams &p, int num_cu)
 {
-    TileChoice t = choose_tile_bf16(p.M, p.N, p.K, num_cu);
+    const size_t parts = p.ws == nullptr || p.counters == nullptr ? 0 : p.ws_bytes / (128 * 128 * sizeof(float));
+    TileChoice t = choose_tile_bf16(p.M, p.N, p.K, num_cu, parts < (size_t)num_cu ? (int)parts : num_cu);
     if (p.n_steps > 0) {
         // Persistent rank step: n_steps * tiles work items share one grid, so a step need not fill the chip
         // alone.  Cost of a tile shape = rounds over the chip x tile area x its measured cost per flop
@@ -468,15 +471,14 @@ double gemm_bf16_tile_us(const GemmParams &p, int num_cu)
         return (double)((items + wgs - 1) / wgs) * round;
     }
     double us = 0.0;
-    if (t.splitk > 1 && p.ws != nullptr && p.counters != nullptr && tiles <= p.max_tiles &&
-        (size_t)(tiles * t.splitk) * t.bm * t.bn * sizeof(float) <= p.ws_bytes) {
+    if (t.splitk > 1) {
         // a step whose k range the launcher splits through the workspace: fitted to 759 steps of 64..1024 x 128..8192 x 512..8192
         // with a B_in, split in 1 to 8 (rms 0.08): 213 x 3496 x 6448 in four 28 us (the few-rows kernel 33), 372 x 4736 x 2184 in two 22
         const double per = ((p.K + 63) / 64 + t.splitk - 1) / t.splitk, all = (double)(tiles * t.splitk);
         us = 7.6 + 0.44 * per + 0.145 * per * all / num_cu + 0.61 * t.splitk + 0.012 * all;
     } else {
         tile_by_estimate(p, num_cu, &us);
-        if (us == 0.0)                               // (no workspace for the splits: 384 x 4096 x 8192 72 us, the few-rows kernel 61)
+        if (choose_tile_bf16(p.M, p.N, p.K, num_cu, num_cu).splitk > 1)   // (no workspace for the splits: 384 x 4096 x 8192 72 us, the few-rows kernel 61)
             us = 1.05 * tile_estimate_us(p, TileChoice{128, 128, 1, true}, num_cu, gemm_share_with_recv(p));
     }
     return us;

@@ -156,13 +156,31 @@ def test_splits_of_a_weight_gradient(dry, m, n, rows, tiles, splits):
     assert grid == tiles * splits or (splits == 1 and grid < tiles)
 
 
-def test_a_workspace_too_small_for_the_partial_tiles_leaves_the_k_range_whole(dry):
+@pytest.mark.parametrize("m,n,rows,tiles,splits,short,fits", [
+    (552, 536, 5768, 25, 7, 6, 5), (480, 304, 4608, 12, 6, 5, 5), (304, 1680, 4600, 42, 6, 4, 4), (144, 640, 7000, 10, 8, 7, 4), (64, 64, 4608, 1, 6, 5, 2)])
+def test_splits_that_a_smaller_workspace_takes(dry, m, n, rows, tiles, splits, short, fits):
+    """Tiles of 64 KiB: all splits to the byte, fewer 16 bytes short, in 8 m n floats the best that fits, in less than two none."""
     grids = []
-    for room in (0, 16):                                          # 25 tiles of 64 KiB in seven splits, to the byte and 16 bytes short
-        calls = dry.calls(lambda: (cf.set_workspace(P(9), (64 << 10) + 25 * 7 * (64 << 10) - room),
-                                   cf.wgrad_step(cf.layer_desc(1, 0, 5768, 536, 552), 0, P(0), P(1), P(2)), cf.set_workspace(None)))
+    for size in (tiles * splits << 16, (tiles * splits << 16) - 16, 8 * m * n * 4, (tiles * 2 << 16) - 16):
+        calls = dry.calls(lambda: (cf.set_workspace(P(9), (64 << 10) + size), cf.wgrad_step(cf.layer_desc(1, 0, rows, n, m), 0, P(0), P(1), P(2)),
+                                   cf.set_workspace(None)))
         grids += [c[1] for c in calls if "gemm" in c[0]]
-    assert grids == [175, 25]
+    assert grids == [tiles * splits, tiles * short, tiles * fits, tiles]
+
+
+@pytest.mark.parametrize("rows,n,k,few_rows", [(363, 3216, 3512, False), (164, 2800, 4640, False), (29, 1024, 8192, True)])
+def test_steps_split_as_far_as_the_workspace_goes(dry, rows, n, k, few_rows):
+    """The rule against the few-rows kernel prices the split that will run: with room for two splits either kernel, never a tile
+    kernel that was priced for four and runs whole."""
+    desc = cf.layer_desc(1, 0, rows, n, k)
+    tiles = -(-rows // 128) * -(-n // 128)
+    seen = []
+    for size in (1 << 30, (64 << 10) + (2 * tiles << 16)):
+        calls = dry.calls(lambda: (cf.set_workspace(P(9), size), cf.ag_step(desc, 0, P(0), P(1), P(2)), cf.set_workspace(None)))
+        seen += [c for c in calls if "gemm" in c[0]]
+    rows_kernel = [c[0].startswith("gemm_rows_kernel") for c in seen]
+    assert rows_kernel[0] == few_rows
+    assert rows_kernel[1] or seen[1][1] == 2 * tiles
 
 
 @pytest.mark.parametrize("kind,p,mc,n,k", [(cf.CF_KIND_WGRAD_X, 8, 721, 536, 552), (cf.CF_KIND_RS, 2, 213, 3496, 6448), (cf.CF_KIND_RS, 2, 130, 5000, 8184),
