@@ -139,8 +139,9 @@ struct TileChoice {
 
 // Chooses the workgroup tile for a chunk GEMM from its shape and the number of
 // compute units (the per-step grids are small against 256 CUs); `parts`: how many
-// partial 128x128 tiles of a split k range the workspace takes, num_cu at the most.
-TileChoice choose_tile_bf16(int M, int N, int K, int num_cu, int parts);
+// partial 128x128 tiles of a split k range the workspace takes, num_cu at the most;
+// `a_t`: a weight gradient.
+TileChoice choose_tile_bf16(int M, int N, int K, int num_cu, int parts, bool a_t);
 
 hipError_t launch_gemm_bf16(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t s, int num_cu);
 // True if launch_gemm_bf16 would run the kernel that honours GemmParams::recv_more for these operands.

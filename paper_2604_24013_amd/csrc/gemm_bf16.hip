@@ -286,13 +286,19 @@ hipError_t launch_cfg(const GemmParams &p, bool w_kn, bool out_bf16, hipStream_t
 
 // What the main loop and the hand-over of a k range split over ks workgroups per 128x128 tile take, in microseconds: a round,
 // the k-tiles of a split and what all of them together ask of the caches, and the partial tiles (64 KiB each) there and back.
-static double bf16_split_us(int tiles, int ktiles, int ks, int num_cu)
+// Weight gradients have lines of their own: a whole range that is short is cheaper there (two 128x128 workgroups to a compute unit
+// up to sixteen k-tiles) than the splits' line says at one, and splits cost more on the last fifth of the chip.
+static double bf16_split_us(int tiles, int ktiles, int ks, int num_cu, bool a_t)
 {
-    const double per = (ktiles + ks - 1) / ks;
-    return 4.5 + 0.34 * per + 0.23 * per * tiles * ks / num_cu + (ks > 1 ? 1.1 + 0.55 * ks + 0.011 * tiles * ks : 0.0);
+    const double per = (ktiles + ks - 1) / ks, share = (double)tiles * ks / num_cu;
+    if (a_t && ks == 1)
+        return 3.9 + 0.42 * per + (6.7 - 0.05 * per) * share;
+    if (a_t)
+        return 7.0 + 0.37 * per + (2.6 + 0.15 * per) * share + 0.54 * ks + (share > 0.8 ? 4.0 * (share - 0.8) : 0.0);
+    return 4.5 + 0.34 * per + 0.23 * per * share + (ks > 1 ? 1.1 + 0.55 * ks + 0.011 * tiles * ks : 0.0);
 }
 
-TileChoice choose_tile_bf16(int M, int N, int K, int num_cu, int parts)
+TileChoice choose_tile_bf16(int M, int N, int K, int num_cu, int parts, bool a_t)
 {
     // Measured on MI355X: the kernels are bound by the rate at which a CU can pull operand tiles
     // through its L1 (64 B/clk), so the largest tile that still fills the chip wins; a grid of at
@@ -305,16 +311,19 @@ TileChoice choose_tile_bf16(int M, int N, int K, int num_cu, int parts)
     if (tiles(256, 128) >= want) return TileChoice{256, 128, 1};
     const int t128 = tiles(128, 128);
     if (t128 > num_cu) return t;                 // two workgroups per CU, two stages each
-    // A grid of one workgroup per compute unit and less: the number of splits with the lowest estimate (us of a launch, fitted to
-    // 229 weight gradients of 128..5768 rows split in 1 to 8, rms 0.06, but for a constant; steps fit it too).  us unsplit / as
-    // chosen: 552 x 536 over 5768 rows 43.7 / 19.5 (in six), 520 x 856 over 2544 in four 25 / 15.4, 776 x 1368 over 912 12.1 (unsplit; two 15).
+    // A grid of one workgroup per compute unit and less: the number of splits with the lowest estimate (us of a launch; fitted to 590
+    // weight gradients of 512..8192 rows into 64..4096 x 64..4096, each whole and in 2 to 8 splits, rms 0.03 beside 1.4 us and more for a
+    // B_in, which all of them pay; steps to a line of 229 earlier ones, rms 0.06).  us whole / as chosen: 552 x 536 over 5768 rows 43.7 /
+    // 20.2 (in seven), 520 x 856 over 2544 in four 22.3 / 15.6, 776 x 1368 over 912 11.9 (whole; in two 13.4), 136 x 152 over 848 9.6 (whole;
+    // in three 11.0), 1168 x 296 over 1232 in three 13.8 / 12.9, 248 x 120 over 1472 in four 13.4 / 11.7.  Of the 590 one is 5 % and more
+    // behind the best, 0.3 % on average; by the steps' line 20 and 0.7 %.
     // Of the splits whose partial tiles the workspace takes: with room for 8 k n floats 144 x 640 over 7000 rows runs in four (in eight
-    // with more room, 18.0 us) 20.8, 296 x 584 over 7752 in five (in seven 20.3) 21.7; left whole they take 47 and 56.
+    // with more room, 18.0 us) 20.8, 296 x 584 over 7752 in five (in eight 20.2) 21.7; left whole they take 47 and 56.
     t.deep = true;
     const int ktiles = (K + 63) / 64;
     double best = 0.0;
     for (int ks = 1; ks <= 8 && (ks == 1 || t128 * ks <= parts) && ktiles >= 2 * ks; ++ks) {
-        const double us = bf16_split_us(t128, ktiles, ks, num_cu);
+        const double us = bf16_split_us(t128, ktiles, ks, num_cu, a_t);
         if (ks == 1 || us < best) {
             best = us;
             t.splitk = ks;
@@ -337,7 +346,7 @@ bool gemm_bf16_takes_recv_list(const GemmParams &p, bool w_kn)
 static TileChoice tile_by_area(const GemmParams &p, int num_cu)
 {
     const size_t parts = p.ws == nullptr || p.counters == nullptr ? 0 : p.ws_bytes / (128 * 128 * sizeof(float));
-    TileChoice t = choose_tile_bf16(p.M, p.N, p.K, num_cu, parts < (size_t)num_cu ? (int)parts : num_cu);
+    TileChoice t = choose_tile_bf16(p.M, p.N, p.K, num_cu, parts < (size_t)num_cu ? (int)parts : num_cu, p.a_t);
     if (p.n_steps > 0) {
         // Persistent rank step: n_steps * tiles work items share one grid, so a step need not fill the chip
         // alone.  Cost of a tile shape = rounds over the chip x tile area x its measured cost per flop
@@ -478,7 +487,7 @@ double gemm_bf16_tile_us(const GemmParams &p, int num_cu)
         us = 7.6 + 0.44 * per + 0.145 * per * all / num_cu + 0.61 * t.splitk + 0.012 * all;
     } else {
         tile_by_estimate(p, num_cu, &us);
-        if (choose_tile_bf16(p.M, p.N, p.K, num_cu, num_cu).splitk > 1)   // (no workspace for the splits: 384 x 4096 x 8192 72 us, the few-rows kernel 61)
+        if (choose_tile_bf16(p.M, p.N, p.K, num_cu, num_cu, p.a_t).splitk > 1)   // (no workspace for the splits: 384 x 4096 x 8192 72 us, the few-rows kernel 61)
             us = 1.05 * tile_estimate_us(p, TileChoice{128, 128, 1, true}, num_cu, gemm_share_with_recv(p));
     }
     return us;

@@ -156,8 +156,16 @@ def test_splits_of_a_weight_gradient(dry, m, n, rows, tiles, splits):
     assert grid == tiles * splits or (splits == 1 and grid < tiles)
 
 
+@pytest.mark.parametrize("m,n,rows,tiles,splits", [(136, 152, 848, 4, 1), (168, 552, 912, 10, 1), (72, 112, 920, 1, 1), (568, 72, 1048, 5, 3),
+                                                   (1168, 296, 1232, 30, 3), (248, 120, 1472, 2, 4)])
+def test_short_weight_gradients_are_split_where_it_pays(dry, m, n, rows, tiles, splits):
+    """us whole / split: 9.6 / 10.8, 10.2 / 11.1, 9.9 / 10.8; 11.5 / 11.3, 13.6 / 12.7, 13.4 / 11.7."""
+    calls = dry.calls(lambda: (cf.set_workspace(P(9), 1 << 30), cf.wgrad_step(cf.layer_desc(1, 0, rows, n, m), 0, P(0), P(1), P(2)), cf.set_workspace(None)))
+    assert [c[1] for c in calls if "gemm" in c[0]] == [tiles * splits]
+
+
 @pytest.mark.parametrize("m,n,rows,tiles,splits,short,fits", [
-    (552, 536, 5768, 25, 7, 6, 5), (480, 304, 4608, 12, 6, 5, 5), (304, 1680, 4600, 42, 6, 4, 4), (144, 640, 7000, 10, 8, 7, 4), (64, 64, 4608, 1, 6, 5, 2)])
+    (552, 536, 5768, 25, 7, 6, 5), (480, 304, 4608, 12, 6, 5, 5), (304, 1680, 4600, 42, 4, 3, 4), (144, 640, 7000, 10, 8, 7, 4), (64, 64, 4608, 1, 6, 5, 2)])
 def test_splits_that_a_smaller_workspace_takes(dry, m, n, rows, tiles, splits, short, fits):
     """Tiles of 64 KiB: all splits to the byte, fewer 16 bytes short, in 8 m n floats the best that fits, in less than two none."""
     grids = []
