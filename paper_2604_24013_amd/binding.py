@@ -268,36 +268,41 @@ def dp_pair_step(p: int, rank: int, step: int, bucket, chunk_elems: int, recv, s
     _check(load().commfuse_dp_pair_step(p, rank, step, _ptr(bucket), chunk_elems, _ptr(recv), _stream(stream)))
 
 
-# The calls of a serving loop: a small step is shorter on the GPU than its call here, so these take tensors' and streams'
-# addresses in line and check the status in line; whatever else stands for one (an int, None) goes through _ptr and _stream.
-# us per call on the host, by _ptr, _stream and _check / in line: rs_step 4.3 / 3.9, run_schedule 4.65 / 4.4; the launch in it 3.
+# The calls of a serving loop: a small step is shorter on the GPU than its call here, so these take addresses in line, of tensors
+# and streams or as plain ints, each argument for itself, and check the status in line; what else may stand for one (None for a
+# tensor, an int of another class) takes the long way.  us per call on a library that launches nothing, all by _ptr, _stream and
+# _check / so: tensors and a stream 2.17 / 1.60, tensors and a stream's handle 2.14 / 1.62, plain ints 1.96 / 1.50, mixed 2.12 / 1.56.
 def rs_step(desc: LayerDesc, step: int, A, W, recv, out, stream=None) -> None:
+    call = (_lib or load()).commfuse_rs_step
     try:
-        status = (_lib or load()).commfuse_rs_step(desc, step, A.data_ptr(), W.data_ptr(), None if recv is None else recv.data_ptr(),
-                                                   out.data_ptr(), None if stream is None else stream.cuda_stream)
+        status = call(desc, step, A if type(A) is int else A.data_ptr(), W if type(W) is int else W.data_ptr(),
+                      recv if recv is None or type(recv) is int else recv.data_ptr(), out if type(out) is int else out.data_ptr(),
+                      stream if stream is None or type(stream) is int else stream.cuda_stream)
     except AttributeError:
-        status = load().commfuse_rs_step(desc, step, _ptr(A), _ptr(W), _ptr(recv), _ptr(out), _stream(stream))
+        status = call(desc, step, *map(_ptr, (A, W, recv, out)), _stream(stream))
     if status:
         _check(status)
 
 
 def rs_step_noalloc(desc: LayerDesc, step: int, A, W, recv, out, stream=None) -> None:
+    call = (_lib or load()).commfuse_rs_step_noalloc
     try:
-        status = (_lib or load()).commfuse_rs_step_noalloc(desc, step, A.data_ptr(), W.data_ptr(),
-                                                           None if recv is None else recv.data_ptr(), out.data_ptr(),
-                                                           None if stream is None else stream.cuda_stream)
+        status = call(desc, step, A if type(A) is int else A.data_ptr(), W if type(W) is int else W.data_ptr(),
+                      recv if recv is None or type(recv) is int else recv.data_ptr(), out if type(out) is int else out.data_ptr(),
+                      stream if stream is None or type(stream) is int else stream.cuda_stream)
     except AttributeError:
-        status = load().commfuse_rs_step_noalloc(desc, step, _ptr(A), _ptr(W), _ptr(recv), _ptr(out), _stream(stream))
+        status = call(desc, step, *map(_ptr, (A, W, recv, out)), _stream(stream))
     if status:
         _check(status)
 
 
 def ag_step(desc: LayerDesc, step: int, shard, W, O, stream=None) -> None:
+    call = (_lib or load()).commfuse_ag_step
     try:
-        status = (_lib or load()).commfuse_ag_step(desc, step, shard.data_ptr(), W.data_ptr(), O.data_ptr(),
-                                                   None if stream is None else stream.cuda_stream)
+        status = call(desc, step, shard if type(shard) is int else shard.data_ptr(), W if type(W) is int else W.data_ptr(),
+                      O if type(O) is int else O.data_ptr(), stream if stream is None or type(stream) is int else stream.cuda_stream)
     except AttributeError:
-        status = load().commfuse_ag_step(desc, step, _ptr(shard), _ptr(W), _ptr(O), _stream(stream))
+        status = call(desc, step, *map(_ptr, (shard, W, O)), _stream(stream))
     if status:
         _check(status)
 
@@ -336,11 +341,12 @@ def make_buffers(A_or_own_shard, W, O, peer_stage: Sequence, slot: Sequence, sen
 
 
 def run_schedule(desc: LayerDesc, kind: int, bufs: Buffers, compute_stream, copy_stream, flags: int = 0) -> None:
+    call = (_lib or load()).commfuse_run_schedule
     try:
-        status = (_lib or load()).commfuse_run_schedule(desc, kind, bufs, None if compute_stream is None else compute_stream.cuda_stream,
-                                                        None if copy_stream is None else copy_stream.cuda_stream, flags)
+        status = call(desc, kind, bufs, compute_stream if compute_stream is None or type(compute_stream) is int else compute_stream.cuda_stream,
+                      copy_stream if copy_stream is None or type(copy_stream) is int else copy_stream.cuda_stream, flags)
     except AttributeError:
-        status = load().commfuse_run_schedule(desc, kind, bufs, _stream(compute_stream), _stream(copy_stream), flags)
+        status = call(desc, kind, bufs, _stream(compute_stream), _stream(copy_stream), flags)
     if status:
         _check(status)
 
