@@ -271,6 +271,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
             }
         };
         const float nm = -m_run;
+        float l_tile = 0.0f;                                         // (a tile adds up by itself: what is small meets the row's sum once per tile)
         auto exponentials = [&](auto e_tag) __attribute__((always_inline)) {   // of elements e and e+1
             constexpr int e = decltype(e_tag)::value;
             bf16x2_t two;
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
                 two[i] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[e >> 4][(e & 15) + i], sl2, nm));
             pf[e >> 3][(e & 7)] = two[0];
             pf[e >> 3][(e & 7) + 1] = two[1];
-            l_run = __builtin_amdgcn_fdot2_f32_bf16(two, ones, l_run, false);
+            l_tile = __builtin_amdgcn_fdot2_f32_bf16(two, ones, l_tile, false);
         };
         float mx = -INFINITY;
         auto segment = [&](auto s_tag) __attribute__((always_inline)) {
@@ -318,6 +319,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
             each<0, 2>(exponentials, std::make_integer_sequence<int, 16>{});
         __builtin_amdgcn_sched_barrier(0);
         each<FIRST, 1>(segment, std::make_integer_sequence<int, 32 - FIRST>{});
+        l_run += l_tile;
         if constexpr (NEXT) {
             settle(kt + 1, sn, mx);
             wait_vmcnt<0>();                                         // V of tile kt+1 and K of tile kt+2 have landed

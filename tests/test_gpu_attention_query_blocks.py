@@ -67,3 +67,25 @@ def test_tiles_of_minus_infinity_have_no_weight(variant, waves, ksplit, first, l
         ref[:, a * 128:(a + 1) * 128] = P @ V[0, a][keep] / P.sum(axis=1, keepdims=True)
     assert not np.isnan(got).any()
     assert H.rel_err(got, ref) <= TOL_ATTN
+
+
+@pytest.mark.parametrize("waves", [8, 4])
+def test_small_probabilities_add_up_in_the_row_sum(variant, waves):
+    """The parked sum of a row, 64 keys of probability 1 and then 64 tiles of 64 keys of 2^-20: a lane adds up half of them, and
+    two such keys are half a unit in the last place of its 32.  A tile adds up by itself first: its sum here is exact, and each of
+    the 65 additions of one rounds by 2^-19 at the most."""
+    S, p, ksplit = 64 * 130, 65, 2
+    c, nt = S // p, 64 * waves
+    ws = variant(waves, ksplit)
+    q, k = np.zeros((1, 1, S, 128)), np.zeros((1, 1, S, 128))
+    q[..., 0] = 1.0
+    k[0, 0, 64:, 0] = -20.0                                          # scores in units of log2(e): 0, and -20
+    Vd, _ = _bf16(np.random.default_rng(3).standard_normal((1, 1, S, 128)))
+    out = torch.full((c, 128), float("nan"), dtype=torch.bfloat16, device=H.DEV)
+    cf.attn_slice(cf.attn_desc(p, 0, 1, 1, S, 128, 64, float(np.log(2.0))), 0, _bf16(q)[0], _bf16(k)[0], Vd, out, None)
+    torch.cuda.synchronize()
+    parts = ws[64 << 10:].view(torch.float32)[:ksplit * 66 * nt].view(ksplit, 66, nt).cpu().double()
+    used = slice(0, min(nt, 2 * c))                                  # two lanes hold a query
+    assert bool((parts[0, 64, used] == 0).all()) and bool((parts[1, 64, used] + 20 < 1e-4).all())   # the references
+    assert float((parts[0, 65, used] - (64 + 2.0 ** -8)).abs().max()) <= 2 * 65 * 2.0 ** -19
+    assert bool((parts[1, 65, used] == 65 * 64).all())
