@@ -313,8 +313,9 @@ enum {
                             group of consecutive (sub-)steps that fills the chip about once, and the
                             deliveries of a group are copied on copy_stream under the launches of the
                             groups before it, one event per group ordering the two streams.  (Few rows in all,
-                            see the end: one group; with CF_FUSED_COPY the launch starts behind what
-                            copy_stream holds.)
+                            see the end: one group.  With CF_FUSED_COPY, for few rows and for an all-gather whose k
+                            is not a multiple of 64: one launch that carries its deliveries, behind what copy_stream
+                            holds and in front of what is enqueued there later.)
                             (The kernel waits for nothing on the device: what it reads has been delivered, or lies in the
                             neighbours' buffers, before the launch.)
                             CF_KIND_RS_PAIR: every arrival is kept (recv_each) and the last step adds

@@ -996,14 +996,19 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
     const int n_groups = (S + group - 1) / group;
     std::vector<hipEvent_t> ev;
     // A few-rows launch that carries its deliveries also takes shapes that no other launch carries them for, whose copies
-    // would be on the copy stream: it starts behind what that stream holds, as they would.  So does an all-gather over a ragged
-    // k range.
+    // would be on the copy stream: it starts behind what that stream holds, and what comes there later (the peers' next
+    // deliveries, a reader of the landed ones) starts behind it, as with them.  So does an all-gather over a ragged k range.
     const bool joined = two_streams && carried && (few_rows || (kind == CF_KIND_AG && r.k % 64 != 0));
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (joined && cs != nullptr)
+        CF_HIP(hipStreamIsCapturing(cs, &capturing));
     if (grouped || joined) {
         if (cf_status st = get_events(1 + (size_t)n_groups, &ev))
             return st;
-        CF_HIP(hipEventRecord(ev[0], cs));               // the copy stream starts behind what the compute stream holds
-        CF_HIP(hipStreamWaitEvent(xs, ev[0], 0));
+    }
+    if (grouped || capturing != hipStreamCaptureStatusNone) {
+        CF_HIP(hipEventRecord(ev[0], cs));               // the copy stream starts behind what the compute stream holds (and so is
+        CF_HIP(hipStreamWaitEvent(xs, ev[0], 0));        // captured with it)
     }
     if (joined) {
         CF_HIP(hipEventRecord(ev[1], xs));
@@ -1210,6 +1215,10 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
             for (int i = 0; i < p - 1; ++i)
                 CF_HIP(hipMemcpyAsync(dsts[i], srcs[i], slot_bytes * m, hipMemcpyDeviceToDevice, cs));
         }
+    }
+    if (joined) {
+        CF_HIP(hipEventRecord(ev[0], cs));
+        CF_HIP(hipStreamWaitEvent(xs, ev[0], 0));
     }
     return CF_OK;
 }

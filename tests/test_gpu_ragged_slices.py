@@ -60,3 +60,35 @@ def test_ragged_slices_land_whole(tile, deep, layout, p, mc, n, k, m):
         # fp32 sums of k products: k roundings of at most half an ulp of the running sum; bf16 results round once more
         tol = 2.0 ** -24 * k ** 0.5 * 4 + (2.0 ** -8 if out == torch.bfloat16 else 0)
         assert float((got - want).abs().max() / want.abs().max()) <= tol
+
+
+@pytest.mark.parametrize("p,mc,n,k", [(4, 272, 1032, 264), (8, 130, 1536, 1096), (8, 8, 1536, 4104)])      # tiles; few rows
+def test_two_streams_keep_the_copy_streams_order(p, mc, n, k):
+    """What is enqueued on the copy stream before the call is read by it, and what is enqueued there after the call finds the
+    deliveries landed and may overwrite the peers' buffers: the compute stream is busy for longer than that takes."""
+    g = torch.Generator(device=DEV).manual_seed(5)
+    rnd = lambda *s: torch.empty(s, device=DEV).normal_(generator=g).bfloat16()
+    fresh, W = [rnd(mc, k) for _ in range(p)], rnd(k, n)
+    nan = lambda t: torch.full_like(t, float("nan"))
+    stage, each, O = [nan(t) for t in fresh[1:]], [nan(t) for t in fresh[1:]], torch.full((p * mc, n), float("nan"), device=DEV)
+    bufs = cf.make_buffers(fresh[0], W, O, stage, (None, None), (None, None), None, each)
+    cs, xs = torch.cuda.Stream(), torch.cuda.Stream()
+    busy = torch.zeros(1 << 28, device=DEV)                          # a pass over it takes longer than the whole rank step
+    torch.cuda.synchronize()
+    with torch.cuda.stream(xs):
+        for t, f in zip(stage, fresh[1:]):
+            t.copy_(f)
+    with torch.cuda.stream(cs):
+        for _ in range(4):
+            busy.add_(1.0)
+    cf.run_schedule(cf.layer_desc(p, 1, mc, n, k), cf.CF_KIND_AG, bufs, cs, xs, cf.CF_PERSISTENT | cf.CF_FUSED_COPY)
+    with torch.cuda.stream(xs):
+        landed = [t.clone() for t in each]
+        for t in stage:
+            t.fill_(float("nan"))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(landed, fresh[1:]))
+    for i, s in enumerate(fresh):
+        want = s.double() @ W.double()
+        c = (1 - i) % p
+        assert float((O[c * mc:(c + 1) * mc].double() - want).abs().max() / want.abs().max()) <= 2.0 ** -24 * k ** 0.5 * 4

@@ -149,6 +149,32 @@ def test_slices_over_a_ragged_k_range_are_carried(dry, monkeypatch, k, pad, off,
     assert kernels[-1].startswith("gemm_bf16_dl_kernel") and (len(kernels) > 1) == copied
 
 
+@pytest.mark.parametrize("kind,p,mc,n,k,carried", [
+    (cf.CF_KIND_AG, 8, 512, 1536, 1096, True), (cf.CF_KIND_AG, 2, 512, 1536, 4104, True),             # a ragged k range
+    (cf.CF_KIND_AG, 8, 8, 1536, 4096, True), (cf.CF_KIND_RS, 8, 8, 4096, 1376, True),                 # few rows
+    (cf.CF_KIND_AG, 8, 512, 1536, 1096, False), (cf.CF_KIND_RS, 8, 8, 4096, 1376, False)])
+@pytest.mark.parametrize("capturing", [False, True])
+def test_the_copy_streams_work_stays_in_order_with_the_deliveries(dry, monkeypatch, kind, p, mc, n, k, carried, capturing):
+    """On two streams: what the copy stream holds comes before the kernel that reads the peers' buffers or before the copies on
+    that stream, and what is enqueued there later comes after them, whoever delivers.  Under capture the copy stream joins first."""
+    if capturing:
+        monkeypatch.setenv("COMMFUSE_DRY_CAPTURING", "1")
+    compute, copy = 0x10, 0x20
+    stage, each, sends = _tables(p)
+    bufs = cf.make_buffers(P(0), P(1), P(2), stage, (None, None), (None, None), None, each, sends)
+    desc = cf.layer_desc(p, 1, mc, n, k)
+    flags = cf.CF_PERSISTENT | (cf.CF_FUSED_COPY if carried else 0)
+    seen = dry.order(lambda: cf.run_schedule(desc, kind, bufs, compute, copy, flags))
+    launches = [i for i, (op, stream, _) in enumerate(seen) if op == "launch" and stream == compute]
+    if not carried:
+        assert any(op in ("launch", "copy") and stream == copy for op, stream, _ in seen)
+        return
+    assert len(launches) == 1 and not any(op in ("launch", "copy") and stream == copy for op, stream, _ in seen)
+    handed_over = lambda ops, a, b: any(x[0] == "record" and x[1] == a and ("wait", b, x[2]) in ops[i:] for i, x in enumerate(ops))
+    assert handed_over(seen[:launches[0]], copy, compute) and handed_over(seen[launches[0]:], compute, copy)
+    assert seen[0][:2] == ("record", compute if capturing else copy) and len(seen) == (7 if capturing else 5)
+
+
 @pytest.mark.parametrize("m,n,rows,tiles,splits", [(552, 536, 5768, 25, 7), (520, 856, 2544, 35, 4), (776, 1368, 912, 77, 1), (2048, 2048, 8192, 256, 1)])
 def test_splits_of_a_weight_gradient(dry, m, n, rows, tiles, splits):
     cf_lib = dry.calls(lambda: (cf.set_workspace(P(9), 1 << 30), cf.wgrad_step(cf.layer_desc(1, 0, rows, n, m), 0, P(0), P(1), P(2)), cf.set_workspace(None)))
