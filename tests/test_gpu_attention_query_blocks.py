@@ -89,3 +89,35 @@ def test_small_probabilities_add_up_in_the_row_sum(variant, waves):
     assert bool((parts[0, 64, used] == 0).all()) and bool((parts[1, 64, used] + 20 < 1e-4).all())   # the references
     assert float((parts[0, 65, used] - (64 + 2.0 ** -8)).abs().max()) <= 2 * 65 * 2.0 ** -19
     assert bool((parts[1, 65, used] == 65 * 64).all())
+
+
+@pytest.mark.parametrize("waves", [8, 4])
+@pytest.mark.parametrize("ksplit", [1, 2])
+@pytest.mark.parametrize("tiles", [2, 5, 8])
+def test_references_that_rise_from_tile_to_tile(variant, waves, ksplit, tiles):
+    """Scores of query i grow by g_i (in units of log2(e)) from one 64-key tile to the next, in the last by half of that: nine and
+    twenty are beyond what the reference may lag behind (eight) and raise it in every tile, from either pair of buffers; three,
+    one half and a fall do not by themselves, but share a wave with those that do -- and keep a visible part of every tile.  In the
+    second half of the queries every other tile falls back, so that the reference rises in tiles of one pair of buffers only."""
+    rng = np.random.default_rng(tiles)
+    S = 64 * tiles - 24
+    grow = np.array([9.0, 0.5, 3.0, -1.0, 20.0, 0.0, 1.0, 8.5])[np.arange(S) % 8]
+    lone = np.arange(S) // 32 % 2 == 1                               # waves in which nothing rises by more than three
+    grow[lone] = np.minimum(grow[lone], 3.0)
+    tile = np.arange(S) // 64
+    step = tile - 0.5 * (tile == tiles - 1)
+    q, k = 0.05 * rng.standard_normal((1, 1, S, 128)), rng.standard_normal((1, 1, S, 128))
+    q[..., :2], k[..., :2] = 0.0, 0.0
+    half = S // 2
+    q[0, 0, :half, 0], q[0, 0, half:, 1] = grow[:half], grow[half:]
+    k[0, 0, :, 0], k[0, 0, :, 1] = step, np.where(tile % 2 == 0, step, 0.0)
+    v = rng.standard_normal((1, 1, S, 128)) + 4.0 * (tile % 3)[None, None, :, None]     # a tile that counts wrongly shows
+    variant(waves, ksplit)
+    (Qd, Q), (Kd, K), (Vd, V) = _bf16(q), _bf16(k), _bf16(v)
+    scale = float(np.float32(np.log(2.0)))
+    got = _attend(Qd, Kd, Vd, scale)
+    s = Q[0, 0] @ K[0, 0].T * scale
+    P = np.exp(s - s.max(axis=1, keepdims=True))
+    ref = P @ V[0, 0] / P.sum(axis=1, keepdims=True)
+    assert not np.isnan(got).any()
+    assert float((np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)).max()) <= TOL_ATTN     # query by query

@@ -175,6 +175,24 @@ def test_the_copy_streams_work_stays_in_order_with_the_deliveries(dry, monkeypat
     assert seen[0][:2] == ("record", compute if capturing else copy) and len(seen) == (7 if capturing else 5)
 
 
+@pytest.mark.parametrize("p,batch,heads,seq,room,kernel,grid", [
+    # keys over waves, 32 queries per workgroup: the only choice without a workspace where query blocks leave a quarter of the chip
+    # idle, and with one as many splits as pay and fit
+    (1, 1, 1, 64, 0, "keys_over_waves", 2), (4, 2, 3, 1120, 0, "keys_over_waves", 54), (4, 2, 3, 1120, 8, "keys_over_waves", 54 * 3),
+    (8, 1, 1, 8192, 8, "keys_over_waves", 32 * 8), (8, 1, 8, 8192, 0, "keys_over_waves", 256), (2, 4, 2, 2362, 1024, "keys_over_waves", 296),
+    # query blocks of 256: the chip is full, or their partials fit
+    (1, 4, 8, 4096, 0, "slice_kernel<8>", 512), (2, 2, 8, 4638, 1024, "slice_kernel<8>", 160 * 2), (2, 2, 8, 4638, 8, "keys_over_waves", 1168),
+    # query blocks of 128, two workgroups per compute unit
+    (8, 1, 8, 8192, 1024, "slice_kernel<4>", 64 * 8), (1, 4, 4, 2048, 1024, "slice_kernel<4>", 256 * 2), (2, 1, 2, 6152, 1024, "slice_kernel<4>", 50 * 10)])
+def test_kernel_and_key_splits_of_an_attention_slice(dry, p, batch, heads, seq, room, kernel, grid):
+    """(`room`: the registered workspace in MiB; 0: none)"""
+    desc = cf.attn_desc(p, 0, batch, heads, seq, 128, 64, 0.1)
+    calls = dry.calls(lambda: (cf.set_workspace(P(9), room << 20) if room else None, cf.attn_slice(desc, 0, P(0), P(1), P(2), P(3)),
+                               cf.set_workspace(None)))
+    (name, workgroups, _), = [c for c in calls if "attn" in c[0]]
+    assert kernel in name and workgroups == grid
+
+
 @pytest.mark.parametrize("m,n,rows,tiles,splits", [(552, 536, 5768, 25, 7), (520, 856, 2544, 35, 4), (776, 1368, 912, 77, 1), (2048, 2048, 8192, 256, 1)])
 def test_splits_of_a_weight_gradient(dry, m, n, rows, tiles, splits):
     cf_lib = dry.calls(lambda: (cf.set_workspace(P(9), 1 << 30), cf.wgrad_step(cf.layer_desc(1, 0, rows, n, m), 0, P(0), P(1), P(2)), cf.set_workspace(None)))
