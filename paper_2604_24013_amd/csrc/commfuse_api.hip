@@ -255,6 +255,16 @@ bool wgrad_can_carry_copy(const Resolved &r)
     return r.mc * r.lda * 2 < lim && r.mc * r.ldw * 2 < lim && r.k * r.ldo * 4 < lim;
 }
 
+void use_workspace(cf::GemmParams &gp, const Workspace &ws)
+{
+    if (ws.ptr == nullptr || ws.bytes <= WS_COUNTER_BYTES)
+        return;
+    gp.counters = static_cast<unsigned *>(ws.ptr);
+    gp.ws = reinterpret_cast<float *>(static_cast<char *>(ws.ptr) + WS_COUNTER_BYTES);
+    gp.ws_bytes = ws.bytes - WS_COUNTER_BYTES;
+    gp.max_tiles = (int)(WS_TILE_COUNTER_BYTES / sizeof(unsigned));
+}
+
 cf_status launch_gemm(const Resolved &r, const void *A_rows, const void *W, const float *recv, void *out,
                       hipStream_t s, const CopyJob *job = nullptr, const float *const *recv_more = nullptr,
                       int n_recv_more = 0, const Workspace *ws_instead = nullptr)
@@ -268,15 +278,7 @@ cf_status launch_gemm(const Resolved &r, const void *A_rows, const void *W, cons
     gp.recv = recv;
     gp.out = out;
     fill_shape(gp, r);
-    {
-        const Workspace ws = ws_instead != nullptr ? *ws_instead : workspace_for(s);   // (the library's own scratch, or the registered one)
-        if (ws.ptr != nullptr && ws.bytes > WS_COUNTER_BYTES) {
-            gp.counters = static_cast<unsigned *>(ws.ptr);
-            gp.ws = reinterpret_cast<float *>(static_cast<char *>(ws.ptr) + WS_COUNTER_BYTES);
-            gp.ws_bytes = ws.bytes - WS_COUNTER_BYTES;
-            gp.max_tiles = (int)(WS_TILE_COUNTER_BYTES / sizeof(unsigned));
-        }
-    }
+    use_workspace(gp, ws_instead != nullptr ? *ws_instead : workspace_for(s));   // (the library's own scratch, or the registered one)
     const int ncu = num_cu_of_current_device();
     if (job != nullptr && job->wait_flag != nullptr) {
         gp.wait_flag = job->wait_flag;
@@ -418,15 +420,7 @@ cf_status wgrad_step_impl(const Resolved &r, int step, const void *left, const v
     }
     if (!cf::gemm_bf16_takes_recv_list(gp, true))
         return fail(CF_ERR_UNSUPPORTED, "the weight-gradient step needs operands below 2 GiB (direct-to-LDS kernel)");
-    {
-        const Workspace ws = workspace_for(s);
-        if (ws.ptr != nullptr && ws.bytes > WS_COUNTER_BYTES) {
-            gp.counters = static_cast<unsigned *>(ws.ptr);
-            gp.ws = reinterpret_cast<float *>(static_cast<char *>(ws.ptr) + WS_COUNTER_BYTES);
-            gp.ws_bytes = ws.bytes - WS_COUNTER_BYTES;
-            gp.max_tiles = (int)(WS_TILE_COUNTER_BYTES / sizeof(unsigned));
-        }
-    }
+    use_workspace(gp, workspace_for(s));
     const int ncu = num_cu_of_current_device();
     if (job != nullptr && job->wait_flag != nullptr) {
         gp.wait_flag = job->wait_flag;
@@ -950,6 +944,7 @@ cf_status enqueue_persistent(const Resolved &r, int kind, const cf_buffers *b, h
         hops.right = kind == CF_KIND_WGRAD_G;
         cf::GemmParams gp;
         fill_wgrad_shape(gp, all);
+        use_workspace(gp, workspace_for(cs));        // (a k range that will be split is not carried)
         hops.to(&gp);
         carried = cf::gemm_bf16_carries_gathered(gp, num_cu_of_current_device());
         hops.block[r.rank] = reinterpret_cast<const void *>(gathered);

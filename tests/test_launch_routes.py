@@ -272,3 +272,18 @@ def test_weight_gradients_of_whole_tiles_carry_their_deliveries(dry, kind, mc, k
     bufs = cf.make_buffers(block(rank), P(1), P(2), stage, (None, None), (None, None), None, each)
     kernels = [c[0] for c in dry.calls(lambda: cf.run_schedule(desc, kind, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY))]
     assert kernels[-1].startswith("gemm_bf16_dl_kernel") and (len(kernels) > 1) == copied
+
+
+@pytest.mark.parametrize("room,copied", [(None, False), (32 << 20, True), (1 << 20, False)])
+def test_weight_gradients_that_are_split_copy_their_deliveries(dry, monkeypatch, room, copied):
+    """The rule that carries looks at the launch as it will run, workspace and all."""
+    monkeypatch.setenv("COMMFUSE_TILE", "256x256")
+    p, mc, k, n = 8, 512, 1024, 1024
+    block = lambda c: P(20) + c * mc * k * 2
+    bufs = cf.make_buffers(block(3), P(1), P(2), [P(10 + i) for i in range(p - 1)], (None, None), (None, None), None,
+                           [block((3 - i) % p) for i in range(1, p)])
+    calls = dry.calls(lambda: (cf.set_workspace(P(9), room) if room else None,
+                               cf.run_schedule(cf.layer_desc(p, 3, mc, n, k), cf.CF_KIND_WGRAD_X, bufs, None, None, ONE_LAUNCH | cf.CF_FUSED_COPY),
+                               cf.set_workspace(None)))
+    kernels = [c[0] for c in calls if "copy" in c[0] or "gemm" in c[0]]
+    assert kernels[-1].startswith("gemm_bf16_dl_kernel<256, 256,") and (len(kernels) > 1) == copied
