@@ -175,6 +175,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
     f32x16_t oacc[DT];
     float m_run = -3.402823466e38f;      // (finite: against -inf a tile whose scores are all -inf would give NaN)
     float l_run = 0.0f;                  // of the keys this lane holds; the query's other half lives in lane ^ 32
+    float l_pair = 0.0f;                 // ... of a pair of tiles, which adds up by itself: what is small meets the row's sum once per pair
 #pragma unroll
     for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -239,6 +240,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
             asm volatile("" : "+v"(alpha));                          // (keeps this a branch, as above)
             m_run = m_new;
             l_run *= alpha;
+            l_pair *= alpha;
 #pragma unroll
             for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -271,7 +273,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
             }
         };
         const float nm = -m_run;
-        float l_tile = 0.0f;                                         // (a tile adds up by itself: what is small meets the row's sum once per tile)
         auto exponentials = [&](auto e_tag) __attribute__((always_inline)) {   // of elements e and e+1
             constexpr int e = decltype(e_tag)::value;
             bf16x2_t two;
@@ -280,7 +281,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
                 two[i] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[e >> 4][(e & 15) + i], sl2, nm));
             pf[e >> 3][(e & 7)] = two[0];
             pf[e >> 3][(e & 7) + 1] = two[1];
-            l_tile = __builtin_amdgcn_fdot2_f32_bf16(two, ones, l_tile, false);
+            l_pair = __builtin_amdgcn_fdot2_f32_bf16(two, ones, e == 0 && B == 0 ? 0.0f : l_pair, false);
+            if constexpr (e == 30 && (B == 1 || !NEXT))
+                l_run += l_pair;
         };
         float mx = -INFINITY;
         auto segment = [&](auto s_tag) __attribute__((always_inline)) {
@@ -319,7 +322,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
             each<0, 2>(exponentials, std::make_integer_sequence<int, 16>{});
         __builtin_amdgcn_sched_barrier(0);
         each<FIRST, 1>(segment, std::make_integer_sequence<int, 32 - FIRST>{});
-        l_run += l_tile;
         if constexpr (NEXT) {
             settle(kt + 1, sn, mx);
             wait_vmcnt<0>();                                         // V of tile kt+1 and K of tile kt+2 have landed
