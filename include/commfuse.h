@@ -135,9 +135,10 @@ cf_status commfuse_rs_step(const cf_layer_desc *desc, int step, const void *A, c
  * tiles) is a file-scope device array inside the library instead of the workspace registered with
  * commfuse_set_workspace, which this call ignores.  The call allocates nothing: no hipMalloc, no hipFree, no
  * allocating library routine.
- *   Limit: (m_chunk / m) * n <= 2,097,152 elements per step (8 k-splits of such a step's fp32 output fill the
- *     64 MiB of partial tiles; 64 KiB of counters beside them); larger steps get CF_ERR_INVALID_ARG and
- *     nothing is enqueued.  Every GPU the library is used on holds its own 64 MiB + 64 KiB array from the
+ *   Limit: (m_chunk / m) * n <= 2,097,152 elements per step (eight fp32 outputs of 64 MiB in all, the size of the
+ *     partial tiles; 64 KiB of counters beside them); larger steps get CF_ERR_INVALID_ARG and nothing is
+ *     enqueued.  (The splits that the library chooses park whole tiles, one of 64 KiB per compute unit at the
+ *     most; a split forced by the environment that does not fit leaves the k range whole.)  Every GPU the library is used on holds its own 64 MiB + 64 KiB array from the
  *     moment the library's code is loaded there until the process ends.
  *   First call on a device: looks up the device address of that GPU's array once (with that device current)
  *     and zeroes the arrival counters with a small fill kernel on `hip_stream`; make that first call outside
@@ -348,20 +349,22 @@ enum {
                             stored on to the landing buffer by one of the workgroups that load it.  Weight gradient:
                             likewise, whichever operand travels, where the launch runs whole 256x256 tiles of dW, the
                             blocks of m_chunk rows are multiples of 64 from 128 on and have no padding between their
-                            rows (same sums, bit for bit; else copied in front).  A carried row
+                            rows, p is at most 15 and every peer_stage and recv_each lies on 16 bytes (same sums, bit for
+                            bit; else copied in front).  A carried row
                             block lands without the padding of its rows, one copied in front with it.  Copied in front,
-                            as without the flag, are: slices of an all-gather with padding between their rows (lda != k)
-                            whose k is not a multiple of 64; partial sums with
+                            as without the flag, are: slices of an all-gather whose k is not a multiple of 64 where they
+                            have padding between their rows (lda != k) or a peer_stage or recv_each lies off the 16-byte
+                            grid; partial sums with
                             padding between their rows (ldo != n), unless 256x256 is the tile by the step's area and k
-                            fills 18 k-tiles of 64 (20 with a ragged last one) -- the attention layer's in any case --;
-                            the other kinds.
+                            fills 18 k-tiles of 64 (20 with a ragged last one) -- the attention layer's in any case.
                             With CF_FUSED_COPY (CF_KIND_RS_PAIR): one pass in front of the launch reads all arrivals
                             from the partners' buffers (peer_stage), lands them (recv_each) and leaves their sum in
                             O, which the last step adds to its product (p = 2: the last step's epilogue reads the one
                             arrival and lands it).  Same sums, bit for bit, as without the flag (but p = 2, whose k order
                             is rotated without it where CF_KIND_RS would).
                             Where a rank step has few rows in all (decoded tokens; the kernel that packs the rows
-                            of every step into one launch) every kind's deliveries are carried, whatever k.
+                            of every step into one launch) every kind's deliveries are carried, whatever k.  (These two
+                            on the 16-byte grid; off it they are copied in front.)
                             Not with CF_DEVICE_WAIT.                                                  */
     CF_DEVICE_WAIT = 64u /* bf16 RS / AG only, needs a registered workspace: the compute
                             stream does not wait for the copy stream between steps;
@@ -471,7 +474,9 @@ const char *commfuse_last_error(void);
  * by the last one to finish.  Optional: without one every tile is computed by a
  * single workgroup.
  *   commfuse_workspace_bytes: size that lets every split choice be used for this
- *     layer (0 if the kind / dtype never splits).  Host-only arithmetic.
+ *     layer (0 if the kind / dtype never splits): 64 KiB and the partial tiles of the
+ *     library's choice, eight fp32 outputs of a step at the least.  In a smaller one k
+ *     is split as far as whole tiles fit.  Host-only arithmetic.
  *   commfuse_set_workspace: registers a caller-owned DEVICE buffer (16-byte
  *     aligned), or clears a registration (NULL / 0).  With hip_stream == NULL the
  *     buffer serves all later calls of this process; with a stream it serves the

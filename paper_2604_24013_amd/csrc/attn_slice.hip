@@ -1,19 +1,21 @@
 // Attention of one query slice against the rank's full keys and values (Alg. 4: scores = Q_s[l] K^T,
 // Softmax, times V), bf16 operands, fp32 accumulation and fp32 online softmax, for gfx950.
 //
-// One workgroup = 4 waves = 4 * 32 * QT queries of one (batch element, head); it walks over the keys in
-// tiles of 64.  Per tile and wave:
+// Query blocks: one workgroup = 8 or 4 waves of 32 queries each of one (batch element, head), which share the key tiles; it
+// walks over the keys in tiles of 64, a pipeline one tile deep (the scores of the next tile under the exponentials of this one).
+// Keys over waves: one workgroup = 32 queries, its eight waves share out the keys in tiles of 32.  Per tile and wave:
 //   S^T = K Q^T      v_mfma_f32_32x32x16_bf16 with the key tile as the MFMA "A" operand and the wave's
 //                    queries (kept in registers for the whole walk) as "B": a lane then owns ONE query
 //                    (lane & 31) and 16 of every 32 keys, so the softmax statistics of a query live in two
 //                    lanes (lane, lane ^ 32) and need one cross-lane exchange per tile;
-//   online softmax   m' = max(m, max S), P = exp2(S - m'), l = l * exp2(m - m') + sum P, O *= exp2(m - m');
+//   online softmax   m' = max(m, max S), P = exp2(S - m'), l = l * exp2(m - m') + sum P, O *= exp2(m - m')
+//                    (query blocks keep m until a probability would exceed 2^8);
 //   O^T += V^T P^T   the probabilities, rounded to bf16, are already in the register layout of an MFMA "B"
 //                    operand if the 16 contraction slots of a slice are taken to mean the keys the lane
 //                    holds (a fixed permutation of the slice's keys); the V tile stays [key x d] in LDS and
 //                    its transposed fragments are fetched with the transposing LDS read at the row offsets
 //                    of that same permutation.  No data moves between lanes, no P tile goes through LDS.
-// K and V tiles go global -> LDS directly (buffer_load ... lds), double-buffered; a key row of 256 bytes has
+// K and V tiles go global -> LDS directly (buffer_load ... lds; query blocks: double-buffered); a key row of 256 bytes has
 // its sixteen 16-byte chunks XOR-ed with (key & 15) so that the fragment reads of 16 consecutive keys hit 16
 // different bank groups; the V tile uses the [k x n] weight-tile layout of the chunk GEMM.
 // Keys beyond the sequence read as zero through the buffer bounds check and are masked to -inf; query rows
@@ -91,6 +93,9 @@ __device__ __forceinline__ void each(F &f, std::integer_sequence<int, I...>)
 // queries x 8192 keys (NW = 8, the chip full) 256 / 237 = 1.16 PFLOP/s at 1.88 GHz (the chip's power limit; 58 % of the cycles
 // are MFMAs, 44 before); 4 heads (one wave per SIMD, NW = 4) 192 / 140; 8 heads x 1024 queries, a quarter of the chip, 190 / 122.
 // What is left, by parts taken out: without the exponentials 223, without any softmax 206, without the LDS reads 216.
+// (A row sum of its own per tile instead of per pair of tiles: one addition and one move more per tile, sixteen tiles a
+// workgroup -- 8 heads x 1024 queries x 8192 keys in eight splits -- 51.1 / 52.2; no sum between the keys and the row's, which
+// loses what is under half a unit in the last place of the row so far, 51.3.)
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void attn_slice_kernel(AttnParams P)
 {

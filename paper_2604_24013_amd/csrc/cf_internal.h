@@ -119,8 +119,8 @@ struct Tuning {
     int stream_recv = -1;           // COMMFUSE_STREAM_RECV: any value keeps a launch on the tile kernels (-1 = unset)
     int mfma16 = -1;                // COMMFUSE_MFMA16 = 0 | 1: 16x16x32 MFMAs in the 256x256 persistent kernel (-1 = unset)
     int persist_wgs = 0;            // COMMFUSE_PERSIST_WGS = cap on the persistent kernel's grid (0 = unset)
-    int carry = -1;                 // COMMFUSE_CARRY = 0: a one-launch RS / AG / pairwise RS never carries its deliveries
-                                    // under CF_FUSED_COPY (-1 = unset, 1: wherever the launch can)
+    int carry = -1;                 // COMMFUSE_CARRY = 0: a one-launch RS / AG / pairwise RS / weight gradient never carries its
+                                    // deliveries under CF_FUSED_COPY (-1 = unset, 1: wherever the launch can)
     int tile_f32_bm = 0;            // COMMFUSE_TILE_F32 = "128x128" | "64x64"             (0 = unset)
     int rows = -1;                  // COMMFUSE_ROWS = 0: never the few-rows kernel            (-1 = unset)
     int rows_mf = 0, rows_nc = 0, rows_ks = 0;   // COMMFUSE_ROWS = "MFxNCxKS": that shape of it (0 = unset)
@@ -149,9 +149,9 @@ bool gemm_bf16_takes_recv_list(const GemmParams &p, bool w_kn);
 // True if launch_gemm_bf16 would run this persistent launch (reduce_scatter: its steps add a received partial;
 // else an all-gather's) on a kernel that honours GemmParams::land_step (the delivery carried by the consumer)
 // for every step that receives.
-// the same for a weight gradient (GemmParams::hop_tiles), of the shape that is launched
-bool gemm_bf16_carries_gathered(const GemmParams &p, int num_cu);
 bool gemm_bf16_carries_delivery(const GemmParams &p, bool w_kn, bool out_bf16, int num_cu, bool reduce_scatter);
+// The same of a weight gradient (GemmParams::hop_tiles), with the shape and the workspace that it will be launched with.
+bool gemm_bf16_carries_gathered(const GemmParams &p, int num_cu);
 // Steps per launch when a persistent rank step of p.n_steps steps is cut into launches that fill the chip about once
 // each (equal groups; p.n_steps when the whole rank step is one round or less).
 int gemm_bf16_steps_per_launch(const GemmParams &p, bool w_kn, int num_cu);

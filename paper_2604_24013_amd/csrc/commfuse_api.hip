@@ -65,7 +65,7 @@ constexpr size_t WS_TILE_COUNTER_BYTES = 60 * 1024;   // split-K arrival counter
 constexpr size_t WS_FLAG_OFFSET = 60 * 1024;          // delivery flags (CF_DEVICE_WAIT): one word per step
 constexpr int WS_MAX_FLAGS = 512;
 constexpr size_t WS_STATUS_OFFSET = 63 * 1024;        // one status word (bit 0: a device-side wait timed out)
-constexpr int WS_MAX_SPLITS = 8;
+constexpr int WS_MAX_SPLITS = 8;                      // sizes below: this many fp32 outputs at the least
 struct Workspace {
     void *ptr = nullptr;
     size_t bytes = 0;
@@ -91,7 +91,7 @@ Workspace workspace_for(hipStream_t s)
 // loaded.  Every GPU the library runs on holds its own copy of the array until the process ends.  In host
 // code the array's name only stands for the symbol; the device address is looked up once per device
 // (static_scratch_of_current_device) and everything below uses that pointer.
-constexpr size_t STATIC_PARTIAL_BYTES = (size_t)64 << 20;                       // 8 k-splits of 2^21 fp32 elements
+constexpr size_t STATIC_PARTIAL_BYTES = (size_t)64 << 20;   // a rule's splits park a tile of 64 KiB per compute unit at the most (16 MiB)
 constexpr size_t STATIC_SCRATCH_BYTES = WS_COUNTER_BYTES + STATIC_PARTIAL_BYTES;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
@@ -1643,7 +1643,7 @@ cf_status commfuse_rs_step_noalloc(const cf_layer_desc *desc, int step, const vo
     Resolved r;
     if (cf_status st = resolve(desc, CF_KIND_RS, &r))
         return st;
-    // the largest step whose k-split partials fit the library's scratch for every split choice
+    // (the limit is the interface's.  Splits that a rule chooses fit by far; one forced by override that does not runs whole)
     if ((size_t)r.mc * (size_t)r.n * sizeof(float) * WS_MAX_SPLITS > STATIC_PARTIAL_BYTES)
         return fail(CF_ERR_INVALID_ARG,
                     "commfuse_rs_step_noalloc: a step output of %lld x %lld fp32 elements exceeds the static scratch "
@@ -1798,6 +1798,7 @@ size_t commfuse_workspace_bytes(const cf_layer_desc *desc, int kind)
         return 0;
     cf::GemmParams step;
     fill_shape(step, r);
+    // (what the splits need is mostly far less; callers give the rest to the attention's key splits and to overrides)
     size_t bytes = (size_t)WS_MAX_SPLITS * (size_t)r.mc * (size_t)r.n * sizeof(float);
     for (const size_t parts : {cf::gemm_rows_ws_bytes(step, r.bf16_in, r.w_kn, ncu), cf::gemm_bf16_split_ws_bytes(step, r.w_kn, ncu)})
         bytes = parts > bytes ? parts : bytes;     // (whole tiles: more than the step's elements)

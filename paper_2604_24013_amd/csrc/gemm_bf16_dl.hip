@@ -1387,7 +1387,10 @@ bool gemm_bf16_dl_supported(const GemmParams &p, bool w_kn)
 // tile shape can.  Slices with padding between their rows only over whole k-tiles: a copy in front moves the padding and the
 // kernel does not, and which of the two a caller finds is part of the interface.  (All slices whose k is no multiple of 64
 // used to be copied in front, us per rank step copied / carried: 4 x 130 x 2280 x 1696 25.4 / 16.6, 8 x 264 x 632 x 2848 40.0 /
-// 26.4, 8 x 103 x 2176 x 816 17.9 / 12.5, 4 x 177 x 2256 x 5976 73.5 / 48.3, 8 x 705 x 4888 x 4184 246 / 242.)
+// 26.4, 8 x 103 x 2176 x 816 17.9 / 12.5, 4 x 177 x 2256 x 5976 73.5 / 48.3, 8 x 705 x 4888 x 4184 246 / 242; of 70 drawn ones of 20
+// GFLOP and more 0.88 on average, three slower by 1 to 3 %, and [n x k] 4 x 400 x 4808 x 4536, one round on 152 compute units, 120 /
+// 128.  On two streams, copied in groups under the launches / carried: 8 x 173 x 1040 x 1720 46.0 / 38.2, 4 x 654 x 400 x 3232 59.6 /
+// 48.1, 8 x 904 x 504 x 3512 84.7 / 78.5; of 30 drawn ones 0.88, none over 1 % slower.)
 bool gemm_bf16_dl_carries_operand(const GemmParams &p)
 {
     return p.n_steps > 0 && !p.a_t && (p.K % BK == 0 || p.lda == p.K);

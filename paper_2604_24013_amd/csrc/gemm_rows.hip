@@ -160,13 +160,30 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams<SEG> P)
     // us per call, columns one by one / in bands: all-gather step 30 x 4080 x 4984 16.9 / 12.6, reduce-scatter step 685 x 1384 x
     // 5168 32.2 / 28.6, all-gather rank step 4 x 34 x 1800 x 2600 16.5 / 13.5, 8 x 8 x 1536 x 4096 11.8 / 10.8, where two tiles share
     // a 128-byte line of W.)
-    const int unit = xcd_remap((int)blockIdx.x, tiles * P.ksplit);
-    int tile_n = unit, split = 0, tile_r = 0;
-    if (const int per_col = P.tiles_r * P.ksplit; per_col > 1) {
-        tile_n = unit / per_col;
-        const int in = unit - tile_n * per_col;
-        split = in / P.tiles_r;
-        tile_r = in - split * P.tiles_r;
+    // One by one, tile column c on XCD c % 8, where that keeps a column's row tiles on one XCD as well and no line is shared: the
+    // rows of [k x n] weights are then read in pieces of a line each by all XCDs at once, not a piece of 512 bytes and more by one.
+    // us, one by one / in bands: steps 64 x 4096 x 8192 19.5 / 21.2, 128 x 4096 x 8192 22.2 / 24.2, 128 x 8192 x 3584 15.7 / 16.5,
+    // 256 x 2048 x 8192 21.4 / 22.6, 100 x 5120 x 640 6.0 / 6.5; reduce-scatter rank steps 8 x 16 x 8192 x 3584 20.8 / 21.6, 4 x 16 x
+    // 6144 x 2048 11.4 / 11.7.  Narrower matrices and launches that land the slices of an all-gather beside the tiles are faster in
+    // bands: 512 x 1024 x 4096 13.5 / 12.6, reduce-scatter 8 x 32 x 2048 x 4096 15.6 / 14.7, all-gather 8 x 8 x 4096 x 4096 15.6 /
+    // 13.2; and so is everything with [n x k] weights (1 x 4096 x 8192 14.8 / 11.5).
+    int tile_n, split = 0, tile_r = 0;
+    if (BF16 && KN && NC == 4 && P.tiles_n % 8 == 0 && P.tiles_n > (SEG == 1 ? 16 : 32) && P.ldw % 64 == 0 && P.copy_wgs == 0) {
+        tile_r = (int)blockIdx.x / P.tiles_n;
+        tile_n = (int)blockIdx.x - tile_r * P.tiles_n;
+        if (P.ksplit > 1) {
+            split = tile_r % P.ksplit;
+            tile_r /= P.ksplit;
+        }
+    } else {
+        const int unit = xcd_remap((int)blockIdx.x, tiles * P.ksplit);
+        tile_n = unit;
+        if (const int per_col = P.tiles_r * P.ksplit; per_col > 1) {
+            tile_n = unit / per_col;
+            const int in = unit - tile_n * per_col;
+            split = in / P.tiles_r;
+            tile_r = in - split * P.tiles_r;
+        }
     }
     const int tile = tile_r * P.tiles_n + tile_n;
     const int n0 = tile_n * TN, r0 = tile_r * TR;
