@@ -164,11 +164,15 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(RowsParams<SEG> P)
     // rows of [k x n] weights are then read in pieces of a line each by all XCDs at once, not a piece of 512 bytes and more by one.
     // us, one by one / in bands: steps 64 x 4096 x 8192 19.5 / 21.2, 128 x 4096 x 8192 22.2 / 24.2, 128 x 8192 x 3584 15.7 / 16.5,
     // 256 x 2048 x 8192 21.4 / 22.6, 100 x 5120 x 640 6.0 / 6.5; reduce-scatter rank steps 8 x 16 x 8192 x 3584 20.8 / 21.6, 4 x 16 x
-    // 6144 x 2048 11.4 / 11.7.  Narrower matrices and launches that land the slices of an all-gather beside the tiles are faster in
+    // 6144 x 2048 11.4 / 11.7.  More tiles than compute units (256): a column's row tiles would fall into two rounds, 384 x 4096 x 8192
+    // 54.1 / 46.6, 512 x 4096 x 4096 32.8 / 30.1.  Narrower matrices and launches that land the slices of an all-gather beside the tiles are faster in
     // bands: 512 x 1024 x 4096 13.5 / 12.6, reduce-scatter 8 x 32 x 2048 x 4096 15.6 / 14.7, all-gather 8 x 8 x 4096 x 4096 15.6 /
-    // 13.2; and so is everything with [n x k] weights (1 x 4096 x 8192 14.8 / 11.5).
+    // 13.2; and so is nearly everything with [n x k] weights (1 x 4096 x 8192 14.8 / 11.5; 131 drawn steps 0.98, but 51 of 6144
+    // columns and more over less than 2048 of k 1.02, 48 x 8192 x 1024 5.9 / 6.5: sending those one by one puts a branch in front of
+    // every step's first load that costs the others 1 %).
     int tile_n, split = 0, tile_r = 0;
-    if (BF16 && KN && NC == 4 && P.tiles_n % 8 == 0 && P.tiles_n > (SEG == 1 ? 16 : 32) && P.ldw % 64 == 0 && P.copy_wgs == 0) {
+    if (BF16 && KN && NC == 4 && P.tiles_n % 8 == 0 && P.tiles_n > (SEG == 1 ? 16 : 32) && P.ldw % 64 == 0 && P.copy_wgs == 0 &&
+        tiles <= 256) {
         tile_r = (int)blockIdx.x / P.tiles_n;
         tile_n = (int)blockIdx.x - tile_r * P.tiles_n;
         if (P.ksplit > 1) {

@@ -38,7 +38,7 @@ def test_every_tile_is_computed_once(shape, rows, cols):
 
 
 @pytest.mark.parametrize("shape", ["1x4x1", "1x4x3", "2x4x1", "4x4x1"])
-@pytest.mark.parametrize("rows,cols,off", [(1, 16, 0), (1, 24, 0), (3, 24, 0), (2, 40, 0), (3, 40, 8), (5, 32, 0)])
+@pytest.mark.parametrize("rows,cols,off", [(1, 16, 0), (1, 24, 0), (3, 24, 0), (2, 40, 0), (3, 40, 8), (5, 32, 0), (8, 40, 0)])
 def test_every_tile_of_whole_lines_is_computed_once(shape, rows, cols, off):
     """64 columns of [k x n] bf16 weights are a 128-byte line: from 24 tile columns on (rank steps: 40) these are dealt out one by
     one, and in bands where rows do not lie on the lines.  A step, and reduce-scatter and all-gather rank steps of four ranks."""
@@ -76,3 +76,27 @@ def test_every_tile_of_whole_lines_is_computed_once(shape, rows, cols, off):
         assert close(rs_out if i == p - 1 else sends[i], product(c) + (B[i - 1].double() if i else 0))
         assert close(ag_out[(1 - i) % p * m:((1 - i) % p + 1) * m], product(i))
     assert all(torch.equal(a, b) for a, b in zip(landed, B)) and all(torch.equal(a, b) for a, b in zip(gathered, slices[1:]))
+
+
+@pytest.mark.parametrize("shape", ["1x1x1", "1x2x1", "2x4x1", "4x4x1", "1x2x3"])
+@pytest.mark.parametrize("rows,n,k", [(1, 6144, 520), (3, 6656, 1096), (2, 6152, 1096), (1, 6144, 2056), (2, 6136, 264)])
+def test_every_tile_of_wide_weights_is_computed_once(shape, rows, n, k):
+    """[n x k] weights of 6144 rows and more over less than 2048 of k go one by one where their tiles come in eights."""
+    mf, nc, ks = map(int, shape.split("x"))
+    m = rows * 16 * mf - 3
+    g = torch.Generator(device=DEV).manual_seed(rows * 100 + k)
+    A = torch.empty(m, k, device=DEV).normal_(generator=g).bfloat16()
+    W = torch.empty(n, k, device=DEV).normal_(generator=g).bfloat16()
+    out = torch.full((m, n), float("nan"), device=DEV)
+    ws = torch.zeros(64 << 20, dtype=torch.uint8, device=DEV)
+    os.environ["COMMFUSE_ROWS"] = shape
+    try:
+        cf.set_workspace(ws)
+        torch.cuda.synchronize()
+        cf.ag_step(cf.layer_desc(1, 0, m, n, k, w_layout=cf.CF_W_NK), 0, A, W, out, None)
+        torch.cuda.synchronize()
+    finally:
+        os.environ.pop("COMMFUSE_ROWS", None)
+        cf.set_workspace(None)
+    want = A.double() @ W.double().t()
+    assert float((out.double() - want).abs().max() / want.abs().max()) <= 2.0 ** -24 * k ** 0.5 * 4
