@@ -343,8 +343,9 @@ def make_buffers(A_or_own_shard, W, O, peer_stage: Sequence, slot: Sequence, sen
 def run_schedule(desc: LayerDesc, kind: int, bufs: Buffers, compute_stream, copy_stream, flags: int = 0) -> None:
     call = (_lib or load()).commfuse_run_schedule
     try:
-        status = call(desc, kind, bufs, compute_stream if compute_stream is None or type(compute_stream) is int else compute_stream.cuda_stream,
-                      copy_stream if copy_stream is None or type(copy_stream) is int else copy_stream.cuda_stream, flags)
+        cs = compute_stream if compute_stream is None or type(compute_stream) is int else compute_stream.cuda_stream
+        xs = cs if copy_stream is compute_stream else copy_stream if copy_stream is None or type(copy_stream) is int else copy_stream.cuda_stream
+        status = call(desc, kind, bufs, cs, xs, flags)
     except AttributeError:
         status = call(desc, kind, bufs, _stream(compute_stream), _stream(copy_stream), flags)
     if status:
